@@ -18,7 +18,7 @@ struct jatam_batch {
     int device;
     int64_t max_n;
     int cus;                       // compute units of the device
-    int occ[2][2][3];              // resident blocks per CU [class][tile bound][stage]
+    jatam::BatchOccupancy occ;     // resident blocks per CU
     jatam_tuning_t tune[2];        // launch parameters per grid class
     uint32_t small_hash[2];        // host copy of the workspace's small_hash
     std::vector<std::pair<jatam_tuning_t, double>> tune_log;   // last autotune
@@ -540,7 +540,7 @@ int jatam_batch_autotune(jatam_batch_t* batch, uint64_t first, int64_t n, int t,
         return JATAM_E_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     const int k = grid_limit <= 16 ? 0 : 1;
-    const int ti = t <= 2 ? 0 : 1;
+    const int geno = jatam::geno_kind(t, c);
     jatam_result_t* ref = scratch;
     jatam_result_t* cand = scratch + n;
     uint32_t* flag = batch->ws.counters + jatam::kCntDiff;
@@ -594,7 +594,7 @@ int jatam_batch_autotune(jatam_batch_t* batch, uint64_t first, int64_t n, int t,
     static const int order[7] = {0, 1, 6, 2, 3, 4, 5};
     for (int fi = 0; fi < 7 && rc == JATAM_OK; ++fi) {
         const int field = order[fi];
-        const int rocc = batch->occ[k][ti][cur.repeat_mapping == 1 ? 2 : 1];
+        const int rocc = batch->occ.blocks[k][geno][cur.repeat_mapping == 1 ? 2 : 1];
         std::vector<int> choices;
         if (field == 0)
             choices = {8, 16, 24, 32, 48};
@@ -605,7 +605,7 @@ int jatam_batch_autotune(jatam_batch_t* batch, uint64_t first, int64_t n, int t,
         else if (field == 6)
             choices = {0, 1, 2};
         else if (field == 1)
-            choices = wave_choices(batch->occ[k][ti][0]);
+            choices = wave_choices(batch->occ.blocks[k][geno][0]);
         else if (field == 2)
             choices = wave_choices(rocc);
         else if (k == 0)
@@ -618,7 +618,8 @@ int jatam_batch_autotune(jatam_batch_t* batch, uint64_t first, int64_t n, int t,
                       : field == 2 ? &trial.repeat_waves : field == 3 ? &trial.wide_layout
                       : field == 4 ? &trial.claim_share : field == 5 ? &trial.claim_chunks
                       : &trial.repeat_mapping;
-            if (*slot == v || (field == 1 && v >= batch->occ[k][ti][0] && cur.first_waves >= v) ||
+            if (*slot == v ||
+                (field == 1 && v >= batch->occ.blocks[k][geno][0] && cur.first_waves >= v) ||
                 (field == 2 && v >= rocc && cur.repeat_waves >= v))
                 continue;
             *slot = v;
@@ -1266,12 +1267,12 @@ jatam_tuning_t default_tuning(int klass)
     return jatam_tuning_t{24, 64, 64, 0, 12, 4, klass == 0 ? 2 : 0};
 }
 
-int max_first_blocks(const int occ[2][2][3], int cus)
+int max_first_blocks(const BatchOccupancy& occ, int cus)
 {
     int m = 1;
     for (int k = 0; k < 2; ++k)
-        for (int i = 0; i < 2; ++i)
-            m = occ[k][i][0] * cus > m ? occ[k][i][0] * cus : m;
+        for (int i = 0; i < kGenoKinds; ++i)
+            m = occ.blocks[k][i][0] * cus > m ? occ.blocks[k][i][0] * cus : m;
     return m;
 }
 
@@ -1324,11 +1325,11 @@ size_t carve_workspace(uint8_t* base, size_t max_n, int max_blocks, bool records
 // items that leave it (populations of large shapes) cost more than it saves.
 constexpr int64_t kWindowMinItems = 1 << 20;
 
-int launch_tuned(const jatam_tuning_t tn[2], const int occ[2][2][3], int cus, BatchArgs a,
+int launch_tuned(const jatam_tuning_t tn[2], const BatchOccupancy& occ, int cus, BatchArgs a,
                  int grid_limit, int max_t, hipStream_t stream, hipEvent_t* marks,
                  uint8_t* launched)
 {
-    const int tm = max_t <= 2 ? 2 : 4, ti = tm == 2 ? 0 : 1;
+    const int geno = geno_kind(max_t, a.c);
     // G <= narrow_max runs in the 16 x 16 layout; with the window on (the
     // default) that is every G <= 32, and the 32 x 32 class reruns only the
     // items of G > 16 that left the window
@@ -1341,13 +1342,14 @@ int launch_tuned(const jatam_tuning_t tn[2], const int occ[2][2][3], int cus, Ba
     StageLaunch launch[2];
     for (int k = 0; k < 2; ++k) {
         const jatam_tuning_t& t = tn[k];
-        const int rocc = occ[k][ti][t.repeat_mapping == 1 ? 2 : 1];
-        const int fw = t.first_waves < occ[k][ti][0] ? t.first_waves : occ[k][ti][0];
+        const int focc = occ.blocks[k][geno][0];
+        const int rocc = occ.blocks[k][geno][t.repeat_mapping == 1 ? 2 : 1];
+        const int fw = t.first_waves < focc ? t.first_waves : focc;
         const int rw = t.repeat_waves < rocc ? t.repeat_waves : rocc;
         launch[k] = StageLaunch{t.refill,       fw * cus,       rw * cus,
                                 t.claim_share, t.claim_chunks, t.repeat_mapping};
     }
-    return launch_batched(a, classes, launch, tm, stream, marks, launched);
+    return launch_batched(a, classes, launch, geno, stream, marks, launched);
 }
 
 BatchArgs batch_args_for(const Params& p, int64_t n, jatam_result_t* out, uint64_t* tally,

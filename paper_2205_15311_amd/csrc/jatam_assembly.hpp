@@ -87,35 +87,39 @@ __device__ __forceinline__ void wave_lds_sync()
 // Assembly state of one run, in registers.
 struct RunState {
     uint32_t nf;       // frontier size
-    uint32_t fsum;     // bit w set: frontier word w may be nonzero
     uint32_t osum;     // bit w set: occupancy word w may be nonzero
-    int size;
-    int steps;
+    int steps;         // placements so far: the structure has steps + 1 tiles
     bool choice;
-    // 32 x 32 layout: frontier sites per group of four rows, 16-bit fields,
-    // groups 0-3 in gca and 4-7 in gcb (the frontier select's first level)
-    uint64_t gca = 0, gcb = 0;
+    // 32 x 32 layout: frontier sites per group of four rows, byte k for rows
+    // 4k .. 4k+3 (at most 4 * 31 sites), the frontier select's first level
+    uint64_t groups;
+
+    __device__ __forceinline__ int size() const { return steps + 1; }
+    // Words that may hold a touched cell: frontier sites lie next to occupied
+    // cells, so in the occupied words or the ones before and after them.
+    template <int W>
+    __device__ __forceinline__ uint32_t touched() const
+    {
+        const uint32_t t = osum | (osum << 1) | (osum >> 1);
+        return W == 16 ? t & 0xFFu : t;
+    }
 };
 
-// 32 x 32 layout: the frontier count of cell q's group of four rows goes up
-// (add) or down by one.  Nothing in the 16 x 16 layout.
+// 32 x 32 layout: one more frontier site at cell q, or one less.  Nothing in
+// the 16 x 16 layout.
 template <int W>
 __device__ __forceinline__ void frontier_group_add(RunState& st, int q, bool add)
 {
     if constexpr (W == 32) {
-        const int grp = q >> 7;
-        const uint64_t one = 1ull << (16 * (grp & 3));
-        const uint64_t d = add ? one : 0ull - one;
-        st.gca += grp < 4 ? d : 0ull;
-        st.gcb += grp < 4 ? 0ull : d;
+        const uint64_t one = 1ull << (8 * (q >> 7));
+        st.groups += add ? one : 0ull - one;
     }
 }
 
-// The tile `tuple` was just placed at p: check its empty neighbours (§3.2).
+// The tile `tuple` lies at p: check its empty neighbours (§3.2).
 // A bondable site on the ring means the structure leaves the box; a site
 // that two distinct tiles can fill is ambiguous; otherwise a free site with
-// one admissible tile joins the frontier with that tile pending.  All reads
-// of the four neighbours are issued before any of them is used.
+// one admissible tile joins the frontier with that tile pending.
 //
 // Invariant: the PEND nibble of a free cell is zero unless the cell is on
 // the frontier, so a new pending tile is written with one LDS atomic OR.  An
@@ -124,44 +128,25 @@ __device__ __forceinline__ void frontier_group_add(RunState& st, int q, bool add
 // `added`, if given, receives bit d for every direction d whose site joined
 // the frontier (the movelist traversal pushes those sites).
 //
-// The check only looks at the neighbours' own bits and nibbles, so the
-// words holding them may be read before p itself is marked (NeighbourWords,
-// read by the step together with p's pending word).
-struct NeighbourWords {
-    int q[4];                          // the cells N, E, S, W of p
-    uint32_t ow[4], fw[4], pw[4];      // their occupancy, frontier, pending words
-};
-
-template <int W, int B>
-__device__ __forceinline__ NeighbourWords read_neighbours(LaneGrid<W, B>& g, int p)
-{
-    constexpr int kMask = W * W - 1;
-    NeighbourWords nw;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const int delta = d == 0 ? -W : d == 1 ? 1 : d == 2 ? W : -1;
-        nw.q[d] = (p + delta) & kMask;
-        nw.ow[d] = g.occ(nw.q[d] >> 5);
-        nw.fw[d] = g.fr(nw.q[d] >> 5);
-        nw.pw[d] = g.pend_word(nw.q[d]);
-    }
-    return nw;
-}
-
+// This is the general form, one direction at a time; run_step below does the
+// same for the four directions of a fresh placement at once.
 template <int W, int B, class Src>
 __device__ __forceinline__ int update_site(const Src& m, LaneGrid<W, B>& g, RunState& st,
                                            int G, int p, uint32_t tuple,
-                                           const NeighbourWords& nw,
                                            uint32_t* added = nullptr)
 {
-    const int* const q = nw.q;
-    const uint32_t* const ow = nw.ow;
-    const uint32_t* const fw = nw.fw;
-    const uint32_t* const pw = nw.pw;
-    SiteOpts opt[4];
+    constexpr int kMask = W * W - 1;
+    int q[4];
+    uint32_t ow[4], fw[4], pw[4];
 #pragma unroll
-    for (int d = 0; d < 4; ++d)
-        opt[d] = m.options_split(tuple, d);
+    for (int d = 0; d < 4; ++d) {
+        const int delta = d == 0 ? -W : d == 1 ? 1 : d == 2 ? W : -1;
+        q[d] = (p + delta) & kMask;
+        ow[d] = g.occ(q[d] >> 5);
+        fw[d] = g.fr(q[d] >> 5);
+        pw[d] = g.pend_word(q[d]);
+    }
+    const uint32_t codes = m.codes(tuple);
     // p lies in the box ([0, G-2]^2), so a neighbour is on the ring exactly
     // when p is on the box's edge in that direction (N and W wrap round the
     // torus onto row or column W-1)
@@ -169,24 +154,19 @@ __device__ __forceinline__ int update_site(const Src& m, LaneGrid<W, B>& g, RunS
     bool unbound = false, ambiguous = false;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
+        const SiteOpts opt = split_code(codes >> (8 * d));
         const bool ring = d == 0 ? py == 0 : d == 1 ? px == G - 2 : d == 2 ? py == G - 2 : px == 0;
         const uint32_t bit = (uint32_t)q[d] & 31u;
-        const bool has = opt[d].has;
         const bool free = ((ow[d] >> bit) & 1u) == 0;
-        const bool live = has && !ring && free;
-        const uint32_t id = opt[d].id;
-        const bool multi = opt[d].multi;
+        const bool live = opt.has && !ring && free;
         const bool in_f = ((fw[d] >> bit) & 1u) != 0;
         const uint32_t sh = ((uint32_t)q[d] & 7u) * 4u;
         const uint32_t pending = (pw[d] >> sh) & 15u;
-        // plain (not short-circuit) logic: every operand is at hand, and
-        // lane masks combine with scalar instructions
-        unbound = unbound | (has & ring);
-        ambiguous = ambiguous | (live & (multi | (in_f & (pending != id))));
-        if (live && !multi && !in_f) {
+        unbound = unbound | (opt.has & ring);
+        ambiguous = ambiguous | (live & (opt.multi | (in_f & (pending != opt.id))));
+        if (live && !opt.multi && !in_f) {
             LaneGrid<W, B>::set_bits(g.fr(q[d] >> 5), 1u << bit);
-            LaneGrid<W, B>::set_bits(g.pend_word(q[d]), id << sh);
-            st.fsum |= 1u << (q[d] >> 5);
+            LaneGrid<W, B>::set_bits(g.pend_word(q[d]), opt.id << sh);
             st.nf += 1;
             frontier_group_add<W>(st, q[d], true);
             if (added != nullptr)
@@ -194,14 +174,6 @@ __device__ __forceinline__ int update_site(const Src& m, LaneGrid<W, B>& g, RunS
         }
     }
     return unbound ? kEvUnbound : ambiguous ? kEvAmbig : kEvNone;
-}
-
-template <int W, int B, class Src>
-__device__ __forceinline__ int update_site(const Src& m, LaneGrid<W, B>& g, RunState& st,
-                                           int G, int p, uint32_t tuple,
-                                           uint32_t* added = nullptr)
-{
-    return update_site(m, g, st, G, p, tuple, read_neighbours(g, p), added);
 }
 
 // Philox block cache of a run: the 4 words of counter block `block`.  Kept
@@ -227,6 +199,7 @@ struct DrawCache {
         return (k & 2u) ? hi : lo;
     }
     // random word s of run `run`: word s mod 4 of counter block s / 4
+    static constexpr bool kPrefetched = false;
     __device__ __forceinline__ uint32_t draw(uint32_t s, int run, uint32_t key0, uint32_t key1,
                                              uint32_t rid_lo, uint32_t rid_hi)
     {
@@ -247,6 +220,7 @@ struct DrawCache {
 // at each such point, so all lanes share one computation about every fourth
 // step (see prefetch).  draw() still computes a missing block itself.
 struct DrawPair {
+    static constexpr bool kPrefetched = false;
     uint32_t te, to;                    // block index held (all ones: none)
     uint32_t e0, e1, e2, e3;            // the even block
     uint32_t o0, o1, o2, o3;            // the odd block
@@ -308,6 +282,7 @@ struct DrawPair {
 // of the next draw is then always present, so draw() reads it without the
 // fallback computation (and the step loop holds one copy of the generator).
 struct PrefetchedDraws {
+    static constexpr bool kPrefetched = true;
     DrawPair& dp;
     __device__ __forceinline__ uint32_t draw(uint32_t s, int, uint32_t, uint32_t, uint32_t,
                                              uint32_t) const
@@ -347,25 +322,16 @@ __device__ __forceinline__ int run_clear(LaneGrid<W, B>& g, RunState& st, Draws&
 {
     // occupied cells keep their tiles in PEND, and a run that ended on an
     // event leaves frontier cells (with their PEND nibbles) behind: clear all
-    for (uint32_t s = st.osum; s; s &= s - 1) {
+    for (uint32_t s = st.touched<W>(); s; s &= s - 1) {
         const int w = __builtin_ctz(s);
         g.occ(w) = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            g.word(Geometry<W>::kPend + 4 * w + k) = 0;
-    }
-    for (uint32_t s = st.fsum; s; s &= s - 1) {
-        const int w = __builtin_ctz(s);
         g.fr(w) = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             g.word(Geometry<W>::kPend + 4 * w + k) = 0;
     }
     st.nf = 0;
-    st.fsum = 0;
-    st.gca = 0;
-    st.gcb = 0;
-    st.size = 1;
+    st.groups = 0;
     st.steps = 0;
     st.choice = false;
     dc.reset();
@@ -375,49 +341,38 @@ __device__ __forceinline__ int run_clear(LaneGrid<W, B>& g, RunState& st, Draws&
     return seed_pos;
 }
 
-// Starts a run: clears what the previous run touched, places the seed
-// (tile 0, unrotated) at the centre and checks its neighbours.
+// Starts a run whose seed has the four site codes `codes` (Bonds::codes of
+// the seed's tuple): clears what the previous run touched, places the seed
+// (tile 0, unrotated) at the centre and puts its sites on the frontier.  In
+// the cleared grid they are free and off the frontier, and with G >= 8 the
+// ring is at least three cells away.
+template <int W, int B, class Draws>
+__device__ __forceinline__ int run_start_known(LaneGrid<W, B>& g, RunState& st, Draws& dc,
+                                               int G, uint32_t codes)
+{
+    const int p = run_clear(g, st, dc, G);
+    if ((codes & kSiteMulti) != 0)
+        return kEvAmbig;
+    st.nf = (uint32_t)__popc(codes & kSiteAny);
+    // a site without an option is written too, as zero bits
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const int q = p + (d == 0 ? -W : d == 1 ? 1 : d == 2 ? W : -1);
+        const uint32_t code = codes >> (8 * d);
+        LaneGrid<W, B>::set_bits(g.fr(q >> 5), ((code >> 7) & 1u) << (q & 31));
+        LaneGrid<W, B>::set_bits(g.pend_word(q), (code & 15u) << ((q & 7) * 4));
+        if constexpr (W == 32)
+            st.groups += (uint64_t)((code >> 7) & 1u) << (8 * (q >> 7));
+    }
+    return kEvNone;
+}
+
+// Starts a run of genotype m.
 template <int W, int B, class Src, class Draws>
 __device__ __forceinline__ int run_start(const Src& m, LaneGrid<W, B>& g, RunState& st,
                                          Draws& dc, int G)
 {
-    const int seed_pos = run_clear(g, st, dc, G);
-    return update_site(m, g, st, G, seed_pos, m.seed());
-}
-
-// run_start for a seed whose four site codes are already known (byte d of
-// `seed_opts` is the options code of the seed's site in direction d).  In
-// the cleared grid every neighbour of the seed is free and off the
-// frontier, so update_site reduces to the ring test and the frontier
-// insertions: no grid reads, no options lookups.
-template <int W, int B, class Draws>
-__device__ __forceinline__ int run_start_known(LaneGrid<W, B>& g, RunState& st, Draws& dc,
-                                               int G, uint32_t seed_opts)
-{
-    constexpr int kMask = W * W - 1;
-    const int p = run_clear(g, st, dc, G);
-    bool unbound = false, ambiguous = false;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const int delta = d == 0 ? -W : d == 1 ? 1 : d == 2 ? W : -1;
-        const int q = (p + delta) & kMask;
-        const uint32_t opt = (seed_opts >> (8 * d)) & 0x3Fu;
-        const int qx = q & (W - 1), qy = q >> Geometry<W>::kLogW;
-        const bool ring = qx >= G - 1 || qy >= G - 1;
-        const bool has = opt != 0;
-        const bool multi = (opt >> 4) >= 2;
-        unbound = unbound || (has && ring);
-        ambiguous = ambiguous || (has && !ring && multi);
-        if (has && !ring && !multi) {
-            const uint32_t sh = ((uint32_t)q & 7u) * 4u;
-            LaneGrid<W, B>::set_bits(g.fr(q >> 5), 1u << (q & 31));
-            LaneGrid<W, B>::set_bits(g.pend_word(q), (opt & 15u) << sh);
-            st.fsum |= 1u << (q >> 5);
-            st.nf += 1;
-            frontier_group_add<W>(st, q, true);
-        }
-    }
-    return unbound ? kEvUnbound : ambiguous ? kEvAmbig : kEvNone;
+    return run_start_known(g, st, dc, G, m.codes(m.seed()));
 }
 
 // A run is over once an event happened or the frontier is empty.  Every step
@@ -427,112 +382,226 @@ __device__ __forceinline__ bool run_over(int ev, const RunState& st, int G)
     return ev != kEvNone || st.nf == 0 || st.steps >= (G - 1) * (G - 1);
 }
 
+// Index of the first of four inclusive prefix counts p0 <= p1 <= p2 (<= p3)
+// above j (j < p3): which of four words holds site j.  *below receives the
+// count before that word.
+__device__ __forceinline__ uint32_t pick4(uint32_t j, uint32_t p0, uint32_t p1, uint32_t p2,
+                                          uint32_t& below)
+{
+    const bool up = j >= p1;
+    const uint32_t q = up ? p2 : p0;
+    const bool odd = j >= q;
+    below = odd ? q : up ? p1 : 0u;
+    return (up ? 2u : 0u) + (odd ? 1u : 0u);
+}
+
+// The check of a fresh placement's four neighbours (§3.2), all at once: byte d
+// of every word belongs to direction d.
+//   codes   Bonds::codes of the placed tile
+//   inside  bit 7 set where the neighbour lies in the box (not on its ring)
+//   occ, fr bit 7 set where it is occupied, on the frontier
+//   pend    its PEND nibble
+// fresh receives bit 7 where a site joins the frontier.  The other rules as
+// in update_site.
+__device__ __forceinline__ int check_sites(uint32_t codes, uint32_t inside, uint32_t occ,
+                                           uint32_t fr, uint32_t pend, uint32_t& fresh)
+{
+    const uint32_t has = codes & kSiteAny;
+    const uint32_t live = has & inside & ~occ;
+    // nibbles that differ: their XOR is 1..15, so adding 0x7F sets bit 7
+    const uint32_t differ = ((pend ^ codes) & 0x0F0F0F0Fu) + 0x7F7F7F7Fu;
+    const uint32_t ambiguous = live & ((codes << 1) | (fr & differ));
+    fresh = live & ~fr;
+    return (has & ~inside) != 0 ? kEvUnbound : ambiguous != 0 ? kEvAmbig : kEvNone;
+}
+
+// Bit 7 of byte d set where cell (x, y)'s neighbour in direction d lies in the
+// box [0, G-2]^2.
+__device__ __forceinline__ uint32_t inside_box(uint32_t x, uint32_t y, int G)
+{
+    // the distances to the four edges, at most 30: zero ones stay below 0x80
+    const uint32_t far = (uint32_t)(G - 2) * 0x00010100u;
+    const uint32_t room = (y | (x << 24)) + (far - ((x << 8) | (y << 16)));
+    return room + 0x7F7F7F7Fu;
+}
+
 // One step: draw the frontier site of rank floor(u*|F|/2^32) in row-major
 // order (u = Philox word `steps` of this run's stream; no draw is needed with
 // one site), place its pending tile and check the new neighbours.
+//
+// A wave is bound here by the instructions it issues and, with few waves or
+// few lanes left, by the length of their chain: two rounds of LDS reads (the
+// frontier words, then the placed cell's and its neighbours' words) and one
+// straight line of integer work without branches, the neighbours' words read
+// as the rows around the cell, the four sites checked together and the
+// touched words written back whole.  About 150 instructions, where one site at
+// a time with branches around each insertion took about 270 (16 x 16) to 350
+// (32 x 32).  Measured with the bond lookup of Bonds: all of S_{2,8} in one
+// call 1.31 -> 1.07 ms, a generation of 65,536 three-tile genotypes at G = 32
+// (its longest run, one placement after the other) 0.93 -> 0.63 ms.
 template <int W, int B, class Src, class Draws>
 __device__ __forceinline__ int run_step(const Src& m, LaneGrid<W, B>& g, RunState& st,
                                         Draws& dc, int G, int run, uint32_t key0,
                                         uint32_t key1, uint32_t rid_lo, uint32_t rid_hi)
 {
+    using Geo = Geometry<W>;
+    const uint32_t nf = st.nf;
     uint32_t j = 0;
-    if (st.nf >= 2) {
-        st.choice = true;
-        j = __umulhi(dc.draw((uint32_t)st.steps, run, key0, key1, rid_lo, rid_hi), st.nf);
+    if constexpr (Draws::kPrefetched) {
+        // with one site any word gives rank 0
+        j = __umulhi(dc.draw((uint32_t)st.steps, run, key0, key1, rid_lo, rid_hi), nf);
+    } else {
+        if (nf >= 2)
+            j = __umulhi(dc.draw((uint32_t)st.steps, run, key0, key1, rid_lo, rid_hi), nf);
     }
-    // the j-th frontier site in row-major order
-    int w = 0;
-    uint32_t fw = 0;
+    st.choice = st.choice | (nf >= 2);
+    // the j-th frontier site in row-major order: its word w (fw), then the
+    // bit.  The bitmap's count always equals nf; were it not so, the run
+    // would end as corrupt (and every address below stays in the lane's grid)
+    uint32_t w, fw, below, total;
     if constexpr (W == 16) {
-        // 8 frontier words, no loop: inclusive prefix counts p0..p7; the
-        // word holding site j is the number of prefixes <= j; the word and
-        // its exclusive prefix are picked by binary trees of selects on that
-        // index (scalars throughout: an array picked at run time would go to
-        // scratch memory)
+        // the eight frontier words and their prefix counts, halved thrice
         const uint32_t f0 = g.fr(0), f1 = g.fr(1), f2 = g.fr(2), f3 = g.fr(3);
         const uint32_t f4 = g.fr(4), f5 = g.fr(5), f6 = g.fr(6), f7 = g.fr(7);
         const uint32_t p0 = __popc(f0), p1 = p0 + __popc(f1), p2 = p1 + __popc(f2);
         const uint32_t p3 = p2 + __popc(f3), p4 = p3 + __popc(f4), p5 = p4 + __popc(f5);
-        const uint32_t p6 = p5 + __popc(f6), p7 = p6 + __popc(f7);
-        if (p7 != st.nf)
-            return kEvCorrupt;   // nf disagrees with the bitmap: cannot happen
-        // p_k <= j exactly when p_k - (j + 1) is negative (all values < 2^9):
-        // sign bits summed, no compare-and-select chains
-        const uint32_t j1 = j + 1u;
-        const uint32_t wi = ((p0 - j1) >> 31) + ((p1 - j1) >> 31) + ((p2 - j1) >> 31) +
-                            ((p3 - j1) >> 31) + ((p4 - j1) >> 31) + ((p5 - j1) >> 31) +
-                            ((p6 - j1) >> 31);
-        const bool b0 = (wi & 1u) != 0, b1 = (wi & 2u) != 0, b2 = (wi & 4u) != 0;
-        const uint32_t fa = b0 ? f1 : f0, fb = b0 ? f3 : f2, fc = b0 ? f5 : f4, fd = b0 ? f7 : f6;
-        const uint32_t ea = b0 ? p0 : 0u, eb = b0 ? p2 : p1, ec = b0 ? p4 : p3, ed = b0 ? p6 : p5;
-        const uint32_t fab = b1 ? fb : fa, fcd = b1 ? fd : fc;
-        const uint32_t eab = b1 ? eb : ea, ecd = b1 ? ed : ec;
-        fw = b2 ? fcd : fab;
-        j -= b2 ? ecd : eab;
-        w = (int)wi;
+        const uint32_t p6 = p5 + __popc(f6);
+        total = p6 + __popc(f7);
+        const bool up = j >= p3;
+        const uint32_t a0 = up ? f4 : f0, a1 = up ? f5 : f1, a2 = up ? f6 : f2, a3 = up ? f7 : f3;
+        const uint32_t q1 = up ? p5 : p1;
+        uint32_t in_half;
+        const uint32_t k = pick4(j, up ? p4 : p0, q1, up ? p6 : p2, in_half);
+        below = k != 0 ? in_half : up ? p3 : 0u;
+        const uint32_t b0 = (k & 2u) ? a2 : a0, b1 = (k & 2u) ? a3 : a1;
+        fw = (k & 1u) ? b1 : b0;
+        w = (up ? 4u : 0u) + k;
     } else {
-        // two levels, one round of LDS reads: the frontier counts of the 8
-        // groups of four rows (registers, 16-bit fields) pick the group, its
-        // four words the row.  Inclusive prefix sums of the group counts:
-        uint64_t pa = st.gca;
-        pa += pa << 16;
-        pa += pa << 32;
-        uint64_t pb = st.gcb;
-        pb += pb << 16;
-        pb += pb << 32;
-        pb += (pa >> 48) * 0x0001000100010001ull;   // groups 4-7 follow groups 0-3
-        if ((uint32_t)(pb >> 48) != st.nf)
-            return kEvCorrupt;   // the counts disagree with nf: cannot happen
-        // the group holding site j is the number of prefixes <= j: a field
-        // p (< 2^15, as j + 1 is) has bit 15 of (p | 2^15) - (j + 1) set
-        // exactly when p > j, with no borrow between fields
-        constexpr uint64_t kHigh = 0x8000800080008000ull;
-        const uint64_t jj = (uint64_t)(j + 1u) * 0x0001000100010001ull;
-        const uint32_t grp = 8u - (uint32_t)__popcll(((pa | kHigh) - jj) & kHigh) -
-                             (uint32_t)__popcll(((pb | kHigh) - jj) & kHigh);
-        const uint32_t gm = (grp - 1u) & 7u;   // the group before, if any
-        const uint64_t below = gm < 4u ? pa : pb;
-        j -= grp == 0u ? 0u : (uint32_t)(below >> (16u * (gm & 3u))) & 0xFFFFu;
-        const int w0 = (int)grp * 4;
+        // two levels: the counts of the eight groups of four rows (one byte
+        // each, in registers) pick the group, its four words the row
+        const uint32_t ga = (uint32_t)st.groups, gb = (uint32_t)(st.groups >> 32);
+        const uint32_t p0 = ga & 0xFFu;
+        const uint32_t p1 = __builtin_amdgcn_udot4(ga, 0x00000101u, 0u, false);
+        const uint32_t p2 = __builtin_amdgcn_udot4(ga, 0x00010101u, 0u, false);
+        const uint32_t p3 = __builtin_amdgcn_udot4(ga, 0x01010101u, 0u, false);
+        const uint32_t p4 = __builtin_amdgcn_udot4(gb, 0x00000001u, p3, false);
+        const uint32_t p5 = __builtin_amdgcn_udot4(gb, 0x00000101u, p3, false);
+        const uint32_t p6 = __builtin_amdgcn_udot4(gb, 0x00010101u, p3, false);
+        total = __builtin_amdgcn_udot4(gb, 0x01010101u, p3, false);
+        const bool up = j >= p3;
+        uint32_t in_half;
+        const uint32_t k = pick4(j, up ? p4 : p0, up ? p5 : p1, up ? p6 : p2, in_half);
+        const uint32_t before = k != 0 ? in_half : up ? p3 : 0u;
+        const uint32_t w0 = 4u * ((up ? 4u : 0u) + k);
         const uint32_t f0 = g.fr(w0), f1 = g.fr(w0 + 1), f2 = g.fr(w0 + 2), f3 = g.fr(w0 + 3);
         const uint32_t c0 = __popc(f0), c1 = c0 + __popc(f1), c2 = c1 + __popc(f2);
-        const uint32_t j1 = j + 1u;
-        const uint32_t wi = ((c0 - j1) >> 31) + ((c1 - j1) >> 31) + ((c2 - j1) >> 31);
-        const bool b0 = (wi & 1u) != 0, b1 = (wi & 2u) != 0;
-        fw = b1 ? (b0 ? f3 : f2) : (b0 ? f1 : f0);
-        j -= b1 ? (b0 ? c2 : c1) : (b0 ? c0 : 0u);
-        w = w0 + (int)wi;
-        if (j >= (uint32_t)__popc(fw))
-            return kEvCorrupt;   // the counts disagree with the bitmap: cannot happen
+        uint32_t in_group;
+        const uint32_t r = pick4(j - before, c0, c1, c2, in_group);
+        below = before + in_group;
+        const uint32_t b0 = (r & 2u) ? f2 : f0, b1 = (r & 2u) ? f3 : f1;
+        fw = (r & 1u) ? b1 : b0;
+        w = w0 + r;
     }
-    // the j-th set bit of the word: j is below the word's frontier count,
-    // nearly always 0..2, so clearing the lowest bit j times beats a
-    // fixed binary search
+    // the site's bit: its rank in the word is nearly always 0..2, so clearing
+    // the lowest bit that often beats a fixed binary search
     uint32_t rest = fw;
-    for (uint32_t k = 0; k < j; ++k)
+    for (uint32_t k = j - below; k > 0u; --k)
         rest &= rest - 1u;
-    const int bit = __builtin_ctz(rest);
-    const int p = (w << 5) | bit;
-    // p's pending word and its neighbours' words in one round of LDS reads,
-    // issued before p leaves the frontier and is marked occupied (the
-    // neighbour check does not look at p's bits)
-    const uint32_t pw = g.pend_word(p);
-    const NeighbourWords nw = read_neighbours(g, p);
-    fw &= ~(1u << bit);
-    g.fr(w) = fw;
-    if (fw == 0)
-        st.fsum &= ~(1u << w);
-    st.nf -= 1;
-    frontier_group_add<W>(st, p, false);
-
-    // place the pending tile (its nibble stays: the cell keeps its tile)
-    const uint32_t sh = ((uint32_t)p & 7u) * 4u;
-    const uint32_t tuple = m.oriented((int)((pw >> sh) & 15u));
-    LaneGrid<W, B>::set_bits(g.occ(w), 1u << bit);
+    const uint32_t bit = (uint32_t)__builtin_ctz(rest | 0x80000000u);
+    int ev;
+    if constexpr (W == 16) {
+        // a word holds two rows.  The cell's own word and the next (odd row)
+        // or previous one (even row) as 64 bits hold the rows above and below
+        // too: shifted so that N is bit 0, W is bit 15, the cell 16, E 17 and
+        // S 32 (off the torus' rim they show ring cells, which are masked)
+        const uint32_t x = bit & 15u, odd = bit >> 4, y = 2u * w + odd;
+        const uint32_t wa = (w + 2u * odd - 1u) & 7u, shift = bit ^ 16u;
+        const uint32_t own = g.occ(w), adj = g.occ(wa), fa = g.fr(wa);
+        // the row's 16 PEND nibbles, and the words above and below the cell
+        const uint32_t prow = Geo::kPend + 2u * y, half = x >> 3;
+        const uint32_t n_at = Geo::kPend + 2u * ((y - 1u) & 15u) + half;
+        const uint32_t s_at = Geo::kPend + 2u * ((y + 1u) & 15u) + half;
+        uint64_t row = ((uint64_t)g.word(prow + 1) << 32) | g.word(prow);
+        const uint32_t pn = g.word(n_at), ps = g.word(s_at), sh = 4u * (x & 7u);
+        const uint64_t occ2 = odd ? ((uint64_t)adj << 32) | own : ((uint64_t)own << 32) | adj;
+        uint64_t fr2 = odd ? ((uint64_t)fa << 32) | fw : ((uint64_t)fw << 32) | fa;
+        // nibbles: 0 the W neighbour, 1 the cell, 2 the E neighbour
+        const uint32_t near = (uint32_t)((row << 4) >> (4u * x));
+        const uint32_t codes = m.codes(m.oriented((near >> 4) & 15u));
+        auto around = [](uint64_t u) -> uint32_t {
+            const uint32_t a = (uint32_t)u, b = (uint32_t)(u >> 32);
+            return ((a << 7) & 0x80u) | ((a >> 2) & 0x8000u) | ((b << 23) & 0x800000u) |
+                   ((a << 16) & 0x80000000u);
+        };
+        const uint32_t pend = ((pn >> sh) & 15u) | (near & 0xF00u) | (((ps >> sh) & 15u) << 16) |
+                              ((near & 15u) << 24);
+        uint32_t fresh;
+        ev = check_sites(codes, inside_box(x, y, G), around(occ2 >> shift),
+                         around(fr2 >> shift), pend, fresh);
+        // the cell leaves the frontier, fresh sites (none of them on it) join
+        const uint32_t flip = ((fresh >> 7) & 1u) | ((fresh >> 16) & 0x8000u) | 0x10000u |
+                              ((fresh << 2) & 0x20000u);
+        fr2 ^= (((uint64_t)((fresh >> 23) & 1u) << 32) | flip) << shift;
+        g.fr(w) = odd ? (uint32_t)fr2 : (uint32_t)(fr2 >> 32);
+        g.fr(wa) = odd ? (uint32_t)(fr2 >> 32) : (uint32_t)fr2;
+        const uint32_t ones = fresh >> 7, ids = codes & ((ones << 4) - ones);
+        row |= ((uint64_t)((ids >> 24) | (ids & 0xF00u)) << (4u * x)) >> 4;
+        g.word(prow) = (uint32_t)row;
+        g.word(prow + 1) = (uint32_t)(row >> 32);
+        g.word(n_at) = pn | ((ids & 15u) << sh);
+        g.word(s_at) = ps | (((ids >> 16) & 15u) << sh);
+        g.occ(w) = own | (1u << bit);
+        st.nf = nf + (uint32_t)__popc(fresh) - 1u;
+    } else {
+        // a word holds one row
+        const uint32_t x = bit, y = w, yn = (y - 1u) & 31u, ys = (y + 1u) & 31u;
+        const uint32_t on = g.occ(yn), own = g.occ(y), os = g.occ(ys);
+        const uint32_t fn = g.fr(yn), fs = g.fr(ys);
+        // eight PEND nibbles a word: the cell's word and the next one in its
+        // row (right half) or the one before (left half) hold E and W
+        const uint32_t at = x >> 3, k = x & 7u, sh = 4u * k;
+        const bool right = k >= 4u;
+        const uint32_t prow = Geo::kPend + 4u * y, pa = prow + ((right ? at + 1u : at - 1u) & 3u);
+        const uint32_t n_at = Geo::kPend + 4u * yn + at, s_at = Geo::kPend + 4u * ys + at;
+        const uint32_t po = g.word(prow + at), pj = g.word(pa), pn = g.word(n_at);
+        const uint32_t ps = g.word(s_at);
+        uint64_t row = right ? ((uint64_t)pj << 32) | po : ((uint64_t)po << 32) | pj;
+        const uint32_t rsh = right ? sh - 4u : sh + 28u;
+        // nibbles: 0 the W neighbour, 1 the cell, 2 the E neighbour
+        const uint32_t near = (uint32_t)(row >> rsh);
+        const uint32_t codes = m.codes(m.oriented((near >> 4) & 15u));
+        // rows rotated so that W is bit 0, the cell 1, E 2
+        auto around = [x](uint32_t n, uint32_t o, uint32_t s) -> uint32_t {
+            const uint32_t a = __builtin_amdgcn_alignbit(o, o, x - 1u);
+            return (((n >> x) & 1u) << 7) | ((a << 13) & 0x8000u) | (((s >> x) & 1u) << 23) |
+                   (a << 31);
+        };
+        const uint32_t pend = ((pn >> sh) & 15u) | (near & 0xF00u) | (((ps >> sh) & 15u) << 16) |
+                              ((near & 15u) << 24);
+        uint32_t fresh;
+        ev = check_sites(codes, inside_box(x, y, G), around(on, own, os), around(fn, fw, fs), pend,
+                         fresh);
+        const uint32_t flip = (fresh >> 31) | 2u | ((fresh >> 13) & 4u);
+        const uint32_t up = (fresh >> 7) & 1u, down = (fresh >> 23) & 1u;
+        g.fr(y) = fw ^ __builtin_amdgcn_alignbit(flip, flip, 1u - x);
+        g.fr(yn) = fn | (up << x);
+        g.fr(ys) = fs | (down << x);
+        const uint32_t ones = fresh >> 7, ids = codes & ((ones << 4) - ones);
+        row |= (uint64_t)((ids >> 24) | (ids & 0xF00u)) << rsh;
+        g.word(prow + at) = right ? (uint32_t)row : (uint32_t)(row >> 32);
+        g.word(pa) = right ? (uint32_t)(row >> 32) : (uint32_t)row;
+        g.word(n_at) = pn | ((ids & 15u) << sh);
+        g.word(s_at) = ps | (((ids >> 16) & 15u) << sh);
+        g.occ(y) = own | (1u << x);
+        st.nf = nf + (uint32_t)__popc(fresh) - 1u;
+        st.groups += (uint64_t)(uint32_t)__popc(fresh & 0x80008000u) << (8u * (y >> 2));
+        st.groups -= 1ull << (8u * (y >> 2));
+        st.groups += (uint64_t)up << (8u * (yn >> 2));
+        st.groups += (uint64_t)down << (8u * (ys >> 2));
+    }
     st.osum |= 1u << w;
-    st.size += 1;
     st.steps += 1;
-    return update_site(m, g, st, G, p, tuple, nw);
+    return total != nf ? kEvCorrupt : ev;
 }
 
 // One run from the seed to completion or to an event.
@@ -575,7 +644,7 @@ __device__ __forceinline__ bool shape_is_forced(const Src& m, LaneGrid<W, B>& g,
                     continue;
                 const uint32_t nq = (g.pend_word(q) >> ((uint32_t)(q & 7) * 4u)) & 15u;
                 // options of the site in direction d + 2 of q's tile: cell p
-                const SiteOpts o = m.options_split(m.oriented((int)nq), (d + 2) & 3);
+                const SiteOpts o = split_code(m.codes(m.oriented(nq)) >> (8 * ((d + 2) & 3)));
                 if (o.has && (o.multi || o.id != id))
                     forced = false;
             }
@@ -655,7 +724,7 @@ __device__ __forceinline__ bool shape_is_guarded(const Src& m, LaneGrid<W, B>& g
                     continue;
                 const uint32_t nq = (g.pend_word(q) >> ((uint32_t)(q & 7) * 4u)) & 15u;
                 // options of the site in direction d + 2 of q's tile: cell p
-                const SiteOpts o = m.options_split(m.oriented((int)nq), (d + 2) & 3);
+                const SiteOpts o = split_code(m.codes(m.oriented(nq)) >> (8 * ((d + 2) & 3)));
                 const bool good = o.has & !o.multi & (o.id == id);
                 const bool conf = o.has & !good;
                 const uint64_t gb = good ? bit : 0ull, cb = conf ? bit : 0ull;
@@ -980,27 +1049,28 @@ __device__ __forceinline__ bool packed_shape_is_guarded(const Src& src, const ui
     const uint64_t seed_bit = 1ull << (int)(word >> 58);
     uint64_t good0 = 0, good1 = 0, good2 = 0, good3 = 0;
     uint64_t conf0 = 0, conf1 = 0, conf2 = 0, conf3 = 0;
-    for (uint64_t cells = shape; cells != 0; cells &= cells - 1) {
+    uint64_t left = tiles;   // the tiles of the cells still to come
+    for (uint64_t cells = shape; cells != 0; cells &= cells - 1, left >>= 4) {
         const int b = __builtin_ctzll(cells);
-        const uint64_t bit = 1ull << b;
-        const uint32_t id = (uint32_t)(tiles >> (4 * __popcll(shape & (bit - 1)))) & 15u;
+        const uint32_t codes = src.codes(src.oriented((uint32_t)left & 15u));
         const int x = b & 7, y = b >> 3;
+        // the edges from this cell into its neighbour p in direction d, which
+        // it enters from direction d + 2
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
             const bool inside = d == 0 ? y > 0 : d == 1 ? x < 7 : d == 2 ? y < 7 : x > 0;
-            const int qb = b + (d == 0 ? -8 : d == 1 ? 1 : d == 2 ? 8 : -1);
-            if (!inside || ((shape >> (qb & 63)) & 1ull) == 0ull)
+            const int pb = b + (d == 0 ? -8 : d == 1 ? 1 : d == 2 ? 8 : -1);
+            if (!inside || ((shape >> (pb & 63)) & 1ull) == 0ull)
                 continue;
-            const uint32_t nq =
-                (uint32_t)(tiles >> (4 * __popcll(shape & ((1ull << qb) - 1)))) & 15u;
-            // options of the site in direction d + 2 of q's tile: cell b
-            const SiteOpts o = src.options_split(src.oriented((int)nq), (d + 2) & 3);
+            const uint64_t bit = 1ull << pb;
+            const uint32_t id = (uint32_t)(tiles >> (4 * __popcll(shape & (bit - 1)))) & 15u;
+            const SiteOpts o = split_code(codes >> (8 * d));
             const bool good = o.has & !o.multi & (o.id == id);
             const bool conf = o.has & !good;
             const uint64_t gb = good ? bit : 0ull, cb = conf ? bit : 0ull;
-            if (d == 0) { good0 |= gb; conf0 |= cb; }
-            else if (d == 1) { good1 |= gb; conf1 |= cb; }
-            else if (d == 2) { good2 |= gb; conf2 |= cb; }
+            if (d == 2) { good0 |= gb; conf0 |= cb; }
+            else if (d == 3) { good1 |= gb; conf1 |= cb; }
+            else if (d == 0) { good2 |= gb; conf2 |= cb; }
             else { good3 |= gb; conf3 |= cb; }
         }
     }
@@ -1191,16 +1261,12 @@ __device__ __forceinline__ int run_assembly_lifo(const Src& m, LaneGrid<W, B>& g
         const int p = stk.get((int)st.nf - 1);
         st.nf -= 1;
         const int w = p >> 5;
-        const uint32_t fw = g.fr(w) & ~(1u << (p & 31));
-        g.fr(w) = fw;
-        if (fw == 0)
-            st.fsum &= ~(1u << w);
+        g.fr(w) = g.fr(w) & ~(1u << (p & 31));
         const uint32_t pw = g.pend_word(p);
         const uint32_t sh = ((uint32_t)p & 7u) * 4u;
-        const uint32_t tuple = m.oriented((int)((pw >> sh) & 15u));
+        const uint32_t tuple = m.oriented((pw >> sh) & 15u);
         LaneGrid<W, B>::set_bits(g.occ(w), 1u << (p & 31));
         st.osum |= 1u << w;
-        st.size += 1;
         st.steps += 1;
         const uint32_t len = st.nf;
         added = 0;

@@ -267,7 +267,7 @@ __device__ __forceinline__ uint32_t size_key(uint32_t size)
     return kSizeBuckets - 1 - b;
 }
 
-template <int W, int TM, int kIn>
+template <int W, class M, int kIn>
 __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int klass)
 {
     const uint32_t small0 = a.small0, small1 = a.small1;
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
     static_assert(kSizeBuckets == 64, "one bucket per lane");
     size_hist[lane_id()] = 0;
     __syncthreads();
-    RunState st{0, 0, 0, 0, 0, false};
+    RunState st{};
     DrawPair dc;
     dc.reset();
 
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
     bool starved = false;                     // the last refill found no chunk left
     uint32_t idx = 0;
     Geno gd{0, 0, 0, 0, false};
-    ModelSource<TM> m;
+    M m{};
     int ev = kEvNone;
 
     for (;;) {
@@ -359,19 +359,19 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                     cls = JATAM_INVALID;
                 } else if (ev != kEvNone) {
                     cls = ev == kEvUnbound ? JATAM_UNBOUND : JATAM_ND_SITE;
-                    rec = jatam_result_t{cls, st.size, 0u, st.steps};
+                    rec = jatam_result_t{cls, st.size(), 0u, st.steps};
                 } else if (!st.choice || a.runs == 1) {
                     // no random word was drawn: every run would be this run
                     cls = JATAM_DET;
                     det = true;
-                    rec = jatam_result_t{JATAM_DET, st.size, 0u, st.steps};
+                    rec = jatam_result_t{JATAM_DET, st.size(), 0u, st.steps};
                 } else {
                     done = false;
                     candidate = true;
                 }
             }
             if (__ballot(det) != 0)
-                rec.hash = det_hash(g, small0, small1, cache, det, st.size, gd.grid);
+                rec.hash = det_hash(g, small0, small1, cache, det, st.size(), gd.grid);
             if (finish) {
                 if (done)
                     out[idx] = rec;
@@ -382,10 +382,10 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
             if (candidate) {
                 const uint32_t pos = staged + (uint32_t)__popcll(cm & lanes_below());
                 seg_idx[pos] = idx;
-                seg_size[pos] = (uint16_t)st.size;
+                seg_size[pos] = (uint16_t)st.size();
                 // the shape, for the proof stage to check without a replay
-                seg_shape[pos] = pack_shape(g, gd.grid, st.size);
-                atomicAdd(&size_hist[size_key((uint32_t)st.size)], 1u);
+                seg_shape[pos] = pack_shape(g, gd.grid, st.size());
+                atomicAdd(&size_hist[size_key((uint32_t)st.size())], 1u);
             }
             staged += (uint32_t)__popcll(cm);
         }
@@ -450,21 +450,14 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                         if (a.narrow_max > 16 ? klass == 0 : grid_class(a, s.grid) == klass)
                             out[i] = jatam_result_t{JATAM_INVALID, 0, 0u, 0};
                     } else if (grid_class(a, s.grid) == klass) {
-                        const Model<TM> sm = build_model<TM>(s.genome, s.t, a.bits, a.c);
-                        const uint32_t seed = seed_tile(sm);
-                        bool ambiguous = false, bonds = false;
-#pragma unroll
-                        for (int d = 0; d < 4; ++d) {
-                            const uint32_t opt = site_options(sm, seed, d);
-                            ambiguous = ambiguous || (opt >> 4) >= 2;
-                            bonds = bonds || opt != 0;
-                            opts |= opt << (8 * d);
-                        }
+                        const M sm = build_bonds<M>(s.genome, s.t, a.bits, a.c);
+                        opts = sm.codes(sm.seed());
+                        const bool ambiguous = (opts & kSiteMulti) != 0;
                         if (ambiguous) {
                             out[i] = jatam_result_t{JATAM_ND_SITE, 1, 0u, 0};
                             done = true;
                             cls = JATAM_ND_SITE;
-                        } else if (!bonds) {
+                        } else if (opts == 0) {   // nothing bonds to the seed
                             out[i] = jatam_result_t{JATAM_DET, 1, small0, 0};
                             done = true;
                             cls = JATAM_DET;
@@ -490,7 +483,7 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                     const uint32_t slot = (head + rank) % kRing;
                     idx = ring[slot];
                     gd = run_geno<W, kIn>(a, first, idx);
-                    m.m = build_model<TM>(gd.genome, gd.t, a.bits, a.c);
+                    m = build_bonds<M>(gd.genome, gd.t, a.bits, a.c);
                     ev = run_start_known(g, st, dc, gd.grid, ring_opt[slot]);
                     busy = true;
                 }
@@ -672,7 +665,7 @@ constexpr uint32_t kNoCandidate = 0xFFFFFFFFu;
 // (lanes with `active`): a guarded shape gets its record here; otherwise
 // the candidate is kept (the return value) for the repeat runs.  Called by
 // the whole wave.
-template <int W, int TM>
+template <int W, class M>
 __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
                                           jatam_result_t* out, LaneGrid<W, 64>& g, RunState& st,
                                           WaveShapeCache& cache, WaveTally& tally, int klass,
@@ -686,7 +679,7 @@ __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
     if (active) {
         idx = a.ws.sorted[klass][pos];
         gd = run_geno<W>(a, first, idx);
-        const ModelSource<TM> src{build_model<TM>(gd.genome, gd.t, a.bits, a.c)};
+        const M src = build_bonds<M>(gd.genome, gd.t, a.bits, a.c);
         const uint4 sh = a.ws.sorted_shape[pos];
         packed = packed_shape_valid(sh);
         if (packed) {
@@ -697,7 +690,7 @@ __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
         } else {
             const int ev = run_assembly(src, g, st, gd.grid, 0, a.key0, a.key1,
                                         (uint32_t)gd.rng_id, (uint32_t)(gd.rng_id >> 32));
-            size = st.size;
+            size = st.size();
             forced = ev == kEvNone && shape_is_guarded(src, g, st, gd.grid);
         }
     }
@@ -711,7 +704,7 @@ __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
     return active && !forced;
 }
 
-template <int W, int TM>
+template <int W, class M>
 __global__ __launch_bounds__(64) void prove_kernel(const BatchArgs a, int klass)
 {
     using Geo = Geometry<W>;
@@ -724,7 +717,7 @@ __global__ __launch_bounds__(64) void prove_kernel(const BatchArgs a, int klass)
     WaveShapeCache cache{cache_mem};
     cache.clear(lane_id());
     __syncthreads();
-    RunState st{0, 0, 0, 0, 0, false};
+    RunState st{};
     WaveTally tally{{0, 0, 0, 0}};
     const uint32_t count = a.ws.counters[kCntCand + klass];
     uint32_t* keep = a.ws.cand_idx[klass];
@@ -735,7 +728,7 @@ __global__ __launch_bounds__(64) void prove_kernel(const BatchArgs a, int klass)
         const bool active = pos < count;
         uint32_t idx;
         const bool kept =
-            prove_one<W, TM>(a, first, out, g, st, cache, tally, klass, active, pos, idx);
+            prove_one<W, M>(a, first, out, g, st, cache, tally, klass, active, pos, idx);
         if (active)
             keep[pos] = kept ? idx : kNoCandidate;
         const uint32_t kc = (uint32_t)__popcll(__ballot(kept));
@@ -862,7 +855,7 @@ __device__ __forceinline__ uint32_t* occ_word(uint4* lo, uint4* hi, uint32_t slo
 // runs skip .. rpass-1 of each candidate, lane jr of group grp making run
 // skip + jr.  round() runs one candidate per group (active groups only) to
 // its record, or (a first pass without a witness) to the second queue.
-template <int W, int TM, bool kTable>
+template <int W, class M>
 struct RepeatWave {
     using Geo = Geometry<W>;
     const BatchArgs& a;
@@ -870,7 +863,7 @@ struct RepeatWave {
     jatam_result_t* out;
     LaneGrid<W, 64> g;       // this lane's grid
     LaneGrid<W, 64> g0;      // the group's lead lane's grid
-    uint32_t (*orient)[64];  // per group: bond table words, then orientation hashes
+    uint32_t (*orient)[64];  // per group: orientation hashes
     WaveShapeCache& cache;
     RunState& st;
     WaveTally& tally;
@@ -906,33 +899,13 @@ struct RepeatWave {
     {
         Geno gd{0, 0, 0, 0, false};
         int ev = kEvNone;
-        if constexpr (kTable) {
-            // the group builds its genotype's bond table together (word j by
-            // lane j of the group), shared through the orientation slots
-            TableSource<TM> src;
-            if (active) {
-                gd = run_geno<W>(a, first, idx);
-                src.m = build_model<TM>(gd.genome, gd.t, a.bits, a.c);
-                for (int j = jr; j < 8; j += R)
-                    orient[j][grp] = bond_table_word(src.m, j);
-            }
-            wave_lds_sync();
-            if (active) {
-#pragma unroll
-                for (int d = 0; d < 4; ++d)
-                    src.side[d] = ((uint64_t)orient[2 * d + 1][grp] << 32) | orient[2 * d][grp];
-                ev = run_assembly(src, g, st, gd.grid, run, a.key0, a.key1, (uint32_t)gd.rng_id,
-                                  (uint32_t)(gd.rng_id >> 32));
-            }
-        } else {
-            if (active) {
-                gd = run_geno<W>(a, first, idx);
-                const ModelSource<TM> src{build_model<TM>(gd.genome, gd.t, a.bits, a.c)};
-                ev = run_assembly(src, g, st, gd.grid, run, a.key0, a.key1, (uint32_t)gd.rng_id,
-                                  (uint32_t)(gd.rng_id >> 32));
-            }
+        if (active) {
+            gd = run_geno<W>(a, first, idx);
+            const M src = build_bonds<M>(gd.genome, gd.t, a.bits, a.c);
+            ev = run_assembly(src, g, st, gd.grid, run, a.key0, a.key1, (uint32_t)gd.rng_id,
+                              (uint32_t)(gd.rng_id >> 32));
         }
-        wave_lds_sync();   // every run's grid is final (and the table slots read)
+        wave_lds_sync();   // every run's grid is final
         // a witness is a later run that hit an event or ended in another
         // shape than run 0 (the lead lane's, or the stored one)
         bool same = true;
@@ -959,7 +932,7 @@ struct RepeatWave {
         const int fw = wm ? (int)__builtin_ctzll(wm) : R;      // R: no witness
         const int wl = lead + (fw < R ? fw : 0);
         const int w_ev = __shfl(ev, wl);
-        const int w_size = __shfl(st.size, wl);
+        const int w_size = __shfl(st.size(), wl);
         const int lead_ev = __shfl(ev, lead);
         int cls;
         if (lead_ev == kEvCorrupt || (fw < R && w_ev == kEvCorrupt))
@@ -998,7 +971,7 @@ struct RepeatWave {
             }
         }
         const bool det = active && cls == JATAM_DET && !undecided;
-        const int size0 = __shfl(st.size, lead);
+        const int size0 = __shfl(st.size(), lead);
         // run 0's shape: from the wave's cache, else the group's lanes share
         // its 8 orientation hashes
         uint64_t key = 0;
@@ -1051,7 +1024,7 @@ struct RepeatWave {
     }
 };
 
-template <int W, int TM, bool kTable>
+template <int W, class M>
 __global__ __launch_bounds__(64) void repeat_kernel(const BatchArgs a, int klass, int rpass,
                                                     int skip, bool store_occ,
                                                     const uint32_t* queue_in,
@@ -1067,9 +1040,9 @@ __global__ __launch_bounds__(64) void repeat_kernel(const BatchArgs a, int klass
     WaveShapeCache cache{cache_mem};
     cache.clear(lane_id());
     __syncthreads();
-    RunState st{0, 0, 0, 0, 0, false};
+    RunState st{};
     WaveTally tally{{0, 0, 0, 0}};
-    RepeatWave<W, TM, kTable> rw(a, smem, orient, cache, st, tally, rpass, skip, store_occ,
+    RepeatWave<W, M> rw(a, smem, orient, cache, st, tally, rpass, skip, store_occ,
                                  queue_out, count_out);
     const uint32_t count = *count_in;
     const uint32_t groups = (uint32_t)rw.groups, grp = (uint32_t)rw.grp;
@@ -1102,7 +1075,7 @@ __global__ __launch_bounds__(64) void repeat_kernel(const BatchArgs a, int klass
 // second queue (count_out, cleared by the first-run kernel), in the 16 x 16 layout
 // with run 0's occupancy stored.
 // ---------------------------------------------------------------------------
-template <int W, int TM, bool kTable>
+template <int W, class M>
 __global__ __launch_bounds__(64) void prove_repeat_kernel(const BatchArgs a, int klass,
                                                           int rpass, uint32_t* queue_out,
                                                           uint32_t* count_out)
@@ -1117,9 +1090,9 @@ __global__ __launch_bounds__(64) void prove_repeat_kernel(const BatchArgs a, int
     WaveShapeCache cache{cache_mem};
     cache.clear(lane_id());
     __syncthreads();
-    RunState st{0, 0, 0, 0, 0, false};
+    RunState st{};
     WaveTally tally{{0, 0, 0, 0}};
-    RepeatWave<W, TM, kTable> rw(a, smem, orient, cache, st, tally, rpass, 0, W == 16,
+    RepeatWave<W, M> rw(a, smem, orient, cache, st, tally, rpass, 0, W == 16,
                                  queue_out, count_out);
     const uint32_t count = a.ws.counters[kCntCand + klass];
     const uint32_t qchunks = (count + 63) / 64;
@@ -1156,7 +1129,7 @@ __global__ __launch_bounds__(64) void prove_repeat_kernel(const BatchArgs a, int
     for (uint32_t c = claim(); c < qchunks; c = claim()) {
         const uint32_t pos = c * 64 + lane;
         uint32_t idx;
-        const bool kept = prove_one<W, TM>(a, rw.first, rw.out, lg, st, cache, tally, klass,
+        const bool kept = prove_one<W, M>(a, rw.first, rw.out, lg, st, cache, tally, klass,
                                            pos < count, pos, idx);
         const uint64_t km = __ballot(kept);
         if (kept)
@@ -1183,11 +1156,10 @@ __global__ __launch_bounds__(64) void prove_repeat_kernel(const BatchArgs a, int
 // ---------------------------------------------------------------------------
 constexpr int kSeqRefill = 8;
 
-template <int W, int TM, bool kTable>
+template <int W, class M>
 __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int klass)
 {
     using Geo = Geometry<W>;
-    using Src = typename std::conditional<kTable, TableSource<TM>, ModelSource<TM>>::type;
     const uint32_t small0 = a.small0, small1 = a.small1;
     const uint64_t first = slice_first(a);
     jatam_result_t* const out = slice_out(a);
@@ -1200,7 +1172,7 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
     WaveShapeCache cache{cache_mem};
     cache.clear(lane_id());
     __syncthreads();
-    RunState st{0, 0, 0, 0, 0, false};
+    RunState st{};
     WaveTally tally{{0, 0, 0, 0}};
     DrawPair dc;
     dc.reset();
@@ -1214,7 +1186,7 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
     uint32_t idx = 0, osum0 = 0;
     int run = 0, ev = kEvNone, steps_sum = 0, size0 = 0;
     Geno gd{0, 0, 0, 0, false};
-    Src src;
+    M src{};
 
     for (;;) {
         const uint64_t idle = __ballot(!busy);
@@ -1229,13 +1201,7 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
                 if (pos < count) {
                     idx = queue[pos];
                     gd = run_geno<W>(a, first, idx);
-                    src.m = build_model<TM>(gd.genome, gd.t, a.bits, a.c);
-                    if constexpr (kTable) {
-#pragma unroll
-                        for (int d = 0; d < 4; ++d)
-                            src.side[d] = ((uint64_t)bond_table_word(src.m, 2 * d + 1) << 32) |
-                                          bond_table_word(src.m, 2 * d);
-                    }
+                    src = build_bonds<M>(gd.genome, gd.t, a.bits, a.c);
                     run = 0;
                     steps_sum = 0;
                     ev = run_start(src, g, st, dc, gd.grid);
@@ -1269,7 +1235,7 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
             } else if (run == 0 && ev != kEvNone) {
                 // (a candidate's run 0 ended cleanly in the first-run stage)
                 cls = ev == kEvUnbound ? JATAM_UNBOUND : JATAM_ND_SITE;
-                rec = jatam_result_t{cls, st.size, 0u, steps_sum};
+                rec = jatam_result_t{cls, st.size(), 0u, steps_sum};
                 done = true;
             } else if (run == 0) {
                 // keep run 0's occupancy: only its nonzero words are ever read
@@ -1278,13 +1244,13 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
                     occ0[w * 64] = g.occ(w);
                 }
                 osum0 = st.osum;
-                size0 = st.size;
+                size0 = st.size();
                 run = 1;
                 ev = run_start(src, g, st, dc, gd.grid);
             } else {
                 // occupancy only grows within a run, so osum is exactly the
                 // set of nonzero words
-                bool same = ev == kEvNone && st.osum == osum0 && st.size == size0;
+                bool same = ev == kEvNone && st.osum == osum0 && st.size() == size0;
                 for (uint32_t sw = osum0; same && sw != 0; sw &= sw - 1) {
                     const int w = __builtin_ctz(sw);
                     same = g.occ(w) == occ0[w * 64];
@@ -1293,7 +1259,7 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
                     cls = ev == kEvUnbound ? JATAM_UNBOUND
                         : ev == kEvAmbig   ? JATAM_ND_SITE
                                            : JATAM_ND_RUNS;
-                    rec = jatam_result_t{cls, st.size, 0u, steps_sum};
+                    rec = jatam_result_t{cls, st.size(), 0u, steps_sum};
                     done = true;
                 } else if (run == R - 1) {
                     cls = JATAM_DET;
@@ -1369,23 +1335,25 @@ static int resident_per_cu(K kernel)
     return occ;
 }
 
-template <int W, int TM>
+template <int W, class M>
 static void occupancy_of(int out[3])
 {
-    out[0] = resident_per_cu(first_run_kernel<W, TM, kInRange>);
+    out[0] = resident_per_cu(first_run_kernel<W, M, kInRange>);
     // the repeat grid runs the proof + first pass kernel and the second pass
-    const int repeat = resident_per_cu(repeat_kernel<W, TM, true>);
-    const int fused = resident_per_cu(prove_repeat_kernel<W, TM, true>);
+    const int repeat = resident_per_cu(repeat_kernel<W, M>);
+    const int fused = resident_per_cu(prove_repeat_kernel<W, M>);
     out[1] = repeat < fused ? repeat : fused;
-    out[2] = resident_per_cu(repeat_seq_kernel<W, TM, true>);
+    out[2] = resident_per_cu(repeat_seq_kernel<W, M>);
 }
 
-void batch_occupancy(int occ[2][2][3])
+void batch_occupancy(BatchOccupancy& occ)
 {
-    occupancy_of<16, 2>(occ[0][0]);
-    occupancy_of<16, 4>(occ[0][1]);
-    occupancy_of<32, 2>(occ[1][0]);
-    occupancy_of<32, 4>(occ[1][1]);
+    occupancy_of<16, Bonds2>(occ.blocks[0][kGenoTwo]);
+    occupancy_of<16, Bonds4>(occ.blocks[0][kGenoFour]);
+    occupancy_of<16, BondsC16>(occ.blocks[0][kGenoC16]);
+    occupancy_of<32, Bonds2>(occ.blocks[1][kGenoTwo]);
+    occupancy_of<32, Bonds4>(occ.blocks[1][kGenoFour]);
+    occupancy_of<32, BondsC16>(occ.blocks[1][kGenoC16]);
 }
 
 __global__ __launch_bounds__(256) void records_differ_kernel(const int4* __restrict__ x,
@@ -1424,60 +1392,48 @@ __global__ void clear_claims_kernel(uint32_t* ctr)
 }
 
 // The first-run kernel compiled for the call's input mode.
-template <int W, int TM>
+template <int W, class M>
 static void launch_first(const BatchArgs& a, uint32_t nb, hipStream_t stream, int klass)
 {
     if (a.items != nullptr)
-        hipLaunchKernelGGL((first_run_kernel<W, TM, kInItems>), dim3(nb), dim3(64), 0, stream, a,
+        hipLaunchKernelGGL((first_run_kernel<W, M, kInItems>), dim3(nb), dim3(64), 0, stream, a,
                            klass);
     else if (a.genomes != nullptr)
-        hipLaunchKernelGGL((first_run_kernel<W, TM, kInList>), dim3(nb), dim3(64), 0, stream, a,
+        hipLaunchKernelGGL((first_run_kernel<W, M, kInList>), dim3(nb), dim3(64), 0, stream, a,
                            klass);
     else
-        hipLaunchKernelGGL((first_run_kernel<W, TM, kInRange>), dim3(nb), dim3(64), 0, stream, a,
+        hipLaunchKernelGGL((first_run_kernel<W, M, kInRange>), dim3(nb), dim3(64), 0, stream, a,
                            klass);
 }
 
 // The R-lanes-per-candidate repeat kernel of grid class k for one pass.
-template <int TM>
-static void launch_repeat(const BatchArgs& a, int k, bool table, uint32_t rb, int rpass,
-                          int skip, bool store_occ, const uint32_t* qin, const uint32_t* cin,
+template <class M>
+static void launch_repeat(const BatchArgs& a, int k, uint32_t rb, int rpass, int skip,
+                          bool store_occ, const uint32_t* qin, const uint32_t* cin,
                           uint32_t* qout, uint32_t* cout, hipStream_t stream)
 {
-    if (k == 0 && table)
-        hipLaunchKernelGGL((repeat_kernel<16, TM, true>), dim3(rb), dim3(64), 0, stream, a, 0,
-                           rpass, skip, store_occ, qin, cin, qout, cout);
-    else if (k == 0)
-        hipLaunchKernelGGL((repeat_kernel<16, TM, false>), dim3(rb), dim3(64), 0, stream, a, 0,
-                           rpass, skip, store_occ, qin, cin, qout, cout);
-    else if (table)
-        hipLaunchKernelGGL((repeat_kernel<32, TM, true>), dim3(rb), dim3(64), 0, stream, a, 1,
-                           rpass, 0, false, qin, cin, qout, cout);
+    if (k == 0)
+        hipLaunchKernelGGL((repeat_kernel<16, M>), dim3(rb), dim3(64), 0, stream, a, 0, rpass,
+                           skip, store_occ, qin, cin, qout, cout);
     else
-        hipLaunchKernelGGL((repeat_kernel<32, TM, false>), dim3(rb), dim3(64), 0, stream, a, 1,
-                           rpass, 0, false, qin, cin, qout, cout);
+        hipLaunchKernelGGL((repeat_kernel<32, M>), dim3(rb), dim3(64), 0, stream, a, 1, rpass, 0,
+                           false, qin, cin, qout, cout);
 }
 
 // The proof + first repeat pass kernel of grid class k.
-template <int TM>
-static void launch_prove_repeat(const BatchArgs& a, int k, bool table, uint32_t rb, int rpass,
+template <class M>
+static void launch_prove_repeat(const BatchArgs& a, int k, uint32_t rb, int rpass,
                                 uint32_t* qout, uint32_t* cout, hipStream_t stream)
 {
-    if (k == 0 && table)
-        hipLaunchKernelGGL((prove_repeat_kernel<16, TM, true>), dim3(rb), dim3(64), 0, stream, a,
-                           0, rpass, qout, cout);
-    else if (k == 0)
-        hipLaunchKernelGGL((prove_repeat_kernel<16, TM, false>), dim3(rb), dim3(64), 0, stream, a,
-                           0, rpass, qout, cout);
-    else if (table)
-        hipLaunchKernelGGL((prove_repeat_kernel<32, TM, true>), dim3(rb), dim3(64), 0, stream, a,
-                           1, rpass, qout, cout);
+    if (k == 0)
+        hipLaunchKernelGGL((prove_repeat_kernel<16, M>), dim3(rb), dim3(64), 0, stream, a, 0,
+                           rpass, qout, cout);
     else
-        hipLaunchKernelGGL((prove_repeat_kernel<32, TM, false>), dim3(rb), dim3(64), 0, stream, a,
-                           1, rpass, qout, cout);
+        hipLaunchKernelGGL((prove_repeat_kernel<32, M>), dim3(rb), dim3(64), 0, stream, a, 1,
+                           rpass, qout, cout);
 }
 
-template <int TM>
+template <class M>
 static void launch_stages(BatchArgs a, const bool classes[2], const StageLaunch launch[2],
                           hipStream_t stream, hipEvent_t* marks, uint8_t* launched)
 {
@@ -1523,17 +1479,15 @@ static void launch_stages(BatchArgs a, const bool classes[2], const StageLaunch 
             hipLaunchKernelGGL(clear_claims_kernel, dim3(1), dim3(64), 0, stream,
                                a.ws.run_claim + k * kClaimCounters * kClaimStride);
         if (k == 0)
-            launch_first<16, TM>(a, nb, stream, 0);
+            launch_first<16, M>(a, nb, stream, 0);
         else
-            launch_first<32, TM>(a, nb, stream, 1);
+            launch_first<32, M>(a, nb, stream, 1);
         end(kStageFirst + kStagesPerClass * k);
         begin(kStageSort + kStagesPerClass * k);
         exclusive_scan(a.ws.seg_hist[k], (uint32_t)kSizeBuckets * nb, a.ws.scan_sums[k],
                        a.ws.counters + kCntCand + k, stream);
         hipLaunchKernelGGL(sort_scatter_kernel, dim3(nb), dim3(256), 0, stream, a, k);
         end(kStageSort + kStagesPerClass * k);
-        // the bond table holds colours 0..7
-        const bool table = a.c <= 8;
         const int mapping = launch[k].repeat_mapping;
         if (mapping == 2 && a.runs > kRepeatFirstRuns) {
             // two passes: the proof and the first pass (runs 0 ..
@@ -1545,10 +1499,10 @@ static void launch_stages(BatchArgs a, const bool classes[2], const StageLaunch 
             uint32_t* q1 = a.ws.cand_idx[k];
             uint32_t* c1 = a.ws.counters + kCntRepeat2 + k;   // cleared by the first runs
             begin(kStageProve + kStagesPerClass * k);
-            launch_prove_repeat<TM>(a, k, table, rb, kRepeatFirstRuns, q1, c1, stream);
+            launch_prove_repeat<M>(a, k, rb, kRepeatFirstRuns, q1, c1, stream);
             end(kStageProve + kStagesPerClass * k);
             begin(kStageRepeat + kStagesPerClass * k);
-            launch_repeat<TM>(a, k, table, rb, a.runs, k == 0 ? kRepeatFirstRuns : 0, false, q1, c1,
+            launch_repeat<M>(a, k, rb, a.runs, k == 0 ? kRepeatFirstRuns : 0, false, q1, c1,
                               nullptr, nullptr, stream);
             end(kStageRepeat + kStagesPerClass * k);
         } else {
@@ -1558,9 +1512,9 @@ static void launch_stages(BatchArgs a, const bool classes[2], const StageLaunch 
             // proof) or the one-lane-per-candidate repeat runs (mapping 1)
             begin(kStageProve + kStagesPerClass * k);
             if (k == 0)
-                hipLaunchKernelGGL((prove_kernel<16, TM>), dim3(nb), dim3(64), 0, stream, a, 0);
+                hipLaunchKernelGGL((prove_kernel<16, M>), dim3(nb), dim3(64), 0, stream, a, 0);
             else
-                hipLaunchKernelGGL((prove_kernel<32, TM>), dim3(nb), dim3(64), 0, stream, a, 1);
+                hipLaunchKernelGGL((prove_kernel<32, M>), dim3(nb), dim3(64), 0, stream, a, 1);
             const uint32_t qchunks = (uint32_t)nchunks;
             exclusive_scan(a.ws.chunk_cnt[k], qchunks, a.ws.chunk_sums[k],
                            a.ws.counters + kCntCand + k, stream, a.ws.counters + kCntCandAll + k);
@@ -1570,36 +1524,32 @@ static void launch_stages(BatchArgs a, const bool classes[2], const StageLaunch 
             end(kStageProve + kStagesPerClass * k);
             begin(kStageRepeat + kStagesPerClass * k);
             if (mapping != 1)
-                launch_repeat<TM>(a, k, table, rb, a.runs, 0, false, a.ws.sorted[k],
+                launch_repeat<M>(a, k, rb, a.runs, 0, false, a.ws.sorted[k],
                                   a.ws.counters + kCntCand + k, nullptr, nullptr, stream);
-            else if (k == 0 && table)
-                hipLaunchKernelGGL((repeat_seq_kernel<16, TM, true>), dim3(rb), dim3(64), 0, stream,
-                                   a, 0);
             else if (k == 0)
-                hipLaunchKernelGGL((repeat_seq_kernel<16, TM, false>), dim3(rb), dim3(64), 0,
-                                   stream, a, 0);
-            else if (table)
-                hipLaunchKernelGGL((repeat_seq_kernel<32, TM, true>), dim3(rb), dim3(64), 0, stream,
-                                   a, 1);
+                hipLaunchKernelGGL((repeat_seq_kernel<16, M>), dim3(rb), dim3(64), 0, stream, a,
+                                   0);
             else
-                hipLaunchKernelGGL((repeat_seq_kernel<32, TM, false>), dim3(rb), dim3(64), 0,
-                                   stream, a, 1);
+                hipLaunchKernelGGL((repeat_seq_kernel<32, M>), dim3(rb), dim3(64), 0, stream, a,
+                                   1);
             end(kStageRepeat + kStagesPerClass * k);
         }
     }
 }
 
-int launch_batched(const BatchArgs& a, const bool classes[2], const StageLaunch launch[2], int tm,
-                   hipStream_t stream, hipEvent_t* marks, uint8_t* launched)
+int launch_batched(const BatchArgs& a, const bool classes[2], const StageLaunch launch[2],
+                   int geno, hipStream_t stream, hipEvent_t* marks, uint8_t* launched)
 {
     if (launched)
         for (int s = 0; s < kStages; ++s)
             launched[s] = 0;
     if (a.n > 0) {
-        if (tm == 2)
-            launch_stages<2>(a, classes, launch, stream, marks, launched);
+        if (geno == kGenoTwo)
+            launch_stages<Bonds2>(a, classes, launch, stream, marks, launched);
+        else if (geno == kGenoFour)
+            launch_stages<Bonds4>(a, classes, launch, stream, marks, launched);
         else
-            launch_stages<4>(a, classes, launch, stream, marks, launched);
+            launch_stages<BondsC16>(a, classes, launch, stream, marks, launched);
     }
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }

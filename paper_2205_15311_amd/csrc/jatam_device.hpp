@@ -5,10 +5,10 @@
 //   philox4x32_10   counter-based generator (Salmon et al., SC'11) that
 //                   replaces the paper's cuRAND XORWOW (§3)
 //   oaat_*          Jenkins one-at-a-time hash (App. F.4), on unsigned bytes
-//   Model           a decoded genotype: tiles, their rotations, duplicate /
-//                   symmetric orientations merged (§3.2), and the bonding
-//                   options of every oriented tile (interaction rule of
-//                   App. B.2: colours bond in adjacent pairs 1-2, 3-4, ...)
+//   Bonds           a decoded genotype: its tiles and, per colour, the tile
+//                   that bonds to it, duplicate and symmetric orientations
+//                   merged (§3.2; interaction rule of App. B.2: colours
+//                   bond in adjacent pairs 1-2, 3-4, ...)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -70,271 +70,184 @@ __device__ __forceinline__ uint32_t oaat_finish(uint32_t h)
 }
 
 // ---------------------------------------------------------------------------
-// A decoded genotype of at most TM tiles (TM = 2 or 4).
+// A decoded genotype of at most TM tiles (TM = 2 or 4) over at most 8 colours
+// (kC16: 16).
 //
-// Oriented tile k = 4*i + r is tile i turned clockwise by r quarter turns; it
-// is held as a 16-bit word of four nibbles, side d (N=0, E=1, S=2, W=3) in
-// bits 4d..4d+3.  For every side s the colours that all 4*TM oriented tiles
-// show on s are packed as nibble k of side_col(s), so one SWAR comparison
-// finds every oriented tile that shows a given colour there.  `reps` has bit
-// 4k+3 set for each k that is the first oriented tile with its colour tuple:
-// duplicates and symmetric orientations collapse onto that representative.
-// With TM = 2 every word is 32 bits, with TM = 4 64 bits.
+// A colour tuple is a word of four bytes, byte d the colour of side d (N=0,
+// E=1, S=2, W=3).  Oriented tile k = 4*i + r is tile i turned clockwise by r
+// quarter turns: its tuple is tile i's word rotated left by 8r bits.  Of the
+// orientations with one tuple only the first counts (the representative):
+// turn r of a tile of period 1, 2 or 4 is turn r mod the period, and a tile
+// in the orbit of an earlier one adds nothing.
+//
+// What bonds to a placed tile's side depends on the side's colour x alone,
+// up to a turn: if side e of tile i has x's partner colour, turn
+// r = d + 2 - e (mod 4) of tile i shows it towards a tile placed d-wards of
+// the site.  So one byte per colour holds everything:
+//   bit 7     some tile bonds to colour x
+//   bit 6     two or more distinct tuples do (the rest is then meaningless)
+//   bits 5-4  the tile's period - 1 (3, 1 or 0)
+//   bits 3-2  the tile i
+//   bits 1-0  (2 - e) mod 4
+// and a byte permute looks up all four sides of a placed tile at once: about
+// ten instructions for the four neighbours of a placement, where a SWAR
+// comparison of each side with every oriented tile took about eighty.
 // ---------------------------------------------------------------------------
-template <int TM>
-struct Model {
-    static_assert(TM == 2 || TM == 4, "TM must be 2 or 4");
-    using Word = typename std::conditional<TM == 2, uint32_t, uint64_t>::type;
-    static constexpr int kOriented = 4 * TM;
-    static constexpr Word kOnes = (Word)0x1111111111111111ull;
-    static constexpr Word kLow3 = (Word)0x7777777777777777ull;
+constexpr uint32_t kSiteAny = 0x80808080u;     // bit 7 of every byte
+constexpr uint32_t kSiteMulti = 0x40404040u;   // bit 6 of every byte
 
-    Word tiles;          // tile i in bits 16i..16i+15, nibble d = colour of side d
-    // nibble k = colour oriented tile k shows on side s; four scalars rather
-    // than an array, so that a side chosen at run time stays in registers
-    Word cols0, cols1, cols2, cols3;
-    Word reps;           // bit 4k+3 set for representative oriented tiles
-    int c;               // colour count
-
-    // by value selects: a choice between the members as lvalues lets the
-    // compiler address the struct by a run-time offset, in scratch memory
-    __device__ __forceinline__ static Word pick(bool c, Word x, Word y) { return c ? x : y; }
-    __device__ __forceinline__ Word side_col(int s) const
-    {
-        return pick(s < 2, pick(s == 0, cols0, cols1), pick(s == 2, cols2, cols3));
-    }
-};
-
-__device__ __forceinline__ uint32_t rotate_tile(uint32_t tile, int r)
-{
-    // side d shows the colour of side (d - r) mod 4: nibbles move up by r
-    const uint32_t s = 4u * (uint32_t)r;
-    return ((tile << s) | (tile >> ((16u - s) & 15u))) & 0xFFFFu;
-}
-
-// Nibbles of a 16-bit tile word in reverse order (side 3 first).
-__device__ __forceinline__ uint32_t reverse_nibbles16(uint32_t t)
-{
-    return ((t & 0xFu) << 12) | ((t & 0xF0u) << 4) | ((t >> 4) & 0xF0u) | ((t >> 12) & 0xFu);
-}
-
-template <int TM>
-__device__ __forceinline__ Model<TM> build_model(uint64_t genome, int t, int bits, int c)
-{
-    using M = Model<TM>;
-    using Word = typename M::Word;
-    M m;
-    const uint32_t cmask = (uint32_t)c - 1u;
-    uint32_t tile[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        uint32_t w = 0;
-        if (i < t) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const int shift = bits * (4 * t - 1 - (4 * i + d));
-                w |= (uint32_t)((genome >> shift) & cmask) << (4 * d);
-            }
-        }
-        tile[i] = w;
-    }
-    m.tiles = 0;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-        m.tiles |= (Word)tile[i] << (16 * i);
-    // side s of rotation r shows colour (s - r) mod 4: over r = 0..3 that is
-    // the tile's nibbles reversed, rotated by s + 1
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        Word col = 0;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-            col |= (Word)rotate_tile(reverse_nibbles16(tile[i]), (s + 1) & 3) << (16 * i);
-        if (s == 0)
-            m.cols0 = col;
-        else if (s == 1)
-            m.cols1 = col;
-        else if (s == 2)
-            m.cols2 = col;
-        else
-            m.cols3 = col;
-    }
-    // representatives: the first orientation of each distinct colour tuple.
-    // Rotation r of a tile repeats rotation 0 iff the tile has r-fold symmetry;
-    // a later tile in the orbit of an earlier one repeats all of its tuples.
-    Word reps = 0;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const uint32_t r1 = rotate_tile(tile[i], 1), r2 = rotate_tile(tile[i], 2);
-        const bool sym4 = r1 == tile[i];
-        const bool sym2 = r2 == tile[i];
-        uint32_t own = sym4 ? 0x1u : sym2 ? 0x3u : 0xFu;     // rotations kept
-        bool repeated = i >= t;
-#pragma unroll
-        for (int i2 = 0; i2 < i; ++i2) {
-            const uint32_t u = tile[i2];
-            repeated = repeated || (i2 < t && (tile[i] == u || r1 == u || r2 == u ||
-                                               rotate_tile(tile[i], 3) == u));
-        }
-        own = repeated ? 0u : own;
-        // bit 4k+3 for k = 4i + r, r in own
-        const uint32_t bitsr = ((own & 1u) << 3) | ((own & 2u) << 6) | ((own & 4u) << 9) |
-                               ((own & 8u) << 12);
-        reps |= (Word)bitsr << (16 * i);
-    }
-    m.reps = reps;
-    m.c = c;
-    return m;
-}
-
-// Colour tuple of oriented tile k: a shift, never an indexed load.
-template <int TM>
-__device__ __forceinline__ uint32_t oriented_tile(const Model<TM>& m, int k)
-{
-    const uint32_t w = (uint32_t)(m.tiles >> (16 * (k >> 2))) & 0xFFFFu;
-    return rotate_tile(w, k & 3);
-}
-
-// Colour tuple of the seed: tile 0, unrotated.
-template <int TM>
-__device__ __forceinline__ uint32_t seed_tile(const Model<TM>& m)
-{
-    return (uint32_t)m.tiles & 0xFFFFu;
-}
-
-// Colour k in every nibble of a model word (k < 16): the byte kk copied to
-// all four bytes by a byte permute.  (Written as k * 0x11111111 it becomes a
-// full 32-bit multiply, a quarter-rate instruction.)
-template <class Word>
-__device__ __forceinline__ Word nibble_splat(uint32_t k)
-{
-    const uint32_t b = k | (k << 4);
-    const uint32_t w = __builtin_amdgcn_perm(b, b, 0u);   // selector 0: byte 0 everywhere
-    if constexpr (sizeof(Word) == 8)
-        return ((uint64_t)w << 32) | w;
-    else
-        return w;
-}
-
-// Bonding options of the empty site next to a placed tile (colour tuple
-// `tuple`) in direction d: the distinct representatives that show the
-// partner of the tile's side-d colour on their side facing back.  Returns
-// min(count, 2) in bits 4..5 and the lowest representative id in bits 0..3
-// (0 when nothing bonds).  No branches: a colour without a partner masks
-// the match instead.
-// The representatives behind site_options: bit 4k+3 of the result is set
-// for each representative k that bonds.
-template <int TM>
-__device__ __forceinline__ typename Model<TM>::Word site_match(const Model<TM>& m, uint32_t tuple,
-                                                               int d)
-{
-    using M = Model<TM>;
-    using Word = typename M::Word;
-    const int x = (int)((tuple >> (4 * d)) & 15u);
-    // partner colour: 1<->2, 3<->4, ...; 0 and a last odd colour have none
-    const int p = ((x + 1) ^ 1) - 1;
-    const bool bonds = p >= 0 && p < m.c;
-    const Word v = m.side_col((d + 2) & 3) ^ nibble_splat<Word>((uint32_t)p & 15u);
-    // high bit of each nibble set iff the nibble is nonzero (no carries escape)
-    const Word nonzero = v | ((v & M::kLow3) + M::kLow3);
-    return bonds ? (~nonzero & m.reps) : (Word)0;
-}
-
-// site_options as its three parts, without packing them into a code: any
-// representative bonds, two or more do, the lowest one's id (meaningless
-// when none does).
+// A site's options as parts: any tile bonds, two or more do, the id of the
+// tile if exactly one does.
 struct SiteOpts {
     bool has, multi;
     uint32_t id;
 };
 
-template <int TM>
-__device__ __forceinline__ SiteOpts site_options_split(const Model<TM>& m, uint32_t tuple, int d)
+__device__ __forceinline__ SiteOpts split_code(uint32_t code)
 {
-    const typename Model<TM>::Word match = site_match(m, tuple, d);
-    SiteOpts o;
-    o.has = match != 0;
-    o.multi = (match & (match - 1)) != 0;
-    // the top bit is representative 4 TM - 1's: or-ing it in changes no
-    // lowest set bit and keeps the count of trailing zeros defined
-    if constexpr (TM == 2)
-        o.id = (uint32_t)__builtin_ctz((uint32_t)match | 0x80000000u) >> 2;
-    else
-        o.id = (uint32_t)__builtin_ctzll((uint64_t)match | (1ull << 63)) >> 2;
-    return o;
+    return SiteOpts{(code & 0x80u) != 0, (code & 0x40u) != 0, code & 15u};
 }
 
-template <int TM>
-__device__ __forceinline__ uint32_t site_options(const Model<TM>& m, uint32_t tuple, int d)
+template <int TM, bool kC16>
+struct Bonds {
+    static_assert(TM == 2 || TM == 4, "TM must be 2 or 4");
+    // scalars, never arrays: a run-time index would put them in scratch memory
+    uint32_t t0, t1, t2, t3;   // tiles (t2, t3 only for TM = 4)
+    uint32_t lo, hi;           // the bytes of colours 0-3 and 4-7
+    uint32_t lo2, hi2;         // of colours 8-11 and 12-15 (kC16 only)
+
+    // Colour tuple of the seed: tile 0, unrotated.
+    __device__ __forceinline__ uint32_t seed() const { return t0; }
+
+    // Colour tuple of oriented tile k.
+    __device__ __forceinline__ uint32_t oriented(uint32_t k) const
+    {
+        uint32_t w = (k & 4u) ? t1 : t0;
+        if constexpr (TM == 4) {
+            const uint32_t w2 = (k & 4u) ? t3 : t2;
+            w = (k & 8u) ? w2 : w;
+        }
+        // rotate left by 8 (k mod 4): the shift amount counts mod 32
+        return __builtin_amdgcn_alignbit(w, w, 0u - 8u * k);
+    }
+
+    // The four sites around a tile with colour tuple `tuple`: byte d is 0 if
+    // nothing bonds in direction d, else 0x80, with 0x40 if two or more
+    // distinct tiles do, and the representative's id in the low four bits.
+    __device__ __forceinline__ uint32_t codes(uint32_t tuple) const
+    {
+        uint32_t w;
+        if constexpr (kC16) {
+            const uint32_t sel = tuple & 0x07070707u;
+            const uint32_t up = (tuple >> 3) & 0x01010101u, mask = (up << 8) - up;
+            w = (__builtin_amdgcn_perm(hi2, lo2, sel) & mask) |
+                (__builtin_amdgcn_perm(hi, lo, sel) & ~mask);
+        } else {
+            w = __builtin_amdgcn_perm(hi, lo, tuple);
+        }
+        // turn d + 2 - e, reduced by the tile's period
+        const uint32_t turn = ((w & 0x03030303u) + 0x03020100u) & (w >> 4) & 0x03030303u;
+        return (w & 0xCCCCCCCCu) | turn;
+    }
+};
+
+// The partner of colour y of c <= 8 colours, times 8, in byte y of the 64-bit
+// constant (0 for a colour without a partner).
+__device__ __forceinline__ uint64_t partner_shifts(int c)
 {
-    using Word = typename Model<TM>::Word;
-    const Word match = site_match(m, tuple, d);
-    const Word lowest = match != 0 ? match : (Word)1;   // ctz of 0 is undefined
-    uint32_t id;
-    if constexpr (TM == 2)
-        id = (uint32_t)__builtin_ctz((uint32_t)lowest) >> 2;
-    else
-        id = (uint32_t)__builtin_ctzll((uint64_t)lowest) >> 2;
-    const uint32_t count = (match & (match - 1)) ? 2u : 1u;
-    return match != 0 ? ((count << 4) | id) : 0u;
+    return c == 8 ? 0x0028301820081000ull : c == 4 ? 0x0000000000081000ull : 0ull;
 }
 
-// ---------------------------------------------------------------------------
-// Sources of bond options for the assembly loop.  Both give, for a placed
-// tile's colour tuple and a direction d, the options code of site_options;
-// the seed's tuple; and the tuple of oriented tile k.
-// ---------------------------------------------------------------------------
-// Options found by the SWAR comparison on every call.
-template <int TM>
-struct ModelSource {
-    Model<TM> m;
-
-    __device__ __forceinline__ uint32_t options(uint32_t tuple, int d) const
-    {
-        return site_options(m, tuple, d);
-    }
-    __device__ __forceinline__ SiteOpts options_split(uint32_t tuple, int d) const
-    {
-        return site_options_split(m, tuple, d);
-    }
-    __device__ __forceinline__ uint32_t seed() const { return seed_tile(m); }
-    __device__ __forceinline__ uint32_t oriented(int k) const { return oriented_tile(m, k); }
+template <class M>
+struct BondsTraits;
+template <int TM, bool kC16>
+struct BondsTraits<Bonds<TM, kC16>> {
+    static constexpr int kTiles = TM;
+    static constexpr bool kWide = kC16;
 };
 
-// Options read from the genotype's bond table (c <= 8): byte x of side[d]
-// is site_options(m, x << 4d, d), the code of shown colour x on side d.  d
-// is a compile-time constant at every call and x only selects a shift, so
-// the table stays in registers (a run-time index into an array, or a choice
-// between two of its elements, would put it in scratch memory).
-template <int TM>
-struct TableSource {
-    Model<TM> m;
-    uint64_t side[4];
-
-    __device__ __forceinline__ uint32_t options(uint32_t tuple, int d) const
-    {
-        const uint32_t x = (tuple >> (4 * d)) & 7u;
-        return (uint32_t)(side[d] >> (8u * x)) & 0x3Fu;
-    }
-    __device__ __forceinline__ SiteOpts options_split(uint32_t tuple, int d) const
-    {
-        const uint32_t code = options(tuple, d);
-        return SiteOpts{code != 0, (code >> 4) >= 2, code & 15u};
-    }
-    __device__ __forceinline__ uint32_t seed() const { return seed_tile(m); }
-    __device__ __forceinline__ uint32_t oriented(int k) const { return oriented_tile(m, k); }
-};
-
-// Word j (0..7) of the bond table: the low (j even) or high half of side[j / 2].
-template <int TM>
-__device__ __forceinline__ uint32_t bond_table_word(const Model<TM>& m, int j)
+template <class M>
+__device__ __forceinline__ M build_bonds(uint64_t genome, int t, int bits, int c)
 {
-    const int d = j >> 1, x0 = 4 * (j & 1);
-    uint32_t w = 0;
+    constexpr int TM = BondsTraits<M>::kTiles;
+    constexpr bool kC16 = BondsTraits<M>::kWide;
+    const uint32_t cmask = (uint32_t)c - 1u;
+    uint32_t tile[TM];
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
-        w |= site_options(m, (uint32_t)(x0 + b) << (4 * d), d) << (8 * b);
-    return w;
+    for (int i = 0; i < TM; ++i) {
+        // tile i's 4 * bits <= 16 bits, N highest
+        const uint32_t v = i < t ? (uint32_t)(genome >> (4 * bits * (t - 1 - i))) : 0u;
+        tile[i] = ((v >> (3 * bits)) & cmask) | (((v >> (2 * bits)) & cmask) << 8) |
+                  (((v >> bits) & cmask) << 16) | ((v & cmask) << 24);
+    }
+    const uint64_t shifts = partner_shifts(c);
+    uint64_t tab = 0, tab2 = 0, multi = 0, multi2 = 0;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const uint32_t w = tile[i];
+        const uint32_t r1 = __builtin_amdgcn_alignbit(w, w, 24u);
+        const uint32_t r2 = __builtin_amdgcn_alignbit(w, w, 16u);
+        const uint32_t r3 = __builtin_amdgcn_alignbit(w, w, 8u);
+        const bool sym4 = r1 == w, sym2 = r2 == w;
+        bool repeated = false;
+#pragma unroll
+        for (int k = 0; k < i; ++k)
+            repeated = repeated | (w == tile[k]) | (r1 == tile[k]) | (r2 == tile[k]) |
+                       (r3 == tile[k]);
+        const uint32_t base = (sym4 ? 0x80u : sym2 ? 0x90u : 0xB0u) | ((uint32_t)i << 2);
+        // one entry per side of the first period; none for a repeated tile
+        // (an absent tile shows colour 0 only, which has no partner)
+        if constexpr (kC16) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t y = (w >> (8 * e)) & 0xFFu;
+                const uint32_t x = ((y + 1u) ^ 1u) - 1u;   // its partner, if below c
+                const bool keep = !repeated && x < (uint32_t)c && (e == 0 || !sym4) &&
+                                  (e < 2 || !sym2);
+                const uint64_t v = (uint64_t)(keep ? base | (uint32_t)((2 - e) & 3) : 0u)
+                                   << (8u * (x & 7u));
+                const uint64_t v1 = x < 8u ? v : 0ull, v2 = x < 8u ? 0ull : v;
+                multi |= tab & v1;
+                tab |= v1;
+                multi2 |= tab2 & v2;
+                tab2 |= v2;
+            }
+        } else {
+            const uint32_t at = __builtin_amdgcn_perm((uint32_t)(shifts >> 32), (uint32_t)shifts, w);
+            const uint32_t first = repeated ? 0u : base | 2u;
+            const uint32_t rest = sym4 ? 0u : first, last = sym2 ? 0u : first;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t b = e == 0 ? first : e == 1 ? rest : last;
+                // (2 - e) mod 4 = 2, 1, 0, 3 in the low bits of a kept entry
+                const uint32_t flip = e == 0 ? 0u : e == 1 ? 3u : e == 2 ? 2u : 1u;
+                const uint64_t v = (uint64_t)(b != 0u ? b ^ flip : 0u) << ((at >> (8 * e)) & 0xFFu);
+                multi |= tab & v;
+                tab |= v;
+            }
+        }
+    }
+    constexpr uint64_t kAny = 0x8080808080808080ull;
+    tab |= (multi & kAny) >> 1;
+    tab2 |= (multi2 & kAny) >> 1;
+    if constexpr (!kC16)
+        tab &= ~0xFFull;   // sides without a partner were entered at colour 0
+    M m;
+    m.t0 = tile[0];
+    m.t1 = tile[1];
+    m.t2 = TM == 4 ? tile[2 % TM] : 0u;
+    m.t3 = TM == 4 ? tile[3 % TM] : 0u;
+    m.lo = (uint32_t)tab;
+    m.hi = (uint32_t)(tab >> 32);
+    m.lo2 = (uint32_t)tab2;
+    m.hi2 = (uint32_t)(tab2 >> 32);
+    return m;
 }
+
+// The genotype types that the kernels are compiled for: up to two tiles, up
+// to four, and any number over 16 colours.
+using Bonds2 = Bonds<2, false>;
+using Bonds4 = Bonds<4, false>;
+using BondsC16 = Bonds<4, true>;
 
 }  // namespace jatam

@@ -141,14 +141,25 @@ struct StageLaunch {
                           // 2: kRepeatFirstRuns lanes first, R lanes for the undecided
 };
 
-// occ[grid class][TM == 2 ? 0 : 1][0 first runs, 1 repeat runs (R lanes per
+// Genotype types that the kernels are compiled for (jatam_device.hpp): up to
+// two tiles, up to four, and any number over 16 colours.
+enum { kGenoTwo = 0, kGenoFour = 1, kGenoC16 = 2, kGenoKinds = 3 };
+inline int geno_kind(int max_t, int c)
+{
+    return c > 8 ? kGenoC16 : max_t <= 2 ? kGenoTwo : kGenoFour;
+}
+
+// blocks[grid class][genotype type][0 first runs, 1 repeat runs (R lanes per
 // candidate), 2 repeat runs (one lane per candidate)]: resident one-wave
 // blocks per CU of the stage kernels.
-void batch_occupancy(int occ[2][2][3]);
+struct BatchOccupancy {
+    int blocks[2][kGenoKinds][3];
+};
+void batch_occupancy(BatchOccupancy& occ);
 // Default launch parameters of a grid class.
 jatam_tuning_t default_tuning(int klass);
 // Largest first-run grid (one-wave blocks) over the classes and tile bounds.
-int max_first_blocks(const int occ[2][2][3], int cus);
+int max_first_blocks(const BatchOccupancy& occ, int cus);
 // Whether the size scan can cover that many first-run blocks.
 bool scan_fits(int max_blocks);
 // Lays out a DeviceWorkspace for calls of up to max_n genotypes and first-run
@@ -206,14 +217,14 @@ BatchArgs batch_args_for(const Params& p, int64_t n, jatam_result_t* out, uint64
 // Launches the pipeline with launch parameters tn[grid class], capped by the
 // residency limits occ on a device of `cus` compute units.  grid_limit: the
 // call's uniform G, or 0 for mixed items (both classes).
-int launch_tuned(const jatam_tuning_t tn[2], const int occ[2][2][3], int cus, BatchArgs a,
+int launch_tuned(const jatam_tuning_t tn[2], const BatchOccupancy& occ, int cus, BatchArgs a,
                  int grid_limit, int max_t, hipStream_t stream, hipEvent_t* marks,
                  uint8_t* launched);
 int batch_init_small_hash(uint32_t* small_hash, hipStream_t stream);
 // When `marks` is not null, an event is recorded on the stream before stage
 // s (marks[2s]) and after it (marks[2s+1]), and launched[s] is set.
-int launch_batched(const BatchArgs& a, const bool classes[2], const StageLaunch launch[2], int tm,
-                   hipStream_t stream, hipEvent_t* marks, uint8_t* launched);
+int launch_batched(const BatchArgs& a, const bool classes[2], const StageLaunch launch[2],
+                   int geno, hipStream_t stream, hipEvent_t* marks, uint8_t* launched);
 // Slice counter of a replayed enumeration: set to 0, or advanced by one.
 int launch_slice_reset(uint32_t* counter, hipStream_t stream);
 int launch_slice_advance(uint32_t* counter, hipStream_t stream);

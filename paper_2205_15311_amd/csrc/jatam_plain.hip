@@ -11,13 +11,13 @@ namespace jatam {
 // Full classification of one genotype (§3.2): up to R runs, first witness
 // in run order decides.  kVariant: JATAM_VARIANT_* flags (C4 hash, movelist
 // traversal with the lane's stack in `stk`).
-template <int W, int B, int TM, int kVariant = 0>
+template <int W, int B, class M, int kVariant = 0>
 __device__ jatam_result_t classify_genotype(LaneGrid<W, B>& g, RunState& st, uint64_t genome,
                                             uint64_t rng_id, const Params& prm,
                                             LaneStack<B> stk = LaneStack<B>{nullptr})
 {
     using Geo = Geometry<W>;
-    const ModelSource<TM> m{build_model<TM>(genome, prm.t, prm.bits, prm.c)};
+    const M m = build_bonds<M>(genome, prm.t, prm.bits, prm.c);
     const uint32_t rid_lo = (uint32_t)rng_id, rid_hi = (uint32_t)(rng_id >> 32);
     uint32_t occ0[Geo::kWords];
     int size0 = 0;
@@ -33,13 +33,13 @@ __device__ jatam_result_t classify_genotype(LaneGrid<W, B>& g, RunState& st, uin
         if (ev == kEvCorrupt)
             return jatam_result_t{JATAM_INVALID, 0, 0u, 0};
         if (ev != kEvNone)
-            return jatam_result_t{ev == kEvUnbound ? JATAM_UNBOUND : JATAM_ND_SITE, st.size, 0u,
+            return jatam_result_t{ev == kEvUnbound ? JATAM_UNBOUND : JATAM_ND_SITE, st.size(), 0u,
                                   work};
         if (r == 0) {
 #pragma unroll
             for (int w = 0; w < Geo::kWords; ++w)
                 occ0[w] = (st.osum >> w) & 1u ? g.occ(w) : 0u;
-            size0 = st.size;
+            size0 = st.size();
             if (!st.choice)
                 break;   // no draw was ever made: every run is this run
         } else {
@@ -48,7 +48,7 @@ __device__ jatam_result_t classify_genotype(LaneGrid<W, B>& g, RunState& st, uin
             for (int w = 0; w < Geo::kWords; ++w)
                 same = same && (((st.osum >> w) & 1u ? g.occ(w) : 0u) == occ0[w]);
             if (!same)
-                return jatam_result_t{JATAM_ND_RUNS, st.size, 0u, work};
+                return jatam_result_t{JATAM_ND_RUNS, st.size(), 0u, work};
         }
     }
     uint32_t hash;
@@ -59,7 +59,7 @@ __device__ jatam_result_t classify_genotype(LaneGrid<W, B>& g, RunState& st, uin
     return jatam_result_t{JATAM_DET, size0, hash, work};
 }
 
-template <int W, int B, int TM>
+template <int W, int B, class M>
 __global__ __launch_bounds__(B) void classify_plain_kernel(const uint64_t* __restrict__ genomes,
                                                            uint64_t first, int64_t n, Params prm,
                                                            jatam_result_t* __restrict__ out)
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(B) void classify_plain_kernel(const uint64_t* __res
         return;
     LaneGrid<W, B> g{smem + threadIdx.x};
     g.clear_all();
-    RunState st{0, 0, 0, 0, 0, false};
+    RunState st{};
 
     const uint64_t genome = genomes ? genomes[i] : first + (uint64_t)i;
     jatam_result_t rec;
@@ -79,14 +79,14 @@ __global__ __launch_bounds__(B) void classify_plain_kernel(const uint64_t* __res
         rec = jatam_result_t{JATAM_INVALID, 0, 0u, 0};
     } else {
         const uint64_t rng_id = genome | ((uint64_t)(uint32_t)prm.t << 56);
-        rec = classify_genotype<W, B, TM>(g, st, genome, rng_id, prm);
+        rec = classify_genotype<W, B, M>(g, st, genome, rng_id, prm);
     }
     out[i] = rec;
 }
 
 // The plain kernel with a classification variant: the lane's movelist stack
 // (kStackWords words) follows the grid words of all lanes in LDS.
-template <int W, int B, int TM, int kVariant>
+template <int W, int B, class M, int kVariant>
 __global__ __launch_bounds__(B) void classify_variant_kernel(const uint64_t* __restrict__ genomes,
                                                              uint64_t first, int64_t n,
                                                              Params prm,
@@ -101,24 +101,24 @@ __global__ __launch_bounds__(B) void classify_variant_kernel(const uint64_t* __r
     LaneGrid<W, B> g{smem + threadIdx.x};
     g.clear_all();
     LaneStack<B> stk{smem + Geo::kLaneWords * B + threadIdx.x};
-    RunState st{0, 0, 0, 0, 0, false};
+    RunState st{};
     const uint64_t genome = genomes ? genomes[i] : first + (uint64_t)i;
     jatam_result_t rec;
     if (prm.genome_bits < 64 && (genome >> prm.genome_bits) != 0) {
         rec = jatam_result_t{JATAM_INVALID, 0, 0u, 0};
     } else {
         const uint64_t rng_id = genome | ((uint64_t)(uint32_t)prm.t << 56);
-        rec = classify_genotype<W, B, TM, kVariant>(g, st, genome, rng_id, prm, stk);
+        rec = classify_genotype<W, B, M, kVariant>(g, st, genome, rng_id, prm, stk);
     }
     out[i] = rec;
 }
 
-template <int W, int B, int TM, int kVariant>
+template <int W, int B, class M, int kVariant>
 static void launch_variant_t(const uint64_t* genomes, uint64_t first, int64_t n,
                              const Params& prm, jatam_result_t* out, hipStream_t stream)
 {
     const int64_t blocks = (n + B - 1) / B;
-    hipLaunchKernelGGL((classify_variant_kernel<W, B, TM, kVariant>), dim3((unsigned)blocks),
+    hipLaunchKernelGGL((classify_variant_kernel<W, B, M, kVariant>), dim3((unsigned)blocks),
                        dim3(B), 0, stream, genomes, first, n, prm, out);
 }
 
@@ -126,17 +126,21 @@ template <int kVariant>
 static void launch_variant_v(const uint64_t* genomes, uint64_t first, int64_t n,
                              const Params& prm, jatam_result_t* out, hipStream_t stream)
 {
-    const bool small = prm.t <= 2;
+    const int geno = geno_kind(prm.t, prm.c);
     if (prm.grid <= 16) {
-        if (small)
-            launch_variant_t<16, 64, 2, kVariant>(genomes, first, n, prm, out, stream);
+        if (geno == kGenoTwo)
+            launch_variant_t<16, 64, Bonds2, kVariant>(genomes, first, n, prm, out, stream);
+        else if (geno == kGenoFour)
+            launch_variant_t<16, 64, Bonds4, kVariant>(genomes, first, n, prm, out, stream);
         else
-            launch_variant_t<16, 64, 4, kVariant>(genomes, first, n, prm, out, stream);
+            launch_variant_t<16, 64, BondsC16, kVariant>(genomes, first, n, prm, out, stream);
     } else if constexpr ((kVariant & JATAM_VARIANT_LIFO) == 0) {
-        if (small)
-            launch_variant_t<32, 64, 2, kVariant>(genomes, first, n, prm, out, stream);
+        if (geno == kGenoTwo)
+            launch_variant_t<32, 64, Bonds2, kVariant>(genomes, first, n, prm, out, stream);
+        else if (geno == kGenoFour)
+            launch_variant_t<32, 64, Bonds4, kVariant>(genomes, first, n, prm, out, stream);
         else
-            launch_variant_t<32, 64, 4, kVariant>(genomes, first, n, prm, out, stream);
+            launch_variant_t<32, 64, BondsC16, kVariant>(genomes, first, n, prm, out, stream);
     }
 }
 
@@ -157,12 +161,12 @@ int launch_variant(const uint64_t* genomes, uint64_t first, int64_t n, const Par
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }
 
-template <int W, int B, int TM>
+template <int W, int B, class M>
 static void launch_plain_t(const uint64_t* genomes, uint64_t first, int64_t n, const Params& prm,
                            jatam_result_t* out, hipStream_t stream)
 {
     const int64_t blocks = (n + B - 1) / B;
-    hipLaunchKernelGGL((classify_plain_kernel<W, B, TM>), dim3((unsigned)blocks), dim3(B), 0,
+    hipLaunchKernelGGL((classify_plain_kernel<W, B, M>), dim3((unsigned)blocks), dim3(B), 0,
                        stream, genomes, first, n, prm, out);
 }
 
@@ -171,17 +175,21 @@ int launch_plain(const uint64_t* genomes, uint64_t first, int64_t n, const Param
 {
     if (n == 0)
         return JATAM_OK;
-    const bool small = prm.t <= 2;
+    const int geno = geno_kind(prm.t, prm.c);
     if (prm.grid <= 16) {
-        if (small)
-            launch_plain_t<16, 256, 2>(genomes, first, n, prm, out, stream);
+        if (geno == kGenoTwo)
+            launch_plain_t<16, 256, Bonds2>(genomes, first, n, prm, out, stream);
+        else if (geno == kGenoFour)
+            launch_plain_t<16, 256, Bonds4>(genomes, first, n, prm, out, stream);
         else
-            launch_plain_t<16, 256, 4>(genomes, first, n, prm, out, stream);
+            launch_plain_t<16, 256, BondsC16>(genomes, first, n, prm, out, stream);
     } else {
-        if (small)
-            launch_plain_t<32, 64, 2>(genomes, first, n, prm, out, stream);
+        if (geno == kGenoTwo)
+            launch_plain_t<32, 64, Bonds2>(genomes, first, n, prm, out, stream);
+        else if (geno == kGenoFour)
+            launch_plain_t<32, 64, Bonds4>(genomes, first, n, prm, out, stream);
         else
-            launch_plain_t<32, 64, 4>(genomes, first, n, prm, out, stream);
+            launch_plain_t<32, 64, BondsC16>(genomes, first, n, prm, out, stream);
     }
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }

@@ -23,7 +23,7 @@ constexpr int kMaxDevices = 64;
 struct StaticDevice {
     bool ready;
     int cus;
-    int occ[2][2][3];
+    jatam::BatchOccupancy occ;
     uint32_t small_hash[2];
     jatam::DeviceWorkspace ws;
 };

@@ -116,7 +116,7 @@ __device__ __forceinline__ bool genome_ok(const TruthArgs& a, uint64_t g)
 // ---------------------------------------------------------------------------
 // Stage 1: one run per genotype; events and proofs decide, the rest queue.
 // ---------------------------------------------------------------------------
-template <int W, int B, int TM>
+template <int W, int B, class M>
 __global__ __launch_bounds__(B) void truth_first_kernel(TruthArgs a)
 {
     using Geo = Geometry<W>;
@@ -126,11 +126,11 @@ __global__ __launch_bounds__(B) void truth_first_kernel(TruthArgs a)
     if (i < (uint64_t)a.n) {
         LaneGrid<W, B> g{smem + threadIdx.x};
         g.clear_all();
-        RunState st{0, 0, 0, 0, 0, false};
+        RunState st{};
         const uint64_t genome = truth_genome(a, i);
         jatam_result_t rec{JATAM_INVALID, 0, 0u, 0};
         if (genome_ok(a, genome)) {
-            const ModelSource<TM> m{build_model<TM>(genome, a.t, a.bits, a.c)};
+            const M m = build_bonds<M>(genome, a.t, a.bits, a.c);
             const uint64_t rid = genome | ((uint64_t)(uint32_t)a.t << 56);
             const int ev = run_assembly(m, g, st, a.grid, 0, a.key0, a.key1, (uint32_t)rid,
                                         (uint32_t)(rid >> 32));
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(B) void truth_first_kernel(TruthArgs a)
             } else if (ev != kEvNone) {
                 rec = jatam_result_t{JATAM_ND_SITE, 0, 0u, 0};
             } else if (!st.choice || shape_is_guarded(m, g, st, a.grid)) {
-                rec = jatam_result_t{JATAM_DET, st.size, shape_hash(g, a.grid), 0};
+                rec = jatam_result_t{JATAM_DET, st.size(), shape_hash(g, a.grid), 0};
             } else {
                 queue = true;
             }
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(B) void truth_first_kernel(TruthArgs a)
 // ---------------------------------------------------------------------------
 // Stage 2: exhaustive exploration, one wave per queued genotype.
 // ---------------------------------------------------------------------------
-template <int W, int TM>
+template <int W, class M>
 __global__ __launch_bounds__(64) void truth_explore_kernel(TruthArgs a)
 {
     using Geo = Geometry<W>;
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(64) void truth_explore_kernel(TruthArgs a)
             break;
         const uint32_t i = a.queue[k];
         const uint64_t genome = truth_genome(a, i);
-        const ModelSource<TM> m{build_model<TM>(genome, a.t, a.bits, a.c)};
+        const M m = build_bonds<M>(genome, a.t, a.bits, a.c);
         const int G = a.grid;
         const int seed = (G / 2 - 1) * W + (G / 2 - 1);
         // level 0: the seed alone (tile id 0: tile 0 unrotated)
@@ -220,13 +220,12 @@ __global__ __launch_bounds__(64) void truth_explore_kernel(TruthArgs a)
             // -- analyse the level's states, insert their successors --------
             for (uint32_t s = (uint32_t)lane; s < width; s += 64) {
                 const uint32_t* src = cur + (size_t)s * L::kWords;
-                RunState st{0, 0, 0, 0, 0, false};
+                RunState st{};
                 for (int w = 0; w < Geo::kWords; ++w) {
                     const uint32_t o = src[L::kOcc + w];
                     g.occ(w) = o;
                     g.fr(w) = 0;
                     st.osum |= (o != 0 ? 1u : 0u) << w;
-                    st.size += __popc(o);
                 }
                 for (int w = 0; w < Geo::kPendWords; ++w)
                     g.word(Geo::kPend + w) = src[L::kPend + w];
@@ -237,7 +236,7 @@ __global__ __launch_bounds__(64) void truth_explore_kernel(TruthArgs a)
                         const int p = (w << 5) | __builtin_ctz(cells);
                         const uint32_t id =
                             (g.pend_word(p) >> ((uint32_t)(p & 7) * 4u)) & 15u;
-                        const int e = update_site(m, g, st, G, p, m.oriented((int)id));
+                        const int e = update_site(m, g, st, G, p, m.oriented(id));
                         ev = e != kEvNone ? e : ev;
                     }
                 }
@@ -248,7 +247,7 @@ __global__ __launch_bounds__(64) void truth_explore_kernel(TruthArgs a)
                     terms[pos] = s;
                 } else {
                     const uint32_t h0 = src[L::kHash];
-                    for (uint32_t fs = st.fsum; fs != 0; fs &= fs - 1) {
+                    for (uint32_t fs = st.touched<W>(); fs != 0; fs &= fs - 1) {
                         const int w = __builtin_ctz(fs);
                         for (uint32_t cells = g.fr(w); cells != 0; cells &= cells - 1) {
                             const uint32_t q = (uint32_t)((w << 5) | __builtin_ctz(cells));
@@ -374,14 +373,14 @@ __global__ void truth_reset_kernel(uint32_t* counters)
         counters[threadIdx.x] = 0;
 }
 
-template <int W, int TM>
+template <int W, class M>
 static void launch_truth_t(const TruthArgs& a, int blocks, hipStream_t s)
 {
     constexpr int B = W == 16 ? 256 : 64;
     const uint64_t nb = ((uint64_t)a.n + B - 1) / B;
     if (nb > 0)
-        hipLaunchKernelGGL((truth_first_kernel<W, B, TM>), dim3((unsigned)nb), dim3(B), 0, s, a);
-    hipLaunchKernelGGL((truth_explore_kernel<W, TM>), dim3(blocks), dim3(64), 0, s, a);
+        hipLaunchKernelGGL((truth_first_kernel<W, B, M>), dim3((unsigned)nb), dim3(B), 0, s, a);
+    hipLaunchKernelGGL((truth_explore_kernel<W, M>), dim3(blocks), dim3(64), 0, s, a);
 }
 
 int launch_truth(const TruthArgs& a, int blocks, hipStream_t s)
@@ -389,17 +388,21 @@ int launch_truth(const TruthArgs& a, int blocks, hipStream_t s)
     if (a.max_level > kMaxTruthLevel || a.max_level == 0)
         return JATAM_E_INVALID_ARG;
     hipLaunchKernelGGL(truth_reset_kernel, dim3(1), dim3(64), 0, s, a.counters);
-    const bool small = a.t <= 2;
+    const int geno = geno_kind(a.t, a.c);
     if (a.grid <= 16) {
-        if (small)
-            launch_truth_t<16, 2>(a, blocks, s);
+        if (geno == kGenoTwo)
+            launch_truth_t<16, Bonds2>(a, blocks, s);
+        else if (geno == kGenoFour)
+            launch_truth_t<16, Bonds4>(a, blocks, s);
         else
-            launch_truth_t<16, 4>(a, blocks, s);
+            launch_truth_t<16, BondsC16>(a, blocks, s);
     } else {
-        if (small)
-            launch_truth_t<32, 2>(a, blocks, s);
+        if (geno == kGenoTwo)
+            launch_truth_t<32, Bonds2>(a, blocks, s);
+        else if (geno == kGenoFour)
+            launch_truth_t<32, Bonds4>(a, blocks, s);
         else
-            launch_truth_t<32, 4>(a, blocks, s);
+            launch_truth_t<32, BondsC16>(a, blocks, s);
     }
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }
