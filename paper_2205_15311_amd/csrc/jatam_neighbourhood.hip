@@ -7,13 +7,11 @@
 // 4 t log2(c) single mutants.  A phenotype is UNBOUND, non-deterministic
 // (either ND class) or a deterministic shape (size and D4 hash).
 //
-// Three kernels: the single mutants of a list or range of genotypes (for
-// classification by any classify call); the counts from the genotypes' and
-// their mutants' records; and the counts from the records of a whole space
-// (S_{1,8}, S_{2,8}: every mutant is a member, so its record is gathered at
-// genome ^ (1 << k), nothing is classified twice).  All integer work: one
-// lane per genotype, its mutants' phenotype keys held in LDS for the
-// distinct count.
+// The single mutants of a list or range of genotypes (for classification by
+// any classify call); the counts from the genotypes' and their mutants'
+// records; and the counts from the records of a whole space (S_{1,8},
+// S_{2,8}: every mutant is a member, so its record is read at genome ^
+// (1 << k), nothing is classified twice).  All integer work.
 #include "jatam_internal.hpp"
 
 namespace jatam {
@@ -71,19 +69,138 @@ __global__ __launch_bounds__(kNbLanes) void neighbourhood_kernel(
     out[i] = count_neighbourhood(lk, phenotype_key(own[i]), nbits);
 }
 
-__global__ __launch_bounds__(kNbLanes) void neighbourhood_space_kernel(
-    const jatam_result_t* __restrict__ space, uint64_t first, uint64_t n, int nbits,
-    jatam_neighbourhood_t* __restrict__ out)
+// ---------------------------------------------------------------------------
+// A whole space's counts.
+//
+// A workgroup takes a window of 2^b genotypes (genome bits 0 .. b-1) and gives
+// every phenotype it meets a number below 64 (a table of exact 64-bit keys in
+// LDS), so a genotype's mutants are a 64-bit set: the distinct count is its
+// population count.  The window's own numbers lie in LDS, one byte each: the
+// mutants of bits below b are found there, four genotypes to a word, and only
+// those of the other bits are read from the records, each as a stretch in the
+// order of the window's own genotypes, which coalesces.
+//
+// Bound by those reads, (1 + bits - b) x 16 bytes a genotype through the
+// caches, so b is as large as leaves a window for every compute unit (2^24
+// genotypes: b = 16, 64 KB of LDS).  The windows of one XCD are neighbours and
+// advance together, so of the bits above b the lowest five meet in its L2.
+// One lane per genotype that gathered all of its mutants' records and
+// compared their keys in pairs took 5.86 ms over S_{2,8}.
+// ---------------------------------------------------------------------------
+constexpr int kNbSlots = 64;
+constexpr uint32_t kNbUnknown = 0xFFu;   // no number: the table was full
+
+// The number of phenotype `key` in the window's table, entered if new.
+__device__ __forceinline__ uint32_t phenotype_number(unsigned long long* table, uint64_t key)
 {
-    __shared__ uint64_t keys[64 * kNbLanes];
-    const uint64_t i = (uint64_t)blockIdx.x * kNbLanes + threadIdx.x;
-    if (i >= n)
-        return;
-    const uint64_t g = first + i;
-    uint64_t* lk = keys + threadIdx.x;
-    for (int k = 0; k < nbits; ++k)
-        lk[k * kNbLanes] = phenotype_key(space[g ^ (1ull << k)]);
-    out[i] = count_neighbourhood(lk, phenotype_key(space[g]), nbits);
+    if (key <= 2ull)
+        return (uint32_t)key - 1u;   // UNBOUND, non-deterministic: entries 0 and 1
+    uint32_t s = ((uint32_t)key * 0x9E3779B1u ^ (uint32_t)(key >> 32) * 0x85EBCA77u) >> 26;
+    for (int probe = 0; probe < kNbSlots; ++probe, s = (s + 1) & (kNbSlots - 1)) {
+        unsigned long long seen =
+            __hip_atomic_load(&table[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (seen == 0ull)
+            seen = atomicCAS(&table[s], 0ull, (unsigned long long)key);
+        if (seen == 0ull || seen == key)
+            return s;
+    }
+    return kNbUnknown;
+}
+
+// Counts of one genotype by reading its mutants' records in pairs: where the
+// window met more phenotypes than the table holds.
+__device__ jatam_neighbourhood_t count_from_space(const jatam_result_t* space, uint64_t g,
+                                                  int nbits)
+{
+    const uint64_t own = phenotype_key(space[g]);
+    int robust = 0, evolv = 0;
+    for (int k = 0; k < nbits; ++k) {
+        const uint64_t kk = phenotype_key(space[g ^ (1ull << k)]);
+        robust += kk == own;
+        bool fresh = kk != own;
+        for (int j = 0; j < k && fresh; ++j)
+            fresh = phenotype_key(space[g ^ (1ull << j)]) != kk;
+        evolv += fresh;
+    }
+    return jatam_neighbourhood_t{robust, evolv};
+}
+
+// Four genotypes' mutants as sets of phenotype numbers.
+struct MutantSets {
+    uint64_t set[4];
+    uint32_t other;     // byte q: mutants with another phenotype than genotype q
+    uint32_t unknown;   // bit 7 of byte q: one of them has no number
+    uint32_t own;       // byte q: genotype q's number
+
+    // one mutant of each genotype, byte q the number of genotype q's
+    __device__ __forceinline__ void add(uint32_t ids)
+    {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            set[q] |= 1ull << ((ids >> (8 * q)) & 63u);
+        // numbers are below 64, so their XOR plus 0x7F has bit 7 iff they differ
+        other += ((((ids ^ own) & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) >> 7) & 0x01010101u;
+        unknown |= ids;
+    }
+};
+
+__global__ __launch_bounds__(1024) void neighbourhood_space_kernel(
+    const jatam_result_t* __restrict__ space, uint64_t first, uint64_t n, int nbits, int b,
+    uint64_t window0, uint32_t windows, jatam_neighbourhood_t* __restrict__ out)
+{
+    extern __shared__ uint32_t ids[];   // 2^b numbers, four to a word
+    __shared__ unsigned long long table[kNbSlots];
+    const uint32_t tid = threadIdx.x, threads = blockDim.x;
+    // workgroups go to the XCDs in turn: each XCD takes neighbouring windows
+    const uint32_t per_xcd = (windows + 7u) / 8u;
+    const uint32_t wi = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
+    if ((blockIdx.x >> 3) >= per_xcd || wi >= windows)
+        return;   // the whole workgroup
+    const uint64_t base = (window0 + wi) << b;
+    for (uint32_t s = tid; s < (uint32_t)kNbSlots; s += threads)
+        table[s] = s < 2u ? s + 1ull : 0ull;
+    __syncthreads();
+    const uint32_t words = (1u << b) / 4u;
+    for (uint32_t i = tid; i < words; i += threads) {
+        uint32_t v = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q)
+            v |= phenotype_number(table, phenotype_key(space[base + 4u * i + q])) << (8 * q);
+        ids[i] = v;
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < words; i += threads) {
+        const uint64_t g0 = base + 4u * i;
+        if (g0 + 3u < first || g0 >= first + n)
+            continue;
+        const uint32_t own = ids[i];
+        MutantSets m{{0ull, 0ull, 0ull, 0ull}, 0u, own, own};
+        // bits 0 and 1: the other genotypes of the word
+        m.add(((own >> 8) & 0x00FF00FFu) | ((own << 8) & 0xFF00FF00u));
+        m.add((own >> 16) | (own << 16));
+        for (int k = 2; k < b; ++k)
+            m.add(ids[i ^ (1u << (k - 2))]);
+        for (int k = b; k < nbits; ++k) {
+            const jatam_result_t* r = space + (g0 ^ (1ull << k));
+            uint32_t v = 0;
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q)
+                v |= phenotype_number(table, phenotype_key(r[q])) << (8 * q);
+            m.add(v);
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            const uint64_t g = g0 + q;
+            if (g < first || g >= first + n)
+                continue;
+            jatam_neighbourhood_t c;
+            c.robust = nbits - (int)((m.other >> (8 * q)) & 0xFFu);
+            c.evolv = __popcll(m.set[q] & ~(1ull << ((own >> (8 * q)) & 63u)));
+            if ((m.unknown >> (8 * q)) & 0x80u)
+                c = count_from_space(space, g, nbits);
+            out[g - first] = c;
+        }
+    }
 }
 
 int launch_mutants(const uint64_t* genomes, uint64_t first, int64_t n, int nbits, uint64_t* out,
@@ -118,11 +235,20 @@ int launch_neighbourhood(const jatam_result_t* own, const jatam_result_t* mut, i
 int launch_neighbourhood_space(const jatam_result_t* space, uint64_t first, int64_t n, int nbits,
                                jatam_neighbourhood_t* out, hipStream_t s)
 {
-    for (int64_t at = 0; at < n; at += (int64_t)1 << 30) {
-        const int64_t k = n - at < ((int64_t)1 << 30) ? n - at : ((int64_t)1 << 30);
-        hipLaunchKernelGGL(neighbourhood_space_kernel,
-                           dim3((unsigned)((k + kNbLanes - 1) / kNbLanes)), dim3(kNbLanes), 0, s,
-                           space, first + (uint64_t)at, (uint64_t)k, nbits, out + at);
+    // windows of 2^16 genotypes (a byte each in LDS), smaller ones while they
+    // would leave compute units idle; at least one thread's four genotypes
+    int b = nbits < 16 ? nbits : 16;
+    while (b > 10 && (n >> b) < 256)
+        --b;
+    const uint32_t words = (1u << b) / 4u;
+    const uint32_t threads = words < 64u ? 64u : words > 1024u ? 1024u : words;
+    const uint64_t w0 = first >> b, w1 = (first + (uint64_t)n - 1u) >> b;
+    const uint64_t per_launch = 1ull << 20;
+    for (uint64_t w = w0; w <= w1; w += per_launch) {
+        const uint32_t windows = (uint32_t)(w1 - w + 1u < per_launch ? w1 - w + 1u : per_launch);
+        hipLaunchKernelGGL(neighbourhood_space_kernel, dim3((windows + 7u) / 8u * 8u),
+                           dim3(threads), (size_t)1 << b, s, space, first, (uint64_t)n, nbits, b,
+                           w, windows, out);
     }
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }

@@ -45,7 +45,8 @@ def test_symmetric_and_repeated_tiles(t, c, grid):
     rng = np.random.default_rng(100 * t + 10 * c + grid)
     gs = symmetric_genomes(rng, 4000, t, c)
     want = ref.classify(gs, t, c=c, grid=grid, runs=12, seed=9)
-    assert len(np.unique(want["cls"])) >= 2
+    # over two colours nothing bonds: every genotype is its seed
+    assert len(np.unique(want["cls"])) >= (1 if c == 2 else 2)
     dev = torch.from_numpy(gs.view(np.int64)).cuda()
     plain = jt.classify(dev, t, c, grid, 12, 9)
     with jt.Batch(len(gs)) as b:
