@@ -176,149 +176,10 @@ __device__ __forceinline__ int update_site(const Src& m, LaneGrid<W, B>& g, RunS
     return unbound ? kEvUnbound : ambiguous ? kEvAmbig : kEvNone;
 }
 
-// Philox block cache of a run: the 4 words of counter block `block`.  Kept
-// as four scalars, never an array: an array picked by a run-time index ends
-// up in scratch memory, one memory round trip per step.
-struct DrawCache {
-    uint32_t block;
-    uint32_t w0, w1, w2, w3;
-
-    __device__ __forceinline__ void reset() { block = 0xFFFFFFFFu; }
-    __device__ __forceinline__ void fill(const Words4& v)
-    {
-        w0 = v.w[0];
-        w1 = v.w[1];
-        w2 = v.w[2];
-        w3 = v.w[3];
-    }
-    // word k (0..3) by two register selects
-    __device__ __forceinline__ uint32_t word(uint32_t k) const
-    {
-        const uint32_t lo = (k & 1u) ? w1 : w0;
-        const uint32_t hi = (k & 1u) ? w3 : w2;
-        return (k & 2u) ? hi : lo;
-    }
-    // random word s of run `run`: word s mod 4 of counter block s / 4
-    static constexpr bool kPrefetched = false;
-    __device__ __forceinline__ uint32_t draw(uint32_t s, int run, uint32_t key0, uint32_t key1,
-                                             uint32_t rid_lo, uint32_t rid_hi)
-    {
-        const uint32_t blk = s >> 2;
-        if (blk != block) {
-            fill(philox4x32_10(blk, (uint32_t)run, rid_lo, rid_hi, key0, key1));
-            block = blk;
-        }
-        return word(s & 3u);
-    }
-};
-
-// Two Philox blocks of a run, one of even and one of odd block index, so
-// that a block can be computed before the run reaches it.  A wave whose
-// lanes run out of phase computes blocks whenever any lane needs one; with
-// one block per lane that happens on most steps with few lanes active.  With
-// two, every lane fills the block it lacks (its current one, else the next)
-// at each such point, so all lanes share one computation about every fourth
-// step (see prefetch).  draw() still computes a missing block itself.
-struct DrawPair {
-    static constexpr bool kPrefetched = false;
-    uint32_t te, to;                    // block index held (all ones: none)
-    uint32_t e0, e1, e2, e3;            // the even block
-    uint32_t o0, o1, o2, o3;            // the odd block
-
-    // Members are only ever combined by value selects: choosing between two
-    // members as lvalues (or storing through such a choice) makes the
-    // compiler address the struct by a run-time offset, in scratch memory.
-    __device__ __forceinline__ static uint32_t pick(bool c, uint32_t x, uint32_t y)
-    {
-        return c ? x : y;
-    }
-    __device__ __forceinline__ void reset()
-    {
-        te = 0xFFFFFFFFu;
-        to = 0xFFFFFFFFu;
-    }
-    // te only ever holds an even index and to an odd one
-    __device__ __forceinline__ bool has(uint32_t blk) const { return te == blk || to == blk; }
-    __device__ __forceinline__ void put(uint32_t blk, const Words4& v)
-    {
-        const bool odd = (blk & 1u) != 0;
-        to = pick(odd, blk, to);
-        o0 = pick(odd, v.w[0], o0);
-        o1 = pick(odd, v.w[1], o1);
-        o2 = pick(odd, v.w[2], o2);
-        o3 = pick(odd, v.w[3], o3);
-        te = pick(odd, te, blk);
-        e0 = pick(odd, e0, v.w[0]);
-        e1 = pick(odd, e1, v.w[1]);
-        e2 = pick(odd, e2, v.w[2]);
-        e3 = pick(odd, e3, v.w[3]);
-    }
-    // the block this lane should compute now, given its next draw index s:
-    // block s/4 if missing, else block s/4 + 1 if missing; false if neither
-    __device__ __forceinline__ bool wanted(uint32_t s, uint32_t& blk) const
-    {
-        const uint32_t b = s >> 2;
-        const bool cur = !has(b);
-        blk = cur ? b : b + 1u;
-        return cur || !has(b + 1u);
-    }
-    __device__ __forceinline__ uint32_t draw(uint32_t s, int run, uint32_t key0, uint32_t key1,
-                                             uint32_t rid_lo, uint32_t rid_hi)
-    {
-        const uint32_t blk = s >> 2;
-        if (!has(blk))
-            put(blk, philox4x32_10(blk, (uint32_t)run, rid_lo, rid_hi, key0, key1));
-        const bool odd = (blk & 1u) != 0;
-        const uint32_t k = s & 3u;
-        const uint32_t x0 = pick(odd, o0, e0), x1 = pick(odd, o1, e1);
-        const uint32_t x2 = pick(odd, o2, e2), x3 = pick(odd, o3, e3);
-        const uint32_t lo = pick((k & 1u) != 0, x1, x0);
-        const uint32_t hi = pick((k & 1u) != 0, x3, x2);
-        return pick((k & 2u) != 0, hi, lo);
-    }
-};
-
-// A DrawPair whose caller runs prefetch_draws before every step: the block
-// of the next draw is then always present, so draw() reads it without the
-// fallback computation (and the step loop holds one copy of the generator).
-struct PrefetchedDraws {
-    static constexpr bool kPrefetched = true;
-    DrawPair& dp;
-    __device__ __forceinline__ uint32_t draw(uint32_t s, int, uint32_t, uint32_t, uint32_t,
-                                             uint32_t) const
-    {
-        const uint32_t blk = s >> 2;
-        const bool odd = (blk & 1u) != 0;
-        const uint32_t k = s & 3u;
-        const uint32_t x0 = DrawPair::pick(odd, dp.o0, dp.e0), x1 = DrawPair::pick(odd, dp.o1, dp.e1);
-        const uint32_t x2 = DrawPair::pick(odd, dp.o2, dp.e2), x3 = DrawPair::pick(odd, dp.o3, dp.e3);
-        const uint32_t lo = DrawPair::pick((k & 1u) != 0, x1, x0);
-        const uint32_t hi = DrawPair::pick((k & 1u) != 0, x3, x2);
-        return DrawPair::pick((k & 2u) != 0, hi, lo);
-    }
-};
-
-// Wave-wide Philox fill for lanes that keep a DrawPair: when the next draw
-// of any stepping lane lacks its block, every stepping lane computes the
-// block it lacks, so one pass of the generator serves the whole wave.  Call
-// with every lane of the wave present (it takes a ballot).
-__device__ __forceinline__ void prefetch_draws(DrawPair& dp, bool stepping, const RunState& st,
-                                               int run, uint32_t key0, uint32_t key1,
-                                               uint32_t rid_lo, uint32_t rid_hi)
-{
-    const uint32_t s = (uint32_t)st.steps;
-    const bool need = stepping && st.nf >= 2 && !dp.has(s >> 2);
-    if (__ballot(need) == 0)
-        return;
-    uint32_t blk = 0;
-    if (stepping && dp.wanted(s, blk))
-        dp.put(blk, philox4x32_10(blk, (uint32_t)run, rid_lo, rid_hi, key0, key1));
-}
-
 // Clears what the previous run touched and places the seed (tile 0,
 // unrotated) at the centre; returns the seed's cell.
-template <int W, int B, class Draws>
-__device__ __forceinline__ int run_clear(LaneGrid<W, B>& g, RunState& st, Draws& dc, int G)
+template <int W, int B>
+__device__ __forceinline__ int run_clear(LaneGrid<W, B>& g, RunState& st, int G)
 {
     // occupied cells keep their tiles in PEND, and a run that ended on an
     // event leaves frontier cells (with their PEND nibbles) behind: clear all
@@ -334,7 +195,6 @@ __device__ __forceinline__ int run_clear(LaneGrid<W, B>& g, RunState& st, Draws&
     st.groups = 0;
     st.steps = 0;
     st.choice = false;
-    dc.reset();
     const int seed_pos = (G / 2 - 1) * W + (G / 2 - 1);
     g.occ(seed_pos >> 5) = 1u << (seed_pos & 31);
     st.osum = 1u << (seed_pos >> 5);
@@ -346,11 +206,11 @@ __device__ __forceinline__ int run_clear(LaneGrid<W, B>& g, RunState& st, Draws&
 // (tile 0, unrotated) at the centre and puts its sites on the frontier.  In
 // the cleared grid they are free and off the frontier, and with G >= 8 the
 // ring is at least three cells away.
-template <int W, int B, class Draws>
-__device__ __forceinline__ int run_start_known(LaneGrid<W, B>& g, RunState& st, Draws& dc,
-                                               int G, uint32_t codes)
+template <int W, int B>
+__device__ __forceinline__ int run_start_known(LaneGrid<W, B>& g, RunState& st, int G,
+                                               uint32_t codes)
 {
-    const int p = run_clear(g, st, dc, G);
+    const int p = run_clear(g, st, G);
     if ((codes & kSiteMulti) != 0)
         return kEvAmbig;
     st.nf = (uint32_t)__popc(codes & kSiteAny);
@@ -368,11 +228,10 @@ __device__ __forceinline__ int run_start_known(LaneGrid<W, B>& g, RunState& st, 
 }
 
 // Starts a run of genotype m.
-template <int W, int B, class Src, class Draws>
-__device__ __forceinline__ int run_start(const Src& m, LaneGrid<W, B>& g, RunState& st,
-                                         Draws& dc, int G)
+template <int W, int B, class Src>
+__device__ __forceinline__ int run_start(const Src& m, LaneGrid<W, B>& g, RunState& st, int G)
 {
-    return run_start_known(g, st, dc, G, m.codes(m.seed()));
+    return run_start_known(g, st, G, m.codes(m.seed()));
 }
 
 // A run is over once an event happened or the frontier is empty.  Every step
@@ -381,6 +240,12 @@ __device__ __forceinline__ bool run_over(int ev, const RunState& st, int G)
 {
     return ev != kEvNone || st.nf == 0 || st.steps >= (G - 1) * (G - 1);
 }
+
+// What draws a run's random words: its Philox key and stream.
+struct RunKey {
+    uint32_t key0, key1, rid_lo, rid_hi;
+    int run;
+};
 
 // Index of the first of four inclusive prefix counts p0 <= p1 <= p2 (<= p3)
 // above j (j < p3): which of four words holds site j.  *below receives the
@@ -425,9 +290,9 @@ __device__ __forceinline__ uint32_t inside_box(uint32_t x, uint32_t y, int G)
     return room + 0x7F7F7F7Fu;
 }
 
-// One step: draw the frontier site of rank floor(u*|F|/2^32) in row-major
-// order (u = Philox word `steps` of this run's stream; no draw is needed with
-// one site), place its pending tile and check the new neighbours.
+// One step: take the frontier site of rank floor(u*|F|/2^32) in row-major
+// order (u = Philox word `steps` of this run's stream; with one site any word
+// gives rank 0), place its pending tile and check the new neighbours.
 //
 // A wave is bound here by the instructions it issues and, with few waves or
 // few lanes left, by the length of their chain: two rounds of LDS reads (the
@@ -439,21 +304,13 @@ __device__ __forceinline__ uint32_t inside_box(uint32_t x, uint32_t y, int G)
 // (32 x 32).  Measured with the bond lookup of Bonds: all of S_{2,8} in one
 // call 1.31 -> 1.07 ms, a generation of 65,536 three-tile genotypes at G = 32
 // (its longest run, one placement after the other) 0.93 -> 0.63 ms.
-template <int W, int B, class Src, class Draws>
-__device__ __forceinline__ int run_step(const Src& m, LaneGrid<W, B>& g, RunState& st,
-                                        Draws& dc, int G, int run, uint32_t key0,
-                                        uint32_t key1, uint32_t rid_lo, uint32_t rid_hi)
+template <int W, int B, class Src>
+__device__ __forceinline__ int run_step(const Src& m, LaneGrid<W, B>& g, RunState& st, int G,
+                                        uint32_t u)
 {
     using Geo = Geometry<W>;
     const uint32_t nf = st.nf;
-    uint32_t j = 0;
-    if constexpr (Draws::kPrefetched) {
-        // with one site any word gives rank 0
-        j = __umulhi(dc.draw((uint32_t)st.steps, run, key0, key1, rid_lo, rid_hi), nf);
-    } else {
-        if (nf >= 2)
-            j = __umulhi(dc.draw((uint32_t)st.steps, run, key0, key1, rid_lo, rid_hi), nf);
-    }
+    const uint32_t j = __umulhi(u, nf);
     st.choice = st.choice | (nf >= 2);
     // the j-th frontier site in row-major order: its word w (fw), then the
     // bit.  The bitmap's count always equals nf; were it not so, the run
@@ -604,16 +461,37 @@ __device__ __forceinline__ int run_step(const Src& m, LaneGrid<W, B>& g, RunStat
     return total != nf ? kEvCorrupt : ev;
 }
 
+// Up to four steps of a run that is not over and whose steps so far are a
+// multiple of four, so that one Philox block holds their words.  A wave whose
+// lanes all start their runs between such groups computes the generator once
+// a group with every running lane taking part, and tests for finished lanes
+// once a group.
+template <int W, int B, class Src>
+__device__ __forceinline__ int run_four(const Src& m, LaneGrid<W, B>& g, RunState& st, int G,
+                                        const RunKey& k)
+{
+    const Words4 u = philox4x32_10((uint32_t)st.steps >> 2, (uint32_t)k.run, k.rid_lo, k.rid_hi,
+                                   k.key0, k.key1);
+    int ev = run_step(m, g, st, G, u.w[0]);
+    if (ev == kEvNone && st.nf != 0) {
+        ev = run_step(m, g, st, G, u.w[1]);
+        if (ev == kEvNone && st.nf != 0) {
+            ev = run_step(m, g, st, G, u.w[2]);
+            if (ev == kEvNone && st.nf != 0)
+                ev = run_step(m, g, st, G, u.w[3]);
+        }
+    }
+    return ev;
+}
+
 // One run from the seed to completion or to an event.
 template <int W, int B, class Src>
 __device__ __forceinline__ int run_assembly(const Src& m, LaneGrid<W, B>& g, RunState& st, int G,
-                                            int run,
-                            uint32_t key0, uint32_t key1, uint32_t rid_lo, uint32_t rid_hi)
+                                            const RunKey& k)
 {
-    DrawCache dc;
-    int ev = run_start(m, g, st, dc, G);
+    int ev = run_start(m, g, st, G);
     while (!run_over(ev, st, G))
-        ev = run_step(m, g, st, dc, G, run, key0, key1, rid_lo, rid_hi);
+        ev = run_four(m, g, st, G, k);
     return ev;
 }
 
@@ -948,22 +826,54 @@ __device__ __forceinline__ bool shape_bitmap8_w16(LaneGrid<16, B>& g, uint64_t& 
     return true;
 }
 
+// The same through the 8 x 8 window around the seed, where nearly every shape
+// lies: four words (the window starts on an even row), shifted to its first
+// column and packed to bytes; the shape lies in it if all its cells are
+// counted there.  About 30 instructions against 110 for any position.
 template <int B>
-__device__ __forceinline__ bool shape_bitmap8_w16(LaneGrid<16, B>& g, uint64_t& m)
+__device__ __forceinline__ bool shape_near_seed_w16(LaneGrid<16, B>& g, int G, int size,
+                                                    uint64_t& m, int& x0, int& y0)
 {
-    int x0, y0;
-    return shape_bitmap8_w16(g, m, x0, y0);
+    const int s = G / 2 - 1;                      // 3 .. 7
+    const int wx = s - 3, wy = (s - 3) & ~1;      // the window's first column and row
+    uint32_t r[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        r[q] = g.occ(wy / 2 + q) >> wx;
+    const uint32_t lo = __builtin_amdgcn_perm(r[1], r[0], 0x06040200u);
+    const uint32_t hi = __builtin_amdgcn_perm(r[3], r[2], 0x06040200u);
+    const uint64_t v = ((uint64_t)hi << 32) | lo;
+    if (__popcll(v) != size)
+        return false;
+    const int rows = __builtin_ctzll(v) & ~7;
+    uint32_t cols = lo | hi;
+    cols |= cols >> 16;
+    cols |= cols >> 8;
+    const int left = __builtin_ctz(cols);
+    m = v >> (rows + left);
+    x0 = wx + left;
+    y0 = wy + rows / 8;
+    return true;
 }
 
-// The cropped shape as an anchored 8 x 8 bitmap, whatever W.
+// The cropped shape of `size` cells as an anchored 8 x 8 bitmap and where it
+// starts; false if its box exceeds 8 x 8.
 template <int W, int B>
-__device__ __forceinline__ bool shape_key8(LaneGrid<W, B>& g, int G, uint64_t& m)
+__device__ __forceinline__ bool shape_key8(LaneGrid<W, B>& g, int G, int size, uint64_t& m,
+                                           int& x0, int& y0)
 {
     if constexpr (W == 16) {
-        return shape_bitmap8_w16(g, m);
+        return shape_near_seed_w16(g, G, size, m, x0, y0) || shape_bitmap8_w16(g, m, x0, y0);
     } else {
-        int w, h;
-        return shape_bitmap8(g, G, m, w, h);
+        const ShapeBox bx = crop(g, G);
+        x0 = bx.xmin;
+        y0 = bx.ymin;
+        if (bx.w > 8 || bx.h > 8)
+            return false;
+        m = 0;
+        for (int y = 0; y < bx.h; ++y)
+            m |= (uint64_t)((g.row(bx.ymin + y) >> bx.xmin) & 0xFFu) << (8 * y);
+        return true;
     }
 }
 
@@ -981,59 +891,28 @@ __device__ __forceinline__ bool packed_shape_valid(const uint4& v)
     return !(v.z == 0xFFFFFFFFu && v.w == 0xFFFFFFFFu);
 }
 
-template <int W, int B>
-__device__ __forceinline__ uint4 pack_shape(LaneGrid<W, B>& g, int G, int size)
+// No packed shape.
+__device__ __forceinline__ uint4 packed_none()
 {
-    const uint4 none = make_uint4(0u, 0u, 0xFFFFFFFFu, 0xFFFFFFFFu);
+    return make_uint4(0u, 0u, 0xFFFFFFFFu, 0xFFFFFFFFu);
+}
+
+// Packs the shape m (shape_key8) whose box starts at (x0, y0).
+template <int W, int B>
+__device__ __forceinline__ uint4 pack_shape(LaneGrid<W, B>& g, int G, int size, uint64_t m,
+                                            int x0, int y0)
+{
     if (size > kPackedCells)
-        return none;
-    if constexpr (W == 16) {
-        // the bitmap from the OCC words in registers; then the two PEND words
-        // of each of the box's rows, all reads issued before any is used
-        uint64_t m;
-        int x0, y0;
-        if (!shape_bitmap8_w16(g, m, x0, y0))
-            return none;
-        uint32_t lo[8], hi[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int y = y0 + r < 16 ? y0 + r : 15;
-            lo[r] = g.word(Geometry<16>::kPend + 2 * y);
-            hi[r] = g.word(Geometry<16>::kPend + 2 * y + 1);
-        }
-        uint64_t tiles = 0;
-        int k = 0;
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            // the row's 8 nibbles from column x0 on
-            const uint32_t row = (uint32_t)((((uint64_t)hi[r] << 32) | lo[r]) >> (4 * x0));
-            for (uint32_t bits = (uint32_t)(m >> (8 * r)) & 0xFFu; bits != 0;
-                 bits &= bits - 1, ++k) {
-                const int x = __builtin_ctz(bits);
-                tiles |= (uint64_t)((row >> (4 * x)) & 15u) << (4 * k);
-            }
-        }
-        const int sc = G / 2 - 1;
-        tiles |= (uint64_t)((sc - y0) * 8 + (sc - x0)) << 58;
-        return make_uint4((uint32_t)m, (uint32_t)(m >> 32), (uint32_t)tiles,
-                          (uint32_t)(tiles >> 32));
-    }
-    const ShapeBox bx = crop(g, G);
-    if (bx.w > 8 || bx.h > 8)
-        return none;
-    uint64_t m = 0;
-    for (int y = 0; y < bx.h; ++y)
-        m |= (uint64_t)((g.row(bx.ymin + y) >> bx.xmin) & 0xFFu) << (8 * y);
+        return packed_none();
     uint64_t tiles = 0;
     int k = 0;
-    for (uint64_t cells = m; cells != 0; cells &= cells - 1, ++k) {
+    for (uint64_t cells = m; cells != 0; cells &= cells - 1, k += 4) {
         const int b = __builtin_ctzll(cells);
-        const int p = (bx.ymin + (b >> 3)) * W + bx.xmin + (b & 7);
-        const uint64_t nib = (g.pend_word(p) >> ((uint32_t)(p & 7) * 4u)) & 15u;
-        tiles |= nib << (4 * k);
+        const int p = (y0 + (b >> 3)) * W + x0 + (b & 7);
+        tiles |= (uint64_t)((g.pend_word(p) >> ((uint32_t)(p & 7) * 4u)) & 15u) << k;
     }
     const int sc = G / 2 - 1;
-    tiles |= (uint64_t)((sc - bx.ymin) * 8 + (sc - bx.xmin)) << 58;
+    tiles |= (uint64_t)((sc - y0) * 8 + (sc - x0)) << 58;
     return make_uint4((uint32_t)m, (uint32_t)(m >> 32), (uint32_t)tiles,
                       (uint32_t)(tiles >> 32));
 }
@@ -1214,13 +1093,36 @@ struct LaneStack {
     __device__ __forceinline__ void set(int i, int v) { *byte(i) = (uint8_t)v; }
 };
 
+// The movelist's words, one Philox block kept.  Scalars, never an array: an
+// array picked by a run-time index ends up in scratch memory.
+struct DrawCache {
+    uint32_t block = 0xFFFFFFFFu;
+    uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
+
+    // random word s of the run: word s mod 4 of counter block s / 4
+    __device__ __forceinline__ uint32_t draw(uint32_t s, const RunKey& k)
+    {
+        const uint32_t blk = s >> 2;
+        if (blk != block) {
+            const Words4 v = philox4x32_10(blk, (uint32_t)k.run, k.rid_lo, k.rid_hi, k.key0,
+                                           k.key1);
+            w0 = v.w[0];
+            w1 = v.w[1];
+            w2 = v.w[2];
+            w3 = v.w[3];
+            block = blk;
+        }
+        const uint32_t lo = (s & 1u) ? w1 : w0, hi = (s & 1u) ? w3 : w2;
+        return (s & 2u) ? hi : lo;
+    }
+};
+
 // Pushes the sites of the directions in `added` (in order N, E, S, W) next to
 // p; len is the stack's length before them.  Returns the new length.
-template <int W, int B, class Draws>
+template <int W, int B>
 __device__ __forceinline__ uint32_t movelist_push(LaneStack<B>& stk, uint32_t len, int p,
-                                                  uint32_t added, Draws& dc, uint32_t& draws,
-                                                  bool& choice, int run, uint32_t key0,
-                                                  uint32_t key1, uint32_t rid_lo, uint32_t rid_hi)
+                                                  uint32_t added, DrawCache& dc, uint32_t& draws,
+                                                  bool& choice, const RunKey& k)
 {
     constexpr int kMask = W * W - 1;
     for (int d = 0; d < 4; ++d) {
@@ -1230,7 +1132,7 @@ __device__ __forceinline__ uint32_t movelist_push(LaneStack<B>& stk, uint32_t le
         const int q = (p + delta) & kMask;
         uint32_t pos = 0;
         if (len > 0u) {
-            pos = __umulhi(dc.draw(draws, run, key0, key1, rid_lo, rid_hi), len + 1u);
+            pos = __umulhi(dc.draw(draws, k), len + 1u);
             draws += 1;
             choice = true;
         }
@@ -1246,17 +1148,15 @@ __device__ __forceinline__ uint32_t movelist_push(LaneStack<B>& stk, uint32_t le
 // event (st.nf is the stack's length throughout).
 template <int W, int B, class Src>
 __device__ __forceinline__ int run_assembly_lifo(const Src& m, LaneGrid<W, B>& g,
-                                                 LaneStack<B>& stk, RunState& st, int G, int run,
-                                                 uint32_t key0, uint32_t key1, uint32_t rid_lo,
-                                                 uint32_t rid_hi)
+                                                 LaneStack<B>& stk, RunState& st, int G,
+                                                 const RunKey& k)
 {
     DrawCache dc;
-    const int seed_pos = run_clear(g, st, dc, G);
+    const int seed_pos = run_clear(g, st, G);
     uint32_t draws = 0, added = 0;
     bool choice = false;
     int ev = update_site(m, g, st, G, seed_pos, m.seed(), &added);
-    movelist_push<W>(stk, 0u, seed_pos, added, dc, draws, choice, run, key0, key1, rid_lo,
-                     rid_hi);
+    movelist_push<W>(stk, 0u, seed_pos, added, dc, draws, choice, k);
     while (ev == kEvNone && st.nf > 0 && st.steps < (G - 1) * (G - 1)) {
         const int p = stk.get((int)st.nf - 1);
         st.nf -= 1;
@@ -1271,7 +1171,7 @@ __device__ __forceinline__ int run_assembly_lifo(const Src& m, LaneGrid<W, B>& g
         const uint32_t len = st.nf;
         added = 0;
         ev = update_site(m, g, st, G, p, tuple, &added);
-        movelist_push<W>(stk, len, p, added, dc, draws, choice, run, key0, key1, rid_lo, rid_hi);
+        movelist_push<W>(stk, len, p, added, dc, draws, choice, k);
     }
     st.choice = choice;
     return ev;

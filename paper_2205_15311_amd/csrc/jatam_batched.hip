@@ -172,6 +172,11 @@ int launch_slice_advance(uint32_t* counter, hipStream_t stream)
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }
 
+__device__ __forceinline__ RunKey run_key(const BatchArgs& a, const Geno& gd, int run)
+{
+    return RunKey{a.key0, a.key1, (uint32_t)gd.rng_id, (uint32_t)(gd.rng_id >> 32), run};
+}
+
 // Grid class of a genotype: 0 = the 16 x 16 layout, 1 = the 32 x 32 layout.
 __device__ __forceinline__ int grid_class(const BatchArgs& a, int grid)
 {
@@ -205,46 +210,24 @@ struct WaveTally {
 constexpr int kShapeCache = 32;
 using WaveShapeCache = ShapeCache<kShapeCache>;
 
-// D4 hash of the DET shape in a lane's OCC, for lanes with `want` (called by
-// the whole wave).  A monomer and a domino have one shape each up to D4:
-// their hashes are computed once per workspace (small_hash_kernel).  Shapes
-// that fit 8 x 8 go through the wave's cache; a miss hashes the bitmap and
-// fills the cache.
-// small0/small1: the monomer's and the domino's hashes, read once per kernel
+// D4 hash of a shape of `size` cells given as its anchored 8 x 8 bitmap (`fits`),
+// else the one in the lane's OCC, for lanes with `want` (called by the whole
+// wave).  A monomer and a domino have one shape each up to D4: their hashes
+// (small0, small1) are computed once per workspace and read once per kernel
 // (a load in the loop would make the wave wait for all its record stores).
+// Bitmaps go through the wave's cache; a miss hashes the bitmap and fills it.
 template <int W>
 __device__ __forceinline__ uint32_t det_hash(LaneGrid<W, 64>& g, uint32_t small0, uint32_t small1,
-                                             WaveShapeCache& cache, bool want, int size, int grid)
+                                             WaveShapeCache& cache, bool want, int size, int grid,
+                                             bool fits, uint64_t key)
 {
     uint32_t h = 0;
     bool miss = false;
-    uint64_t key = 0;
     if (want) {
         if (size <= 2) {
             h = size <= 1 ? small0 : small1;
-        } else if (shape_key8(g, grid, key)) {
-            if (!cache.lookup(key, h)) {
-                h = bitmap8_shape_hash(key);
-                miss = true;
-            }
-        } else {
+        } else if (!fits) {
             h = shape_hash(g, grid);
-        }
-    }
-    cache.insert(miss, key, h, lane_id());
-    return h;
-}
-
-// D4 hash of a shape given as its anchored 8 x 8 bitmap, for lanes with
-// `want` (called by the whole wave), through the wave's cache.
-__device__ __forceinline__ uint32_t packed_hash(uint64_t key, uint32_t small0, uint32_t small1,
-                                                WaveShapeCache& cache, bool want, int size)
-{
-    uint32_t h = 0;
-    bool miss = false;
-    if (want) {
-        if (size <= 2) {
-            h = size <= 1 ? small0 : small1;
         } else if (!cache.lookup(key, h)) {
             h = bitmap8_shape_hash(key);
             miss = true;
@@ -287,8 +270,6 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
     size_hist[lane_id()] = 0;
     __syncthreads();
     RunState st{};
-    DrawPair dc;
-    dc.reset();
 
     const uint32_t wave = blockIdx.x, nwaves = gridDim.x;
     if (wave == 0) {
@@ -370,8 +351,14 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                     candidate = true;
                 }
             }
+            // the shape's bitmap, for the hash or for the proof stage
+            uint64_t key = 0;
+            int x0 = 0, y0 = 0;
+            bool fits = false;
+            if (det || candidate)
+                fits = shape_key8(g, gd.grid, st.size(), key, x0, y0);
             if (__ballot(det) != 0)
-                rec.hash = det_hash(g, small0, small1, cache, det, st.size(), gd.grid);
+                rec.hash = det_hash(g, small0, small1, cache, det, st.size(), gd.grid, fits, key);
             if (finish) {
                 if (done)
                     out[idx] = rec;
@@ -384,7 +371,8 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                 seg_idx[pos] = idx;
                 seg_size[pos] = (uint16_t)st.size();
                 // the shape, for the proof stage to check without a replay
-                seg_shape[pos] = pack_shape(g, gd.grid, st.size());
+                seg_shape[pos] =
+                    fits ? pack_shape(g, gd.grid, st.size(), key, x0, y0) : packed_none();
                 atomicAdd(&size_hist[size_key((uint32_t)st.size())], 1u);
             }
             staged += (uint32_t)__popcll(cm);
@@ -484,7 +472,7 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                     idx = ring[slot];
                     gd = run_geno<W, kIn>(a, first, idx);
                     m = build_bonds<M>(gd.genome, gd.t, a.bits, a.c);
-                    ev = run_start_known(g, st, dc, gd.grid, ring_opt[slot]);
+                    ev = run_start_known(g, st, gd.grid, ring_opt[slot]);
                     busy = true;
                 }
             }
@@ -499,24 +487,19 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                 break;
             continue;
         }
-        // -- steps until enough lanes wait for a refill (every lane, once no
-        // chunk is left), at least one step: finished lanes keep their run's
-        // state until the finish pass above takes them, so records, hashes
-        // and staging are done once per refill rather than at every step ---
+        // -- groups of four steps until enough lanes wait for a refill (every
+        // lane, once no chunk is left), at least one group: finished lanes
+        // keep their run's state until the finish pass above takes them, so
+        // records, hashes and staging are done once per refill rather than at
+        // every step.  Lanes start runs between groups only, so the groups of
+        // all lanes coincide ----------------------------------------------
         const uint32_t enough = queued == 0 && starved ? 65u : (uint32_t)a.refill;
         for (;;) {
             const bool stepping = busy && !run_over(ev, st, gd.grid);
             if (__ballot(stepping) == 0)
                 break;
-            prefetch_draws(dc, stepping, st, 0, a.key0, a.key1, (uint32_t)gd.rng_id,
-                           (uint32_t)(gd.rng_id >> 32));
-            if (stepping) {
-                // prefetch_draws above made the block of every stepping
-                // lane's next draw present
-                PrefetchedDraws pd{dc};
-                ev = run_step(m, g, st, pd, gd.grid, 0, a.key0, a.key1, (uint32_t)gd.rng_id,
-                              (uint32_t)(gd.rng_id >> 32));
-            }
+            if (stepping)
+                ev = run_four(m, g, st, gd.grid, run_key(a, gd, 0));
             const uint64_t waiting = __ballot(!busy || run_over(ev, st, gd.grid));
             if ((uint32_t)__popcll(waiting) >= enough)
                 break;
@@ -688,16 +671,16 @@ __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
             size = __popcll(key);
             forced = packed_shape_is_guarded(src, sh);
         } else {
-            const int ev = run_assembly(src, g, st, gd.grid, 0, a.key0, a.key1,
-                                        (uint32_t)gd.rng_id, (uint32_t)(gd.rng_id >> 32));
+            const int ev = run_assembly(src, g, st, gd.grid, run_key(a, gd, 0));
             size = st.size();
             forced = ev == kEvNone && shape_is_guarded(src, g, st, gd.grid);
+            int x0, y0;
+            packed = forced && shape_key8(g, gd.grid, size, key, x0, y0);
         }
     }
-    // hashes: a packed shape's from its bitmap, a replayed one's from the grid
-    uint32_t h = det_hash(g, a.small0, a.small1, cache, forced && !packed, size, gd.grid);
-    const uint32_t hp = packed_hash(key, a.small0, a.small1, cache, forced && packed, size);
-    h = packed ? hp : h;
+    // the hash of a packed or replayed shape from its bitmap, if it has one
+    const uint32_t h =
+        det_hash(g, a.small0, a.small1, cache, forced, size, gd.grid, packed, key);
     if (forced)
         out[idx] = jatam_result_t{JATAM_DET, size, h, (size - 1) * a.runs};
     tally.add(forced, JATAM_DET);
@@ -902,8 +885,7 @@ struct RepeatWave {
         if (active) {
             gd = run_geno<W>(a, first, idx);
             const M src = build_bonds<M>(gd.genome, gd.t, a.bits, a.c);
-            ev = run_assembly(src, g, st, gd.grid, run, a.key0, a.key1, (uint32_t)gd.rng_id,
-                              (uint32_t)(gd.rng_id >> 32));
+            ev = run_assembly(src, g, st, gd.grid, run_key(a, gd, run));
         }
         wave_lds_sync();   // every run's grid is final
         // a witness is a later run that hit an event or ended in another
@@ -978,7 +960,8 @@ struct RepeatWave {
         bool small = false, hit = false;
         uint32_t cached = 0;
         if (det && size0 > 2) {
-            small = shape_key8(g0, gd.grid, key);
+            int x0, y0;
+            small = shape_key8(g0, gd.grid, size0, key, x0, y0);
             hit = small && cache.lookup(key, cached);
             if (!hit) {
                 if (small) {
@@ -1174,8 +1157,6 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
     __syncthreads();
     RunState st{};
     WaveTally tally{{0, 0, 0, 0}};
-    DrawPair dc;
-    dc.reset();
 
     const int R = a.runs;
     const uint32_t count = a.ws.counters[kCntCand + klass];
@@ -1204,7 +1185,7 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
                     src = build_bonds<M>(gd.genome, gd.t, a.bits, a.c);
                     run = 0;
                     steps_sum = 0;
-                    ev = run_start(src, g, st, dc, gd.grid);
+                    ev = run_start(src, g, st, gd.grid);
                     busy = true;
                 }
             }
@@ -1217,11 +1198,8 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
                 break;
             continue;
         }
-        const uint32_t rid_lo = (uint32_t)gd.rng_id, rid_hi = (uint32_t)(gd.rng_id >> 32);
-        const bool stepping = busy && !run_over(ev, st, gd.grid);
-        prefetch_draws(dc, stepping, st, run, a.key0, a.key1, rid_lo, rid_hi);
-        if (stepping)
-            ev = run_step(src, g, st, dc, gd.grid, run, a.key0, a.key1, rid_lo, rid_hi);
+        if (busy && !run_over(ev, st, gd.grid))
+            ev = run_four(src, g, st, gd.grid, run_key(a, gd, run));
         const bool ended = busy && run_over(ev, st, gd.grid);
         bool done = false, det = false;
         int cls = 0;
@@ -1246,7 +1224,7 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
                 osum0 = st.osum;
                 size0 = st.size();
                 run = 1;
-                ev = run_start(src, g, st, dc, gd.grid);
+                ev = run_start(src, g, st, gd.grid);
             } else {
                 // occupancy only grows within a run, so osum is exactly the
                 // set of nonzero words
@@ -1268,13 +1246,17 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
                     done = true;
                 } else {
                     run += 1;
-                    ev = run_start(src, g, st, dc, gd.grid);
+                    ev = run_start(src, g, st, gd.grid);
                 }
             }
         }
         // the grid holds run R-1's shape, which is run 0's
-        if (__ballot(det) != 0)
-            rec.hash = det_hash(g, small0, small1, cache, det, size0, gd.grid);
+        if (__ballot(det) != 0) {
+            uint64_t key = 0;
+            int x0, y0;
+            const bool fits = det && shape_key8(g, gd.grid, size0, key, x0, y0);
+            rec.hash = det_hash(g, small0, small1, cache, det, size0, gd.grid, fits, key);
+        }
         if (done) {
             out[idx] = rec;
             busy = false;

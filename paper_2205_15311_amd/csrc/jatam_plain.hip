@@ -24,11 +24,11 @@ __device__ jatam_result_t classify_genotype(LaneGrid<W, B>& g, RunState& st, uin
     int work = 0;
     for (int r = 0; r < prm.runs; ++r) {
         int ev;
+        const RunKey key{prm.key0, prm.key1, rid_lo, rid_hi, r};
         if constexpr ((kVariant & JATAM_VARIANT_LIFO) != 0)
-            ev = run_assembly_lifo(m, g, stk, st, prm.grid, r, prm.key0, prm.key1, rid_lo,
-                                   rid_hi);
+            ev = run_assembly_lifo(m, g, stk, st, prm.grid, key);
         else
-            ev = run_assembly(m, g, st, prm.grid, r, prm.key0, prm.key1, rid_lo, rid_hi);
+            ev = run_assembly(m, g, st, prm.grid, key);
         work += st.steps;
         if (ev == kEvCorrupt)
             return jatam_result_t{JATAM_INVALID, 0, 0u, 0};

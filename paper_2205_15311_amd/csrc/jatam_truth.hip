@@ -132,8 +132,9 @@ __global__ __launch_bounds__(B) void truth_first_kernel(TruthArgs a)
         if (genome_ok(a, genome)) {
             const M m = build_bonds<M>(genome, a.t, a.bits, a.c);
             const uint64_t rid = genome | ((uint64_t)(uint32_t)a.t << 56);
-            const int ev = run_assembly(m, g, st, a.grid, 0, a.key0, a.key1, (uint32_t)rid,
-                                        (uint32_t)(rid >> 32));
+            const int ev = run_assembly(
+                m, g, st, a.grid,
+                RunKey{a.key0, a.key1, (uint32_t)rid, (uint32_t)(rid >> 32), 0});
             if (ev == kEvCorrupt) {
                 rec = jatam_result_t{JATAM_INVALID, 0, 0u, 0};
             } else if (ev != kEvNone) {
