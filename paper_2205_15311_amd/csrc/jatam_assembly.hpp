@@ -266,9 +266,10 @@ __device__ __forceinline__ uint32_t pick4(uint32_t j, uint32_t p0, uint32_t p1, 
 //   inside  bit 7 set where the neighbour lies in the box (not on its ring)
 //   occ, fr bit 7 set where it is occupied, on the frontier
 //   pend    its PEND nibble
-// fresh receives bit 7 where a site joins the frontier.  The other rules as
-// in update_site.
-__device__ __forceinline__ int check_sites(uint32_t codes, uint32_t inside, uint32_t occ,
+// fresh receives bit 7 where a site joins the frontier.  Returns the events as
+// bits: bit 7 of a byte where the structure leaves the box, bit 6 where a site
+// is ambiguous (event_of gives the event; the rules as in update_site).
+__device__ __forceinline__ uint32_t check_sites(uint32_t codes, uint32_t inside, uint32_t occ,
                                            uint32_t fr, uint32_t pend, uint32_t& fresh)
 {
     const uint32_t has = codes & kSiteAny;
@@ -277,7 +278,14 @@ __device__ __forceinline__ int check_sites(uint32_t codes, uint32_t inside, uint
     const uint32_t differ = ((pend ^ codes) & 0x0F0F0F0Fu) + 0x7F7F7F7Fu;
     const uint32_t ambiguous = live & ((codes << 1) | (fr & differ));
     fresh = live & ~fr;
-    return (has & ~inside) != 0 ? kEvUnbound : ambiguous != 0 ? kEvAmbig : kEvNone;
+    return (has & ~inside) | (ambiguous >> 1);
+}
+
+// The event of a step's bits: bit 0 set, the grid is corrupt; else check_sites'.
+__device__ __forceinline__ int event_of(uint32_t bits)
+{
+    return bits == 0 ? kEvNone : (bits & 1u) ? kEvCorrupt
+           : (bits & kSiteAny) != 0 ? kEvUnbound : kEvAmbig;
 }
 
 // Bit 7 of byte d set where cell (x, y)'s neighbour in direction d lies in the
@@ -304,8 +312,10 @@ __device__ __forceinline__ uint32_t inside_box(uint32_t x, uint32_t y, int G)
 // (32 x 32).  Measured with the bond lookup of Bonds: all of S_{2,8} in one
 // call 1.31 -> 1.07 ms, a generation of 65,536 three-tile genotypes at G = 32
 // (its longest run, one placement after the other) 0.93 -> 0.63 ms.
+//
+// Returns the step's event bits (event_of).
 template <int W, int B, class Src>
-__device__ __forceinline__ int run_step(const Src& m, LaneGrid<W, B>& g, RunState& st, int G,
+__device__ __forceinline__ uint32_t run_step(const Src& m, LaneGrid<W, B>& g, RunState& st, int G,
                                         uint32_t u)
 {
     using Geo = Geometry<W>;
@@ -365,7 +375,7 @@ __device__ __forceinline__ int run_step(const Src& m, LaneGrid<W, B>& g, RunStat
     for (uint32_t k = j - below; k > 0u; --k)
         rest &= rest - 1u;
     const uint32_t bit = (uint32_t)__builtin_ctz(rest | 0x80000000u);
-    int ev;
+    uint32_t ev;
     if constexpr (W == 16) {
         // a word holds two rows.  The cell's own word and the next (odd row)
         // or previous one (even row) as 64 bits hold the rows above and below
@@ -458,7 +468,7 @@ __device__ __forceinline__ int run_step(const Src& m, LaneGrid<W, B>& g, RunStat
     }
     st.osum |= 1u << w;
     st.steps += 1;
-    return total != nf ? kEvCorrupt : ev;
+    return ev | min(total ^ nf, 1u);
 }
 
 // Up to four steps of a run that is not over and whose steps so far are a
@@ -472,16 +482,16 @@ __device__ __forceinline__ int run_four(const Src& m, LaneGrid<W, B>& g, RunStat
 {
     const Words4 u = philox4x32_10((uint32_t)st.steps >> 2, (uint32_t)k.run, k.rid_lo, k.rid_hi,
                                    k.key0, k.key1);
-    int ev = run_step(m, g, st, G, u.w[0]);
-    if (ev == kEvNone && st.nf != 0) {
+    uint32_t ev = run_step(m, g, st, G, u.w[0]);
+    if (ev == 0 && st.nf != 0) {
         ev = run_step(m, g, st, G, u.w[1]);
-        if (ev == kEvNone && st.nf != 0) {
+        if (ev == 0 && st.nf != 0) {
             ev = run_step(m, g, st, G, u.w[2]);
-            if (ev == kEvNone && st.nf != 0)
+            if (ev == 0 && st.nf != 0)
                 ev = run_step(m, g, st, G, u.w[3]);
         }
     }
-    return ev;
+    return event_of(ev);
 }
 
 // One run from the seed to completion or to an event.

@@ -119,14 +119,20 @@ struct Bonds {
     // Colour tuple of the seed: tile 0, unrotated.
     __device__ __forceinline__ uint32_t seed() const { return t0; }
 
+    // by value: a choice between two members as lvalues makes the compiler
+    // address the struct by a run-time offset, in scratch memory (a memory
+    // round trip in every step)
+    __device__ __forceinline__ static uint32_t pick(bool c, uint32_t x, uint32_t y)
+    {
+        return c ? x : y;
+    }
+
     // Colour tuple of oriented tile k.
     __device__ __forceinline__ uint32_t oriented(uint32_t k) const
     {
-        uint32_t w = (k & 4u) ? t1 : t0;
-        if constexpr (TM == 4) {
-            const uint32_t w2 = (k & 4u) ? t3 : t2;
-            w = (k & 8u) ? w2 : w;
-        }
+        uint32_t w = pick((k & 4u) != 0, t1, t0);
+        if constexpr (TM == 4)
+            w = pick((k & 8u) != 0, pick((k & 4u) != 0, t3, t2), w);
         // rotate left by 8 (k mod 4): the shift amount counts mod 32
         return __builtin_amdgcn_alignbit(w, w, 0u - 8u * k);
     }
