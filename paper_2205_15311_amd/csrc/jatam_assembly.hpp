@@ -36,10 +36,19 @@ struct Geometry {
     static constexpr int kLaneWords = 2 * kWords + kPendWords;
 };
 
+// LDS atomic OR without return: sets bits with no read on the critical path.
+__device__ __forceinline__ void set_bits(uint32_t& w, uint32_t bits)
+{
+    __hip_atomic_fetch_or(&w, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Per-lane view of the workgroup's LDS.
 template <int W, int B>
 struct LaneGrid {
     using Geo = Geometry<W>;
+    static constexpr int kW = W;
+    static constexpr bool kLean = false;
+    static constexpr int kPend = Geo::kPend;
     uint32_t* base;   // &smem[threadIdx.x]
 
     __device__ __forceinline__ uint32_t& word(int k) { return base[k * B]; }
@@ -55,11 +64,6 @@ struct LaneGrid {
             word(k) = 0;
     }
     __device__ __forceinline__ uint32_t& pend_word(int p) { return word(Geo::kPend + (p >> 3)); }
-    // LDS atomic OR without return: sets bits with no read on the critical path
-    __device__ __forceinline__ static void set_bits(uint32_t& w, uint32_t bits)
-    {
-        __hip_atomic_fetch_or(&w, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
     __device__ __forceinline__ uint32_t row(int y)
     {
         if constexpr (W == 32) {
@@ -67,6 +71,60 @@ struct LaneGrid {
         } else {
             return (occ(y >> 1) >> ((y & 1) * 16)) & 0xFFFFu;
         }
+    }
+};
+
+// The grid of the first-run kernel, one wave a workgroup: FR and PEND only,
+// 40 words a lane instead of 48 (16 x 16) or 160 instead of 192 (32 x 32),
+// which lets 14 waves instead of 10, or 4 instead of 3, share a CU's LDS.  A
+// nibble holds tag = id + 1 (mod 16), and a cell off the frontier is occupied
+// exactly when its nibble is not zero: so a step reads, tests and writes three
+// words less too.  Id 15 has tag 0, which is fine on the frontier (FR tells);
+// a cell placed with it takes the tag 1 instead, and the run's tiles count as
+// lost (its shape is then replayed rather than unpacked by the proof stage).
+// The occupied cells near the seed are kept as a bitmap in a register
+// (RunState::near) for the shape at the run's end.
+//
+// Row W-1 is never part of the box: the words that only it uses (`spare`,
+// spare_words() of them) are free for the wave's own data.  A step may read
+// them and write them back unchanged, and nothing clears them.
+template <int W>
+struct LeanGrid {
+    using Geo = Geometry<W>;
+    static constexpr int kW = W;
+    static constexpr bool kLean = true;
+    static constexpr int kFr = 0;
+    static constexpr int kPend = Geo::kWords;
+    static constexpr int kLaneWords = Geo::kWords + Geo::kPendWords;
+    // all lanes' PEND words of row W-1, and (W = 32) its FR word
+    static constexpr int kSpare = (kLaneWords - W / 8) * 64;
+    static constexpr int kSpareFr = W == 32 ? (W - 1) * 64 : -1;
+    uint32_t* base;   // &smem[lane]
+
+    __device__ __forceinline__ uint32_t& word(int k) { return base[k * 64]; }
+    __device__ __forceinline__ uint32_t& fr(int w) { return word(kFr + w); }
+    __device__ __forceinline__ uint32_t& pend_word(int p) { return word(kPend + (p >> 3)); }
+    __device__ __forceinline__ void clear_all()
+    {
+        for (int k = 0; k < kLaneWords; ++k)
+            word(k) = 0;
+    }
+    // Row y's occupied cells, once no frontier is left.
+    __device__ __forceinline__ uint32_t row(int y)
+    {
+        uint32_t r = 0;
+#pragma unroll
+        for (int h = 0; h < W / 16; ++h) {
+            const int at = kPend + y * (W / 8) + 2 * h;
+            uint64_t v = ((uint64_t)word(at + 1) << 32) | word(at);
+            v |= v >> 2;
+            v = (v | (v >> 1)) & 0x1111111111111111ull;
+            v = (v | (v >> 3)) & 0x0303030303030303ull;
+            v = (v | (v >> 6)) & 0x000F000F000F000Full;
+            v = (v | (v >> 12)) & 0x000000FF000000FFull;
+            r |= (uint32_t)((v | (v >> 24)) & 0xFFFFu) << (16 * h);
+        }
+        return r;
     }
 };
 
@@ -93,6 +151,10 @@ struct RunState {
     // 32 x 32 layout: frontier sites per group of four rows, byte k for rows
     // 4k .. 4k+3 (at most 4 * 31 sites), the frontier select's first level
     uint64_t groups;
+    // LeanGrid: the occupied cells of the 8 x 8 window whose cell (3, 3) is the
+    // seed, and whether a placed tile's id was lost
+    uint64_t near;
+    uint32_t lost;
 
     __device__ __forceinline__ int size() const { return steps + 1; }
     // Words that may hold a touched cell: frontier sites lie next to occupied
@@ -165,8 +227,8 @@ __device__ __forceinline__ int update_site(const Src& m, LaneGrid<W, B>& g, RunS
         unbound = unbound | (opt.has & ring);
         ambiguous = ambiguous | (live & (opt.multi | (in_f & (pending != opt.id))));
         if (live && !opt.multi && !in_f) {
-            LaneGrid<W, B>::set_bits(g.fr(q[d] >> 5), 1u << bit);
-            LaneGrid<W, B>::set_bits(g.pend_word(q[d]), opt.id << sh);
+            set_bits(g.fr(q[d] >> 5), 1u << bit);
+            set_bits(g.pend_word(q[d]), opt.id << sh);
             st.nf += 1;
             frontier_group_add<W>(st, q[d], true);
             if (added != nullptr)
@@ -178,25 +240,39 @@ __device__ __forceinline__ int update_site(const Src& m, LaneGrid<W, B>& g, RunS
 
 // Clears what the previous run touched and places the seed (tile 0,
 // unrotated) at the centre; returns the seed's cell.
-template <int W, int B>
-__device__ __forceinline__ int run_clear(LaneGrid<W, B>& g, RunState& st, int G)
+template <class Grid>
+__device__ __forceinline__ int run_clear(Grid& g, RunState& st, int G)
 {
+    constexpr int W = Grid::kW;
     // occupied cells keep their tiles in PEND, and a run that ended on an
     // event leaves frontier cells (with their PEND nibbles) behind: clear all
-    for (uint32_t s = st.touched<W>(); s; s &= s - 1) {
+    // (but row W-1, which no run touches)
+    uint32_t touched = st.touched<W>();
+    if constexpr (W == 32)
+        touched &= 0x7FFFFFFFu;
+    for (uint32_t s = touched; s; s &= s - 1) {
         const int w = __builtin_ctz(s);
-        g.occ(w) = 0;
+        if constexpr (!Grid::kLean)
+            g.occ(w) = 0;
         g.fr(w) = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            g.word(Geometry<W>::kPend + 4 * w + k) = 0;
+        const int second = W == 16 && w == 7 ? 0 : 2;
+        g.word(Grid::kPend + 4 * w) = 0;
+        g.word(Grid::kPend + 4 * w + 1) = 0;
+        g.word(Grid::kPend + 4 * w + second) = 0;
+        g.word(Grid::kPend + 4 * w + second + 1) = 0;
     }
     st.nf = 0;
     st.groups = 0;
     st.steps = 0;
     st.choice = false;
     const int seed_pos = (G / 2 - 1) * W + (G / 2 - 1);
-    g.occ(seed_pos >> 5) = 1u << (seed_pos & 31);
+    if constexpr (Grid::kLean) {
+        g.pend_word(seed_pos) = 1u << ((seed_pos & 7) * 4);   // id 0
+        st.near = 1ull << 27;
+        st.lost = 0;
+    } else {
+        g.occ(seed_pos >> 5) = 1u << (seed_pos & 31);
+    }
     st.osum = 1u << (seed_pos >> 5);
     return seed_pos;
 }
@@ -206,10 +282,10 @@ __device__ __forceinline__ int run_clear(LaneGrid<W, B>& g, RunState& st, int G)
 // (tile 0, unrotated) at the centre and puts its sites on the frontier.  In
 // the cleared grid they are free and off the frontier, and with G >= 8 the
 // ring is at least three cells away.
-template <int W, int B>
-__device__ __forceinline__ int run_start_known(LaneGrid<W, B>& g, RunState& st, int G,
-                                               uint32_t codes)
+template <class Grid>
+__device__ __forceinline__ int run_start_known(Grid& g, RunState& st, int G, uint32_t codes)
 {
+    constexpr int W = Grid::kW;
     const int p = run_clear(g, st, G);
     if ((codes & kSiteMulti) != 0)
         return kEvAmbig;
@@ -218,18 +294,19 @@ __device__ __forceinline__ int run_start_known(LaneGrid<W, B>& g, RunState& st, 
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         const int q = p + (d == 0 ? -W : d == 1 ? 1 : d == 2 ? W : -1);
-        const uint32_t code = codes >> (8 * d);
-        LaneGrid<W, B>::set_bits(g.fr(q >> 5), ((code >> 7) & 1u) << (q & 31));
-        LaneGrid<W, B>::set_bits(g.pend_word(q), (code & 15u) << ((q & 7) * 4));
+        const uint32_t code = codes >> (8 * d), any = (code >> 7) & 1u;
+        const uint32_t nibble = Grid::kLean ? (code + any) & 15u : code & 15u;
+        set_bits(g.fr(q >> 5), any << (q & 31));
+        set_bits(g.pend_word(q), nibble << ((q & 7) * 4));
         if constexpr (W == 32)
-            st.groups += (uint64_t)((code >> 7) & 1u) << (8 * (q >> 7));
+            st.groups += (uint64_t)any << (8 * (q >> 7));
     }
     return kEvNone;
 }
 
 // Starts a run of genotype m.
-template <int W, int B, class Src>
-__device__ __forceinline__ int run_start(const Src& m, LaneGrid<W, B>& g, RunState& st, int G)
+template <class Grid, class Src>
+__device__ __forceinline__ int run_start(const Src& m, Grid& g, RunState& st, int G)
 {
     return run_start_known(g, st, G, m.codes(m.seed()));
 }
@@ -266,16 +343,18 @@ __device__ __forceinline__ uint32_t pick4(uint32_t j, uint32_t p0, uint32_t p1, 
 //   inside  bit 7 set where the neighbour lies in the box (not on its ring)
 //   occ, fr bit 7 set where it is occupied, on the frontier
 //   pend    its PEND nibble
+//   tags    the nibbles that the placed tile's sites would have
 // fresh receives bit 7 where a site joins the frontier.  Returns the events as
 // bits: bit 7 of a byte where the structure leaves the box, bit 6 where a site
 // is ambiguous (event_of gives the event; the rules as in update_site).
 __device__ __forceinline__ uint32_t check_sites(uint32_t codes, uint32_t inside, uint32_t occ,
-                                           uint32_t fr, uint32_t pend, uint32_t& fresh)
+                                                uint32_t fr, uint32_t pend, uint32_t tags,
+                                                uint32_t& fresh)
 {
     const uint32_t has = codes & kSiteAny;
     const uint32_t live = has & inside & ~occ;
     // nibbles that differ: their XOR is 1..15, so adding 0x7F sets bit 7
-    const uint32_t differ = ((pend ^ codes) & 0x0F0F0F0Fu) + 0x7F7F7F7Fu;
+    const uint32_t differ = ((pend ^ tags) & 0x0F0F0F0Fu) + 0x7F7F7F7Fu;
     const uint32_t ambiguous = live & ((codes << 1) | (fr & differ));
     fresh = live & ~fr;
     return (has & ~inside) | (ambiguous >> 1);
@@ -314,11 +393,12 @@ __device__ __forceinline__ uint32_t inside_box(uint32_t x, uint32_t y, int G)
 // (its longest run, one placement after the other) 0.93 -> 0.63 ms.
 //
 // Returns the step's event bits (event_of).
-template <int W, int B, class Src>
-__device__ __forceinline__ uint32_t run_step(const Src& m, LaneGrid<W, B>& g, RunState& st, int G,
-                                        uint32_t u)
+template <class Grid, class Src>
+__device__ __forceinline__ uint32_t run_step(const Src& m, Grid& g, RunState& st, int G,
+                                             uint32_t u)
 {
-    using Geo = Geometry<W>;
+    constexpr int W = Grid::kW;
+    constexpr bool kLean = Grid::kLean;
     const uint32_t nf = st.nf;
     const uint32_t j = __umulhi(u, nf);
     st.choice = st.choice | (nf >= 2);
@@ -370,102 +450,141 @@ __device__ __forceinline__ uint32_t run_step(const Src& m, LaneGrid<W, B>& g, Ru
         w = w0 + r;
     }
     // the site's bit: its rank in the word is nearly always 0..2, so clearing
-    // the lowest bit that often beats a fixed binary search
+    // the lowest bit that often beats a fixed binary search; the first three
+    // without a branch
     uint32_t rest = fw;
-    for (uint32_t k = j - below; k > 0u; --k)
+    int rank = (int)(j - below);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        rest &= (rest - 1u) | (uint32_t)((rank - 1) >> 31);
+        rank = max(rank - 1, 0);
+    }
+    for (; rank > 0; --rank)
         rest &= rest - 1u;
     const uint32_t bit = (uint32_t)__builtin_ctz(rest | 0x80000000u);
-    uint32_t ev;
+    uint32_t ev, x, y, fresh;
     if constexpr (W == 16) {
         // a word holds two rows.  The cell's own word and the next (odd row)
         // or previous one (even row) as 64 bits hold the rows above and below
         // too: shifted so that N is bit 0, W is bit 15, the cell 16, E 17 and
         // S 32 (off the torus' rim they show ring cells, which are masked)
-        const uint32_t x = bit & 15u, odd = bit >> 4, y = 2u * w + odd;
-        const uint32_t wa = (w + 2u * odd - 1u) & 7u, shift = bit ^ 16u;
-        const uint32_t own = g.occ(w), adj = g.occ(wa), fa = g.fr(wa);
+        const uint32_t odd = bit >> 4, wa = (w + 2u * odd - 1u) & 7u, shift = bit ^ 16u;
+        x = bit & 15u;
+        y = 2u * w + odd;
+        const uint32_t fa = g.fr(wa);
         // the row's 16 PEND nibbles, and the words above and below the cell
-        const uint32_t prow = Geo::kPend + 2u * y, half = x >> 3;
-        const uint32_t n_at = Geo::kPend + 2u * ((y - 1u) & 15u) + half;
-        const uint32_t s_at = Geo::kPend + 2u * ((y + 1u) & 15u) + half;
+        const uint32_t prow = Grid::kPend + 2u * y, half = x >> 3;
+        const uint32_t n_at = Grid::kPend + 2u * ((y - 1u) & 15u) + half;
+        const uint32_t s_at = Grid::kPend + 2u * ((y + 1u) & 15u) + half;
         uint64_t row = ((uint64_t)g.word(prow + 1) << 32) | g.word(prow);
         const uint32_t pn = g.word(n_at), ps = g.word(s_at), sh = 4u * (x & 7u);
-        const uint64_t occ2 = odd ? ((uint64_t)adj << 32) | own : ((uint64_t)own << 32) | adj;
         uint64_t fr2 = odd ? ((uint64_t)fa << 32) | fw : ((uint64_t)fw << 32) | fa;
-        // nibbles: 0 the W neighbour, 1 the cell, 2 the E neighbour
-        const uint32_t near = (uint32_t)((row << 4) >> (4u * x));
-        const uint32_t codes = m.codes(m.oriented((near >> 4) & 15u));
         auto around = [](uint64_t u) -> uint32_t {
             const uint32_t a = (uint32_t)u, b = (uint32_t)(u >> 32);
             return ((a << 7) & 0x80u) | ((a >> 2) & 0x8000u) | ((b << 23) & 0x800000u) |
                    ((a << 16) & 0x80000000u);
         };
+        const uint32_t fr = around(fr2 >> shift);
+        // nibbles: 0 the W neighbour, 1 the cell, 2 the E neighbour
+        const uint32_t near = (uint32_t)((row << 4) >> (4u * x)), own = (near >> 4) & 15u;
         const uint32_t pend = ((pn >> sh) & 15u) | (near & 0xF00u) | (((ps >> sh) & 15u) << 16) |
                               ((near & 15u) << 24);
-        uint32_t fresh;
-        ev = check_sites(codes, inside_box(x, y, G), around(occ2 >> shift),
-                         around(fr2 >> shift), pend, fresh);
+        uint32_t codes, tags, occ, mark = 0;
+        if constexpr (kLean) {
+            codes = m.codes(m.oriented(own - 1u));
+            tags = codes + 0x01010101u;
+            occ = (pend + 0x7F7F7F7Fu) & ~fr;
+            if constexpr (Src::kManyIds) {   // id 15: see LeanGrid
+                mark = (own - 1u) >> 31;
+                st.lost |= mark;
+            }
+        } else {
+            const uint32_t o = g.occ(w), oa = g.occ(wa);
+            codes = m.codes(m.oriented(own));
+            tags = codes;
+            occ = around((odd ? ((uint64_t)oa << 32) | o : ((uint64_t)o << 32) | oa) >> shift);
+            g.occ(w) = o | (1u << bit);
+        }
+        ev = check_sites(codes, inside_box(x, y, G), occ, fr, pend, tags, fresh);
         // the cell leaves the frontier, fresh sites (none of them on it) join
         const uint32_t flip = ((fresh >> 7) & 1u) | ((fresh >> 16) & 0x8000u) | 0x10000u |
                               ((fresh << 2) & 0x20000u);
         fr2 ^= (((uint64_t)((fresh >> 23) & 1u) << 32) | flip) << shift;
         g.fr(w) = odd ? (uint32_t)fr2 : (uint32_t)(fr2 >> 32);
         g.fr(wa) = odd ? (uint32_t)(fr2 >> 32) : (uint32_t)fr2;
-        const uint32_t ones = fresh >> 7, ids = codes & ((ones << 4) - ones);
-        row |= ((uint64_t)((ids >> 24) | (ids & 0xF00u)) << (4u * x)) >> 4;
+        const uint32_t ones = fresh >> 7, ids = tags & ((ones << 4) - ones);
+        row |= ((uint64_t)((ids >> 24) | (mark << 4) | (ids & 0xF00u)) << (4u * x)) >> 4;
         g.word(prow) = (uint32_t)row;
         g.word(prow + 1) = (uint32_t)(row >> 32);
         g.word(n_at) = pn | ((ids & 15u) << sh);
         g.word(s_at) = ps | (((ids >> 16) & 15u) << sh);
-        g.occ(w) = own | (1u << bit);
-        st.nf = nf + (uint32_t)__popc(fresh) - 1u;
     } else {
         // a word holds one row
-        const uint32_t x = bit, y = w, yn = (y - 1u) & 31u, ys = (y + 1u) & 31u;
-        const uint32_t on = g.occ(yn), own = g.occ(y), os = g.occ(ys);
+        x = bit;
+        y = w;
+        const uint32_t yn = (y - 1u) & 31u, ys = (y + 1u) & 31u;
         const uint32_t fn = g.fr(yn), fs = g.fr(ys);
         // eight PEND nibbles a word: the cell's word and the next one in its
         // row (right half) or the one before (left half) hold E and W
         const uint32_t at = x >> 3, k = x & 7u, sh = 4u * k;
         const bool right = k >= 4u;
-        const uint32_t prow = Geo::kPend + 4u * y, pa = prow + ((right ? at + 1u : at - 1u) & 3u);
-        const uint32_t n_at = Geo::kPend + 4u * yn + at, s_at = Geo::kPend + 4u * ys + at;
+        const uint32_t prow = Grid::kPend + 4u * y, pa = prow + ((right ? at + 1u : at - 1u) & 3u);
+        const uint32_t n_at = Grid::kPend + 4u * yn + at, s_at = Grid::kPend + 4u * ys + at;
         const uint32_t po = g.word(prow + at), pj = g.word(pa), pn = g.word(n_at);
         const uint32_t ps = g.word(s_at);
         uint64_t row = right ? ((uint64_t)pj << 32) | po : ((uint64_t)po << 32) | pj;
         const uint32_t rsh = right ? sh - 4u : sh + 28u;
         // nibbles: 0 the W neighbour, 1 the cell, 2 the E neighbour
-        const uint32_t near = (uint32_t)(row >> rsh);
-        const uint32_t codes = m.codes(m.oriented((near >> 4) & 15u));
+        const uint32_t near = (uint32_t)(row >> rsh), own = (near >> 4) & 15u;
+        const uint32_t pend = ((pn >> sh) & 15u) | (near & 0xF00u) | (((ps >> sh) & 15u) << 16) |
+                              ((near & 15u) << 24);
         // rows rotated so that W is bit 0, the cell 1, E 2
         auto around = [x](uint32_t n, uint32_t o, uint32_t s) -> uint32_t {
             const uint32_t a = __builtin_amdgcn_alignbit(o, o, x - 1u);
             return (((n >> x) & 1u) << 7) | ((a << 13) & 0x8000u) | (((s >> x) & 1u) << 23) |
                    (a << 31);
         };
-        const uint32_t pend = ((pn >> sh) & 15u) | (near & 0xF00u) | (((ps >> sh) & 15u) << 16) |
-                              ((near & 15u) << 24);
-        uint32_t fresh;
-        ev = check_sites(codes, inside_box(x, y, G), around(on, own, os), around(fn, fw, fs), pend,
-                         fresh);
+        const uint32_t fr = around(fn, fw, fs);
+        uint32_t codes, tags, occ, mark = 0;
+        if constexpr (kLean) {
+            codes = m.codes(m.oriented(own - 1u));
+            tags = codes + 0x01010101u;
+            occ = (pend + 0x7F7F7F7Fu) & ~fr;
+            if constexpr (Src::kManyIds) {   // id 15: see LeanGrid
+                mark = (own - 1u) >> 31;
+                st.lost |= mark;
+            }
+        } else {
+            const uint32_t on = g.occ(yn), o = g.occ(y), os = g.occ(ys);
+            codes = m.codes(m.oriented(own));
+            tags = codes;
+            occ = around(on, o, os);
+            g.occ(y) = o | (1u << x);
+        }
+        ev = check_sites(codes, inside_box(x, y, G), occ, fr, pend, tags, fresh);
         const uint32_t flip = (fresh >> 31) | 2u | ((fresh >> 13) & 4u);
         const uint32_t up = (fresh >> 7) & 1u, down = (fresh >> 23) & 1u;
         g.fr(y) = fw ^ __builtin_amdgcn_alignbit(flip, flip, 1u - x);
         g.fr(yn) = fn | (up << x);
         g.fr(ys) = fs | (down << x);
-        const uint32_t ones = fresh >> 7, ids = codes & ((ones << 4) - ones);
-        row |= (uint64_t)((ids >> 24) | (ids & 0xF00u)) << rsh;
+        const uint32_t ones = fresh >> 7, ids = tags & ((ones << 4) - ones);
+        row |= (uint64_t)((ids >> 24) | (mark << 4) | (ids & 0xF00u)) << rsh;
         g.word(prow + at) = right ? (uint32_t)row : (uint32_t)(row >> 32);
         g.word(pa) = right ? (uint32_t)(row >> 32) : (uint32_t)row;
         g.word(n_at) = pn | ((ids & 15u) << sh);
         g.word(s_at) = ps | (((ids >> 16) & 15u) << sh);
-        g.occ(y) = own | (1u << x);
-        st.nf = nf + (uint32_t)__popc(fresh) - 1u;
         st.groups += (uint64_t)(uint32_t)__popc(fresh & 0x80008000u) << (8u * (y >> 2));
         st.groups -= 1ull << (8u * (y >> 2));
         st.groups += (uint64_t)up << (8u * (yn >> 2));
         st.groups += (uint64_t)down << (8u * (ys >> 2));
     }
+    if constexpr (kLean) {
+        // the cell in the window at the seed (cells before it wrap to large
+        // numbers)
+        const uint32_t dx = x - (uint32_t)(G / 2 - 4), dy = y - (uint32_t)(G / 2 - 4);
+        st.near |= (uint64_t)((dx | dy) < 8u ? 1u : 0u) << ((8u * dy + dx) & 63u);
+    }
+    st.nf = nf + (uint32_t)__popc(fresh) - 1u;
     st.osum |= 1u << w;
     st.steps += 1;
     return ev | min(total ^ nf, 1u);
@@ -476,8 +595,8 @@ __device__ __forceinline__ uint32_t run_step(const Src& m, LaneGrid<W, B>& g, Ru
 // lanes all start their runs between such groups computes the generator once
 // a group with every running lane taking part, and tests for finished lanes
 // once a group.
-template <int W, int B, class Src>
-__device__ __forceinline__ int run_four(const Src& m, LaneGrid<W, B>& g, RunState& st, int G,
+template <class Grid, class Src>
+__device__ __forceinline__ int run_four(const Src& m, Grid& g, RunState& st, int G,
                                         const RunKey& k)
 {
     const Words4 u = philox4x32_10((uint32_t)st.steps >> 2, (uint32_t)k.run, k.rid_lo, k.rid_hi,
@@ -495,8 +614,8 @@ __device__ __forceinline__ int run_four(const Src& m, LaneGrid<W, B>& g, RunStat
 }
 
 // One run from the seed to completion or to an event.
-template <int W, int B, class Src>
-__device__ __forceinline__ int run_assembly(const Src& m, LaneGrid<W, B>& g, RunState& st, int G,
+template <class Grid, class Src>
+__device__ __forceinline__ int run_assembly(const Src& m, Grid& g, RunState& st, int G,
                                             const RunKey& k)
 {
     int ev = run_start(m, g, st, G);
@@ -546,10 +665,10 @@ struct ShapeBox {
     int xmin, ymin, w, h;
 };
 
-template <int W, int B>
-__device__ __forceinline__ ShapeBox crop(LaneGrid<W, B>& g, int G)
+template <class Grid>
+__device__ __forceinline__ ShapeBox crop(Grid& g, int G)
 {
-    int ymin = W, ymax = -1;
+    int ymin = Grid::kW, ymax = -1;
     uint32_t cols = 0;
     for (int y = 0; y < G - 1; ++y) {
         const uint32_t r = g.row(y);
@@ -650,8 +769,8 @@ __device__ __forceinline__ bool shape_is_guarded(const Src& m, LaneGrid<W, B>& g
 // group: bit 2 transposes, bit 0 mirrors x, bit 1 mirrors y.  Cells are
 // listed in row-major order of the oriented frame, each as the bytes x, y
 // (§3.3, App. F.4).
-template <int W, int B>
-__device__ __forceinline__ uint32_t orientation_hash(LaneGrid<W, B>& g, const ShapeBox& bx, int k)
+template <class Grid>
+__device__ __forceinline__ uint32_t orientation_hash(Grid& g, const ShapeBox& bx, int k)
 {
     const bool transpose = k & 4, flip_x = k & 1, flip_y = k & 2;
     const int wt = transpose ? bx.h : bx.w, ht = transpose ? bx.w : bx.h;
@@ -766,19 +885,28 @@ __device__ __forceinline__ uint64_t image8(uint64_t m, int w, int h, int k)
 }
 
 // The cropped shape held in OCC as an 8 x 8 bitmap; false if it does not fit.
-template <int W, int B>
-__device__ __forceinline__ bool shape_bitmap8(LaneGrid<W, B>& g, int G, uint64_t& m, int& w,
-                                              int& h)
+template <class Grid>
+__device__ __forceinline__ bool shape_bitmap8(Grid& g, int G, uint64_t& m, int& w, int& h,
+                                              int& x0, int& y0)
 {
     const ShapeBox bx = crop(g, G);
     w = bx.w;
     h = bx.h;
+    x0 = bx.xmin;
+    y0 = bx.ymin;
     if (bx.w > 8 || bx.h > 8)
         return false;
     m = 0;
     for (int y = 0; y < bx.h; ++y)
         m |= (uint64_t)((g.row(bx.ymin + y) >> bx.xmin) & 0xFFu) << (8 * y);
     return true;
+}
+
+template <class Grid>
+__device__ __forceinline__ bool shape_bitmap8(Grid& g, int G, uint64_t& m, int& w, int& h)
+{
+    int x0, y0;
+    return shape_bitmap8(g, G, m, w, h, x0, y0);
 }
 
 // Width and height of an anchored 8 x 8 bitmap (not empty).
@@ -836,55 +964,53 @@ __device__ __forceinline__ bool shape_bitmap8_w16(LaneGrid<16, B>& g, uint64_t& 
     return true;
 }
 
-// The same through the 8 x 8 window around the seed, where nearly every shape
-// lies: four words (the window starts on an even row), shifted to its first
-// column and packed to bytes; the shape lies in it if all its cells are
-// counted there.  About 30 instructions against 110 for any position.
-template <int B>
-__device__ __forceinline__ bool shape_near_seed_w16(LaneGrid<16, B>& g, int G, int size,
-                                                    uint64_t& m, int& x0, int& y0)
+// A bitmap v of an 8 x 8 window (not empty), anchored at its first row and
+// column, which start at (wx, wy) of the grid.
+__device__ __forceinline__ uint64_t anchor8(uint64_t v, int wx, int wy, int& x0, int& y0)
 {
-    const int s = G / 2 - 1;                      // 3 .. 7
-    const int wx = s - 3, wy = (s - 3) & ~1;      // the window's first column and row
-    uint32_t r[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        r[q] = g.occ(wy / 2 + q) >> wx;
-    const uint32_t lo = __builtin_amdgcn_perm(r[1], r[0], 0x06040200u);
-    const uint32_t hi = __builtin_amdgcn_perm(r[3], r[2], 0x06040200u);
-    const uint64_t v = ((uint64_t)hi << 32) | lo;
-    if (__popcll(v) != size)
-        return false;
     const int rows = __builtin_ctzll(v) & ~7;
-    uint32_t cols = lo | hi;
+    uint32_t cols = (uint32_t)v | (uint32_t)(v >> 32);
     cols |= cols >> 16;
     cols |= cols >> 8;
     const int left = __builtin_ctz(cols);
-    m = v >> (rows + left);
     x0 = wx + left;
     y0 = wy + rows / 8;
-    return true;
+    return v >> (rows + left);
 }
 
-// The cropped shape of `size` cells as an anchored 8 x 8 bitmap and where it
-// starts; false if its box exceeds 8 x 8.
-template <int W, int B>
-__device__ __forceinline__ bool shape_key8(LaneGrid<W, B>& g, int G, int size, uint64_t& m,
-                                           int& x0, int& y0)
+// The cropped shape of a finished run as an anchored 8 x 8 bitmap and where it
+// starts; false if its box exceeds 8 x 8.  Nearly every shape lies in an 8 x 8
+// window around the seed, and does so exactly if all of its cells are counted
+// there: the lean grid keeps that window in a register; in the 16 x 16 layout
+// it is four words (from an even row), shifted to its first column and packed
+// to bytes, about 30 instructions against 110 for a box anywhere.
+template <class Grid>
+__device__ __forceinline__ bool shape_key8(Grid& g, const RunState& st, int G, int size,
+                                           uint64_t& m, int& x0, int& y0)
 {
-    if constexpr (W == 16) {
-        return shape_near_seed_w16(g, G, size, m, x0, y0) || shape_bitmap8_w16(g, m, x0, y0);
-    } else {
-        const ShapeBox bx = crop(g, G);
-        x0 = bx.xmin;
-        y0 = bx.ymin;
-        if (bx.w > 8 || bx.h > 8)
-            return false;
-        m = 0;
-        for (int y = 0; y < bx.h; ++y)
-            m |= (uint64_t)((g.row(bx.ymin + y) >> bx.xmin) & 0xFFu) << (8 * y);
-        return true;
+    const int s = G / 2 - 1;
+    if constexpr (Grid::kLean) {
+        if (__popcll(st.near) == size) {
+            m = anchor8(st.near, s - 3, s - 3, x0, y0);
+            return true;
+        }
+    } else if constexpr (Grid::kW == 16) {
+        const int wx = s - 3, wy = (s - 3) & ~1;
+        uint32_t r[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            r[q] = g.occ(wy / 2 + q) >> wx;
+        const uint32_t lo = __builtin_amdgcn_perm(r[1], r[0], 0x06040200u);
+        const uint32_t hi = __builtin_amdgcn_perm(r[3], r[2], 0x06040200u);
+        const uint64_t v = ((uint64_t)hi << 32) | lo;
+        if (__popcll(v) == size) {
+            m = anchor8(v, wx, wy, x0, y0);
+            return true;
+        }
+        return shape_bitmap8_w16(g, m, x0, y0);
     }
+    int w, h;
+    return shape_bitmap8(g, G, m, w, h, x0, y0);
 }
 
 // ---------------------------------------------------------------------------
@@ -908,18 +1034,19 @@ __device__ __forceinline__ uint4 packed_none()
 }
 
 // Packs the shape m (shape_key8) whose box starts at (x0, y0).
-template <int W, int B>
-__device__ __forceinline__ uint4 pack_shape(LaneGrid<W, B>& g, int G, int size, uint64_t m,
-                                            int x0, int y0)
+template <class Grid>
+__device__ __forceinline__ uint4 pack_shape(Grid& g, const RunState& st, int G, int size,
+                                            uint64_t m, int x0, int y0)
 {
-    if (size > kPackedCells)
+    if (size > kPackedCells || (Grid::kLean && st.lost != 0))
         return packed_none();
     uint64_t tiles = 0;
     int k = 0;
     for (uint64_t cells = m; cells != 0; cells &= cells - 1, k += 4) {
         const int b = __builtin_ctzll(cells);
-        const int p = (y0 + (b >> 3)) * W + x0 + (b & 7);
-        tiles |= (uint64_t)((g.pend_word(p) >> ((uint32_t)(p & 7) * 4u)) & 15u) << k;
+        const int p = (y0 + (b >> 3)) * Grid::kW + x0 + (b & 7);
+        const uint32_t nibble = (g.pend_word(p) >> ((uint32_t)(p & 7) * 4u)) & 15u;
+        tiles |= (uint64_t)(Grid::kLean ? nibble - 1u : nibble) << k;
     }
     const int sc = G / 2 - 1;
     tiles |= (uint64_t)((sc - y0) * 8 + (sc - x0)) << 58;
@@ -1175,7 +1302,7 @@ __device__ __forceinline__ int run_assembly_lifo(const Src& m, LaneGrid<W, B>& g
         const uint32_t pw = g.pend_word(p);
         const uint32_t sh = ((uint32_t)p & 7u) * 4u;
         const uint32_t tuple = m.oriented((pw >> sh) & 15u);
-        LaneGrid<W, B>::set_bits(g.occ(w), 1u << (p & 31));
+        set_bits(g.occ(w), 1u << (p & 31));
         st.osum |= 1u << w;
         st.steps += 1;
         const uint32_t len = st.nf;
@@ -1188,8 +1315,8 @@ __device__ __forceinline__ int run_assembly_lifo(const Src& m, LaneGrid<W, B>& g
 }
 
 // D4-invariant hash of the shape held in OCC, computed by one lane.
-template <int W, int B>
-__device__ uint32_t shape_hash(LaneGrid<W, B>& g, int G)
+template <class Grid>
+__device__ uint32_t shape_hash(Grid& g, int G)
 {
     uint32_t hs[8];
     uint64_t m;

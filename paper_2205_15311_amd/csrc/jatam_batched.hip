@@ -216,8 +216,8 @@ using WaveShapeCache = ShapeCache<kShapeCache>;
 // (small0, small1) are computed once per workspace and read once per kernel
 // (a load in the loop would make the wave wait for all its record stores).
 // Bitmaps go through the wave's cache; a miss hashes the bitmap and fills it.
-template <int W>
-__device__ __forceinline__ uint32_t det_hash(LaneGrid<W, 64>& g, uint32_t small0, uint32_t small1,
+template <class Grid>
+__device__ __forceinline__ uint32_t det_hash(Grid& g, uint32_t small0, uint32_t small1,
                                              WaveShapeCache& cache, bool want, int size, int grid,
                                              bool fits, uint64_t key)
 {
@@ -254,16 +254,30 @@ template <int W, class M, int kIn>
 __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int klass)
 {
     const uint32_t small0 = a.small0, small1 = a.small1;
-    using Geo = Geometry<W>;
+    using Grid = LeanGrid<W>;
     const uint64_t first = slice_first(a);
     jatam_result_t* const out = slice_out(a);
-    __shared__ uint32_t smem[Geo::kLaneWords * 64];
-    __shared__ uint32_t ring[kRing];       // survivor indices
-    __shared__ uint32_t ring_opt[kRing];   // their seeds' four site codes
-    __shared__ uint4 cache_mem[kShapeCache];
-    __shared__ uint32_t size_hist[kSizeBuckets];   // sizes this wave staged, by bucket
-    LaneGrid<W, 64> g{smem + threadIdx.x};
+    // The wave's survivor ring, seed codes, hash cache and size counts, as far
+    // as they fit in the grid's spare words: 11,520 bytes of LDS in all for
+    // W = 16 (9 granules of 1,280: 14 waves a CU) and 40,960 for W = 32
+    // (4 waves), where the seed codes are worked out again at the start.
+    constexpr bool kKeepCodes = W == 16;
+    constexpr int kOwnWords = W == 16 ? kRing + 4 * kShapeCache + kSizeBuckets : 1;
+    __shared__ __attribute__((aligned(16))) uint32_t smem[Grid::kLaneWords * 64];
+    __shared__ __attribute__((aligned(16))) uint32_t own_words[kOwnWords];
+    uint32_t* const ring = smem + Grid::kSpare;   // survivor indices
+    uint32_t* const ring_opt = own_words;         // their seeds' site codes (kKeepCodes)
+    uint4* const cache_mem =
+        reinterpret_cast<uint4*>(W == 16 ? own_words + kRing : smem + Grid::kSpare + kRing);
+    // sizes this wave staged, by bucket
+    uint32_t* const size_hist =
+        W == 16 ? own_words + kRing + 4 * kShapeCache : smem + Grid::kSpareFr;
+    static_assert(W == 32 || kRing <= 64 * (W / 8), "the ring fits row 15's PEND words");
+    static_assert(W == 16 || (kRing + 4 * kShapeCache <= 64 * (W / 8) && kSizeBuckets <= 64),
+                  "ring and cache fit row 31's PEND words, the counts its FR words");
+    Grid g{smem + threadIdx.x};
     g.clear_all();
+    __syncthreads();
     WaveShapeCache cache{cache_mem};
     cache.clear(lane_id());
     static_assert(kSizeBuckets == 64, "one bucket per lane");
@@ -356,7 +370,7 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
             int x0 = 0, y0 = 0;
             bool fits = false;
             if (det || candidate)
-                fits = shape_key8(g, gd.grid, st.size(), key, x0, y0);
+                fits = shape_key8(g, st, gd.grid, st.size(), key, x0, y0);
             if (__ballot(det) != 0)
                 rec.hash = det_hash(g, small0, small1, cache, det, st.size(), gd.grid, fits, key);
             if (finish) {
@@ -372,7 +386,7 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                 seg_size[pos] = (uint16_t)st.size();
                 // the shape, for the proof stage to check without a replay
                 seg_shape[pos] =
-                    fits ? pack_shape(g, gd.grid, st.size(), key, x0, y0) : packed_none();
+                    fits ? pack_shape(g, st, gd.grid, st.size(), key, x0, y0) : packed_none();
                 atomicAdd(&size_hist[size_key((uint32_t)st.size())], 1u);
             }
             staged += (uint32_t)__popcll(cm);
@@ -459,7 +473,8 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                 if (keep) {
                     const uint32_t slot = (head + queued + (uint32_t)__popcll(km & lanes_below())) % kRing;
                     ring[slot] = i;
-                    ring_opt[slot] = opts;
+                    if constexpr (kKeepCodes)
+                        ring_opt[slot] = opts;
                 }
                 queued += (uint32_t)__popcll(km);
             }
@@ -472,7 +487,8 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                     idx = ring[slot];
                     gd = run_geno<W, kIn>(a, first, idx);
                     m = build_bonds<M>(gd.genome, gd.t, a.bits, a.c);
-                    ev = run_start_known(g, st, gd.grid, ring_opt[slot]);
+                    ev = run_start_known(g, st, gd.grid,
+                                         kKeepCodes ? ring_opt[slot] : m.codes(m.seed()));
                     busy = true;
                 }
             }
@@ -675,7 +691,7 @@ __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
             size = st.size();
             forced = ev == kEvNone && shape_is_guarded(src, g, st, gd.grid);
             int x0, y0;
-            packed = forced && shape_key8(g, gd.grid, size, key, x0, y0);
+            packed = forced && shape_key8(g, st, gd.grid, size, key, x0, y0);
         }
     }
     // the hash of a packed or replayed shape from its bitmap, if it has one
@@ -961,7 +977,7 @@ struct RepeatWave {
         uint32_t cached = 0;
         if (det && size0 > 2) {
             int x0, y0;
-            small = shape_key8(g0, gd.grid, size0, key, x0, y0);
+            small = shape_key8(g0, st, gd.grid, size0, key, x0, y0);
             hit = small && cache.lookup(key, cached);
             if (!hit) {
                 if (small) {
@@ -1254,7 +1270,7 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
         if (__ballot(det) != 0) {
             uint64_t key = 0;
             int x0, y0;
-            const bool fits = det && shape_key8(g, gd.grid, size0, key, x0, y0);
+            const bool fits = det && shape_key8(g, st, gd.grid, size0, key, x0, y0);
             rec.hash = det_hash(g, small0, small1, cache, det, size0, gd.grid, fits, key);
         }
         if (done) {

@@ -111,6 +111,7 @@ __device__ __forceinline__ SiteOpts split_code(uint32_t code)
 template <int TM, bool kC16>
 struct Bonds {
     static_assert(TM == 2 || TM == 4, "TM must be 2 or 4");
+    static constexpr bool kManyIds = TM == 4;   // ids up to 15, else up to 7
     // scalars, never arrays: a run-time index would put them in scratch memory
     uint32_t t0, t1, t2, t3;   // tiles (t2, t3 only for TM = 4)
     uint32_t lo, hi;           // the bytes of colours 0-3 and 4-7
