@@ -1299,7 +1299,10 @@ size_t carve_workspace(uint8_t* base, size_t max_n, int max_blocks, bool records
     w.counters = (uint32_t*)take(kCntWords * sizeof(uint32_t));
     w.run_claim = (uint32_t*)take(2 * kClaimCounters * kClaimStride * sizeof(uint32_t));
     w.queue_claim = (uint32_t*)take(2 * kClaimCounters * kClaimStride * sizeof(uint32_t));
+    w.tally_slots =
+        (unsigned long long*)take(kTallySlots * kTallyStride * sizeof(unsigned long long));
     w.small_hash = (uint32_t*)take(2 * sizeof(uint32_t));
+    w.seg_left = (uint32_t*)take(mb * sizeof(uint32_t));
     w.records = records ? (jatam_result_t*)take(n * sizeof(jatam_result_t)) : nullptr;
     for (int k = 0; k < 2; ++k) {
         w.seg_count[k] = (uint32_t*)take(mb * sizeof(uint32_t));

@@ -65,6 +65,7 @@ struct Geno {
     int t;
     int grid;
     bool valid;
+    bool windowed;   // run in a window of its own grid (run_geno)
 };
 
 // `first`: the range mode's first genotype of this call (a.first, moved by
@@ -131,12 +132,13 @@ __device__ __forceinline__ Geno fetch_geno_in(const BatchArgs& a, uint64_t first
 // first placement that exposes a bondable site on the window's ring, such a
 // run is the run in its own G x G grid (same cells relative to the seed,
 // same row-major order, same draws); a run that reaches the window's ring
-// ends UNBOUND here and the item is run again in its own grid (see
-// overflow_count_kernel).
+// ends UNBOUND here, without a record: the item is listed to run again in its
+// own grid (DeviceWorkspace::overflow).
 template <int W, int kIn = kInRuntime>
 __device__ __forceinline__ Geno run_geno(const BatchArgs& a, uint64_t first, uint32_t i)
 {
     Geno g = fetch_geno_in<kIn>(a, first, i);
+    g.windowed = W == 16 && g.grid > 16;
     if constexpr (W == 16)
         g.grid = g.grid < 16 ? g.grid : 16;
     return g;
@@ -187,7 +189,10 @@ __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 
 __device__ __forceinline__ uint64_t lanes_below() { return (1ull << lane_id()) - 1; }
 
-// Per-wave class counts, flushed with one atomic per class at the end.
+// Per-wave class counts, added at the wave's end to one of kTallySlots sets of
+// counters in blocks of their own (tally_kernel adds them to the caller's): four
+// atomics a wave on the caller's four words serialised, 0.1 ms a call over
+// S_{2,8}.
 struct WaveTally {
     uint32_t n[4];
     __device__ __forceinline__ void add(bool done, int cls)
@@ -196,15 +201,32 @@ struct WaveTally {
         for (int k = 0; k < 4; ++k)
             n[k] += (uint32_t)__popcll(__ballot(done && cls == k));
     }
-    __device__ __forceinline__ void flush(unsigned long long* tally) const
+    __device__ __forceinline__ void flush(const BatchArgs& a) const
     {
-        if (tally != nullptr && lane_id() == 0)
+        if (a.tally != nullptr && lane_id() == 0) {
+            unsigned long long* const slot =
+                a.ws.tally_slots + (blockIdx.x % kTallySlots) * kTallyStride;
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 if (n[k])
-                    atomicAdd(&tally[k], (unsigned long long)n[k]);
+                    atomicAdd(&slot[k], (unsigned long long)n[k]);
+        }
     }
 };
+
+// The counter sets' sums to the caller's tally: wave k sums class k.
+__global__ __launch_bounds__(256) void tally_kernel(const unsigned long long* __restrict__ slots,
+                                                    unsigned long long* tally)
+{
+    static_assert(kTallySlots == 64, "one slot a lane");
+    const int k = (int)(threadIdx.x >> 6);
+    unsigned long long v = slots[lane_id() * kTallyStride + k];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+        v += __shfl_xor(v, off);
+    if (lane_id() == 0 && v != 0)
+        atomicAdd(&tally[k], v);
+}
 
 // LDS entries of the per-wave shape-hash cache.
 constexpr int kShapeCache = 32;
@@ -328,6 +350,7 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
     uint32_t part = wave % (uint32_t)kClaimCounters, parts_dry = 0;
     uint32_t head = 0, queued = 0;            // survivor ring (wave-uniform)
     uint32_t staged = 0;                      // candidates in this wave's segment
+    uint32_t left = 0;                        // items that left the window, from its end
     uint32_t* seg_idx = a.ws.cand_idx[klass] + (size_t)wave * a.seg_cap;
     uint16_t* seg_size = a.ws.cand_size[klass] + (size_t)wave * a.seg_cap;
     uint4* seg_shape = a.ws.cand_shape + (size_t)wave * a.seg_cap;
@@ -336,7 +359,7 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
     bool busy = false;
     bool starved = false;                     // the last refill found no chunk left
     uint32_t idx = 0;
-    Geno gd{0, 0, 0, 0, false};
+    Geno gd{};
     M m{};
     int ev = kEvNone;
 
@@ -344,12 +367,15 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
         // -- lanes whose first run is over: records, hashes, staging ----------
         const bool finish = busy && run_over(ev, st, gd.grid);
         if (__ballot(finish) != 0) {
-            bool done = false, candidate = false, det = false;
+            bool done = false, candidate = false, det = false, leaves = false;
             int cls = 0;
             jatam_result_t rec{0, 0, 0u, 0};
             if (finish) {
                 done = true;
-                if (ev == kEvCorrupt) {
+                if (W == 16 && ev == kEvUnbound && gd.windowed) {
+                    done = false;
+                    leaves = true;
+                } else if (ev == kEvCorrupt) {
                     rec = jatam_result_t{JATAM_INVALID, 0, 0u, 0};
                     cls = JATAM_INVALID;
                 } else if (ev != kEvNone) {
@@ -390,6 +416,12 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                 atomicAdd(&size_hist[size_key((uint32_t)st.size())], 1u);
             }
             staged += (uint32_t)__popcll(cm);
+            if constexpr (W == 16) {
+                const uint64_t lm = __ballot(leaves);
+                if (leaves)
+                    seg_idx[a.seg_cap - 1u - left - (uint32_t)__popcll(lm & lanes_below())] = idx;
+                left += (uint32_t)__popcll(lm);
+            }
         }
         // -- refill idle lanes once enough of them wait -----------------------
         const uint64_t idle = __ballot(!busy);
@@ -404,7 +436,8 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                 } else {
                     if (claim_next == claim_end) {
                         if (!claims_left ||
-                            staged + (64u - nidle) + queued + claim_size * 64u > a.seg_cap) {
+                            staged + left + (64u - nidle) + queued + claim_size * 64u >
+                                a.seg_cap) {
                             starved = true;
                             break;
                         }
@@ -521,11 +554,14 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
                 break;
         }
     }
-    if (lane_id() == 0)
+    if (lane_id() == 0) {
         a.ws.seg_count[klass][wave] = staged;
+        if constexpr (W == 16)
+            a.ws.seg_left[wave] = left;
+    }
     wave_lds_sync();   // every staged size counted
     a.ws.seg_hist[klass][(uint32_t)lane_id() * nwaves + wave] = size_hist[lane_id()];
-    tally.flush(a.tally);
+    tally.flush(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -594,10 +630,9 @@ __global__ __launch_bounds__(kScanBlock) void scan_blocks_kernel(uint32_t* h, ui
 
 // In-place exclusive scan of the block totals (one block, any count: each
 // thread takes a run of them); *total_out receives their sum.
-__global__ __launch_bounds__(kScanBlock) void scan_sums_kernel(uint32_t* sums, uint32_t nblocks,
-                                                               uint32_t* total_out)
+__device__ __forceinline__ void scan_one_block(uint32_t* wsum, uint32_t* sums, uint32_t nblocks,
+                                               uint32_t* total_out)
 {
-    __shared__ uint32_t wsum[kScanBlock / 64 + 1];
     const uint32_t per = (nblocks + kScanBlock - 1) / kScanBlock;
     const uint32_t lo = threadIdx.x * per, hi = min(nblocks, lo + per);
     uint32_t v = 0;
@@ -614,18 +649,35 @@ __global__ __launch_bounds__(kScanBlock) void scan_sums_kernel(uint32_t* sums, u
         *total_out = total;
 }
 
+// With `left` given, its nleft entries are scanned too, their sum to *left_out.
+__global__ __launch_bounds__(kScanBlock) void scan_sums_kernel(uint32_t* sums, uint32_t nblocks,
+                                                               uint32_t* total_out,
+                                                               uint32_t* left, uint32_t nleft,
+                                                               uint32_t* left_out)
+{
+    __shared__ uint32_t wsum[kScanBlock / 64 + 1];
+    scan_one_block(wsum, sums, nblocks, total_out);
+    if (left != nullptr) {
+        __syncthreads();
+        scan_one_block(wsum, left, nleft, left_out);
+    }
+}
+
 static void exclusive_scan(uint32_t* h, uint32_t total, uint32_t* sums, uint32_t* total_out,
-                           hipStream_t stream, const uint32_t* items = nullptr)
+                           hipStream_t stream, const uint32_t* items = nullptr,
+                           uint32_t* left = nullptr, uint32_t nleft = 0,
+                           uint32_t* left_out = nullptr)
 {
     const uint32_t blocks = (total + kScanBlock - 1) / kScanBlock;
     hipLaunchKernelGGL(scan_blocks_kernel, dim3(blocks), dim3(kScanBlock), 0, stream, h, total,
                        sums, items);
     hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kScanBlock), 0, stream, sums, blocks,
-                       total_out);
+                       total_out, left, nleft, left_out);
 }
 
-// One block per segment: place its candidates with LDS cursors per bucket.
-__global__ __launch_bounds__(256) void sort_scatter_kernel(BatchArgs a, int klass)
+// One block per segment: place its candidates with LDS cursors per bucket, and
+// (`left`) list its items that left the window.
+__global__ __launch_bounds__(256) void sort_scatter_kernel(BatchArgs a, int klass, bool left)
 {
     __shared__ uint32_t cursor[kSizeBuckets];
     const uint32_t seg = blockIdx.x, nseg = gridDim.x;
@@ -642,6 +694,13 @@ __global__ __launch_bounds__(256) void sort_scatter_kernel(BatchArgs a, int klas
         const uint32_t pos = atomicAdd(&cursor[size_key(sz[i])], 1u);
         a.ws.sorted[klass][pos] = ix[i];
         a.ws.sorted_shape[pos] = sh[i];
+    }
+    if (left) {
+        // the segment's last entries; seg_left holds the exclusive scan now
+        const uint32_t from = a.ws.seg_left[seg];
+        const uint32_t to = seg + 1 < nseg ? a.ws.seg_left[seg + 1] : a.ws.counters[kCntOverflow];
+        for (uint32_t i = threadIdx.x; i < to - from; i += 256)
+            a.ws.overflow[from + i] = ix[a.seg_cap - 1u - i];
     }
 }
 
@@ -673,7 +732,7 @@ __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
     bool forced = false, packed = false;
     int size = 0;
     uint64_t key = 0;
-    Geno gd{0, 0, 0, 0, false};
+    Geno gd{};
     idx = 0;
     if (active) {
         idx = a.ws.sorted[klass][pos];
@@ -739,7 +798,7 @@ __global__ __launch_bounds__(64) void prove_kernel(const BatchArgs a, int klass)
         // counts overwrites kCntCand)
         a.ws.counters[kCntCandAll + klass] = count;
     }
-    tally.flush(a.tally);
+    tally.flush(a);
 }
 
 // Kept candidates to the front of the queue, in order: a grid-stride loop
@@ -763,58 +822,27 @@ __global__ __launch_bounds__(256) void compact_kernel(const BatchArgs a, int kla
 
 // ---------------------------------------------------------------------------
 // The 16 x 16 window (items of G > 16 classified in the 16 x 16 layout, see
-// run_geno).  An item whose record came out UNBOUND there exposed a bondable
-// site on the window's ring in some run up to the deciding one; every other
-// item's record is exact: no run up to the deciding one left the window, so
-// those runs equal the runs in the item's own grid.  The items that left are
-// listed, in queue order, for a rerun of the pipeline in 32 x 32 grids: one
-// wave per chunk of 64 queue positions counts them, a scan places them.
+// run_geno).  An item that comes out UNBOUND there exposed a bondable site on
+// the window's ring in some run up to the deciding one; every other item's
+// record is exact: no run up to the deciding one left the window, so those
+// runs equal the runs in the item's own grid.  The items that left get no
+// record but are listed for a rerun of the pipeline in 32 x 32 grids: those of
+// the first runs behind their wave's staged candidates, moved to the list with
+// the size sort, those of the repeat runs appended to it here.  (Finding them
+// by a pass over all items' records took 0.86 of 7.0 ms on 2^26 mixed items.)
+// Called by the whole wave.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ bool left_window(const BatchArgs& a, uint64_t first,
-                                            const jatam_result_t* out, uint32_t pos,
-                                            uint32_t& i)
+__device__ __forceinline__ void append_overflow(const BatchArgs& a, bool leaves, uint32_t idx)
 {
-    i = pos;
-    if (pos >= (uint64_t)a.n)
-        return false;
-    if (a.order != nullptr) {
-        i = a.order[pos];
-        if (i >= (uint64_t)a.n)
-            return false;
-    }
-    const Geno s = fetch_geno(a, first, i);
-    return s.valid && s.grid > 16 && grid_class(a, s.grid) == 0 && out[i].cls == JATAM_UNBOUND;
-}
-
-__global__ __launch_bounds__(256) void overflow_count_kernel(const BatchArgs a)
-{
-    const uint32_t c = blockIdx.x * 4 + threadIdx.x / 64;   // one chunk per wave
-    if (c >= (uint32_t)((a.n + 63) / 64))
+    const uint64_t m = __ballot(leaves);
+    if (m == 0)
         return;
-    uint32_t i;
-    const bool left = left_window(a, slice_first(a), slice_out(a), c * 64 + (uint32_t)lane_id(), i);
-    const uint64_t m = __ballot(left);
+    uint32_t at = 0;
     if (lane_id() == 0)
-        a.ws.chunk_cnt[1][c] = (uint32_t)__popcll(m);
-}
-
-__global__ __launch_bounds__(256) void overflow_scatter_kernel(const BatchArgs a)
-{
-    if (blockIdx.x == 0 && threadIdx.x == 0 && a.tally != nullptr) {
-        // the window pass counted these items UNBOUND; the rerun counts them
-        atomicAdd(&a.tally[JATAM_UNBOUND],
-                  0ull - (unsigned long long)a.ws.counters[kCntOverflow]);
-    }
-    const uint32_t c = blockIdx.x * 4 + threadIdx.x / 64;
-    if (c >= (uint32_t)((a.n + 63) / 64))
-        return;
-    uint32_t i;
-    const bool left = left_window(a, slice_first(a), slice_out(a), c * 64 + (uint32_t)lane_id(), i);
-    const uint64_t m = __ballot(left);
-    if (left) {
-        const uint32_t base = a.ws.chunk_cnt[1][c] + a.ws.chunk_sums[1][c / kScanBlock];
-        a.ws.overflow[base + (uint32_t)__popcll(m & lanes_below())] = i;
-    }
+        at = atomicAdd(a.ws.counters + kCntOverflow, (uint32_t)__popcll(m));
+    at = (uint32_t)__shfl((int)at, 0);
+    if (leaves)
+        a.ws.overflow[at + (uint32_t)__popcll(m & lanes_below())] = idx;
 }
 
 // ---------------------------------------------------------------------------
@@ -896,7 +924,7 @@ struct RepeatWave {
     // run 0's occupancy, read when skip > 0).  Called by the whole wave.
     __device__ void round(bool active, uint32_t idx, uint32_t slot)
     {
-        Geno gd{0, 0, 0, 0, false};
+        Geno gd{};
         int ev = kEvNone;
         if (active) {
             gd = run_geno<W>(a, first, idx);
@@ -993,7 +1021,11 @@ struct RepeatWave {
             }
         }
         wave_lds_sync();
-        const bool done = active && jr == 0 && !undecided;
+        const bool leaves =
+            W == 16 && active && jr == 0 && cls == JATAM_UNBOUND && gd.windowed;
+        if constexpr (W == 16)
+            append_overflow(a, leaves, idx);
+        const bool done = active && jr == 0 && !undecided && !leaves;
         uint32_t h = 0;
         if (done) {
             jatam_result_t rec;
@@ -1060,7 +1092,7 @@ __global__ __launch_bounds__(64) void repeat_kernel(const BatchArgs a, int klass
             next_idx = queue_in[base + stride + grp];
         rw.round(active, idx, base + grp);
     }
-    tally.flush(a.tally);
+    tally.flush(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -1140,7 +1172,7 @@ __global__ __launch_bounds__(64) void prove_repeat_kernel(const BatchArgs a, int
     }
     while (npend > 0)
         round_of(npend < groups ? npend : groups);
-    tally.flush(a.tally);
+    tally.flush(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -1182,7 +1214,7 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
     bool busy = false;
     uint32_t idx = 0, osum0 = 0;
     int run = 0, ev = kEvNone, steps_sum = 0, size0 = 0;
-    Geno gd{0, 0, 0, 0, false};
+    Geno gd{};
     M src{};
 
     for (;;) {
@@ -1273,13 +1305,17 @@ __global__ __launch_bounds__(64) void repeat_seq_kernel(const BatchArgs a, int k
             const bool fits = det && shape_key8(g, st, gd.grid, size0, key, x0, y0);
             rec.hash = det_hash(g, small0, small1, cache, det, size0, gd.grid, fits, key);
         }
+        const bool leaves = W == 16 && done && cls == JATAM_UNBOUND && gd.windowed;
         if (done) {
-            out[idx] = rec;
+            if (!leaves)
+                out[idx] = rec;
             busy = false;
         }
-        tally.add(done, cls);
+        if constexpr (W == 16)
+            append_overflow(a, leaves, idx);
+        tally.add(done && !leaves, cls);
     }
-    tally.flush(a.tally);
+    tally.flush(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -1381,12 +1417,14 @@ int launch_records_differ(const jatam_result_t* x, const jatam_result_t* y, uint
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }
 
-// Zeroes one counter word (a kernel rather than a memset: graph-safe).
-// Clears the claim counters of one grid class (before its first-run kernel).
-__global__ void clear_claims_kernel(uint32_t* ctr)
+// Clears the first-run claim counters of one grid class and, if given, the
+// tally's counter sets (a kernel rather than a memset: graph-safe).
+__global__ __launch_bounds__(256) void clear_kernel(uint32_t* claims, unsigned long long* slots)
 {
     if (threadIdx.x < kClaimCounters)
-        ctr[threadIdx.x * kClaimStride] = 0u;
+        claims[threadIdx.x * kClaimStride] = 0u;
+    if (slots != nullptr && threadIdx.x < 4 * kTallySlots)
+        slots[(threadIdx.x >> 2) * kTallyStride + (threadIdx.x & 3u)] = 0ull;
 }
 
 // The first-run kernel compiled for the call's input mode.
@@ -1464,27 +1502,27 @@ static void launch_stages(BatchArgs a, const bool classes[2], const StageLaunch 
         begin(kStageFirst + kStagesPerClass * k);
         if (k == 1 && a.narrow_max > 16) {
             // the 32 x 32 class reruns only the items that left the window
-            const uint32_t blocks = (uint32_t)((nchunks + 3) / 4);
-            hipLaunchKernelGGL(overflow_count_kernel, dim3(blocks), dim3(256), 0, stream, a);
-            exclusive_scan(a.ws.chunk_cnt[1], (uint32_t)nchunks, a.ws.chunk_sums[1],
-                           a.ws.counters + kCntOverflow, stream);
-            hipLaunchKernelGGL(overflow_scatter_kernel, dim3(blocks), dim3(256), 0, stream, a);
             a.order = a.ws.overflow;
             a.n_dev = a.ws.counters + kCntOverflow;
             a.narrow_max = 16;
         }
-        if (a.dyn16 > 0)
-            hipLaunchKernelGGL(clear_claims_kernel, dim3(1), dim3(64), 0, stream,
-                               a.ws.run_claim + k * kClaimCounters * kClaimStride);
+        // the call's first class clears the tally's counter sets
+        const bool clear_tally = a.tally != nullptr && (k == 0 || !classes[0]);
+        if (a.dyn16 > 0 || clear_tally)
+            hipLaunchKernelGGL(clear_kernel, dim3(1), dim3(256), 0, stream,
+                               a.ws.run_claim + k * kClaimCounters * kClaimStride,
+                               clear_tally ? a.ws.tally_slots : nullptr);
         if (k == 0)
             launch_first<16, M>(a, nb, stream, 0);
         else
             launch_first<32, M>(a, nb, stream, 1);
         end(kStageFirst + kStagesPerClass * k);
         begin(kStageSort + kStagesPerClass * k);
+        const bool window = k == 0 && a.narrow_max > 16;
         exclusive_scan(a.ws.seg_hist[k], (uint32_t)kSizeBuckets * nb, a.ws.scan_sums[k],
-                       a.ws.counters + kCntCand + k, stream);
-        hipLaunchKernelGGL(sort_scatter_kernel, dim3(nb), dim3(256), 0, stream, a, k);
+                       a.ws.counters + kCntCand + k, stream, nullptr,
+                       window ? a.ws.seg_left : nullptr, nb, a.ws.counters + kCntOverflow);
+        hipLaunchKernelGGL(sort_scatter_kernel, dim3(nb), dim3(256), 0, stream, a, k, window);
         end(kStageSort + kStagesPerClass * k);
         const int mapping = launch[k].repeat_mapping;
         if (mapping == 2 && a.runs > kRepeatFirstRuns) {
@@ -1533,6 +1571,9 @@ static void launch_stages(BatchArgs a, const bool classes[2], const StageLaunch 
             end(kStageRepeat + kStagesPerClass * k);
         }
     }
+    if (a.tally != nullptr)
+        hipLaunchKernelGGL(tally_kernel, dim3(1), dim3(256), 0, stream,
+                           (const unsigned long long*)a.ws.tally_slots, a.tally);
 }
 
 int launch_batched(const BatchArgs& a, const bool classes[2], const StageLaunch launch[2],

@@ -49,6 +49,9 @@ constexpr int kScanBlock = 1024;    // histogram entries per block of the size s
 constexpr int kClaimCounters = 8;
 constexpr int kClaimStride = 64;   // words between two counters
 constexpr int kMaxScanBlocks = 1024;
+// Sets of class counters that waves add to, each in a 256-byte block of its own.
+constexpr int kTallySlots = 64;
+constexpr int kTallyStride = 32;   // 64-bit words between two sets
 
 // Entries of the candidate staging arrays for calls of up to max_n items on
 // at most max_blocks first-run waves: nb waves of ceil(chunks / nb) dealt-out
@@ -67,11 +70,13 @@ struct DeviceWorkspace {
     uint32_t* run_claim;      // [2 * kClaimCounters * kClaimStride]: first-run claim
                               // counter x of class k at word (k * 8 + x) * kClaimStride
     uint32_t* queue_claim;    // the same for the fused proof kernel's queue chunks
+    unsigned long long* tally_slots;   // [kTallySlots * kTallyStride]
     uint32_t* seg_count[2];   // [max_blocks] candidates staged by each wave
+    uint32_t* seg_left;       // [max_blocks] items of each wave that left the 16 x 16
+                              // window, at its segment's end
     uint32_t* seg_hist[2];    // [kSizeBuckets * max_blocks] bucket-major counts
     uint32_t* scan_sums[2];   // [kMaxScanBlocks] block totals of the histogram scan
-    uint32_t* chunk_cnt[2];   // [max_n / 64 + 1] kept candidates per queue chunk, and
-                              // ([1]) items per input chunk that left the 16 x 16 window
+    uint32_t* chunk_cnt[2];   // [max_n / 64 + 1] kept candidates per queue chunk
     uint32_t* chunk_sums[2];  // [max_n / 64 / kScanBlock + 1] block totals of their scan
     uint32_t* cand_idx[2];    // [staging_entries(max_n, max_blocks)]: per-wave
                               // segments of the first-run grid, each its dealt-out
@@ -103,8 +108,7 @@ struct BatchArgs {
                                     // covers first + s*n .. (graph replays)
     int out_per_slice;              // with `slice`: records go to out + s*n
     int narrow_max;                 // largest G classified with the 16 x 16 layout;
-                                    // above 16 the layout is a window (see
-                                    // overflow_count_kernel)
+                                    // above 16 the layout is a window (see run_geno)
     const uint32_t* n_dev;          // nullptr, or the item count on the device
                                     // (first-run stage; at most n)
     int refill;                     // idle lanes that trigger a refill (1..64, per class)
