@@ -64,6 +64,11 @@ struct LaneGrid {
             word(k) = 0;
     }
     __device__ __forceinline__ uint32_t& pend_word(int p) { return word(Geo::kPend + (p >> 3)); }
+    // the tile's id at an occupied cell
+    __device__ __forceinline__ uint32_t tile_id(int p)
+    {
+        return (pend_word(p) >> ((uint32_t)(p & 7) * 4u)) & 15u;
+    }
     __device__ __forceinline__ uint32_t row(int y)
     {
         if constexpr (W == 32) {
@@ -109,6 +114,13 @@ struct LeanGrid {
         for (int k = 0; k < kLaneWords; ++k)
             word(k) = 0;
     }
+    // Once no frontier is left: whether a cell is occupied, and the tile's id there.
+    __device__ __forceinline__ uint32_t nibble(int p)
+    {
+        return (pend_word(p) >> ((uint32_t)(p & 7) * 4u)) & 15u;
+    }
+    __device__ __forceinline__ bool occupied(int p) { return nibble(p) != 0; }
+    __device__ __forceinline__ uint32_t tile_id(int p) { return (nibble(p) - 1u) & 15u; }
     // Row y's occupied cells, once no frontier is left.
     __device__ __forceinline__ uint32_t row(int y)
     {
@@ -631,28 +643,22 @@ __device__ __forceinline__ int run_assembly(const Src& m, Grid& g, RunState& st,
 // of the shape and nowhere else (a site outside the shape that any shape
 // cell bonds to would have stayed on the frontier, or ended the run as
 // UNBOUND), and never meets an ambiguous site: every run ends in this shape.
-// The seed cell's nibble is 0, the id of the unrotated seed tile.
-template <int W, int B, class Src>
-__device__ __forceinline__ bool shape_is_forced(const Src& m, LaneGrid<W, B>& g,
-                                                const RunState& st)
+// The seed cell's id is 0, the unrotated seed tile's.
+template <class Grid, class Src>
+__device__ __forceinline__ bool shape_is_forced(const Src& m, Grid& g, int G)
 {
-    constexpr int kMask = W * W - 1;
+    constexpr int W = Grid::kW, kMask = W * W - 1;
     bool forced = true;
-    for (uint32_t s = st.osum; s != 0 && forced; s &= s - 1) {
-        const int w = __builtin_ctz(s);
-        for (uint32_t cells = g.occ(w); cells != 0 && forced; cells &= cells - 1) {
-            const int p = (w << 5) | __builtin_ctz(cells);
-            const uint32_t id = (g.pend_word(p) >> ((uint32_t)(p & 7) * 4u)) & 15u;
+    for (int y = 0; y < G - 1 && forced; ++y) {
+        for (uint32_t cells = g.row(y); cells != 0 && forced; cells &= cells - 1) {
+            const int p = y * W + __builtin_ctz(cells);
+            // the site of this cell's tile in direction d: the neighbour q
+            const uint32_t codes = m.codes(m.oriented(g.tile_id(p)));
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-                const int delta = d == 0 ? -W : d == 1 ? 1 : d == 2 ? W : -1;
-                const int q = (p + delta) & kMask;
-                if (!g.occupied(q))
-                    continue;
-                const uint32_t nq = (g.pend_word(q) >> ((uint32_t)(q & 7) * 4u)) & 15u;
-                // options of the site in direction d + 2 of q's tile: cell p
-                const SiteOpts o = split_code(m.codes(m.oriented(nq)) >> (8 * ((d + 2) & 3)));
-                if (o.has && (o.multi || o.id != id))
+                const int q = (p + (d == 0 ? -W : d == 1 ? 1 : d == 2 ? W : -1)) & kMask;
+                const SiteOpts o = split_code(codes >> (8 * d));
+                if (g.occupied(q) && o.has && (o.multi || o.id != g.tile_id(q)))
                     forced = false;
             }
         }
@@ -701,66 +707,58 @@ __device__ __forceinline__ ShapeBox crop(Grid& g, int G)
 // (every cell of the shape has a good edge from a cell placed before it in
 // run 0).  With no conflicts this is shape_is_forced.
 //
-// The flood fills run on 64-bit bitmaps of the shape's bounding box, which
-// must fit 8 x 8; a larger shape is tested with shape_is_forced instead.
-template <int W, int B, class Src>
-__device__ __forceinline__ bool shape_is_guarded(const Src& m, LaneGrid<W, B>& g,
-                                                 const RunState& st, int G)
+// This test takes the shape as an anchored 8 x 8 bitmap and the tile ids by
+// cell; the flood fills run on 64-bit bitmaps.  A larger shape is tested with
+// shape_is_forced instead.
+template <class Src, class IdOf>
+__device__ __forceinline__ bool bitmap_is_guarded(const Src& src, uint64_t shape,
+                                                  uint64_t seed_bit, const IdOf& id_of)
 {
-    constexpr int kMask = W * W - 1;
-    const ShapeBox bx = crop(g, G);
-    if (bx.w > 8 || bx.h > 8)
-        return shape_is_forced(m, g, st);
-    // per cell p of the 8 x 8 frame, bit (y - ymin) * 8 + (x - xmin):
-    // good_d / conf_d: the edge into p from its neighbour in direction d
-    uint64_t shape = 0, good0 = 0, good1 = 0, good2 = 0, good3 = 0;
+    // good_d / conf_d: bit of cell p set for the edge into p from its
+    // neighbour in direction d
+    uint64_t good0 = 0, good1 = 0, good2 = 0, good3 = 0;
     uint64_t conf0 = 0, conf1 = 0, conf2 = 0, conf3 = 0;
-    for (uint32_t s = st.osum; s != 0; s &= s - 1) {
-        const int w = __builtin_ctz(s);
-        for (uint32_t cells = g.occ(w); cells != 0; cells &= cells - 1) {
-            const int p = (w << 5) | __builtin_ctz(cells);
-            const int fx = (p & (W - 1)) - bx.xmin, fy = (p >> Geometry<W>::kLogW) - bx.ymin;
-            const uint64_t bit = 1ull << (fy * 8 + fx);
-            shape |= bit;
-            const uint32_t id = (g.pend_word(p) >> ((uint32_t)(p & 7) * 4u)) & 15u;
+    int k = 0;
+    for (uint64_t cells = shape; cells != 0; cells &= cells - 1, ++k) {
+        const int b = __builtin_ctzll(cells);
+        const uint32_t codes = src.codes(src.oriented(id_of(b, k)));
+        const int x = b & 7, y = b >> 3;
+        // the edges from this cell into its neighbour p in direction d, which
+        // it enters from direction d + 2
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const int delta = d == 0 ? -W : d == 1 ? 1 : d == 2 ? W : -1;
-                const int q = (p + delta) & kMask;
-                if (!g.occupied(q))
-                    continue;
-                const uint32_t nq = (g.pend_word(q) >> ((uint32_t)(q & 7) * 4u)) & 15u;
-                // options of the site in direction d + 2 of q's tile: cell p
-                const SiteOpts o = split_code(m.codes(m.oriented(nq)) >> (8 * ((d + 2) & 3)));
-                const bool good = o.has & !o.multi & (o.id == id);
-                const bool conf = o.has & !good;
-                const uint64_t gb = good ? bit : 0ull, cb = conf ? bit : 0ull;
-                if (d == 0) { good0 |= gb; conf0 |= cb; }
-                else if (d == 1) { good1 |= gb; conf1 |= cb; }
-                else if (d == 2) { good2 |= gb; conf2 |= cb; }
-                else { good3 |= gb; conf3 |= cb; }
-            }
+        for (int d = 0; d < 4; ++d) {
+            const bool inside = d == 0 ? y > 0 : d == 1 ? x < 7 : d == 2 ? y < 7 : x > 0;
+            const int pb = b + (d == 0 ? -8 : d == 1 ? 1 : d == 2 ? 8 : -1);
+            if (!inside || ((shape >> (pb & 63)) & 1ull) == 0ull)
+                continue;
+            const uint64_t bit = 1ull << pb;
+            const SiteOpts o = split_code(codes >> (8 * d));
+            const bool good =
+                o.has & !o.multi & (o.id == id_of(pb, __popcll(shape & (bit - 1))));
+            const bool conf = o.has & !good;
+            const uint64_t gb = good ? bit : 0ull, cb = conf ? bit : 0ull;
+            if (d == 2) { good0 |= gb; conf0 |= cb; }
+            else if (d == 3) { good1 |= gb; conf1 |= cb; }
+            else if (d == 0) { good2 |= gb; conf2 |= cb; }
+            else { good3 |= gb; conf3 |= cb; }
         }
     }
-    const int seed = (G / 2 - 1) * W + (G / 2 - 1);
-    const uint64_t seed_bit =
-        1ull << (((seed >> Geometry<W>::kLogW) - bx.ymin) * 8 + ((seed & (W - 1)) - bx.xmin));
     // conflicts into the seed never count: the seed is placed first
     uint64_t todo = (conf0 | conf1 | conf2 | conf3) & ~seed_bit;
     bool guarded = true;
     for (; todo != 0 && guarded; todo &= todo - 1) {
         const uint64_t pb = todo & (~todo + 1);
         // the conflicting neighbours of p: N is 8 bits down, S 8 up, E 1 up, W 1 down
-        const uint64_t src = ((conf0 & pb) >> 8) | ((conf2 & pb) << 8) | ((conf1 & pb) << 1) |
-                             ((conf3 & pb) >> 1);
+        const uint64_t from = ((conf0 & pb) >> 8) | ((conf2 & pb) << 8) | ((conf1 & pb) << 1) |
+                              ((conf3 & pb) >> 1);
         const uint64_t allowed = shape & ~pb;
         uint64_t reach = seed_bit, prev = 0;
-        while (reach != prev && (reach & src) == 0) {
+        while (reach != prev && (reach & from) == 0) {
             prev = reach;
             reach |= (((reach << 8) & good0) | ((reach >> 1) & good1) | ((reach >> 8) & good2) |
                       ((reach << 1) & good3)) & allowed;
         }
-        guarded = (reach & src) == 0;
+        guarded = (reach & from) == 0;
     }
     return guarded;
 }
@@ -1013,6 +1011,21 @@ __device__ __forceinline__ bool shape_key8(Grid& g, const RunState& st, int G, i
     return shape_bitmap8(g, G, m, w, h, x0, y0);
 }
 
+// Whether two finished runs' grids hold the same cells (lean grids of one wave).
+template <int W>
+__device__ __forceinline__ bool same_cells(LeanGrid<W>& g, LeanGrid<W>& h, int G)
+{
+    bool same = true;
+    for (int k = 0; k < (G - 1) * (W / 8); ++k) {
+        // nibbles: set exactly where occupied
+        uint32_t v = g.word(LeanGrid<W>::kPend + k), u = h.word(LeanGrid<W>::kPend + k);
+        v |= v >> 2;
+        u |= u >> 2;
+        same = same && (((v | (v >> 1)) ^ (u | (u >> 1))) & 0x11111111u) == 0;
+    }
+    return same;
+}
+
 // ---------------------------------------------------------------------------
 // A run's final shape packed into 16 bytes, for the proof stage to check
 // without replaying the run: .x/.y the anchored 8 x 8 bitmap (bit 8y + x),
@@ -1045,8 +1058,7 @@ __device__ __forceinline__ uint4 pack_shape(Grid& g, const RunState& st, int G, 
     for (uint64_t cells = m; cells != 0; cells &= cells - 1, k += 4) {
         const int b = __builtin_ctzll(cells);
         const int p = (y0 + (b >> 3)) * Grid::kW + x0 + (b & 7);
-        const uint32_t nibble = (g.pend_word(p) >> ((uint32_t)(p & 7) * 4u)) & 15u;
-        tiles |= (uint64_t)(Grid::kLean ? nibble - 1u : nibble) << k;
+        tiles |= (uint64_t)g.tile_id(p) << k;
     }
     const int sc = G / 2 - 1;
     tiles |= (uint64_t)((sc - y0) * 8 + (sc - x0)) << 58;
@@ -1054,58 +1066,31 @@ __device__ __forceinline__ uint4 pack_shape(Grid& g, const RunState& st, int G, 
                       (uint32_t)(tiles >> 32));
 }
 
-// shape_is_guarded for a packed shape (same edges, same test), from
-// registers: cell b's tile is nibble popcount(m below b) of the tile word.
+// bitmap_is_guarded for a packed shape, from registers: the k-th cell's tile is
+// nibble k of the tile word.
 template <class Src>
 __device__ __forceinline__ bool packed_shape_is_guarded(const Src& src, const uint4& v)
 {
     const uint64_t shape = ((uint64_t)v.y << 32) | v.x;
-    const uint64_t word = ((uint64_t)v.w << 32) | v.z;
-    const uint64_t tiles = word & ((1ull << 56) - 1);
-    const uint64_t seed_bit = 1ull << (int)(word >> 58);
-    uint64_t good0 = 0, good1 = 0, good2 = 0, good3 = 0;
-    uint64_t conf0 = 0, conf1 = 0, conf2 = 0, conf3 = 0;
-    uint64_t left = tiles;   // the tiles of the cells still to come
-    for (uint64_t cells = shape; cells != 0; cells &= cells - 1, left >>= 4) {
-        const int b = __builtin_ctzll(cells);
-        const uint32_t codes = src.codes(src.oriented((uint32_t)left & 15u));
-        const int x = b & 7, y = b >> 3;
-        // the edges from this cell into its neighbour p in direction d, which
-        // it enters from direction d + 2
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            const bool inside = d == 0 ? y > 0 : d == 1 ? x < 7 : d == 2 ? y < 7 : x > 0;
-            const int pb = b + (d == 0 ? -8 : d == 1 ? 1 : d == 2 ? 8 : -1);
-            if (!inside || ((shape >> (pb & 63)) & 1ull) == 0ull)
-                continue;
-            const uint64_t bit = 1ull << pb;
-            const uint32_t id = (uint32_t)(tiles >> (4 * __popcll(shape & (bit - 1)))) & 15u;
-            const SiteOpts o = split_code(codes >> (8 * d));
-            const bool good = o.has & !o.multi & (o.id == id);
-            const bool conf = o.has & !good;
-            const uint64_t gb = good ? bit : 0ull, cb = conf ? bit : 0ull;
-            if (d == 2) { good0 |= gb; conf0 |= cb; }
-            else if (d == 3) { good1 |= gb; conf1 |= cb; }
-            else if (d == 0) { good2 |= gb; conf2 |= cb; }
-            else { good3 |= gb; conf3 |= cb; }
-        }
-    }
-    uint64_t todo = (conf0 | conf1 | conf2 | conf3) & ~seed_bit;
-    bool guarded = true;
-    for (; todo != 0 && guarded; todo &= todo - 1) {
-        const uint64_t pb = todo & (~todo + 1);
-        const uint64_t src_bits = ((conf0 & pb) >> 8) | ((conf2 & pb) << 8) |
-                                  ((conf1 & pb) << 1) | ((conf3 & pb) >> 1);
-        const uint64_t allowed = shape & ~pb;
-        uint64_t reach = seed_bit, prev = 0;
-        while (reach != prev && (reach & src_bits) == 0) {
-            prev = reach;
-            reach |= (((reach << 8) & good0) | ((reach >> 1) & good1) | ((reach >> 8) & good2) |
-                      ((reach << 1) & good3)) & allowed;
-        }
-        guarded = (reach & src_bits) == 0;
-    }
-    return guarded;
+    const uint64_t tiles = ((uint64_t)v.w << 32) | v.z;
+    return bitmap_is_guarded(src, shape, 1ull << (int)(tiles >> 58),
+                             [tiles](int, int k) { return (uint32_t)(tiles >> (4 * k)) & 15u; });
+}
+
+// Whether the shape left by a finished run is guarded; false, too, if one of
+// its tiles' ids was lost (LeanGrid).  key, x0, y0: shape_key8's, if it `fits`.
+template <class Grid, class Src>
+__device__ __forceinline__ bool shape_is_guarded(const Src& m, Grid& g, const RunState& st,
+                                                 int G, bool fits, uint64_t key, int x0, int y0)
+{
+    if (Grid::kLean && st.lost != 0)
+        return false;
+    if (!fits)
+        return shape_is_forced(m, g, G);
+    const int s = G / 2 - 1;
+    return bitmap_is_guarded(m, key, 1ull << ((s - y0) * 8 + (s - x0)), [&](int b, int) {
+        return g.tile_id((y0 + (b >> 3)) * Grid::kW + x0 + (b & 7));
+    });
 }
 
 // D4 hash of a shape given as an anchored 8 x 8 bitmap, by one lane.

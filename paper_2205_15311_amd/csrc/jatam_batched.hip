@@ -725,7 +725,7 @@ constexpr uint32_t kNoCandidate = 0xFFFFFFFFu;
 // the whole wave.
 template <int W, class M>
 __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
-                                          jatam_result_t* out, LaneGrid<W, 64>& g, RunState& st,
+                                          jatam_result_t* out, LeanGrid<W>& g, RunState& st,
                                           WaveShapeCache& cache, WaveTally& tally, int klass,
                                           bool active, uint32_t pos, uint32_t& idx)
 {
@@ -748,9 +748,9 @@ __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
         } else {
             const int ev = run_assembly(src, g, st, gd.grid, run_key(a, gd, 0));
             size = st.size();
-            forced = ev == kEvNone && shape_is_guarded(src, g, st, gd.grid);
-            int x0, y0;
-            packed = forced && shape_key8(g, st, gd.grid, size, key, x0, y0);
+            int x0 = 0, y0 = 0;
+            packed = ev == kEvNone && shape_key8(g, st, gd.grid, size, key, x0, y0);
+            forced = ev == kEvNone && shape_is_guarded(src, g, st, gd.grid, packed, key, x0, y0);
         }
     }
     // the hash of a packed or replayed shape from its bitmap, if it has one
@@ -765,12 +765,11 @@ __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
 template <int W, class M>
 __global__ __launch_bounds__(64) void prove_kernel(const BatchArgs a, int klass)
 {
-    using Geo = Geometry<W>;
     const uint64_t first = slice_first(a);
     jatam_result_t* const out = slice_out(a);
-    __shared__ uint32_t smem[Geo::kLaneWords * 64];
+    __shared__ uint32_t smem[LeanGrid<W>::kLaneWords * 64];
     __shared__ uint4 cache_mem[kShapeCache];
-    LaneGrid<W, 64> g{smem + threadIdx.x};
+    LeanGrid<W> g{smem + threadIdx.x};
     g.clear_all();
     WaveShapeCache cache{cache_mem};
     cache.clear(lane_id());
@@ -868,14 +867,24 @@ __device__ __forceinline__ int wave_inclusive_sum(int v)
 //
 // A candidate left undecided by runs 0 .. k-1 ended all of them in run 0's
 // occupancy, with size0 - 1 placements each.  In the 16 x 16 layout the
-// first pass stores that occupancy (8 words at the candidate's queue_out
-// position: words 0-3 in cand_shape, free after the size sort, 4-7 in
-// occ_hi), and the second pass (skip = k) then makes runs k .. R-1 only,
-// each compared with the stored words.
-__device__ __forceinline__ uint32_t* occ_word(uint4* lo, uint4* hi, uint32_t slot, int w)
+// first pass stores that occupancy at the candidate's queue_out position: its
+// bitmap near the seed and its size in cand_shape (free after the size sort)
+// if all of it lies there, else eight words, 0-3 in cand_shape and 4-7 in
+// occ_hi.  The second pass (skip = k) then makes runs k .. R-1 only, each
+// compared with what is stored.
+constexpr uint32_t kStoredNear = 0xFFFFFFFFu;   // as word 3: columns 15 are never occupied
+
+// Occupancy word w (rows 2w and 2w + 1) of a finished run in the 16 x 16 layout;
+// row 15, never occupied, holds the wave's own data.
+__device__ __forceinline__ uint32_t occ_word(LeanGrid<16>& g, int w)
 {
-    // words 0..3 of a slot in lo[slot], words 4..7 in hi[slot]
-    return w < 4 ? (uint32_t*)&lo[slot] + w : (uint32_t*)&hi[slot] + (w - 4);
+    return g.row(2 * w) | (w < 7 ? g.row(2 * w + 1) << 16 : 0u);
+}
+
+__device__ __forceinline__ uint64_t shfl64(uint64_t v, int lane)
+{
+    return ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(v >> 32), lane) << 32) |
+           (uint32_t)__shfl((int)(uint32_t)v, lane);
 }
 
 // The LDS and the per-lane layout of the R-lanes-per-candidate repeat runs:
@@ -884,12 +893,11 @@ __device__ __forceinline__ uint32_t* occ_word(uint4* lo, uint4* hi, uint32_t slo
 // its record, or (a first pass without a witness) to the second queue.
 template <int W, class M>
 struct RepeatWave {
-    using Geo = Geometry<W>;
     const BatchArgs& a;
     uint64_t first;
     jatam_result_t* out;
-    LaneGrid<W, 64> g;       // this lane's grid
-    LaneGrid<W, 64> g0;      // the group's lead lane's grid
+    LeanGrid<W> g;           // this lane's grid
+    LeanGrid<W> g0;          // the group's lead lane's grid
     uint32_t (*orient)[64];  // per group: orientation hashes
     WaveShapeCache& cache;
     RunState& st;
@@ -916,7 +924,7 @@ struct RepeatWave {
         lead = grp * R;            // lane making run `skip`
         tail = lead + R - 1;       // lane making run rpass-1
         gmask = R == 64 ? ~0ull : ((1ull << R) - 1);
-        g0 = LaneGrid<W, 64>{smem + lead};
+        g0 = LeanGrid<W>{smem + lead};
     }
 
     // `active`: this lane's group has candidate idx (wave-uniform per group);
@@ -933,26 +941,35 @@ struct RepeatWave {
         }
         wave_lds_sync();   // every run's grid is final
         // a witness is a later run that hit an event or ended in another
-        // shape than run 0 (the lead lane's, or the stored one)
+        // shape than run 0 (the lead lane's, or the stored one): compared by
+        // the bitmaps near the seed where run 0's holds all of its cells,
+        // else cell by cell
         bool same = true;
-        int stored_size = 0;                          // run 0's size, from the store
-        if constexpr (W == 16) {
-            if (skip > 0 && active) {
-                uint4* const lo = a.ws.cand_shape;
-                uint4* const hi = a.ws.occ_hi;
+        int size0 = __shfl(st.size(), lead);          // run 0's (skip = 0: the lead's)
+        uint64_t near0 = shfl64(st.near, lead);
+        if (W == 16 && skip > 0 && active) {
+            const uint4 lo = a.ws.cand_shape[slot];
+            if (lo.w == kStoredNear) {
+                near0 = ((uint64_t)lo.y << 32) | lo.x;
+                size0 = (int)lo.z;
+            } else {
+                const uint4 hi = a.ws.occ_hi[slot];
+                const uint32_t o[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                size0 = 0;
+                near0 = 0;
 #pragma unroll
-                for (int w = 0; w < Geo::kWords; ++w) {
-                    const uint32_t o = *occ_word(lo, hi, slot, w);
-                    stored_size += __popc(o);
-                    same = same && g.occ(w) == o;
+                for (int w = 0; w < 8; ++w) {
+                    size0 += __popc(o[w]);
+                    if constexpr (W == 16)
+                        same = same && (ev != kEvNone || occ_word(g, w) == o[w]);
                 }
             }
         }
-        if (skip == 0 && active && jr > 0 && ev == kEvNone) {
-#pragma unroll
-            for (int w = 0; w < Geo::kWords; ++w)
-                same = same && g.occ(w) == g0.occ(w);
-        }
+        const bool near_all = __popcll(near0) == size0;
+        if (active && near_all)
+            same = st.near == near0 && st.size() == size0;
+        else if (active && skip == 0 && ev == kEvNone)
+            same = same_cells(g, g0, gd.grid);
         const bool witness = active && (skip > 0 || jr > 0) && (ev != kEvNone || !same);
         const uint64_t wm = (__ballot(witness) >> lead) & gmask;
         const int fw = wm ? (int)__builtin_ctzll(wm) : R;      // R: no witness
@@ -974,7 +991,7 @@ struct RepeatWave {
         const int last = fw < R ? fw : R - 1;
         const int incl = wave_inclusive_sum(active && jr <= last ? st.steps : 0);
         const int steps = __shfl(incl, tail) - __shfl(incl, lead) + __shfl(st.steps, lead) +
-                          skip * (__shfl(stored_size, lead) - 1);
+                          skip * (size0 - 1);
         // without a witness in a first pass the candidate waits for the second
         const bool undecided = active && fw == R && !all_runs && cls == JATAM_DET;
         const uint64_t um = __ballot(undecided && jr == 0);
@@ -987,17 +1004,21 @@ struct RepeatWave {
             if (undecided && jr == 0)
                 queue_out[qslot] = idx;
             if constexpr (W == 16) {
-                // every run of the group ended in run 0's occupancy: lane jr
-                // stores words jr, jr + R, ... of its own
-                const uint32_t gslot = (uint32_t)__shfl((int)qslot, lead);
-                if (store_occ && undecided) {
-                    for (int w = jr; w < Geo::kWords; w += R)
-                        *occ_word(a.ws.cand_shape, a.ws.occ_hi, gslot, w) = g.occ(w);
+                if (store_occ && undecided && jr == 0) {
+                    if (near_all) {
+                        a.ws.cand_shape[qslot] = make_uint4((uint32_t)near0,
+                                                            (uint32_t)(near0 >> 32),
+                                                            (uint32_t)size0, kStoredNear);
+                    } else {
+                        a.ws.cand_shape[qslot] = make_uint4(occ_word(g, 0), occ_word(g, 1),
+                                                            occ_word(g, 2), occ_word(g, 3));
+                        a.ws.occ_hi[qslot] = make_uint4(occ_word(g, 4), occ_word(g, 5),
+                                                        occ_word(g, 6), occ_word(g, 7));
+                    }
                 }
             }
         }
         const bool det = active && cls == JATAM_DET && !undecided;
-        const int size0 = __shfl(st.size(), lead);
         // run 0's shape: from the wave's cache, else the group's lanes share
         // its 8 orientation hashes
         uint64_t key = 0;
@@ -1005,7 +1026,9 @@ struct RepeatWave {
         uint32_t cached = 0;
         if (det && size0 > 2) {
             int x0, y0;
-            small = shape_key8(g0, st, gd.grid, size0, key, x0, y0);
+            RunState run0{};
+            run0.near = near0;
+            small = shape_key8(g0, run0, gd.grid, size0, key, x0, y0);
             hit = small && cache.lookup(key, cached);
             if (!hit) {
                 if (small) {
@@ -1062,11 +1085,10 @@ __global__ __launch_bounds__(64) void repeat_kernel(const BatchArgs a, int klass
                                                     const uint32_t* count_in,
                                                     uint32_t* queue_out, uint32_t* count_out)
 {
-    using Geo = Geometry<W>;
-    __shared__ uint32_t smem[Geo::kLaneWords * 64];
+    __shared__ uint32_t smem[LeanGrid<W>::kLaneWords * 64];
     __shared__ uint32_t orient[8][64];
     __shared__ uint4 cache_mem[kShapeCache];
-    LaneGrid<W, 64> lg{smem + threadIdx.x};
+    LeanGrid<W> lg{smem + threadIdx.x};
     lg.clear_all();
     WaveShapeCache cache{cache_mem};
     cache.clear(lane_id());
@@ -1111,12 +1133,12 @@ __global__ __launch_bounds__(64) void prove_repeat_kernel(const BatchArgs a, int
                                                           int rpass, uint32_t* queue_out,
                                                           uint32_t* count_out)
 {
-    using Geo = Geometry<W>;
-    __shared__ uint32_t smem[Geo::kLaneWords * 64];
+    __shared__ uint32_t smem[LeanGrid<W>::kLaneWords * 64];
     __shared__ uint32_t orient[8][64];
     __shared__ uint4 cache_mem[kShapeCache];
-    __shared__ uint32_t pend[128];   // unproven candidates waiting for a round
-    LaneGrid<W, 64> lg{smem + threadIdx.x};
+    // unproven candidates waiting for a round, in the grid's spare words
+    uint32_t* const pend = smem + LeanGrid<W>::kSpare;
+    LeanGrid<W> lg{smem + threadIdx.x};
     lg.clear_all();
     WaveShapeCache cache{cache_mem};
     cache.clear(lane_id());

@@ -139,10 +139,14 @@ __global__ __launch_bounds__(B) void truth_first_kernel(TruthArgs a)
                 rec = jatam_result_t{JATAM_INVALID, 0, 0u, 0};
             } else if (ev != kEvNone) {
                 rec = jatam_result_t{JATAM_ND_SITE, 0, 0u, 0};
-            } else if (!st.choice || shape_is_guarded(m, g, st, a.grid)) {
-                rec = jatam_result_t{JATAM_DET, st.size(), shape_hash(g, a.grid), 0};
             } else {
-                queue = true;
+                uint64_t key = 0;
+                int x0 = 0, y0 = 0;
+                const bool fits = shape_key8(g, st, a.grid, st.size(), key, x0, y0);
+                if (!st.choice || shape_is_guarded(m, g, st, a.grid, fits, key, x0, y0))
+                    rec = jatam_result_t{JATAM_DET, st.size(), shape_hash(g, a.grid), 0};
+                else
+                    queue = true;
             }
         }
         if (!queue)
