@@ -175,16 +175,17 @@ int jatam_batch_classify_items(jatam_batch_t* batch, const jatam_item_t* items, 
                                uint64_t* tally, void* stream);
 
 /*
- * Enumeration of a lexicographic range in slices, with HIP graphs: the
- * pipeline of one slice of `slice` genotypes (and, if `shapes` is given, the
- * shape histogram of its records) is captured once into a graph whose
- * kernels read the slice number from a device counter, then the graph is
- * launched `slices` times on `stream`, the counter advancing by one per
- * replay.  Covers genotypes first .. first + slice*slices - 1 (§3.4: the
- * paper's slice-by-slice enumeration, here without host work per slice).
+ * Enumeration of a lexicographic range in slices: genotypes first .. first +
+ * slice*slices - 1 (§3.4: the paper's slice-by-slice enumeration, here
+ * without host work per slice).  For G <= 16 the slices are classified
+ * together by the one-launch kernel, which needs no room per genotype.  Above,
+ * with HIP graphs: the pipeline of one slice of `slice` genotypes (and, if
+ * `shapes` is given, the shape histogram of its records) is captured once into
+ * a graph whose kernels read the slice number from a device counter, then the
+ * graph is launched `slices` times on `stream`, the counter advancing by one
+ * per replay.
  *   out     device, slice*slices records in genotype order, or NULL to keep
- *           only the tally and the histogram (records of each slice then go
- *           to the workspace and are overwritten by the next slice)
+ *           only the tally and the histogram
  *   tally   NULL or device uint64[4], ADDED to (as jatam_batch_classify)
  *   shapes, shapes_capacity
  *           NULL, or a table as for jatam_shape_histogram, ADDED to
@@ -220,7 +221,9 @@ int jatam_batch_set_refill(jatam_batch_t* batch, int idle_lanes);
 
 /*
  * Launch parameters of the pipeline for one grid class (G <= 16 or
- * 16 < G <= 32).  None of them changes a record.
+ * 16 < G <= 32).  None of them changes a record.  Calls of up to 2^20 items
+ * with the default parameters of both classes and without the timing hook are
+ * made by one launch that does the whole classification instead.
  *   refill        first runs: a wave refills once this many of its 64 lanes
  *                 are idle, 1..64 (default 24)
  *   first_waves   persistent one-wave workgroups per CU of the first-run

@@ -10,7 +10,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libjatam.so")
-SOURCES = ["jatam_plain.hip", "jatam_batched.hip", "jatam_ga.hip", "jatam_mlp.hip",
+SOURCES = ["jatam_plain.hip", "jatam_batched.hip", "jatam_solo.hip", "jatam_ga.hip", "jatam_mlp.hip",
            "jatam_select.hip", "jatam_tally.hip", "jatam_static.hip", "jatam_truth.hip",
            "jatam_neighbourhood.hip", "jatam_roulette.hip", "jatam_api.cpp"]
 

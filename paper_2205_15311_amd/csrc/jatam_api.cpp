@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -20,7 +21,6 @@ struct jatam_batch {
     int cus;                       // compute units of the device
     jatam::BatchOccupancy occ;     // resident blocks per CU
     jatam_tuning_t tune[2];        // launch parameters per grid class
-    uint32_t small_hash[2];        // host copy of the workspace's small_hash
     std::vector<std::pair<jatam_tuning_t, double>> tune_log;   // last autotune
     jatam::DeviceWorkspace ws;
     void* allocations[24];
@@ -69,6 +69,57 @@ std::vector<int> wave_choices(int occ)
     return v;
 }
 
+// Compute units and residency limits of a device, queried once per device.
+struct DeviceLimits {
+    std::once_flag once;
+    int cus = 0;
+    int solo[2][jatam::kGenoKinds] = {};
+};
+
+// The current device's limits; nullptr if they cannot be had.
+const DeviceLimits* device_limits()
+{
+    static DeviceLimits limits[64];
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
+        return nullptr;
+    DeviceLimits& d = limits[dev];
+    std::call_once(d.once, [&d, dev] {
+        if (hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev) !=
+            hipSuccess)
+            d.cus = 0;
+        jatam::solo_occupancy(d.solo);
+    });
+    return d.cus > 0 ? &d : nullptr;
+}
+
+// Classification without a workspace: the one-launch kernel, every chunk dealt
+// out (there is nowhere to keep claim counters).
+int classify_solo(const uint64_t* genotypes, uint64_t first, int64_t n, const jatam::Params& p,
+                  jatam_result_t* out, hipStream_t stream)
+{
+    if (n == 0)
+        return JATAM_OK;
+    const DeviceLimits* d = device_limits();
+    if (d == nullptr)
+        return JATAM_E_HIP;
+    const int geno = jatam::geno_kind(p.t, p.c);
+    const bool classes[2] = {p.grid <= 16, p.grid > 16};
+    const int waves[2] = {d->solo[0][geno] * d->cus, d->solo[1][geno] * d->cus};
+    constexpr int64_t kPiece = (int64_t)1 << 31;   // item positions are 32 bits
+    for (int64_t at = 0; at < n; at += kPiece) {
+        jatam::BatchArgs a =
+            jatam::batch_args_for(p, n - at < kPiece ? n - at : kPiece, out + at, nullptr,
+                                  jatam::DeviceWorkspace{});
+        a.genomes = genotypes != nullptr ? genotypes + at : nullptr;
+        a.first = first + (uint64_t)at;
+        const int rc = jatam::launch_solo(a, classes, waves, geno, nullptr, 0, stream);
+        if (rc != JATAM_OK)
+            return rc;
+    }
+    return JATAM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -97,7 +148,7 @@ int jatam_classify(const uint64_t* genotypes, int64_t n, int t, int c, int grid_
         return rc;
     if (n < 0 || (n > 0 && (genotypes == nullptr || out == nullptr)))
         return JATAM_E_INVALID_ARG;
-    return jatam::launch_plain(genotypes, 0, n, p, out, (hipStream_t)stream);
+    return classify_solo(genotypes, 0, n, p, out, (hipStream_t)stream);
 }
 
 int jatam_classify_range(uint64_t first, int64_t n, int t, int c, int grid_limit, int runs,
@@ -117,7 +168,7 @@ int jatam_classify_range(uint64_t first, int64_t n, int t, int c, int grid_limit
         if (p.genome_bits < 64 && (last >> p.genome_bits) != 0)
             return JATAM_E_INVALID_ARG;
     }
-    return jatam::launch_plain(nullptr, first, n, p, out, (hipStream_t)stream);
+    return classify_solo(nullptr, first, n, p, out, (hipStream_t)stream);
 }
 
 int jatam_classify_variant(const uint64_t* genotypes, uint64_t first, int64_t n, int t, int c,
@@ -267,13 +318,6 @@ int jatam_batch_create(int64_t max_n, jatam_batch_t** batch)
         return JATAM_E_HIP;
     }
     jatam::carve_workspace(base, (size_t)max_n, max_blocks, true, &b->ws);
-    if (jatam::batch_init_small_hash(b->ws.small_hash, nullptr) != JATAM_OK ||
-        hipDeviceSynchronize() != hipSuccess ||
-        hipMemcpy(b->small_hash, b->ws.small_hash, sizeof(b->small_hash),
-                  hipMemcpyDeviceToHost) != hipSuccess) {
-        free_batch(b);
-        return JATAM_E_HIP;
-    }
     *batch = b;
     return JATAM_OK;
 }
@@ -304,7 +348,7 @@ static int batch_check(jatam_batch_t* b, int64_t n, const void* out)
 static jatam::BatchArgs batch_args(jatam_batch_t* b, const jatam::Params& p, int64_t n,
                                    jatam_result_t* out, uint64_t* tally)
 {
-    return jatam::batch_args_for(p, n, out, tally, b->ws, b->small_hash);
+    return jatam::batch_args_for(p, n, out, tally, b->ws);
 }
 
 int jatam_batch_classify(jatam_batch_t* batch, const uint64_t* genotypes, int64_t n, int t,
@@ -467,6 +511,27 @@ int jatam_batch_enumerate(jatam_batch_t* batch, uint64_t first, int64_t slice, i
         if (hipStreamSynchronize(batch->graph_stream) != hipSuccess)
             return JATAM_E_HIP;
         drop_graph(batch);
+    }
+    if (grid_limit <= 16) {
+        // the one-launch kernel needs no staging, so the slices are taken
+        // together, and counts shapes itself, so records that nobody asked
+        // for are not written at all
+        const int geno = jatam::geno_kind(t, c);
+        const bool classes[2] = {true, false};
+        const int waves[2] = {batch->occ.solo[0][geno] * batch->cus, 1};
+        constexpr uint64_t kPiece = 1ull << 31;   // item positions are 32 bits
+        for (uint64_t at = 0; at < total; at += kPiece) {
+            jatam::BatchArgs a = batch_args(
+                batch, p, (int64_t)(total - at < kPiece ? total - at : kPiece),
+                out != nullptr ? out + at : nullptr, tally);
+            a.first = first + at;
+            a.refill = batch->tune[0].refill;
+            a.dyn16 = batch->tune[0].claim_share;
+            a.claim_chunks = batch->tune[0].claim_chunks;
+            if ((rc = jatam::launch_solo(a, classes, waves, geno, shapes, log2cap, s)) != JATAM_OK)
+                return rc;
+        }
+        return JATAM_OK;
     }
     jatam::BatchArgs a = batch_args(batch, p, slice, out != nullptr ? out : batch->ws.records,
                                     tally);
@@ -1301,7 +1366,6 @@ size_t carve_workspace(uint8_t* base, size_t max_n, int max_blocks, bool records
     w.queue_claim = (uint32_t*)take(2 * kClaimCounters * kClaimStride * sizeof(uint32_t));
     w.tally_slots =
         (unsigned long long*)take(kTallySlots * kTallyStride * sizeof(unsigned long long));
-    w.small_hash = (uint32_t*)take(2 * sizeof(uint32_t));
     w.seg_left = (uint32_t*)take(mb * sizeof(uint32_t));
     w.records = records ? (jatam_result_t*)take(n * sizeof(jatam_result_t)) : nullptr;
     for (int k = 0; k < 2; ++k) {
@@ -1328,11 +1392,35 @@ size_t carve_workspace(uint8_t* base, size_t max_n, int max_blocks, bool records
 // items that leave it (populations of large shapes) cost more than it saves.
 constexpr int64_t kWindowMinItems = 1 << 20;
 
+// Calls up to this many items take the one-launch kernel by default.  Measured
+// on lists (one launch against the pipeline, us): two tiles at G = 16, 10^3
+// items 55 : 135, 65,536 121 : 173, 2^20 218 : 248, 2^22 522 : 395; three tiles
+// 53 : 136, 91 : 196, 199 : 327, 471 : 455; three tiles at G = 32 59 : 114,
+// 382 : 465, 540 : 743 (the pipeline's window), 1448 : 925.
+constexpr int64_t kSoloItems = 1 << 20;
+
+static bool same_tuning(const jatam_tuning_t& x, const jatam_tuning_t& y)
+{
+    return x.refill == y.refill && x.first_waves == y.first_waves &&
+           x.repeat_waves == y.repeat_waves && x.wide_layout == y.wide_layout &&
+           x.claim_share == y.claim_share && x.claim_chunks == y.claim_chunks &&
+           x.repeat_mapping == y.repeat_mapping;
+}
+
 int launch_tuned(const jatam_tuning_t tn[2], const BatchOccupancy& occ, int cus, BatchArgs a,
                  int grid_limit, int max_t, hipStream_t stream, hipEvent_t* marks,
                  uint8_t* launched)
 {
     const int geno = geno_kind(max_t, a.c);
+    // Small calls: one launch instead of the pipeline's eight.  Only with the
+    // default parameters and without the timing hook, which are about the
+    // pipeline's stages.
+    if (a.n <= kSoloItems && marks == nullptr && a.slice == nullptr && same_tuning(tn[0], default_tuning(0)) &&
+        same_tuning(tn[1], default_tuning(1))) {
+        const bool one[2] = {grid_limit <= 16, grid_limit == 0 || grid_limit > 16};
+        const int waves[2] = {occ.solo[0][geno] * cus, occ.solo[1][geno] * cus};
+        return launch_solo(a, one, waves, geno, nullptr, 0, stream);
+    }
     // G <= narrow_max runs in the 16 x 16 layout; with the window on (the
     // default) that is every G <= 32, and the 32 x 32 class reruns only the
     // items of G > 16 that left the window
@@ -1356,7 +1444,7 @@ int launch_tuned(const jatam_tuning_t tn[2], const BatchOccupancy& occ, int cus,
 }
 
 BatchArgs batch_args_for(const Params& p, int64_t n, jatam_result_t* out, uint64_t* tally,
-                         const DeviceWorkspace& ws, const uint32_t small_hash[2])
+                         const DeviceWorkspace& ws)
 {
     BatchArgs a;
     a.genomes = nullptr;
@@ -1379,8 +1467,6 @@ BatchArgs batch_args_for(const Params& p, int64_t n, jatam_result_t* out, uint64
     a.dyn16 = 0;
     a.claim_chunks = 1;
     a.seg_cap = 0;
-    a.small0 = small_hash[0];
-    a.small1 = small_hash[1];
     a.out = out;
     a.tally = reinterpret_cast<unsigned long long*>(tally);
     a.ws = ws;

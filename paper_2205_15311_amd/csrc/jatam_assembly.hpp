@@ -20,6 +20,7 @@
 #pragma once
 
 #include "jatam_device.hpp"
+#include "jatam_shapes.hpp"
 
 namespace jatam {
 
@@ -788,6 +789,42 @@ __device__ __forceinline__ uint32_t orientation_hash(Grid& g, const ShapeBox& bx
     return oaat_finish(hv);
 }
 
+// D4 hashes of the monomer and the domino, which have one shape each up to D4.
+constexpr uint32_t oaat_add_c(uint32_t h, uint32_t byte)
+{
+    h += byte;
+    h += h << 10;
+    return h ^ (h >> 6);
+}
+constexpr uint32_t oaat_finish_c(uint32_t h)
+{
+    h += h << 3;
+    h ^= h >> 11;
+    return h + (h << 15);
+}
+// One orientation of n cells in a row from (0, 0), along x or y.
+constexpr uint32_t line_hash_c(int n, bool along_x)
+{
+    uint32_t h = 0;
+    for (int i = 0; i < n; ++i) {
+        h = oaat_add_c(h, along_x ? (uint32_t)i : 0u);
+        h = oaat_add_c(h, along_x ? 0u : (uint32_t)i);
+    }
+    return oaat_finish_c(h);
+}
+// Of a line's eight images four lie along x and four along y.
+constexpr uint32_t line_shape_hash_c(int n)
+{
+    const uint32_t x = line_hash_c(n, true), y = line_hash_c(n, false);
+    const uint32_t lo = x < y ? x : y, hi = x < y ? y : x;
+    uint32_t h = 0;
+    for (int i = 0; i < 8; ++i)
+        for (int b = 0; b < 4; ++b)
+            h = oaat_add_c(h, ((i < 4 ? lo : hi) >> (8 * b)) & 0xFFu);
+    return oaat_finish_c(h);
+}
+constexpr uint32_t kMonomerHash = line_shape_hash_c(1), kDominoHash = line_shape_hash_c(2);
+
 // The 8 orientation hashes sorted ascending, hashed again as 32
 // little-endian bytes: the same value for every image of the shape.
 __device__ __forceinline__ uint32_t combine_orientations(uint32_t hs[8])
@@ -1110,11 +1147,14 @@ __device__ __forceinline__ uint32_t bitmap8_shape_hash(uint64_t m)
 // the hash the shape has).  N entries {bitmap lo, bitmap hi, hash, 0},
 // direct mapped; an all-zero key marks an empty entry (no shape is empty).
 // Lanes read it freely; entries are written one lane at a time.  For
-// workgroups of one wave (insert synchronises the workgroup).
+// workgroups of one wave (insert synchronises the workgroup).  With a shape
+// table, an entry's last word counts the DET records of its bitmap that the
+// table does not have yet (and small_count those of one and two cells).
 template <int N>
 struct ShapeCache {
     static_assert((N & (N - 1)) == 0, "N must be a power of two");
     uint4* e;
+    uint32_t* small_count = nullptr;
 
     __device__ __forceinline__ static uint32_t slot(uint64_t m)
     {
@@ -1135,16 +1175,47 @@ struct ShapeCache {
     // Called by the whole wave of a one-wave workgroup: every lane with
     // `want` stores its entry, in lane order (a later lane with the same
     // slot overwrites), then the wave's later lookups see the entries.
-    __device__ __forceinline__ void insert(bool want, uint64_t m, uint32_t hash, int lane)
+    __device__ __forceinline__ void insert(bool want, uint64_t m, uint32_t hash, int lane,
+                                           const ShapeTable& table = ShapeTable{})
     {
         uint64_t pending = __ballot(want);
         if (pending == 0)
             return;
         for (; pending != 0; pending &= pending - 1) {
-            if (lane == __builtin_ctzll(pending))
+            if (lane == __builtin_ctzll(pending)) {
+                if (table.entries != nullptr)
+                    flush_entry(slot(m), table);
                 e[slot(m)] = make_uint4((uint32_t)m, (uint32_t)(m >> 32), hash, 0u);
+            }
         }
         wave_lds_sync();
+    }
+    // Counts a DET record of bitmap m in its entry; false if it has none.
+    __device__ __forceinline__ bool count(uint64_t m)
+    {
+        uint4& v = e[slot(m)];
+        if (v.x != (uint32_t)m || v.y != (uint32_t)(m >> 32))
+            return false;
+        atomicAdd(&v.w, 1u);
+        return true;
+    }
+    __device__ __forceinline__ void flush_entry(uint32_t i, const ShapeTable& table)
+    {
+        const uint4 v = e[i];
+        if (v.w != 0)
+            table.add(shape_key(v.z, __popc(v.x) + __popc(v.y)), v.w);
+    }
+    // Every count to the table, at the wave's end.
+    __device__ __forceinline__ void flush(const ShapeTable& table, int lane)
+    {
+        if (table.entries == nullptr)
+            return;
+        wave_lds_sync();
+        for (int i = lane; i < N; i += 64)
+            flush_entry((uint32_t)i, table);
+        if (lane < 2 && small_count[lane] != 0)
+            table.add(shape_key(lane == 0 ? kMonomerHash : kDominoHash, lane + 1),
+                      small_count[lane]);
     }
 };
 

@@ -21,8 +21,6 @@ struct Params {
     uint32_t key1;
 };
 
-int launch_plain(const uint64_t* genomes, uint64_t first, int64_t n, const Params& prm,
-                 jatam_result_t* out, hipStream_t stream);
 int launch_variant(const uint64_t* genomes, uint64_t first, int64_t n, const Params& prm,
                    int variant, jatam_result_t* out, hipStream_t stream);
 
@@ -91,7 +89,6 @@ struct DeviceWorkspace {
     uint4* occ_hi;            // [max_n] words 4-7 of the run-0 occupancy a first
                               // repeat pass stores for the second (words 0-3 go to
                               // cand_shape)
-    uint32_t* small_hash;     // [2]: D4 hash of the monomer and of the domino
     jatam_result_t* records;  // [max_n] records of a GA generation
 };
 
@@ -116,8 +113,6 @@ struct BatchArgs {
                                     // device counters rather than dealt out (0..16)
     int claim_chunks;               // most chunks one claim takes (1..kMaxClaimChunks)
     uint32_t seg_cap;               // staging slots per wave (set per launch)
-    uint32_t small0, small1;        // D4 hashes of the monomer and the domino (the
-                                    // workspace's small_hash, copied at creation)
     jatam_result_t* out;
     unsigned long long* tally;      // nullptr or [4], accumulated
     DeviceWorkspace ws;
@@ -156,8 +151,10 @@ inline int geno_kind(int max_t, int c)
 // blocks[grid class][genotype type][0 first runs, 1 repeat runs (R lanes per
 // candidate), 2 repeat runs (one lane per candidate)]: resident one-wave
 // blocks per CU of the stage kernels.
+// solo[grid class][genotype type]: those of the one-launch kernel.
 struct BatchOccupancy {
     int blocks[2][kGenoKinds][3];
+    int solo[2][kGenoKinds];
 };
 void batch_occupancy(BatchOccupancy& occ);
 // Default launch parameters of a grid class.
@@ -217,16 +214,25 @@ int launch_neighbourhood_space(const jatam_result_t* space, uint64_t first, int6
                                jatam_neighbourhood_t* out, hipStream_t s);
 // Arguments of a pipelined call over a workspace (range mode, no order).
 BatchArgs batch_args_for(const Params& p, int64_t n, jatam_result_t* out, uint64_t* tally,
-                         const DeviceWorkspace& ws, const uint32_t small_hash[2]);
+                         const DeviceWorkspace& ws);
 // Launches the pipeline with launch parameters tn[grid class], capped by the
 // residency limits occ on a device of `cus` compute units.  grid_limit: the
 // call's uniform G, or 0 for mixed items (both classes).
 int launch_tuned(const jatam_tuning_t tn[2], const BatchOccupancy& occ, int cus, BatchArgs a,
                  int grid_limit, int max_t, hipStream_t stream, hipEvent_t* marks,
                  uint8_t* launched);
-int batch_init_small_hash(uint32_t* small_hash, hipStream_t stream);
 // When `marks` is not null, an event is recorded on the stream before stage
 // s (marks[2s]) and after it (marks[2s+1]), and launched[s] is set.
+// The one-launch classification (jatam_solo.hip) of the grid classes `classes`,
+// each on up to waves[class] one-wave workgroups; a.out may be null; shapes:
+// nullptr, or the table of 2^log2cap entries that DET shapes are added to.
+void solo_occupancy(int solo[2][kGenoKinds]);
+int launch_solo(const BatchArgs& a, const bool classes[2], const int waves[2], int geno,
+                jatam_shape_count_t* shapes, int log2cap, hipStream_t stream);
+// Clears one class's first-run claim counters and, if given, the tally's
+// counter sets; and adds the counter sets to the caller's tally.
+void launch_clear(uint32_t* claims, unsigned long long* slots, hipStream_t stream);
+void launch_tally(const unsigned long long* slots, unsigned long long* tally, hipStream_t stream);
 int launch_batched(const BatchArgs& a, const bool classes[2], const StageLaunch launch[2],
                    int geno, hipStream_t stream, hipEvent_t* marks, uint8_t* launched);
 // Slice counter of a replayed enumeration: set to 0, or advanced by one.

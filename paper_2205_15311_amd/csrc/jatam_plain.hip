@@ -1,4 +1,4 @@
-// jatam_plain.hip - plain classification kernel: one lane per genotype.
+// jatam_plain.hip - classification variants, one lane per genotype.
 //
 // Each lane decodes its genotype, makes up to R assembly runs in sequence and
 // writes one 16-byte record (§3.2, §3.3).  The grid of a lane lives in LDS
@@ -59,32 +59,7 @@ __device__ jatam_result_t classify_genotype(LaneGrid<W, B>& g, RunState& st, uin
     return jatam_result_t{JATAM_DET, size0, hash, work};
 }
 
-template <int W, int B, class M>
-__global__ __launch_bounds__(B) void classify_plain_kernel(const uint64_t* __restrict__ genomes,
-                                                           uint64_t first, int64_t n, Params prm,
-                                                           jatam_result_t* __restrict__ out)
-{
-    using Geo = Geometry<W>;
-    __shared__ uint32_t smem[Geo::kLaneWords * B];
-    const int64_t i = (int64_t)blockIdx.x * B + threadIdx.x;
-    if (i >= n)
-        return;
-    LaneGrid<W, B> g{smem + threadIdx.x};
-    g.clear_all();
-    RunState st{};
-
-    const uint64_t genome = genomes ? genomes[i] : first + (uint64_t)i;
-    jatam_result_t rec;
-    if (prm.genome_bits < 64 && (genome >> prm.genome_bits) != 0) {
-        rec = jatam_result_t{JATAM_INVALID, 0, 0u, 0};
-    } else {
-        const uint64_t rng_id = genome | ((uint64_t)(uint32_t)prm.t << 56);
-        rec = classify_genotype<W, B, M>(g, st, genome, rng_id, prm);
-    }
-    out[i] = rec;
-}
-
-// The plain kernel with a classification variant: the lane's movelist stack
+// Classification with a variant: the lane's movelist stack
 // (kStackWords words) follows the grid words of all lanes in LDS.
 template <int W, int B, class M, int kVariant>
 __global__ __launch_bounds__(B) void classify_variant_kernel(const uint64_t* __restrict__ genomes,
@@ -157,39 +132,6 @@ int launch_variant(const uint64_t* genomes, uint64_t first, int64_t n, const Par
     case 2: launch_variant_v<2>(genomes, first, n, prm, out, stream); break;
     case 3: launch_variant_v<3>(genomes, first, n, prm, out, stream); break;
     default: return JATAM_E_INVALID_ARG;
-    }
-    return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
-}
-
-template <int W, int B, class M>
-static void launch_plain_t(const uint64_t* genomes, uint64_t first, int64_t n, const Params& prm,
-                           jatam_result_t* out, hipStream_t stream)
-{
-    const int64_t blocks = (n + B - 1) / B;
-    hipLaunchKernelGGL((classify_plain_kernel<W, B, M>), dim3((unsigned)blocks), dim3(B), 0,
-                       stream, genomes, first, n, prm, out);
-}
-
-int launch_plain(const uint64_t* genomes, uint64_t first, int64_t n, const Params& prm,
-                 jatam_result_t* out, hipStream_t stream)
-{
-    if (n == 0)
-        return JATAM_OK;
-    const int geno = geno_kind(prm.t, prm.c);
-    if (prm.grid <= 16) {
-        if (geno == kGenoTwo)
-            launch_plain_t<16, 256, Bonds2>(genomes, first, n, prm, out, stream);
-        else if (geno == kGenoFour)
-            launch_plain_t<16, 256, Bonds4>(genomes, first, n, prm, out, stream);
-        else
-            launch_plain_t<16, 256, BondsC16>(genomes, first, n, prm, out, stream);
-    } else {
-        if (geno == kGenoTwo)
-            launch_plain_t<32, 64, Bonds2>(genomes, first, n, prm, out, stream);
-        else if (geno == kGenoFour)
-            launch_plain_t<32, 64, Bonds4>(genomes, first, n, prm, out, stream);
-        else
-            launch_plain_t<32, 64, BondsC16>(genomes, first, n, prm, out, stream);
     }
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }

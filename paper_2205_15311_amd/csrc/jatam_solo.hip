@@ -1,0 +1,340 @@
+// jatam_solo.hip - the whole classification in one launch: every wave takes
+// genotypes from the seed's screen to their records by itself, without queues in
+// device memory.
+//
+// A wave screens chunks of its input and keeps each lane busy with first runs
+// (as first_run_kernel does).  What a clean first run leaves open goes through
+// two lists in LDS: packed shapes, proven 64 at a time by all lanes together
+// (the proof of one candidate by its own lane would leave the others idle),
+// and the candidates that are not proven, whose repeat runs the wave makes in
+// rounds (RepeatWave) when its first runs are done, or before if the list fills
+// up: runs 0-3 of sixteen candidates at a time, then all R runs of those
+// without a witness; all R at once where R is at most eight.
+//
+// Against the pipeline of jatam_batched.hip it needs one launch instead of
+// eight, no workspace and no staging (150 bytes a candidate through HBM), and no
+// wave waits for another's first runs; it pays with proofs of mixed sizes and
+// with repeat rounds that no other wave shares.
+#include "jatam_waves.hpp"
+
+namespace jatam {
+
+constexpr int kSoloPend = 128;    // unproven candidates: drained above 64
+constexpr int kSoloShapes = 64;   // packed shapes waiting for a proof
+
+template <int W, class M, int kIn>
+__global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
+                                                  uint32_t chunk_items, bool direct_tally,
+                                                  ShapeTable table)
+{
+    using Grid = LeanGrid<W>;
+    const uint64_t first = a.first;
+    jatam_result_t* const out = a.out;
+    __shared__ __attribute__((aligned(16))) uint32_t smem[Grid::kLaneWords * 64];
+    __shared__ uint4 shapes[kSoloShapes];
+    __shared__ uint32_t shape_idx[kSoloShapes];
+    __shared__ uint32_t pend[kSoloPend];
+    __shared__ uint32_t orient[8 * kSoloGroups];
+    __shared__ uint4 cache_mem[kShapeCache];
+    __shared__ uint32_t small_count[2];
+    uint32_t* const ring = smem + Grid::kSpare;   // survivor indices
+    // the second list of a drain: the shapes are all proven then
+    uint32_t* const undecided = reinterpret_cast<uint32_t*>(shapes);
+    static_assert(kRing <= 64 * (W / 8), "the ring fits row W-1's PEND words");
+    static_assert(kSoloPend * 4 <= sizeof(shapes), "the undecided list fits the shapes'");
+    const uint32_t lane = (uint32_t)lane_id();
+    Grid g{smem + threadIdx.x};
+    g.clear_all();
+    WaveShapeCache cache{cache_mem, small_count};
+    cache.clear((int)lane);
+    if (lane < 2)
+        small_count[lane] = 0;
+    __syncthreads();
+    RunState st{};
+    WaveTally tally{{0, 0, 0, 0}};
+    const uint32_t n_items = (uint32_t)a.n;
+    ChunkSource chunks;
+    chunks.init(a, klass, (n_items + chunk_items - 1) / chunk_items);
+    uint32_t head = 0, queued = 0, nshapes = 0, npend = 0;   // wave-uniform
+    bool busy = false, starved = false;
+    uint32_t idx = 0;
+    Geno gd{};
+    M m{};
+    int ev = kEvNone;
+
+    // Records of the waiting shapes that are guarded; the rest to the list of
+    // unproven candidates.
+    auto prove_shapes = [&]() {
+        wave_lds_sync();
+        const bool active = lane < nshapes;
+        bool forced = false;
+        int size = 0;
+        uint32_t i = 0;
+        uint64_t key = 0;
+        if (active) {
+            i = shape_idx[lane];
+            const uint4 sh = shapes[lane];
+            const Geno s = run_geno<W, kIn>(a, first, i);
+            forced = packed_shape_is_guarded(build_bonds<M>(s.genome, s.t, a.bits, a.c), sh);
+            key = ((uint64_t)sh.y << 32) | sh.x;
+            size = __popcll(key);
+        }
+        const uint32_t h = det_hash(g, cache, forced, size, 0, true, key, table);
+        if (forced && out != nullptr)
+            out[i] = jatam_result_t{JATAM_DET, size, h, (size - 1) * a.runs};
+        count_shapes(table, cache, forced, size, true, key, h);
+        tally.add(forced, JATAM_DET);
+        const uint64_t km = __ballot(active && !forced);
+        if (active && !forced)
+            pend[npend + (uint32_t)__popcll(km & lanes_below())] = i;
+        npend += (uint32_t)__popcll(km);
+        nshapes = 0;
+        wave_lds_sync();
+    };
+    // Repeat rounds of rpass lanes per candidate over a list of indices; what
+    // they leave undecided to the second list.  Returns its length.
+    auto rounds = [&](int rpass, uint32_t* list, uint32_t count) -> uint32_t {
+        RepeatWave<W, M, true> rw(a, smem, orient, cache, st, tally, rpass, 0, false, undecided,
+                                  nullptr, table);
+        const uint32_t groups = (uint32_t)rw.groups, grp = (uint32_t)rw.grp;
+        for (uint32_t at = 0; at < count; at += groups) {
+            const bool active = grp < groups && at + grp < count;
+            rw.round(active, active ? list[at + grp] : 0u, 0u);
+        }
+        wave_lds_sync();
+        return rw.kept;
+    };
+
+    for (;;) {
+        // -- lanes whose first run is over ------------------------------------
+        const bool finish = busy && run_over(ev, st, gd.grid);
+        if (__ballot(finish) != 0) {
+            bool done = false, candidate = false, det = false, pack = false;
+            int cls = 0, steps = st.steps;
+            jatam_result_t rec{0, 0, 0u, 0};
+            if (finish) {
+                done = true;
+                if (ev == kEvCorrupt) {
+                    rec = jatam_result_t{JATAM_INVALID, 0, 0u, 0};
+                    cls = JATAM_INVALID;
+                } else if (ev != kEvNone) {
+                    cls = ev == kEvUnbound ? JATAM_UNBOUND : JATAM_ND_SITE;
+                    rec = jatam_result_t{cls, st.size(), 0u, st.steps};
+                } else if (!st.choice || a.runs == 1) {
+                    // no random word was drawn: every run would be this run
+                    det = true;
+                } else {
+                    done = false;
+                    candidate = true;
+                }
+            }
+            uint64_t key = 0;
+            int x0 = 0, y0 = 0;
+            bool fits = false;
+            uint4 packed = packed_none();
+            if (det || candidate)
+                fits = shape_key8(g, st, gd.grid, st.size(), key, x0, y0);
+            if (candidate) {
+                if (fits)
+                    packed = pack_shape(g, st, gd.grid, st.size(), key, x0, y0);
+                pack = packed_shape_valid(packed);
+                // a shape too large to wait for the others is checked at once
+                if (!pack && shape_is_guarded(m, g, st, gd.grid, fits, key, x0, y0)) {
+                    candidate = false;
+                    det = true;
+                    steps = st.steps * a.runs;
+                }
+            }
+            if (__ballot(det) != 0) {
+                const uint32_t h =
+                    det_hash(g, cache, det, st.size(), gd.grid, fits, key, table);
+                count_shapes(table, cache, det, st.size(), fits, key, h);
+                if (det) {
+                    done = true;
+                    cls = JATAM_DET;
+                    rec = jatam_result_t{JATAM_DET, st.size(), h, steps};
+                }
+            }
+            if (done && out != nullptr)
+                out[idx] = rec;
+            busy = busy && !finish;
+            tally.add(done, cls);
+            const uint64_t pm = __ballot(candidate && pack);
+            if (nshapes + (uint32_t)__popcll(pm) > (uint32_t)kSoloShapes)
+                prove_shapes();
+            if (candidate && pack) {
+                const uint32_t at = nshapes + (uint32_t)__popcll(pm & lanes_below());
+                shapes[at] = packed;
+                shape_idx[at] = idx;
+            }
+            nshapes += (uint32_t)__popcll(pm);
+            const uint64_t um = __ballot(candidate && !pack);
+            if (candidate && !pack)
+                pend[npend + (uint32_t)__popcll(um & lanes_below())] = idx;
+            npend += (uint32_t)__popcll(um);
+        }
+        // -- refill idle lanes once enough of them wait, unless the list of
+        // unproven candidates has to be worked off first: every waiting shape
+        // and every busy lane may add one to it, and after a refill 64 lanes
+        // are busy ------------------------------------------------------------
+        const uint64_t idle = __ballot(!busy);
+        const uint32_t nidle = (uint32_t)__popcll(idle);
+        if (npend + nshapes + 64u > (uint32_t)kSoloPend && nshapes != 0)
+            prove_shapes();
+        const bool full = npend + 64u > (uint32_t)kSoloPend;
+        if (!full && (nidle >= (uint32_t)a.refill || nidle == 64)) {
+            starved = false;
+            while (queued < nidle) {
+                uint32_t chunk;
+                if (!chunks.take(chunk, true)) {
+                    starved = true;
+                    break;
+                }
+                uint32_t i, opts;
+                int cls;
+                jatam_result_t rec;
+                const uint32_t pos = chunk * chunk_items + lane;
+                const bool wrote = screen_item<M, kIn>(
+                    a, first, klass, pos, lane < chunk_items && pos < n_items, i, opts, cls, rec);
+                const bool keep = cls == kScreenKeep;
+                if (wrote && out != nullptr)
+                    out[i] = rec;
+                count_shapes(table, cache, wrote && cls == JATAM_DET, 1, true, 1ull, kMonomerHash);
+                tally.add(wrote && cls != JATAM_INVALID, cls);
+                const uint64_t km = __ballot(keep);
+                if (keep)
+                    ring[(head + queued + (uint32_t)__popcll(km & lanes_below())) % kRing] = i;
+                queued += (uint32_t)__popcll(km);
+            }
+            wave_lds_sync();   // ring writes visible to the whole wave
+            const uint32_t take = queued < nidle ? queued : nidle;
+            if (!busy) {
+                const uint32_t rank = (uint32_t)__popcll(idle & lanes_below());
+                if (rank < take) {
+                    idx = ring[(head + rank) % kRing];
+                    gd = run_geno<W, kIn>(a, first, idx);
+                    m = build_bonds<M>(gd.genome, gd.t, a.bits, a.c);
+                    ev = run_start_known(g, st, gd.grid, m.codes(m.seed()));
+                    busy = true;
+                }
+            }
+            head = (head + take) % kRing;
+            queued -= take;
+            wave_lds_sync();   // ring slots read before they are refilled
+        }
+        if (__ballot(busy) == 0) {
+            const bool over = queued == 0 && starved;
+            if (full || over) {
+                prove_shapes();
+                if (a.runs > 2 * kRepeatFirstRuns) {
+                    const uint32_t left = rounds(kRepeatFirstRuns, pend, npend);
+                    rounds(a.runs, undecided, left);
+                } else {
+                    rounds(a.runs, pend, npend);
+                }
+                npend = 0;
+            }
+            if (over)
+                break;
+            continue;
+        }
+        // -- groups of four steps until enough lanes wait (every lane, once no
+        // chunk is left or a drain is due), at least one group ----------------
+        const uint32_t enough = full || (queued == 0 && starved) ? 65u : (uint32_t)a.refill;
+        for (;;) {
+            const bool stepping = busy && !run_over(ev, st, gd.grid);
+            if (__ballot(stepping) == 0)
+                break;
+            if (stepping)
+                ev = run_four(m, g, st, gd.grid, run_key(a, gd, 0));
+            const uint64_t waiting = __ballot(!busy || run_over(ev, st, gd.grid));
+            if ((uint32_t)__popcll(waiting) >= enough)
+                break;
+        }
+    }
+    cache.flush(table, (int)lane);
+    if (direct_tally)
+        tally.add_to(a.tally);
+    else
+        tally.flush(a);
+}
+
+// ---------------------------------------------------------------------------
+// Host side.
+// ---------------------------------------------------------------------------
+void solo_occupancy(int solo[2][kGenoKinds])
+{
+    solo[0][kGenoTwo] = resident_per_cu(solo_kernel<16, Bonds2, kInRange>);
+    solo[0][kGenoFour] = resident_per_cu(solo_kernel<16, Bonds4, kInRange>);
+    solo[0][kGenoC16] = resident_per_cu(solo_kernel<16, BondsC16, kInRange>);
+    solo[1][kGenoTwo] = resident_per_cu(solo_kernel<32, Bonds2, kInRange>);
+    solo[1][kGenoFour] = resident_per_cu(solo_kernel<32, Bonds4, kInRange>);
+    solo[1][kGenoC16] = resident_per_cu(solo_kernel<32, BondsC16, kInRange>);
+}
+
+template <int W, class M>
+static void launch_solo_t(const BatchArgs& a, int klass, uint32_t blocks, uint32_t chunk_items,
+                          bool direct, const ShapeTable& table, hipStream_t stream)
+{
+    if (a.items != nullptr)
+        hipLaunchKernelGGL((solo_kernel<W, M, kInItems>), dim3(blocks), dim3(64), 0, stream, a,
+                           klass, chunk_items, direct, table);
+    else if (a.genomes != nullptr)
+        hipLaunchKernelGGL((solo_kernel<W, M, kInList>), dim3(blocks), dim3(64), 0, stream, a,
+                           klass, chunk_items, direct, table);
+    else
+        hipLaunchKernelGGL((solo_kernel<W, M, kInRange>), dim3(blocks), dim3(64), 0, stream, a,
+                           klass, chunk_items, direct, table);
+}
+
+int launch_solo(const BatchArgs& a, const bool classes[2], const int waves[2], int geno,
+                jatam_shape_count_t* shapes, int log2cap, hipStream_t stream)
+{
+    if (a.n <= 0)
+        return JATAM_OK;
+    const ShapeTable table{shapes, log2cap};
+    // every wave some items: chunks shrink to one item each where there are
+    // fewer items than lanes
+    uint32_t blocks[2], chunk[2], most = 0;
+    for (int k = 0; k < 2; ++k) {
+        const uint64_t per = ((uint64_t)a.n + (uint64_t)waves[k] - 1) / (uint64_t)waves[k];
+        chunk[k] = per < 64 ? (uint32_t)per : 64u;
+        const uint64_t nchunks = ((uint64_t)a.n + chunk[k] - 1) / chunk[k];
+        blocks[k] = nchunks < (uint64_t)waves[k] ? (uint32_t)nchunks : (uint32_t)waves[k];
+        if (classes[k])
+            most = blocks[k] > most ? blocks[k] : most;
+    }
+    // few waves add to the caller's tally themselves (their atomics on its four
+    // words serialise, about 12 ns each); more go through the counter sets
+    const bool direct = a.tally == nullptr || most <= 1024;
+    bool cleared = false;
+    for (int k = 0; k < 2; ++k) {
+        if (!classes[k])
+            continue;
+        const bool slots = !direct && !cleared;
+        if (a.dyn16 > 0 || slots)
+            launch_clear(a.ws.run_claim + k * kClaimCounters * kClaimStride,
+                         slots ? a.ws.tally_slots : nullptr, stream);
+        cleared = true;
+        if (k == 0) {
+            if (geno == kGenoTwo)
+                launch_solo_t<16, Bonds2>(a, 0, blocks[0], chunk[0], direct, table, stream);
+            else if (geno == kGenoFour)
+                launch_solo_t<16, Bonds4>(a, 0, blocks[0], chunk[0], direct, table, stream);
+            else
+                launch_solo_t<16, BondsC16>(a, 0, blocks[0], chunk[0], direct, table, stream);
+        } else {
+            if (geno == kGenoTwo)
+                launch_solo_t<32, Bonds2>(a, 1, blocks[1], chunk[1], direct, table, stream);
+            else if (geno == kGenoFour)
+                launch_solo_t<32, Bonds4>(a, 1, blocks[1], chunk[1], direct, table, stream);
+            else
+                launch_solo_t<32, BondsC16>(a, 1, blocks[1], chunk[1], direct, table, stream);
+        }
+    }
+    if (!direct)
+        launch_tally(a.ws.tally_slots, a.tally, stream);
+    return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
+}
+
+}  // namespace jatam

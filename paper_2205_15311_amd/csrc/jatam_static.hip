@@ -24,7 +24,6 @@ struct StaticDevice {
     bool ready;
     int cus;
     jatam::BatchOccupancy occ;
-    uint32_t small_hash[2];
     jatam::DeviceWorkspace ws;
 };
 
@@ -38,9 +37,8 @@ __device__ __align__(256) uint8_t scratch[kStaticBytes];
 namespace {
 
 // Set-up on the current device, once: the array's device address, the
-// residency limits, the workspace layout and the two small-shape hashes (a
-// kernel and a copy on the null stream, synchronised; so the first call on a
-// device must not be under graph capture).
+// residency limits and the workspace layout (runtime queries, so the first
+// call on a device must not be under graph capture).
 int static_setup(int dev, StaticDevice** out)
 {
     std::lock_guard<std::mutex> lock(g_setup);
@@ -60,11 +58,6 @@ int static_setup(int dev, StaticDevice** out)
                 kStaticBytes)
             return JATAM_E_UNSUPPORTED;
         jatam::carve_workspace(ptr, (size_t)kStaticMaxN, max_blocks, false, &d.ws);
-        if (jatam::batch_init_small_hash(d.ws.small_hash, nullptr) != JATAM_OK ||
-            hipDeviceSynchronize() != hipSuccess ||
-            hipMemcpy(d.small_hash, d.ws.small_hash, sizeof(d.small_hash),
-                      hipMemcpyDeviceToHost) != hipSuccess)
-            return JATAM_E_HIP;
         d.ready = true;
     }
     *out = &d;
@@ -92,7 +85,7 @@ extern "C" int jatam_classify_static(const uint64_t* genotypes, int64_t n, int t
     const int sc = static_setup(dev, &d);
     if (sc != JATAM_OK)
         return sc;
-    jatam::BatchArgs a = jatam::batch_args_for(p, n, out, tally, d->ws, d->small_hash);
+    jatam::BatchArgs a = jatam::batch_args_for(p, n, out, tally, d->ws);
     a.genomes = genotypes;
     const jatam_tuning_t tune[2] = {jatam::default_tuning(0), jatam::default_tuning(1)};
     return jatam::launch_tuned(tune, d->occ, d->cus, a, grid_limit, t, (hipStream_t)stream,
