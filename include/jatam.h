@@ -605,10 +605,11 @@ enum { JATAM_UNDECIDED = -2 };
 
 typedef struct jatam_truth jatam_truth_t;
 
-/* Workspace for calls of up to max_n genotypes: the queue of genotypes one
- * run leaves open, and per exploring wave (waves in [1, 4096]) two levels of
- * max_level states (max_level in [1, 2^18]; 644 bytes per state) and a hash
- * table of 2 * max_level slots.  Allocates and zeroes device memory
+/* Workspace for calls of up to max_n genotypes: the queues of genotypes one
+ * run leaves open and of those whose search passes sixteen states a level (8
+ * bytes per genotype), and per wave that explores the latter (waves in [1,
+ * 4096]) two levels of max_level states (max_level in [1, 2^18]; 644 bytes per
+ * state) and a hash table of 2 * max_level slots.  Allocates and zeroes device memory
  * (synchronises the device). */
 int jatam_truth_create(int64_t max_n, int32_t max_level, int32_t waves, jatam_truth_t** out);
 int jatam_truth_destroy(jatam_truth_t* w);

@@ -229,6 +229,16 @@ int launch_tuned(const jatam_tuning_t tn[2], const BatchOccupancy& occ, int cus,
 void solo_occupancy(int solo[2][kGenoKinds]);
 int launch_solo(const BatchArgs& a, const bool classes[2], const int waves[2], int geno,
                 jatam_shape_count_t* shapes, int log2cap, hipStream_t stream);
+// The true class's first stage: run 0 of a.n genotypes (range or list; at most
+// 2^31) with the true class's records for those it decides; the others' indices
+// + base to items[*count ...].
+struct OpenList {
+    uint32_t* items;
+    uint32_t* count;
+    uint32_t base;
+};
+void launch_first_open(const BatchArgs& a, int waves, int geno, const OpenList& open,
+                       hipStream_t stream);
 // Clears one class's first-run claim counters and, if given, the tally's
 // counter sets; and adds the counter sets to the caller's tally.
 void launch_clear(uint32_t* claims, unsigned long long* slots, hipStream_t stream);
@@ -347,8 +357,10 @@ struct TruthArgs {
     uint32_t key0, key1;            // key of the one run of the first stage
     int64_t cap;                    // most states explored per genotype
     jatam_result_t* out;
-    uint32_t* counters;             // [0] queued genotypes, [1] next one to explore
-    uint32_t* queue;                // [n]
+    uint32_t* counters;             // [0] genotypes in queue, [1] genotypes in wide,
+                                    // [2] next of those to explore
+    uint32_t* queue;                // [n] to explore
+    uint32_t* wide;                 // [n] too wide for the search in LDS
     uint32_t max_level;             // states per level (<= 2^18)
     int table_log2;                 // slots of each wave's table (>= 2 * max_level)
     uint32_t* arena;                // per wave: 2 levels of max_level states
@@ -360,7 +372,13 @@ struct TruthArgs {
 // Words of one stored state in the exploration (occupancy, tiles, hash).
 constexpr int truth_state_words(int W) { return W * W / 32 + W * W / 8 + 1; }
 constexpr uint32_t kMaxTruthLevel = 1u << 18;   // states per level (18-bit parent index)
-int launch_truth(const TruthArgs& a, int blocks, hipStream_t s);
+// Waves of the three stages: resident ones of the first two per grid class and
+// genotype type, and the wide search's, which the workspace has room for.
+struct TruthWaves {
+    int first[2][kGenoKinds], narrow[2][kGenoKinds];
+    int wide;
+};
+int launch_truth(const TruthArgs& a, const Params& p, const TruthWaves& waves, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Shape histogram.

@@ -15,6 +15,9 @@
 // eight, no workspace and no staging (150 bytes a candidate through HBM), and no
 // wave waits for another's first runs; it pays with proofs of mixed sizes and
 // with repeat rounds that no other wave shares.
+//
+// The same kernel makes the first stage of the true class (kOpen): run 0 of every
+// genotype and the proof, and what these leave open to a list in device memory.
 #include "jatam_waves.hpp"
 
 namespace jatam {
@@ -22,10 +25,10 @@ namespace jatam {
 constexpr int kSoloPend = 128;    // unproven candidates: drained above 64
 constexpr int kSoloShapes = 64;   // packed shapes waiting for a proof
 
-template <int W, class M, int kIn>
+template <int W, class M, int kIn, bool kOpen>
 __global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
                                                   uint32_t chunk_items, bool direct_tally,
-                                                  ShapeTable table)
+                                                  ShapeTable table, OpenList open)
 {
     using Grid = LeanGrid<W>;
     const uint64_t first = a.first;
@@ -81,7 +84,7 @@ __global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
         }
         const uint32_t h = det_hash(g, cache, forced, size, 0, true, key, table);
         if (forced && out != nullptr)
-            out[i] = jatam_result_t{JATAM_DET, size, h, (size - 1) * a.runs};
+            out[i] = jatam_result_t{JATAM_DET, size, h, kOpen ? 0 : (size - 1) * a.runs};
         count_shapes(table, cache, forced, size, true, key, h);
         tally.add(forced, JATAM_DET);
         const uint64_t km = __ballot(active && !forced);
@@ -89,6 +92,18 @@ __global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
             pend[npend + (uint32_t)__popcll(km & lanes_below())] = i;
         npend += (uint32_t)__popcll(km);
         nshapes = 0;
+        wave_lds_sync();
+    };
+    // kOpen: the unproven candidates to the call's list.
+    auto hand_over = [&]() {
+        wave_lds_sync();
+        uint32_t at = 0;
+        if (lane == 0 && npend != 0)
+            at = atomicAdd(open.count, npend);
+        at = (uint32_t)__shfl((int)at, 0);
+        for (uint32_t j = lane; j < npend; j += 64)
+            open.items[at + j] = open.base + pend[j];
+        npend = 0;
         wave_lds_sync();
     };
     // Repeat rounds of rpass lanes per candidate over a list of indices; what
@@ -118,9 +133,10 @@ __global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
                     rec = jatam_result_t{JATAM_INVALID, 0, 0u, 0};
                     cls = JATAM_INVALID;
                 } else if (ev != kEvNone) {
-                    cls = ev == kEvUnbound ? JATAM_UNBOUND : JATAM_ND_SITE;
-                    rec = jatam_result_t{cls, st.size(), 0u, st.steps};
-                } else if (!st.choice || a.runs == 1) {
+                    cls = ev == kEvUnbound && !kOpen ? JATAM_UNBOUND : JATAM_ND_SITE;
+                    rec = kOpen ? jatam_result_t{cls, 0, 0u, 0}
+                                : jatam_result_t{cls, st.size(), 0u, st.steps};
+                } else if (!st.choice || (!kOpen && a.runs == 1)) {
                     // no random word was drawn: every run would be this run
                     det = true;
                 } else {
@@ -152,7 +168,7 @@ __global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
                 if (det) {
                     done = true;
                     cls = JATAM_DET;
-                    rec = jatam_result_t{JATAM_DET, st.size(), h, steps};
+                    rec = jatam_result_t{JATAM_DET, st.size(), h, kOpen ? 0 : steps};
                 }
             }
             if (done && out != nullptr)
@@ -181,7 +197,9 @@ __global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
         const uint32_t nidle = (uint32_t)__popcll(idle);
         if (npend + nshapes + 64u > (uint32_t)kSoloPend && nshapes != 0)
             prove_shapes();
-        const bool full = npend + 64u > (uint32_t)kSoloPend;
+        if (kOpen && npend + 64u > (uint32_t)kSoloPend)
+            hand_over();
+        const bool full = !kOpen && npend + 64u > (uint32_t)kSoloPend;
         if (!full && (nidle >= (uint32_t)a.refill || nidle == 64)) {
             starved = false;
             while (queued < nidle) {
@@ -197,6 +215,8 @@ __global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
                 const bool wrote = screen_item<M, kIn>(
                     a, first, klass, pos, lane < chunk_items && pos < n_items, i, opts, cls, rec);
                 const bool keep = cls == kScreenKeep;
+                if (kOpen && cls == JATAM_ND_SITE)
+                    rec.size = 0;
                 if (wrote && out != nullptr)
                     out[i] = rec;
                 count_shapes(table, cache, wrote && cls == JATAM_DET, 1, true, 1ull, kMonomerHash);
@@ -226,7 +246,9 @@ __global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
             const bool over = queued == 0 && starved;
             if (full || over) {
                 prove_shapes();
-                if (a.runs > 2 * kRepeatFirstRuns) {
+                if constexpr (kOpen) {
+                    hand_over();
+                } else if (a.runs > 2 * kRepeatFirstRuns) {
                     const uint32_t left = rounds(kRepeatFirstRuns, pend, npend);
                     rounds(a.runs, undecided, left);
                 } else {
@@ -252,6 +274,8 @@ __global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
                 break;
         }
     }
+    if constexpr (kOpen)
+        return;
     cache.flush(table, (int)lane);
     if (direct_tally)
         tally.add_to(a.tally);
@@ -264,27 +288,71 @@ __global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
 // ---------------------------------------------------------------------------
 void solo_occupancy(int solo[2][kGenoKinds])
 {
-    solo[0][kGenoTwo] = resident_per_cu(solo_kernel<16, Bonds2, kInRange>);
-    solo[0][kGenoFour] = resident_per_cu(solo_kernel<16, Bonds4, kInRange>);
-    solo[0][kGenoC16] = resident_per_cu(solo_kernel<16, BondsC16, kInRange>);
-    solo[1][kGenoTwo] = resident_per_cu(solo_kernel<32, Bonds2, kInRange>);
-    solo[1][kGenoFour] = resident_per_cu(solo_kernel<32, Bonds4, kInRange>);
-    solo[1][kGenoC16] = resident_per_cu(solo_kernel<32, BondsC16, kInRange>);
+    solo[0][kGenoTwo] = resident_per_cu(solo_kernel<16, Bonds2, kInRange, false>);
+    solo[0][kGenoFour] = resident_per_cu(solo_kernel<16, Bonds4, kInRange, false>);
+    solo[0][kGenoC16] = resident_per_cu(solo_kernel<16, BondsC16, kInRange, false>);
+    solo[1][kGenoTwo] = resident_per_cu(solo_kernel<32, Bonds2, kInRange, false>);
+    solo[1][kGenoFour] = resident_per_cu(solo_kernel<32, Bonds4, kInRange, false>);
+    solo[1][kGenoC16] = resident_per_cu(solo_kernel<32, BondsC16, kInRange, false>);
 }
 
-template <int W, class M>
+template <int W, class M, bool kOpen>
 static void launch_solo_t(const BatchArgs& a, int klass, uint32_t blocks, uint32_t chunk_items,
-                          bool direct, const ShapeTable& table, hipStream_t stream)
+                          bool direct, const ShapeTable& table, const OpenList& open,
+                          hipStream_t stream)
 {
-    if (a.items != nullptr)
-        hipLaunchKernelGGL((solo_kernel<W, M, kInItems>), dim3(blocks), dim3(64), 0, stream, a,
-                           klass, chunk_items, direct, table);
-    else if (a.genomes != nullptr)
-        hipLaunchKernelGGL((solo_kernel<W, M, kInList>), dim3(blocks), dim3(64), 0, stream, a,
-                           klass, chunk_items, direct, table);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64), 0, stream, a, klass, chunk_items,
+                           direct, table, open);
+    };
+    if (a.genomes != nullptr)
+        go(solo_kernel<W, M, kInList, kOpen>);
+    else if (kOpen || a.items == nullptr)
+        go(solo_kernel<W, M, kInRange, kOpen>);
     else
-        hipLaunchKernelGGL((solo_kernel<W, M, kInRange>), dim3(blocks), dim3(64), 0, stream, a,
-                           klass, chunk_items, direct, table);
+        go(solo_kernel<W, M, kOpen ? kInRange : kInItems, kOpen>);
+}
+
+// Waves and chunk size for n items on at most `waves` waves: every wave some
+// items, so chunks shrink to one item each where there are fewer items than
+// lanes.
+static uint32_t solo_blocks(uint64_t n, int waves, uint32_t& chunk)
+{
+    const uint64_t per = (n + (uint64_t)waves - 1) / (uint64_t)waves;
+    chunk = per < 64 ? (uint32_t)per : 64u;
+    const uint64_t nchunks = (n + chunk - 1) / chunk;
+    return nchunks < (uint64_t)waves ? (uint32_t)nchunks : (uint32_t)waves;
+}
+
+template <bool kOpen>
+static void launch_solo_class(const BatchArgs& a, int klass, int geno, uint32_t blocks,
+                              uint32_t chunk, bool direct, const ShapeTable& table,
+                              const OpenList& open, hipStream_t stream)
+{
+    if (klass == 0) {
+        if (geno == kGenoTwo)
+            launch_solo_t<16, Bonds2, kOpen>(a, 0, blocks, chunk, direct, table, open, stream);
+        else if (geno == kGenoFour)
+            launch_solo_t<16, Bonds4, kOpen>(a, 0, blocks, chunk, direct, table, open, stream);
+        else
+            launch_solo_t<16, BondsC16, kOpen>(a, 0, blocks, chunk, direct, table, open, stream);
+    } else {
+        if (geno == kGenoTwo)
+            launch_solo_t<32, Bonds2, kOpen>(a, 1, blocks, chunk, direct, table, open, stream);
+        else if (geno == kGenoFour)
+            launch_solo_t<32, Bonds4, kOpen>(a, 1, blocks, chunk, direct, table, open, stream);
+        else
+            launch_solo_t<32, BondsC16, kOpen>(a, 1, blocks, chunk, direct, table, open, stream);
+    }
+}
+
+void launch_first_open(const BatchArgs& a, int waves, int geno, const OpenList& open,
+                       hipStream_t stream)
+{
+    uint32_t chunk;
+    const uint32_t blocks = solo_blocks((uint64_t)a.n, waves, chunk);
+    launch_solo_class<true>(a, a.grid <= 16 ? 0 : 1, geno, blocks, chunk, true, ShapeTable{},
+                            open, stream);
 }
 
 int launch_solo(const BatchArgs& a, const bool classes[2], const int waves[2], int geno,
@@ -293,14 +361,9 @@ int launch_solo(const BatchArgs& a, const bool classes[2], const int waves[2], i
     if (a.n <= 0)
         return JATAM_OK;
     const ShapeTable table{shapes, log2cap};
-    // every wave some items: chunks shrink to one item each where there are
-    // fewer items than lanes
     uint32_t blocks[2], chunk[2], most = 0;
     for (int k = 0; k < 2; ++k) {
-        const uint64_t per = ((uint64_t)a.n + (uint64_t)waves[k] - 1) / (uint64_t)waves[k];
-        chunk[k] = per < 64 ? (uint32_t)per : 64u;
-        const uint64_t nchunks = ((uint64_t)a.n + chunk[k] - 1) / chunk[k];
-        blocks[k] = nchunks < (uint64_t)waves[k] ? (uint32_t)nchunks : (uint32_t)waves[k];
+        blocks[k] = solo_blocks((uint64_t)a.n, waves[k], chunk[k]);
         if (classes[k])
             most = blocks[k] > most ? blocks[k] : most;
     }
@@ -316,21 +379,8 @@ int launch_solo(const BatchArgs& a, const bool classes[2], const int waves[2], i
             launch_clear(a.ws.run_claim + k * kClaimCounters * kClaimStride,
                          slots ? a.ws.tally_slots : nullptr, stream);
         cleared = true;
-        if (k == 0) {
-            if (geno == kGenoTwo)
-                launch_solo_t<16, Bonds2>(a, 0, blocks[0], chunk[0], direct, table, stream);
-            else if (geno == kGenoFour)
-                launch_solo_t<16, Bonds4>(a, 0, blocks[0], chunk[0], direct, table, stream);
-            else
-                launch_solo_t<16, BondsC16>(a, 0, blocks[0], chunk[0], direct, table, stream);
-        } else {
-            if (geno == kGenoTwo)
-                launch_solo_t<32, Bonds2>(a, 1, blocks[1], chunk[1], direct, table, stream);
-            else if (geno == kGenoFour)
-                launch_solo_t<32, Bonds4>(a, 1, blocks[1], chunk[1], direct, table, stream);
-            else
-                launch_solo_t<32, BondsC16>(a, 1, blocks[1], chunk[1], direct, table, stream);
-        }
+        launch_solo_class<false>(a, k, geno, blocks[k], chunk[k], direct, table, OpenList{},
+                                 stream);
     }
     if (!direct)
         launch_tally(a.ws.tally_slots, a.tally, stream);

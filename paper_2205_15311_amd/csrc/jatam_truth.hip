@@ -8,31 +8,33 @@
 //   ND   some order meets an event (a bondable ring site, an ambiguous
 //        site) or ends in a second shape (occupancy, without rotation).
 //
-// Two stages.
-//   first<W>    one lane per genotype makes one run (any order will do).  An
-//               event in it is reachable: ND.  A run that never chose
-//               between two sites is the only order: DET.  A guarded shape
-//               (no conflicting neighbour can be placed before the cell it
-//               conflicts with, so every order places the same tiles) is
+// Three stages.
+//   first       run 0 of every genotype (any order will do; solo_kernel's first
+//               runs).  An event in it is reachable: ND.  A run that never
+//               chose between two sites is the only order: DET.  A guarded
+//               shape (no conflicting neighbour can be placed before the cell
+//               it conflicts with, so every order places the same tiles) is
 //               DET.  Anything else is queued.
-//   explore<W>  one wave per queued genotype, breadth first over the event-
-//               free states (sets of placed (cell, tile) pairs), level by
+//   narrow<W>   queued genotypes, sixteen lanes each: breadth first over the
+//               event-free states (sets of placed (cell, tile) pairs), level by
 //               level (a state of level L has L + 1 tiles, so states of one
-//               level are only ever reached from the level before).  Each
-//               lane takes a state, rebuilds its grid in LDS and checks every
-//               occupied cell's empty neighbours from scratch (the isotropic
-//               check of §3.2); an event ends the search (ND), an empty
-//               frontier is a terminal shape, compared with the first one
-//               found.  Successors are deduplicated in a per-wave open-
-//               addressing table whose 64-bit slots hold a 32-bit state hash
-//               and the successor itself (parent index, cell, tile), so
-//               equal hashes are settled by comparing the two states exactly
-//               and no lane ever waits for another.  More than `cap` states:
-//               undecided.
+//               level are only ever reached from the level before), a state in
+//               each lane's own LDS grid, with its frontier.  An event ends the
+//               search (ND), an empty frontier is a terminal shape, compared
+//               with the first one found.  Successors are deduplicated in an
+//               open-addressing table in LDS whose 64-bit slots hold a 32-bit
+//               state hash and the successor itself (parent, cell, tile), so
+//               equal hashes are settled by comparing the two states exactly and
+//               no lane ever waits for another.  More than `cap` states:
+//               undecided.  A level of more than sixteen states: to the next
+//               stage.
+//   wide<W>     the same search, one wave per genotype, with the levels in
+//               device memory; a state's frontier is rebuilt from its tiles.
 #include <new>
 
 #include "jatam_assembly.hpp"
 #include "jatam_internal.hpp"
+#include "jatam_waves.hpp"
 
 namespace jatam {
 
@@ -106,69 +108,262 @@ __device__ __forceinline__ uint64_t truth_genome(const TruthArgs& a, uint64_t i)
     return a.genomes != nullptr ? a.genomes[i] : a.first + i;
 }
 
-__device__ __forceinline__ bool genome_ok(const TruthArgs& a, uint64_t g)
-{
-    return a.genome_bits == 64 || (g >> a.genome_bits) == 0;
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// Stage 1: one run per genotype; events and proofs decide, the rest queue.
+// Narrow searches: sixteen lanes per queued genotype, everything in LDS.
+//
+// Bound by the chain of LDS reads and writes per level (copying a state's grid,
+// placing a tile, checking its neighbours), whatever the width.  A search has
+// seven states on average over S_{2,8}, at most 19, and never more than sixteen a
+// level, so a wave takes four at once.  The 35,553 searches of a quarter of
+// S_{2,8}: 72 us; one wave a search with its levels in device memory (the wide
+// search, 256 waves) 5.4 ms.
 // ---------------------------------------------------------------------------
-template <int W, int B, class M>
-__global__ __launch_bounds__(B) void truth_first_kernel(TruthArgs a)
+constexpr int kNarrow = 16;          // states per level, and lanes per genotype
+constexpr int kNarrowSlots = 2 * kNarrow;
+
+// Whether two successors of states in the wave's grids are the same set of pairs.
+// The PEND nibble of the successor's new cell, on the frontier of its parent, is
+// the tile placed there, so its parent's nibbles are the successor's too.
+template <int W>
+__device__ __forceinline__ bool same_successor(const uint32_t* states, uint32_t a, uint32_t b)
 {
     using Geo = Geometry<W>;
-    __shared__ uint32_t smem[Geo::kLaneWords * B];
-    const uint64_t i = (uint64_t)blockIdx.x * B + threadIdx.x;
-    bool queue = false;
-    if (i < (uint64_t)a.n) {
-        LaneGrid<W, B> g{smem + threadIdx.x};
-        g.clear_all();
-        RunState st{};
-        const uint64_t genome = truth_genome(a, i);
-        jatam_result_t rec{JATAM_INVALID, 0, 0u, 0};
-        if (genome_ok(a, genome)) {
-            const M m = build_bonds<M>(genome, a.t, a.bits, a.c);
-            const uint64_t rid = genome | ((uint64_t)(uint32_t)a.t << 56);
-            const int ev = run_assembly(
-                m, g, st, a.grid,
-                RunKey{a.key0, a.key1, (uint32_t)rid, (uint32_t)(rid >> 32), 0});
-            if (ev == kEvCorrupt) {
-                rec = jatam_result_t{JATAM_INVALID, 0, 0u, 0};
-            } else if (ev != kEvNone) {
-                rec = jatam_result_t{JATAM_ND_SITE, 0, 0u, 0};
-            } else {
-                uint64_t key = 0;
-                int x0 = 0, y0 = 0;
-                const bool fits = shape_key8(g, st, a.grid, st.size(), key, x0, y0);
-                if (!st.choice || shape_is_guarded(m, g, st, a.grid, fits, key, x0, y0))
-                    rec = jatam_result_t{JATAM_DET, st.size(), shape_hash(g, a.grid), 0};
-                else
-                    queue = true;
+    if ((a >> 14) == (b >> 14))
+        return a == b;
+    const uint32_t* const sa = states + (a >> 14);
+    const uint32_t* const sb = states + (b >> 14);
+    const uint32_t ca = (a >> 4) & 1023u, cb = (b >> 4) & 1023u;
+    for (uint32_t w = 0; w < (uint32_t)Geo::kWords; ++w) {
+        const uint32_t oa = sa[(Geo::kOcc + w) * 64] | ((ca >> 5) == w ? 1u << (ca & 31u) : 0u);
+        const uint32_t ob = sb[(Geo::kOcc + w) * 64] | ((cb >> 5) == w ? 1u << (cb & 31u) : 0u);
+        if (oa != ob)
+            return false;
+        if (oa == 0)
+            continue;
+        uint32_t differ = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            uint32_t cells = (oa >> (8 * k)) & 0xFFu;   // one bit a nibble
+            cells = (cells | (cells << 12)) & 0x000F000Fu;
+            cells = (cells | (cells << 6)) & 0x03030303u;
+            cells = (cells | (cells << 3)) & 0x11111111u;
+            const uint32_t at = (Geo::kPend + 4 * w + k) * 64;
+            differ |= (sa[at] ^ sb[at]) & (cells * 15u);
+        }
+        if (differ != 0)
+            return false;
+    }
+    return true;
+}
+
+template <int W, class M>
+__global__ __launch_bounds__(64) void truth_narrow_kernel(TruthArgs a)
+{
+    using Geo = Geometry<W>;
+    constexpr int kGroups = 64 / kNarrow;
+    constexpr int kCopy = 8;   // words copied at a time: all read, then all written
+    static_assert(Geo::kLaneWords % kCopy == 0, "whole copies");
+    __shared__ uint32_t smem[Geo::kLaneWords * 64];
+    __shared__ unsigned long long tables[kGroups][kNarrowSlots];
+    __shared__ uint32_t lists[kGroups][kNarrow];     // the next level's states
+    __shared__ uint32_t refs[kGroups][Geo::kWords];  // the first terminal shapes
+    __shared__ uint32_t nexts[kGroups];
+    const uint32_t lane = (uint32_t)lane_id(), sub = lane % kNarrow, grp = lane / kNarrow;
+    const uint32_t lead = grp * kNarrow;
+    const uint64_t mates = ((1ull << kNarrow) - 1) << lead;   // the group's lanes
+    unsigned long long* const table = tables[grp];
+    LaneGrid<W, 64> g{smem + lane};
+    g.clear_all();
+    RunState st{};
+    const int G = a.grid;
+    const uint32_t nq = a.counters[0];
+    uint64_t k = (uint64_t)blockIdx.x * kGroups + grp;
+    // uniform over the group
+    bool busy = false, have_ref = false;
+    uint32_t i = 0, width = 0;
+    int64_t total = 0;
+    int ref_size = 0;
+    M m{};
+    // the lane's state: its hash, and the event met in reaching it
+    uint32_t hash = 0;
+    int ev = kEvNone;
+    for (;;) {
+        // -- groups without a genotype take their next one --------------------
+        while (!busy && k < nq) {
+            i = a.queue[k];
+            k += (uint64_t)gridDim.x * kGroups;
+            const uint64_t genome = truth_genome(a, i);
+            m = build_bonds<M>(genome, a.t, a.bits, a.c);
+            busy = true;
+            if constexpr (M::kManyIds) {
+                // the first stage loses the id of the sixteenth oriented tile
+                // and proves nothing then: its proof is made up for here
+                if (a.t == 4) {
+                    bool guarded = false;
+                    if (sub == 0) {
+                        const uint64_t rid = genome | ((uint64_t)(uint32_t)a.t << 56);
+                        run_assembly(m, g, st, G,
+                                     RunKey{a.key0, a.key1, (uint32_t)rid,
+                                            (uint32_t)(rid >> 32), 0});
+                        uint64_t key = 0;
+                        int x0 = 0, y0 = 0;
+                        const bool fits = shape_key8(g, st, G, st.size(), key, x0, y0);
+                        guarded = shape_is_guarded(m, g, st, G, fits, key, x0, y0);
+                        if (guarded)
+                            a.out[i] = jatam_result_t{JATAM_DET, st.size(), shape_hash(g, G), 0};
+                    }
+                    busy = (__ballot(guarded) & mates) == 0;
+                }
+            }
+            if (busy) {
+                // level 0: the seed alone (tile id 0: tile 0 unrotated)
+                if (sub == 0) {
+                    ev = run_start(m, g, st, G);
+                    hash = pair_mix((uint32_t)((G / 2 - 1) * W + (G / 2 - 1)), 0u);
+                }
+                width = 1;
+                total = 1;
+                have_ref = false;
             }
         }
-        if (!queue)
-            a.out[i] = rec;
-    }
-    const uint64_t qm = __ballot(queue);
-    if (qm != 0) {
-        const int lane = (int)__lane_id();
-        uint32_t base = 0;
-        if (lane == __builtin_ctzll(qm))
-            base = atomicAdd(a.counters + 0, (uint32_t)__popcll(qm));
-        base = (uint32_t)__shfl((int)base, __builtin_ctzll(qm));
-        if (queue)
-            a.queue[base + (uint32_t)__popcll(qm & ((1ull << lane) - 1))] = (uint32_t)i;
+        if (__ballot(busy) == 0)
+            break;
+        // -- the level's events and terminal shapes, and its successors --------
+        const bool mine = busy && sub < width;
+        const bool event = (__ballot(mine && ev != kEvNone) & mates) != 0;
+        const bool terminal = mine && !event && st.nf == 0;
+        for (uint32_t j = sub; j < (uint32_t)kNarrowSlots; j += kNarrow)
+            table[j] = 0ull;
+        if (sub == 0)
+            nexts[grp] = 0;
+        wave_lds_sync();
+        bool wide = false;
+        if (mine && !event && !terminal) {
+            for (uint32_t fs = st.touched<W>(); fs != 0; fs &= fs - 1) {
+                const int w = __builtin_ctz(fs);
+                for (uint32_t cells = g.fr(w); cells != 0; cells &= cells - 1) {
+                    const uint32_t q = (uint32_t)((w << 5) | __builtin_ctz(cells));
+                    const uint32_t tile = g.tile_id((int)q);
+                    const uint32_t succ = succ_pack(sub, q, tile);
+                    const uint32_t h = hash ^ pair_mix(q, tile);
+                    const unsigned long long key = ((unsigned long long)(h | 1u) << 32) | succ;
+                    uint32_t slot = h % kNarrowSlots;
+                    uint32_t probe = 0;
+                    for (; probe < (uint32_t)kNarrowSlots; ++probe) {
+                        const unsigned long long old = atomicCAS(&table[slot], 0ull, key);
+                        if (old == 0ull) {
+                            const uint32_t pos = atomicAdd(&nexts[grp], 1u);
+                            if (pos < (uint32_t)kNarrow && pos < a.max_level)
+                                lists[grp][pos] = succ;
+                            else
+                                wide = true;
+                            break;
+                        }
+                        if ((old >> 32) == (key >> 32) &&
+                            same_successor<W>(smem + lead, (uint32_t)old, succ))
+                            break;   // already inserted by another path
+                        slot = (slot + 1u) % kNarrowSlots;
+                    }
+                    wide = wide || probe == (uint32_t)kNarrowSlots;   // table full
+                }
+            }
+        }
+        wave_lds_sync();
+        const uint32_t found = nexts[grp];
+        const bool too_wide = (__ballot(wide) & mates) != 0;
+        const uint64_t tm = __ballot(terminal) & mates;
+        const uint32_t first = tm != 0 ? (uint32_t)__builtin_ctzll(tm) : lane;
+        const int first_size = __shfl(st.size(), (int)first);
+        if (tm != 0 && !have_ref) {
+            if (lane == first)
+                for (int w = 0; w < Geo::kWords; ++w)
+                    refs[grp][w] = g.occ(w);
+            have_ref = true;
+            ref_size = first_size;
+        }
+        wave_lds_sync();
+        bool other = false;
+        if (terminal)
+            for (int w = 0; w < Geo::kWords; ++w)
+                other = other || g.occ(w) != refs[grp][w];
+        const bool second = (__ballot(other) & mates) != 0;
+        // -- the end of the search ---------------------------------------------
+        bool stop = true, report = true;
+        int verdict = -2;   // undecided
+        if (event)
+            verdict = JATAM_ND_SITE;
+        else if (too_wide)
+            report = false;
+        else if (second)
+            verdict = JATAM_ND_SITE;
+        else if (total + (int64_t)found > a.cap)
+            verdict = -2;
+        else if (found == 0)
+            verdict = have_ref ? JATAM_DET : -2;
+        else
+            stop = false;
+        if (busy && stop && sub == 0) {
+            if (report) {
+                jatam_result_t rec{verdict, 0, 0u,
+                                   (int32_t)(total < 0x7FFFFFFF ? total : 0x7FFFFFFF)};
+                if (verdict == JATAM_DET) {
+                    // without successors every state of the level is terminal
+                    rec.size = ref_size;
+                    rec.hash = shape_hash(g, G);
+                }
+                a.out[i] = rec;
+            } else {
+                a.wide[atomicAdd(a.counters + 1, 1u)] = i;
+            }
+        }
+        busy = busy && !stop;
+        // -- the next level's states, each in the grid of its lane ----------------
+        const bool child = busy && sub < found;
+        const uint32_t succ = child ? lists[grp][sub] : sub << 14;
+        const uint32_t from = lead + (succ >> 14);
+        const uint32_t* const src = smem + from;
+        wave_lds_sync();
+#pragma unroll 1
+        for (int w = 0; w < Geo::kLaneWords; w += kCopy) {
+            uint32_t v[kCopy];
+#pragma unroll
+            for (int j = 0; j < kCopy; ++j)
+                v[j] = src[(w + j) * 64];
+            wave_lds_sync();
+            if (child)
+#pragma unroll
+                for (int j = 0; j < kCopy; ++j)
+                    g.word(w + j) = v[j];
+            wave_lds_sync();
+        }
+        const uint32_t nf = (uint32_t)__shfl((int)st.nf, (int)from);
+        const uint32_t osum = (uint32_t)__shfl((int)st.osum, (int)from);
+        const int steps = __shfl(st.steps, (int)from);
+        const uint32_t parent_hash = (uint32_t)__shfl((int)hash, (int)from);
+        if (child) {
+            const uint32_t q = (succ >> 4) & 1023u, tile = succ & 15u;
+            st.nf = nf - 1u;
+            st.osum = osum | (1u << (q >> 5));
+            st.steps = steps + 1;
+            hash = parent_hash ^ pair_mix(q, tile);
+            g.occ((int)(q >> 5)) |= 1u << (q & 31u);
+            g.fr((int)(q >> 5)) &= ~(1u << (q & 31u));
+            ev = update_site(m, g, st, G, (int)q, m.oriented(tile));
+        }
+        if (busy) {
+            width = found;
+            total += found;
+        }
     }
 }
 
 // ---------------------------------------------------------------------------
-// Stage 2: exhaustive exploration, one wave per queued genotype.
+// Wide searches: one wave per genotype, the levels in device memory.
 // ---------------------------------------------------------------------------
 template <int W, class M>
-__global__ __launch_bounds__(64) void truth_explore_kernel(TruthArgs a)
+__global__ __launch_bounds__(64) void truth_wide_kernel(TruthArgs a)
 {
     using Geo = Geometry<W>;
     using L = StateLayout<W>;
@@ -188,11 +383,11 @@ __global__ __launch_bounds__(64) void truth_explore_kernel(TruthArgs a)
     for (;;) {
         uint32_t k = 0;
         if (lane == 0)
-            k = atomicAdd(a.counters + 1, 1u);
+            k = atomicAdd(a.counters + 2, 1u);
         k = (uint32_t)__shfl((int)k, 0);
-        if (k >= a.counters[0])
+        if (k >= a.counters[1])
             break;
-        const uint32_t i = a.queue[k];
+        const uint32_t i = a.wide[k];
         const uint64_t genome = truth_genome(a, i);
         const M m = build_bonds<M>(genome, a.t, a.bits, a.c);
         const int G = a.grid;
@@ -372,42 +567,90 @@ __global__ __launch_bounds__(64) void truth_explore_kernel(TruthArgs a)
     }
 }
 
+// Words of the counters and, after them, one class's claim counters.
+constexpr int kTruthCounters = 64;
+constexpr int kTruthReset = kTruthCounters + kClaimCounters * kClaimStride;
+
 __global__ void truth_reset_kernel(uint32_t* counters)
 {
-    if (threadIdx.x < 2)
-        counters[threadIdx.x] = 0;
+    for (int k = (int)threadIdx.x; k < kTruthReset; k += (int)blockDim.x)
+        counters[k] = 0;
 }
 
 template <int W, class M>
-static void launch_truth_t(const TruthArgs& a, int blocks, hipStream_t s)
+static void launch_truth_t(const TruthArgs& a, int narrow, int wide, hipStream_t s)
 {
-    constexpr int B = W == 16 ? 256 : 64;
-    const uint64_t nb = ((uint64_t)a.n + B - 1) / B;
-    if (nb > 0)
-        hipLaunchKernelGGL((truth_first_kernel<W, B, M>), dim3((unsigned)nb), dim3(B), 0, s, a);
-    hipLaunchKernelGGL((truth_explore_kernel<W, M>), dim3(blocks), dim3(64), 0, s, a);
+    // (a queue that holds every genotype gives each group of lanes one)
+    const uint64_t most = ((uint64_t)a.n * kNarrow + 63) / 64;
+    const uint32_t blocks = most < (uint64_t)narrow ? (uint32_t)most : (uint32_t)narrow;
+    hipLaunchKernelGGL((truth_narrow_kernel<W, M>), dim3(blocks), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((truth_wide_kernel<W, M>), dim3(wide), dim3(64), 0, s, a);
 }
 
-int launch_truth(const TruthArgs& a, int blocks, hipStream_t s)
+template <class M>
+static void truth_waves_t(TruthWaves& w, int geno, int cus)
+{
+    w.narrow[0][geno] = cus * resident_per_cu(truth_narrow_kernel<16, M>);
+    w.narrow[1][geno] = cus * resident_per_cu(truth_narrow_kernel<32, M>);
+}
+
+static bool truth_waves(TruthWaves& w)
+{
+    int dev = -1, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus < 1)
+        return false;
+    solo_occupancy(w.first);
+    for (auto& klass : w.first)
+        for (int& n : klass)
+            n *= cus;
+    truth_waves_t<Bonds2>(w, kGenoTwo, cus);
+    truth_waves_t<Bonds4>(w, kGenoFour, cus);
+    truth_waves_t<BondsC16>(w, kGenoC16, cus);
+    return true;
+}
+
+int launch_truth(const TruthArgs& a, const Params& p, const TruthWaves& waves, hipStream_t s)
 {
     if (a.max_level > kMaxTruthLevel || a.max_level == 0)
         return JATAM_E_INVALID_ARG;
-    hipLaunchKernelGGL(truth_reset_kernel, dim3(1), dim3(64), 0, s, a.counters);
-    const int geno = geno_kind(a.t, a.c);
-    if (a.grid <= 16) {
+    const int geno = geno_kind(a.t, a.c), klass = a.grid <= 16 ? 0 : 1;
+    hipLaunchKernelGGL(truth_reset_kernel, dim3(1), dim3(256), 0, s, a.counters);
+    // the first stage's chunks are claimed as in the classification's first runs
+    // (a quarter of S_{2,8} 0.37 ms, all of them dealt out 0.50)
+    DeviceWorkspace ws{};
+    uint32_t* const claims = a.counters + kTruthCounters;
+    ws.run_claim = claims - klass * kClaimCounters * kClaimStride;
+    const jatam_tuning_t tuning = default_tuning(klass);
+    constexpr int64_t kPiece = (int64_t)1 << 31;
+    for (int64_t at = 0; at < a.n; at += kPiece) {
+        BatchArgs b =
+            batch_args_for(p, a.n - at < kPiece ? a.n - at : kPiece, a.out + at, nullptr, ws);
+        b.dyn16 = tuning.claim_share;
+        b.claim_chunks = tuning.claim_chunks;
+        if (at > 0)
+            launch_clear(claims, nullptr, s);
+        b.genomes = a.genomes != nullptr ? a.genomes + at : nullptr;
+        b.first = a.first + (uint64_t)at;
+        launch_first_open(b, waves.first[klass][geno], geno,
+                          OpenList{a.queue, a.counters, (uint32_t)at}, s);
+    }
+    const int narrow = waves.narrow[klass][geno];
+    if (klass == 0) {
         if (geno == kGenoTwo)
-            launch_truth_t<16, Bonds2>(a, blocks, s);
+            launch_truth_t<16, Bonds2>(a, narrow, waves.wide, s);
         else if (geno == kGenoFour)
-            launch_truth_t<16, Bonds4>(a, blocks, s);
+            launch_truth_t<16, Bonds4>(a, narrow, waves.wide, s);
         else
-            launch_truth_t<16, BondsC16>(a, blocks, s);
+            launch_truth_t<16, BondsC16>(a, narrow, waves.wide, s);
     } else {
         if (geno == kGenoTwo)
-            launch_truth_t<32, Bonds2>(a, blocks, s);
+            launch_truth_t<32, Bonds2>(a, narrow, waves.wide, s);
         else if (geno == kGenoFour)
-            launch_truth_t<32, Bonds4>(a, blocks, s);
+            launch_truth_t<32, Bonds4>(a, narrow, waves.wide, s);
         else
-            launch_truth_t<32, BondsC16>(a, blocks, s);
+            launch_truth_t<32, BondsC16>(a, narrow, waves.wide, s);
     }
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }
@@ -420,8 +663,7 @@ int launch_truth(const TruthArgs& a, int blocks, hipStream_t s)
 struct jatam_truth {
     int64_t max_n;
     uint32_t max_level;
-    int waves;
-    int table_log2;
+    jatam::TruthWaves waves;
     void* region;
     jatam::TruthArgs a;   // workspace pointers
 };
@@ -452,7 +694,7 @@ int truth_launch(jatam_truth_t* w, const uint64_t* genotypes, uint64_t first, in
     a.key1 = p.key1;
     a.cap = cap;
     a.out = out;
-    return jatam::launch_truth(a, w->waves, (hipStream_t)stream);
+    return jatam::launch_truth(a, p, w->waves, (hipStream_t)stream);
 }
 
 }  // namespace
@@ -472,19 +714,22 @@ int jatam_truth_create(int64_t max_n, int32_t max_level, int32_t waves, jatam_tr
         return JATAM_E_HIP;
     w->max_n = max_n;
     w->max_level = (uint32_t)max_level;
-    w->waves = waves;
+    w->waves.wide = waves;
+    if (!jatam::truth_waves(w->waves)) {
+        delete w;
+        return JATAM_E_HIP;
+    }
     int tl = 1;
     while ((int64_t(1) << tl) < 2 * (int64_t)max_level)
         ++tl;
-    w->table_log2 = tl;
     // both grid classes fit the 32 x 32 state size
     const size_t sw = (size_t)jatam::truth_state_words(32);
-    const size_t counters = 256;
+    const size_t counters = ((size_t)jatam::kTruthReset * 4 + 255) / 256 * 256;
     const size_t queue = ((size_t)max_n * 4 + 255) / 256 * 256;
     const size_t arena = (size_t)waves * 2 * max_level * sw * 4;
     const size_t lists = ((size_t)waves * max_level * 4 + 255) / 256 * 256;
     const size_t tables = (size_t)waves * (size_t(1) << tl) * 8;
-    const size_t total = counters + queue + 2 * lists + arena + tables;
+    const size_t total = counters + 2 * queue + 2 * lists + arena + tables;
     uint8_t* base = nullptr;
     if (hipMalloc((void**)&base, total) != hipSuccess) {
         delete w;
@@ -505,6 +750,8 @@ int jatam_truth_create(int64_t max_n, int32_t max_level, int32_t waves, jatam_tr
     a.tables = (unsigned long long*)(base + off);
     off += tables;
     a.queue = (uint32_t*)(base + off);
+    off += queue;
+    a.wide = (uint32_t*)(base + off);
     off += queue;
     a.lists = (uint32_t*)(base + off);
     off += lists;
