@@ -240,7 +240,7 @@ def surrogate_path(args, jt, torch, batch, out, stream, timed, verify):
             "score_roofline": {"bound": "mfma", "achieved": flops / score_s / 1e12,
                                "peak": BF16_PEAK / 1e12, "unit": "TFLOP/s",
                                "frac": flops / score_s / BF16_PEAK,
-                               "kernel": "mlp_score_persistent_kernel<2>",
+                               "kernel": "mlp_score_kernel<2, 4>",
                                "flops_per_genome": score_flops(T)},
             "train_s": train_s, "train_steps": steps, "final_batch_loss": float(loss.item()),
             "train_data": "exact classifications at G=16 of 2^20 uniform three-tile "
@@ -747,7 +747,7 @@ def main():
             "value": TOTAL * args.steps / (plain_total_ms / 1e3),
             "ms_per_step": plain_total_ms / args.steps, "bit_exact": plain_ok,
             "mean_launch_ms": plain_mean_launch_s * 1e3,
-            "kernel": "classify_plain_kernel<16,256>, 2^20 genotypes per launch",
+            "kernel": "solo_kernel<16>, 2^20 genotypes per launch",
             "roofline_frac": plain_ops_per_launch / plain_mean_launch_s / VALU_PEAK_OPS}
 
     # launch parameters chosen by the library's autotuner (untimed; it

@@ -1042,6 +1042,7 @@ int jatam_mlp_create(int64_t max_batch, int c, jatam_mlp_t** mlp)
               mlp_alloc(m, (size_t)jatam::kMlpIn * Hd * 2, (void**)&a.w1b) &&
               mlp_alloc(m, Hd * Hd * 2, (void**)&a.w2b) &&
               mlp_alloc(m, Hd * jatam::kMlpOut * 2, (void**)&a.w3b) &&
+              mlp_alloc(m, (size_t)jatam::kMlpIn * Hd * 2, (void**)&a.w1t) &&
               mlp_alloc(m, Hd * Hd * 2, (void**)&a.w2t) &&
               mlp_alloc(m, 16 * Hd * 2, (void**)&a.w3t) &&
               mlp_alloc(m, B * jatam::kMlpIn * 2, (void**)&a.x) &&

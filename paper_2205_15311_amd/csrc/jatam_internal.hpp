@@ -293,6 +293,7 @@ struct MlpArgs {
     uint16_t* w1b;       // bf16 copies of the weights
     uint16_t* w2b;
     uint16_t* w3b;
+    uint16_t* w1t;       // [256][96] bf16 W1 transposed (k contiguous)
     uint16_t* w2t;       // [256][256] bf16 W2 transposed (k contiguous)
     uint16_t* w3t;       // [16][256] bf16 W3 transposed, rows 4..15 zero
     uint16_t* x;         // [batch][96] one-hot inputs (bf16)

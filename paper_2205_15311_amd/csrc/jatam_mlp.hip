@@ -39,14 +39,15 @@ __device__ __forceinline__ uint16_t bf16_bits(float f)
 __device__ __forceinline__ float bf16_float(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // Keeps the bf16 copy of weight i (flat index) equal to its fp32 master.
-// Also keeps the transposed copies the fused scoring kernel reads with k
-// contiguous: w2t[n][k] = W2[k][n] and w3t[k][j] = W3[j][k] (rows 4..15 of
-// w3t stay zero).
+// Also keeps the transposed copies the scoring kernels read with k contiguous:
+// w1t[n][k] = W1[k][n], w2t[n][k] = W2[k][n] and w3t[k][j] = W3[j][k] (rows
+// 4..15 of w3t stay zero).
 __device__ __forceinline__ void refresh_bf16(const MlpArgs& a, int i, float w)
 {
     const uint16_t b = bf16_bits(w);
     if (i < kMlpOffB1) {
         a.w1b[i] = b;
+        a.w1t[(i % kMlpHidden) * kMlpIn + i / kMlpHidden] = b;
     } else if (i >= kMlpOffW2 && i < kMlpOffB2) {
         const int r = i - kMlpOffW2;
         a.w2b[r] = b;
@@ -239,154 +240,29 @@ __global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// Fused scoring: 64 samples per workgroup in one pass.  The layer-1 gather
-// writes h1 (bf16) to LDS; h1 W2 runs on the matrix cores, each wave taking
-// 64 columns of all 64 rows (4 x 4 MFMA tiles, W2 read k-contiguous from its
-// transposed copy); bias, ReLU and bf16 rounding give h2, which overwrites h1
-// in LDS; the head h2 W3 is one more MFMA tile per wave (W3 padded to 16
-// columns); then softmax and the score.  Same rounding points as the
-// separate kernels (h1, h2 in bf16; fp32 sums).
+// Scoring in one pass: a wave takes 16 NB samples through the whole network by
+// itself, W2 (128 KB) and the first 64 rows of W1 staged in LDS once a launch in
+// the order the matrix cores take them.  The one-hot input is a matrix like any
+// other, built in registers.  Every product is computed transposed, features x
+// samples, so a lane's four results are consecutive features of one sample:
+// bias, ReLU and rounding to bf16 by pairs, and two lane swaps make them the next
+// product's B operand.  Activations stay in registers, and the loop has no
+// barrier and writes no LDS.  The head's partial products, one per 32 hidden
+// features, are added in their order.
+//
+// Bound by the matrix cores: scores of all 2^24 two-tile genotypes take 2.2 to
+// 2.4 ms, 1.15 to 1.28 PFLOP/s, what a large library product reaches (1.21).  Eight waves that
+// shared a tile of 64 samples, each with 32 hidden columns and their weights in
+// registers, took 6.26 ms, most of it rounding to bf16 in integer steps, LDS
+// writes of single values and two barriers a tile.  (Same rounding points and k
+// order: the same bits.)
+//
+// NB: more samples a wave mean fewer LDS reads per product, and fewer waves with
+// work.  Two-tile genomes, NB = 1 / 2 / 4: 32,768 of them 12.1 / 12.7 / 17.3 us,
+// 65,536 18.5 / 16.4 / 18.0, 131,072 30.2 / 26.1 / 24.8, 2^24 3.09 / 2.59 / 2.41 ms.
+// So NB rises once every wave of the chip has 16 samples, and again at 32.
 // ---------------------------------------------------------------------------
-constexpr int kScoreRows = 64;
-constexpr int kH1Pitch = kMlpHidden + 8;
-
-__global__ __launch_bounds__(256) void mlp_score_kernel(MlpArgs a, const uint64_t* genomes,
-                                                        const uint8_t* tvec, int t_all,
-                                                        uint32_t n, float* scores)
-{
-    __shared__ __attribute__((aligned(16))) uint16_t hs[kScoreRows][kH1Pitch];
-    __shared__ float head[kScoreRows][kMlpOut];
-    const int tid = (int)threadIdx.x, wave = tid >> 6, l = tid & 63;
-    const uint32_t s0 = blockIdx.x * kScoreRows;
-    const uint32_t cmask = (uint32_t)a.c - 1u;
-    // layer 1: 8 columns of 8 samples per thread
-    {
-        const int c8 = (tid & 31) * 8;
-        float b1v[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            b1v[q] = a.p.b1[c8 + q];
-        for (int i = 0; i < 8; ++i) {
-            const int row = (tid >> 5) + 8 * i;
-            const uint32_t sidx = s0 + (uint32_t)row;
-            uint32_t packed[4] = {0u, 0u, 0u, 0u};
-            if (sidx < n) {
-                const uint64_t g = genomes[sidx];
-                const int t = mlp_tiles(tvec != nullptr ? tvec[sidx] : t_all);
-                float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                for (int e = 0; e < 4 * t; ++e) {
-                    const uint32_t colour =
-                        (uint32_t)(g >> (a.bits * (4 * t - 1 - e))) & cmask;
-                    const uint4 w = *reinterpret_cast<const uint4*>(
-                        a.w1b + (size_t)(e * 8 + colour) * kMlpHidden + c8);
-                    const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                        acc[q] += bf16_float((uint16_t)(ww[q >> 1] >> (16 * (q & 1))));
-                }
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const float v = acc[q] + b1v[q];
-                    packed[q >> 1] |= (uint32_t)bf16_bits(v > 0.f ? v : 0.f) << (16 * (q & 1));
-                }
-            }
-            *reinterpret_cast<uint4*>(&hs[row][c8]) =
-                make_uint4(packed[0], packed[1], packed[2], packed[3]);
-        }
-    }
-    __syncthreads();
-    // h1 W2
-    const int n0 = 64 * wave;
-    floatx4 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < kMlpHidden; k0 += 32) {
-        bf16x8 af[4], bfr[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            af[i] = *reinterpret_cast<const bf16x8*>(&hs[16 * i + (l & 15)][k0 + 8 * (l >> 4)]);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            bfr[j] = *reinterpret_cast<const bf16x8*>(
-                a.w2t + (size_t)(n0 + 16 * j + (l & 15)) * kMlpHidden + k0 + 8 * (l >> 4));
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0,
-                                                                     0, 0);
-    }
-    __syncthreads();   // every wave has read h1
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int col = n0 + 16 * j + (l & 15);
-        const float b2 = a.p.b2[col];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float z = acc[i][j][e] + b2;
-                hs[16 * i + 4 * (l >> 4) + e][col] = bf16_bits(z > 0.f ? z : 0.f);
-            }
-    }
-    __syncthreads();
-    // head: wave w takes rows 16w..16w+15
-    floatx4 o = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < kMlpHidden; k0 += 32) {
-        const bf16x8 af =
-            *reinterpret_cast<const bf16x8*>(&hs[16 * wave + (l & 15)][k0 + 8 * (l >> 4)]);
-        const bf16x8 bfr = *reinterpret_cast<const bf16x8*>(
-            a.w3t + (size_t)(l & 15) * kMlpHidden + k0 + 8 * (l >> 4));
-        o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr, o, 0, 0, 0);
-    }
-    if ((l & 15) < kMlpOut) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            head[16 * wave + 4 * (l >> 4) + e][l & 15] = o[e] + a.p.b3[l & 15];
-    }
-    __syncthreads();
-    if (tid < kScoreRows && s0 + (uint32_t)tid < n) {
-        const float o0 = head[tid][0], o1 = head[tid][1], o2 = head[tid][2], o3 = head[tid][3];
-        // expected size of a deterministic structure: P(DET) e^pred - 1
-        const float mx = fmaxf(o0, fmaxf(o1, o2));
-        const float e0 = expf(o0 - mx), e1 = expf(o1 - mx), e2 = expf(o2 - mx);
-        scores[s0 + tid] = e2 / (e0 + e1 + e2) * expf(o3) - 1.f;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Persistent scoring: eight waves per workgroup, wave w owning hidden columns
-// 32w .. 32w+31 of both layers.  Its slices of W1, W2 and W3 are loaded into
-// registers once per launch as MFMA B operands, so a tile of 64 genomes
-// costs no weight traffic at all:
-//   layer 1   the one-hot input is a matrix like any other: each lane builds
-//             its A operand (8 bf16 of one edge's one-hot row) from the
-//             genome in registers, x W1 in v_mfma_f32_16x16x32_bf16 (2 k
-//             blocks for two-tile genomes, 3 for three), + b1, ReLU, bf16
-//             -> h1 in LDS (the wave's 32 columns)
-//   layer 2   h1 (all 256 columns, from LDS) x the wave's W2 slice, + b2,
-//             ReLU, bf16 -> the wave's h2 columns in LDS
-//   head      the wave's 32 h2 columns x W3 rows 32w.. (one k block): a
-//             partial [64 x 4], summed over the 8 waves in wave order (so
-//             scores do not depend on timing), softmax, score
-// Two workgroup barriers per tile.  Rounding points as everywhere else: h1
-// and h2 in bf16, fp32 sums.
-// ---------------------------------------------------------------------------
-constexpr int kSc2Waves = 8;
-constexpr int kSc2Rows = 64;
-constexpr int kSc2Pitch = kMlpHidden + 8;   // bf16 per LDS row (16-lane reads conflict-free)
-
-// LDS writes of the wave before this point are seen by its reads after it
-// (a wave's LDS operations complete in order; only the compiler is held).
-__device__ __forceinline__ void mlp_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+constexpr int kScoreWaves = 8;
 
 __device__ __forceinline__ bf16x8 load_bf16x8(const uint16_t* p)
 {
@@ -412,137 +288,220 @@ __device__ __forceinline__ bf16x8 onehot_operand(uint64_t g, int t, int bits, ui
     return v;
 }
 
-// kind: JATAM_PREDICT_SCREEN, _COST or _P_UNBOUND (what is written per genome).
-template <int KB1>
-__global__ __launch_bounds__(512) void mlp_score_persistent_kernel(MlpArgs a,
-                                                                   const uint64_t* genomes,
-                                                                   const uint8_t* tvec, int t_all,
-                                                                   uint32_t n, float* scores,
-                                                                   int kind)
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float floatx2;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+
+// Two non-negative floats as bf16, rounded to nearest even.
+__device__ __forceinline__ uint32_t bf16_pair(float lo, float hi)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t h1s[kSc2Rows][kSc2Pitch];
-    __shared__ __attribute__((aligned(16))) uint16_t h2s[kSc2Rows][kSc2Pitch];
-    __shared__ float part[kSc2Waves][kSc2Rows][kMlpOut];
+    const bf16x2 v = __builtin_convertvector((floatx2{lo, hi}), bf16x2);
+    uint32_t u;
+    __builtin_memcpy(&u, &v, sizeof(u));
+    return u;
+}
+
+// With 16 lanes a row and values a, b of four rows each: rows (a0, b0, a2, b2)
+// and (a1, b1, a3, b3); rows (a0, a1, b0, b1) and (a2, a3, b2, b3).
+__device__ __forceinline__ void swap_rows16(uint32_t& a, uint32_t& b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+
+__device__ __forceinline__ void swap_rows32(uint32_t& a, uint32_t& b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+
+// Results of 32 features x 16 samples (two MFMA blocks: a lane of row q holds
+// features 4q + i and 16 + 4q + i of its sample) plus bias, ReLU, as bf16: the B
+// operand of a 32-feature k block (features 8q + i).
+__device__ __forceinline__ bf16x8 relu_operand(const floatx4& z0, const floatx4& z1,
+                                               const float4& b0, const float4& b1)
+{
+    uint32_t p0 = bf16_pair(fmaxf(z0[0] + b0.x, 0.f), fmaxf(z0[1] + b0.y, 0.f));
+    uint32_t p1 = bf16_pair(fmaxf(z0[2] + b0.z, 0.f), fmaxf(z0[3] + b0.w, 0.f));
+    uint32_t r0 = bf16_pair(fmaxf(z1[0] + b1.x, 0.f), fmaxf(z1[1] + b1.y, 0.f));
+    uint32_t r1 = bf16_pair(fmaxf(z1[2] + b1.z, 0.f), fmaxf(z1[3] + b1.w, 0.f));
+    swap_rows32(p0, r0);
+    swap_rows16(p0, r0);
+    swap_rows32(p1, r1);
+    swap_rows16(p1, r1);
+    const uint32_t w[4] = {p0, p1, r0, r1};
+    bf16x8 v;
+    __builtin_memcpy(&v, w, sizeof(v));
+    return v;
+}
+
+__device__ __forceinline__ float score_of(float o0, float o1, float o2, float o3, int kind)
+{
+    const float mx = fmaxf(o0, fmaxf(o1, o2));
+    const float e0 = expf(o0 - mx), e1 = expf(o1 - mx), e2 = expf(o2 - mx);
+    const float inv = 1.f / (e0 + e1 + e2);
+    return kind == JATAM_PREDICT_COST        ? expf(o3) - 1.f
+           : kind == JATAM_PREDICT_P_UNBOUND ? e0 * inv
+                                             : e2 * inv * expf(o3) - 1.f;
+}
+
+// kind: JATAM_PREDICT_SCREEN, _COST or _P_UNBOUND (what is written per genome);
+// KB1: k blocks of 32 inputs that can be nonzero.
+template <int KB1, int NB>
+__global__ __launch_bounds__(512) void mlp_score_kernel(MlpArgs a, const uint64_t* genomes,
+                                                               const uint8_t* tvec, int t_all,
+                                                               uint32_t n, float* scores, int kind)
+{
+    constexpr int kW1 = KB1 < 2 ? KB1 : 2;   // k blocks of W1 in LDS (a third does not fit)
+    constexpr int kHalf = NB < 2 ? NB : 2;   // sample blocks of a pass of layer 1
+    constexpr uint32_t kRows = 16 * NB;
+    // [32 features][k block][half of the features][lane]
+    __shared__ bf16x8 w2s[8 * 8 * 2 * 64];
+    __shared__ bf16x8 w1s[8 * kW1 * 2 * 64];
     const int tid = (int)threadIdx.x, wave = tid >> 6, l = tid & 63;
     const int r16 = l & 15, q = l >> 4;
-    const int col0 = 32 * wave;
     const uint32_t cmask = (uint32_t)a.c - 1u;
-    // the wave's weights, as B operands: lane holds B[8q + i][r16] of each block
-    bf16x8 w1f[KB1][2], w2f[8][2], w3f;
-#pragma unroll
-    for (int kb = 0; kb < KB1; ++kb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-            uint16_t v[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                v[i] = a.w1b[(size_t)(32 * kb + 8 * q + i) * kMlpHidden + col0 + 16 * nb + r16];
-            __builtin_memcpy(&w1f[kb][nb], v, sizeof(v));
+    for (int f = wave; f < 8 * 8 * 2; f += kScoreWaves)
+        w2s[f * 64 + l] =
+            load_bf16x8(a.w2t + (size_t)(32 * (f >> 4) + 16 * (f & 1) + r16) * kMlpHidden +
+                        32 * ((f >> 1) & 7) + 8 * q);
+    for (int f = wave; f < 8 * kW1 * 2; f += kScoreWaves)
+        w1s[f * 64 + l] =
+            load_bf16x8(a.w1t + (size_t)(32 * (f / (2 * kW1)) + 16 * (f & 1) + r16) * kMlpIn +
+                        32 * ((f >> 1) % kW1) + 8 * q);
+    __syncthreads();
+    const float b3v[4] = {a.p.b3[0], a.p.b3[1], a.p.b3[2], a.p.b3[3]};
+    const uint32_t tiles = (n + kRows - 1) / kRows;
+    const uint32_t stride = kScoreWaves * gridDim.x;
+    uint32_t tile = (uint32_t)wave * gridDim.x + blockIdx.x;
+    // the genome and tile count of sample l of a tile, loaded a tile ahead
+    uint64_t next_g = 0;
+    int next_t = 0;
+    auto fetch = [&](uint32_t of) {
+        const uint32_t sidx = of * kRows + (uint32_t)l % kRows;
+        next_g = 0;
+        next_t = 0;
+        if (of < tiles && sidx < n) {
+            next_g = genomes[sidx];
+            next_t = mlp_tiles(tvec != nullptr ? tvec[sidx] : t_all);
         }
+    };
+    fetch(tile);
+    for (; tile < tiles; tile += stride) {
+        const uint64_t own_g = next_g;
+        const int own_t = next_t;
+        fetch(tile + stride < tile ? tiles : tile + stride);
+        // -- layer 1, kHalf sample blocks at a time ---------------------------------
+        bf16x8 h1[NB][8];
 #pragma unroll
-    for (int kb = 0; kb < 8; ++kb)
+        for (int n0 = 0; n0 < NB; n0 += kHalf) {
+            // the one-hot input, as B operands: row q holds edge 4 kb + q
+            bf16x8 x[kHalf][KB1];
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-            w2f[kb][nb] = load_bf16x8(a.w2t + (size_t)(col0 + 16 * nb + r16) * kMlpHidden +
-                                      32 * kb + 8 * q);
-    w3f = load_bf16x8(a.w3t + (size_t)r16 * kMlpHidden + col0 + 8 * q);
-    const float b1v[2] = {a.p.b1[col0 + r16], a.p.b1[col0 + 16 + r16]};
-    const float b2v[2] = {a.p.b2[col0 + r16], a.p.b2[col0 + 16 + r16]};
-    const float b3v = tid < kSc2Rows * kMlpOut ? a.p.b3[tid & 3] : 0.f;
-
-    const uint32_t tiles = (n + kSc2Rows - 1) / kSc2Rows;
-    for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-        const uint32_t s0 = tile * kSc2Rows;
-        // -- layer 1: one-hot x W1 ----------------------------------------
-        floatx4 acc[4][2];
+            for (int nb = 0; nb < kHalf; ++nb) {
+                const int from = 16 * (n0 + nb) + r16;
+                const uint64_t g = ((uint64_t)(uint32_t)__shfl((int)(own_g >> 32), from) << 32) |
+                                   (uint32_t)__shfl((int)(uint32_t)own_g, from);
+                const int t = __shfl(own_t, from);
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-            const uint32_t sidx = s0 + (uint32_t)(16 * mb + r16);
-            uint64_t g = 0;
-            int t = 0;
-            if (sidx < n) {
-                g = genomes[sidx];
-                t = mlp_tiles(tvec != nullptr ? tvec[sidx] : t_all);
+                for (int kb = 0; kb < KB1; ++kb)
+                    x[nb][kb] = onehot_operand(g, t, a.bits, cmask, 4 * kb + q);
             }
-            acc[mb][0] = floatx4{0.f, 0.f, 0.f, 0.f};
-            acc[mb][1] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kb = 0; kb < KB1; ++kb) {
-                const bf16x8 x = onehot_operand(g, t, a.bits, cmask, 4 * kb + q);
-                acc[mb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, w1f[kb][0], acc[mb][0],
-                                                                     0, 0, 0);
-                acc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, w1f[kb][1], acc[mb][1],
-                                                                     0, 0, 0);
-            }
-        }
+            for (int fb = 0; fb < 8; ++fb) {
+                floatx4 acc[2][kHalf];
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+                for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
+                    for (int nb = 0; nb < kHalf; ++nb)
+                        acc[m][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+                const float4 b0 = *reinterpret_cast<const float4*>(a.p.b1 + 32 * fb + 4 * q);
+                const float4 b1 = *reinterpret_cast<const float4*>(a.p.b1 + 32 * fb + 16 + 4 * q);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float z = acc[mb][nb][i] + b1v[nb];
-                    h1s[16 * mb + 4 * q + i][col0 + 16 * nb + r16] = bf16_bits(z > 0.f ? z : 0.f);
-                }
-        __syncthreads();   // h1 complete; the previous tile's partial heads consumed
-        // -- layer 2: h1 x W2 (the wave's columns) ------------------------
+                for (int kb = 0; kb < KB1; ++kb)
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-            acc[mb][0] = floatx4{0.f, 0.f, 0.f, 0.f};
-            acc[mb][1] = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
+                    for (int m = 0; m < 2; ++m) {
+                        const bf16x8 w =
+                            kb < kW1 ? w1s[((fb * kW1 + kb) * 2 + m) * 64 + l]
+                                     : load_bf16x8(a.w1t +
+                                                   (size_t)(32 * fb + 16 * m + r16) * kMlpIn +
+                                                   32 * kb + 8 * q);
 #pragma unroll
-        for (int kb = 0; kb < 8; ++kb) {
+                        for (int nb = 0; nb < kHalf; ++nb)
+                            acc[m][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                w, x[nb][kb], acc[m][nb], 0, 0, 0);
+                    }
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
-                const bf16x8 af = load_bf16x8(&h1s[16 * mb + r16][32 * kb + 8 * q]);
-                acc[mb][0] =
-                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2f[kb][0], acc[mb][0], 0, 0, 0);
-                acc[mb][1] =
-                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2f[kb][1], acc[mb][1], 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float z = acc[mb][nb][i] + b2v[nb];
-                    h2s[16 * mb + 4 * q + i][col0 + 16 * nb + r16] = bf16_bits(z > 0.f ? z : 0.f);
-                }
-        mlp_wave_sync();   // the wave reads back only its own h2 columns
-        // -- head: the wave's partial h2 W3 -------------------------------
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-            const bf16x8 af = load_bf16x8(&h2s[16 * mb + r16][col0 + 8 * q]);
-            const floatx4 o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                af, w3f, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-            if (r16 < kMlpOut)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    part[wave][16 * mb + 4 * q + i][r16] = o[i];
-        }
-        __syncthreads();   // partial heads complete; h1 free for the next tile
-        if (tid < kSc2Rows * kMlpOut) {
-            const int row = tid >> 2, o = tid & 3;
-            float v = 0.f;
-#pragma unroll
-            for (int w = 0; w < kSc2Waves; ++w)
-                v += part[w][row][o];
-            v += b3v;
-            // gather the row's four outputs in its lane quad
-            const float o0 = __shfl(v, (l & ~3) + 0), o1 = __shfl(v, (l & ~3) + 1);
-            const float o2 = __shfl(v, (l & ~3) + 2), o3 = __shfl(v, (l & ~3) + 3);
-            if (o == 0 && s0 + (uint32_t)row < n) {
-                const float mx = fmaxf(o0, fmaxf(o1, o2));
-                const float e0 = expf(o0 - mx), e1 = expf(o1 - mx), e2 = expf(o2 - mx);
-                const float inv = 1.f / (e0 + e1 + e2);
-                scores[s0 + row] = kind == JATAM_PREDICT_COST        ? expf(o3) - 1.f
-                                   : kind == JATAM_PREDICT_P_UNBOUND ? e0 * inv
-                                                                     : e2 * inv * expf(o3) - 1.f;
+                for (int nb = 0; nb < kHalf; ++nb)
+                    h1[n0 + nb][fb] = relu_operand(acc[0][nb], acc[1][nb], b0, b1);
+                if (fb & 1)
+                    __builtin_amdgcn_sched_barrier(0);
             }
         }
+        // -- layer 2 and the head, 32 hidden features at a time ---------------------
+        floatx4 out[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            out[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        const bf16x8* w = w2s + l;
+        bf16x8 w0 = w[0], w1 = w[64];
+#pragma unroll 1
+        for (int fb = 0; fb < 8; ++fb) {
+            floatx4 acc[2][NB];
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[m][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            const float4 b0 = *reinterpret_cast<const float4*>(a.p.b2 + 32 * fb + 4 * q);
+            const float4 b1 = *reinterpret_cast<const float4*>(a.p.b2 + 32 * fb + 16 + 4 * q);
+            const bf16x8 w3 = load_bf16x8(a.w3t + (size_t)r16 * kMlpHidden + 32 * fb + 8 * q);
+#pragma unroll
+            for (int kb = 0; kb < 8; ++kb) {
+                // the next k block's operands on their way (the last one's: the next
+                // features', or past the end the first ones again)
+                w = kb == 7 && fb == 7 ? w2s + l : w + 128;
+                const bf16x8 v0 = w[0], v1 = w[64];
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[0][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0, h1[nb][kb],
+                                                                         acc[0][nb], 0, 0, 0);
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[1][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, h1[nb][kb],
+                                                                         acc[1][nb], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                w0 = v0;
+                w1 = v1;
+            }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const bf16x8 h2 = relu_operand(acc[0][nb], acc[1][nb], b0, b1);
+                // a partial per 32 features, added in their order
+                out[nb] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    w3, h2, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            }
+        }
+        // -- the four outputs of sample r16 of block nb are row 0's: to row nb -----
+        float o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t v[4];
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+                v[nb] = __float_as_uint(out[nb < NB ? nb : 0][i]);
+            if constexpr (NB > 1)
+                swap_rows16(v[0], v[1]);
+            if constexpr (NB > 2) {
+                swap_rows16(v[2], v[3]);
+                swap_rows32(v[0], v[2]);
+            }
+            o[i] = __uint_as_float(v[0]) + b3v[i];
+        }
+        const uint32_t sidx = tile * kRows + (uint32_t)l;
+        if (l < (int)kRows && sidx < n)
+            scores[sidx] = score_of(o[0], o[1], o[2], o[3], kind);
     }
 }
 
@@ -819,27 +778,26 @@ int mlp_launch_score(const MlpArgs& a, const uint64_t* genomes, const uint8_t* t
         return JATAM_OK;
     // k blocks of the one-hot input that can be nonzero: 4 edges per block
     const int kb1 = tvec != nullptr ? 3 : t_all;
-    int dev = 0, cus = 0, per_cu = 0;
+    int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return JATAM_E_HIP;
-    const void* fn = kb1 == 1   ? (const void*)mlp_score_persistent_kernel<1>
-                     : kb1 == 2 ? (const void*)mlp_score_persistent_kernel<2>
-                                : (const void*)mlp_score_persistent_kernel<3>;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 512, 0) != hipSuccess)
-        return JATAM_E_HIP;
-    per_cu = per_cu < 1 ? 1 : per_cu;
-    const uint32_t tiles = (n + kSc2Rows - 1) / kSc2Rows;
-    const uint32_t blocks = tiles < (uint32_t)(cus * per_cu) ? tiles : (uint32_t)(cus * per_cu);
+    // one workgroup fills a CU's LDS (NB: see the kernel)
+    const uint64_t waves = (uint64_t)cus * kScoreWaves;
+    const int nb = n <= 16 * waves ? 1 : n <= 32 * waves ? 2 : 4;
+    const uint32_t tiles = (n + 16u * nb - 1) / (16u * nb);
+    const uint32_t blocks = tiles < (uint32_t)cus ? tiles : (uint32_t)cus;
+    auto launch = [&](auto one, auto two, auto four) {
+        hipLaunchKernelGGL(nb == 1 ? one : nb == 2 ? two : four, dim3(blocks),
+                           dim3(64 * kScoreWaves), 0, s, a, genomes, tvec, t_all, n, scores,
+                           kind);
+    };
     if (kb1 == 1)
-        hipLaunchKernelGGL(mlp_score_persistent_kernel<1>, dim3(blocks), dim3(512), 0, s, a,
-                           genomes, tvec, t_all, n, scores, kind);
+        launch(mlp_score_kernel<1, 1>, mlp_score_kernel<1, 2>, mlp_score_kernel<1, 4>);
     else if (kb1 == 2)
-        hipLaunchKernelGGL(mlp_score_persistent_kernel<2>, dim3(blocks), dim3(512), 0, s, a,
-                           genomes, tvec, t_all, n, scores, kind);
+        launch(mlp_score_kernel<2, 1>, mlp_score_kernel<2, 2>, mlp_score_kernel<2, 4>);
     else
-        hipLaunchKernelGGL(mlp_score_persistent_kernel<3>, dim3(blocks), dim3(512), 0, s, a,
-                           genomes, tvec, t_all, n, scores, kind);
+        launch(mlp_score_kernel<3, 1>, mlp_score_kernel<3, 2>, mlp_score_kernel<3, 4>);
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }
 
