@@ -1127,8 +1127,7 @@ int jatam_mlp_forward(jatam_mlp_t* mlp, const uint64_t* genomes, const uint8_t* 
     for (int64_t at = 0; at < n; at += mlp->max_batch) {
         const int64_t k = n - at < mlp->max_batch ? n - at : mlp->max_batch;
         const int rc = jatam::mlp_launch_forward(mlp->a, genomes + at, t ? t + at : nullptr, t_all,
-                                                 (uint32_t)k, pad32(k), nullptr,
-                                                 out4 + at * jatam::kMlpOut, s);
+                                                 (uint32_t)k, out4 + at * jatam::kMlpOut, s);
         if (rc != JATAM_OK)
             return rc;
     }
@@ -1143,14 +1142,9 @@ int jatam_mlp_train_step(jatam_mlp_t* mlp, const uint64_t* genomes, const uint8_
         labels == nullptr || !(lr >= 0.f) ||
         (t == nullptr && (t_all < 1 || t_all > 3)))
         return JATAM_E_INVALID_ARG;
-    const hipStream_t s = (hipStream_t)stream;
-    int rc = jatam::mlp_launch_forward(mlp->a, genomes, t, t_all, (uint32_t)n, pad32(n), labels,
-                                       nullptr, s);
-    if (rc == JATAM_OK)
-        rc = jatam::mlp_launch_backward(mlp->a, (uint32_t)n, pad32(n), loss_out, s);
-    if (rc == JATAM_OK && lr > 0.f)
-        rc = jatam::mlp_launch_adam(mlp->a, lr, ++mlp->step, s);
-    return rc;
+    const int step = lr > 0.f ? ++mlp->step : mlp->step;
+    return jatam::mlp_launch_train(mlp->a, genomes, t, t_all, labels, (uint32_t)n, pad32(n), lr,
+                                   step, loss_out, (hipStream_t)stream);
 }
 
 int jatam_mlp_predict(jatam_mlp_t* mlp, int kind, const uint64_t* genomes, const uint8_t* t,

@@ -290,17 +290,17 @@ struct MlpArgs {
     MlpTensors g;        // gradients of the last training step
     float* m;            // Adam first moments
     float* v;            // Adam second moments
-    uint16_t* w1b;       // bf16 copies of the weights
-    uint16_t* w2b;
-    uint16_t* w3b;
-    uint16_t* w1t;       // [256][96] bf16 W1 transposed (k contiguous)
-    uint16_t* w2t;       // [256][256] bf16 W2 transposed (k contiguous)
-    uint16_t* w3t;       // [16][256] bf16 W3 transposed, rows 4..15 zero
-    uint16_t* x;         // [batch][96] one-hot inputs (bf16)
-    uint16_t* h1;        // [batch][256] bf16
-    uint16_t* h2;        // [batch][256] bf16
-    uint16_t* dh2;       // [batch][256] bf16
-    uint16_t* dh1;       // [batch][256] bf16
+    uint16_t* w1b;       // bf16 copies of the weights (refresh_bf16 in jatam_mlp.hip):
+    uint16_t* w1t;       // W1 as rows and as an operand,
+    uint16_t* w2b;       // W2 as operands of both directions,
+    uint16_t* w2t;
+    uint16_t* w3b;       // W3 as it is
+    uint16_t* w3t;       // and [16][256] transposed, rows 4..15 zero
+    uint16_t* x;         // one-hot inputs, 96 a sample: these five bf16, in the order
+    uint16_t* h1;        // of matrix operands (operand_at in jatam_mlp.hip);
+    uint16_t* h2;        // 256 a sample
+    uint16_t* dh2;
+    uint16_t* dh1;
     float* dout;         // [batch][4]
     float* loss;         // [batch] per-sample loss
     float* partial;      // partial sums of the backward reductions
@@ -314,11 +314,10 @@ int mlp_launch_score(const MlpArgs& a, const uint64_t* genomes, const uint8_t* t
                      uint32_t n, float* scores, int kind, hipStream_t s);
 int mlp_launch_refresh(const MlpArgs& a, hipStream_t s);
 int mlp_launch_forward(const MlpArgs& a, const uint64_t* genomes, const uint8_t* tvec, int t_all,
-                       uint32_t n, uint32_t n_pad, const jatam_result_t* labels, float* out4,
-                       hipStream_t s);
-int mlp_launch_backward(const MlpArgs& a, uint32_t n, uint32_t n_pad, float* loss_out,
-                        hipStream_t s);
-int mlp_launch_adam(const MlpArgs& a, float lr, int step, hipStream_t s);
+                       uint32_t n, float* out4, hipStream_t s);
+int mlp_launch_train(const MlpArgs& a, const uint64_t* genomes, const uint8_t* tvec, int t_all,
+                     const jatam_result_t* labels, uint32_t n, uint32_t n_pad, float lr, int step,
+                     float* loss_out, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Top-k selection (jatam_select.hip).

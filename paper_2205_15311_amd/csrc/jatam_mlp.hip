@@ -12,13 +12,18 @@
 // bf16; h1, h2 and the hidden gradients are stored as bf16; every product
 // accumulates in fp32.
 //
-//   layer 1      a gather: the sum of 4t rows of W1 (a one-hot input times a
-//                matrix is no work for a matrix core)
+//   layer 1      in training a gather, the sum of 4t rows of W1; in scoring a
+//                product with the one-hot input like the others
 //   h1 W2, dh2 W2^T, h1^T dh2, x^T dh1
-//                bf16 MFMA GEMMs (v_mfma_f32_16x16x32_bf16), one wave per
-//                16 x 16 output tile, fused bias/ReLU/mask epilogues
+//                bf16 matrix products (v_mfma_f32_16x16x32_bf16) with bias, ReLU
+//                and masks applied to the results in registers
 //   head, loss   per-sample dot products of length 256 and a softmax
 //   Adam         elementwise over the 91,652 fp32 parameters
+//
+// Operand layout of the 16x16x32 MFMA (one wave): lane l holds
+//   A[l % 16][8 * (l / 16) + i], i < 8      (16 x 32, M x K)
+//   B[8 * (l / 16) + i][l % 16], i < 8      (32 x 16, K x N)
+// and receives D[4 * (l / 16) + i][l % 16], i < 4.
 #include "jatam_device.hpp"
 #include "jatam_internal.hpp"
 
@@ -38,20 +43,28 @@ __device__ __forceinline__ uint16_t bf16_bits(float f)
 
 __device__ __forceinline__ float bf16_float(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-// Keeps the bf16 copy of weight i (flat index) equal to its fp32 master.
-// Also keeps the transposed copies the scoring kernels read with k contiguous:
-// w1t[n][k] = W1[k][n], w2t[n][k] = W2[k][n] and w3t[k][j] = W3[j][k] (rows
-// 4..15 of w3t stay zero).
+// Element (n, k) of a weight operand of K k's in the order of the matrix cores'
+// loads: blocks of 16 n x 32 k (1 KB), lane n % 16 + 16 (k % 32 / 8) of a block
+// with 8 k's.
+__device__ __forceinline__ int weight_at(int n, int k, int K)
+{
+    return ((n / 16) * (K / 32) + k / 32) * 512 + (k % 32 / 8 * 16 + n % 16) * 8 + k % 8;
+}
+
+// Keeps the bf16 copies of weight i (flat index) equal to its fp32 master: W1
+// as rows (w1b), W1, W2 and its transpose as operands (w1t, w2t: n the hidden
+// unit, k the input; w2b the other way round), W3 as it is (w3b) and transposed
+// (w3t[k][j] = W3[j][k]; rows 4..15 stay zero).
 __device__ __forceinline__ void refresh_bf16(const MlpArgs& a, int i, float w)
 {
     const uint16_t b = bf16_bits(w);
     if (i < kMlpOffB1) {
         a.w1b[i] = b;
-        a.w1t[(i % kMlpHidden) * kMlpIn + i / kMlpHidden] = b;
+        a.w1t[weight_at(i % kMlpHidden, i / kMlpHidden, kMlpIn)] = b;
     } else if (i >= kMlpOffW2 && i < kMlpOffB2) {
         const int r = i - kMlpOffW2;
-        a.w2b[r] = b;
-        a.w2t[(r % kMlpHidden) * kMlpHidden + r / kMlpHidden] = b;
+        a.w2t[weight_at(r % kMlpHidden, r / kMlpHidden, kMlpHidden)] = b;
+        a.w2b[weight_at(r / kMlpHidden, r % kMlpHidden, kMlpHidden)] = b;
     } else if (i >= kMlpOffW3 && i < kMlpOffB3) {
         const int r = i - kMlpOffW3;
         a.w3b[r] = b;
@@ -62,182 +75,6 @@ __device__ __forceinline__ void refresh_bf16(const MlpArgs& a, int i, float w)
 // Tiles the network reads of a genome of t tiles: the input has 12 edge slots
 // (3 tiles), so a t outside 1..3 is read as no tiles at all (zero input).
 __device__ __forceinline__ int mlp_tiles(int t) { return t >= 1 && t <= 3 ? t : 0; }
-
-// ---------------------------------------------------------------------------
-// Layer 1: h1 = bf16(relu(sum of W1 rows + b1)); also the one-hot x (bf16).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void mlp_layer1_kernel(MlpArgs a, const uint64_t* genomes,
-                                                         const uint8_t* tvec, int t_all,
-                                                         uint32_t n)
-{
-    const uint32_t b = blockIdx.x;          // sample (rows n..gridDim.x-1 are padding)
-    const int j = threadIdx.x;              // hidden unit
-    if (b >= n) {
-        a.h1[(size_t)b * kMlpHidden + j] = 0;
-        if (j < kMlpIn)
-            a.x[(size_t)b * kMlpIn + j] = 0;
-        return;
-    }
-    const uint64_t g = genomes[b];
-    const int t = mlp_tiles(tvec != nullptr ? tvec[b] : t_all);
-    const uint32_t cmask = (uint32_t)a.c - 1u;
-    float acc = 0.f;
-    for (int e = 0; e < kMlpEdges; ++e) {
-        if (e >= 4 * t)
-            break;
-        const uint32_t colour = (uint32_t)(g >> (a.bits * (4 * t - 1 - e))) & cmask;
-        acc += bf16_float(a.w1b[(e * 8 + colour) * kMlpHidden + j]);
-    }
-    acc += a.p.b1[j];
-    a.h1[(size_t)b * kMlpHidden + j] = bf16_bits(acc > 0.f ? acc : 0.f);   // +0, never -0
-    if (j < kMlpIn) {
-        const int e = j >> 3;
-        uint32_t hot = 0;
-        if (e < 4 * t)
-            hot = ((uint32_t)(g >> (a.bits * (4 * t - 1 - e))) & cmask) == (uint32_t)(j & 7);
-        a.x[(size_t)b * kMlpIn + j] = hot ? (uint16_t)0x3F80u : (uint16_t)0;   // 1.0 or 0.0
-    }
-}
-
-// ---------------------------------------------------------------------------
-// GEMM: C[M x N] = sum_k A(m, k) B(k, n), bf16 operands addressed by strides
-// (so transposes cost nothing), fp32 accumulation in v_mfma_f32_16x16x32_bf16.
-// One wave computes one 16 x 16 tile; K is a multiple of 32.
-//
-// Operand layout of the 16x16x32 MFMA (one wave): lane l holds
-//   A[l % 16][8 * (l / 16) + i], i < 8      (16 x 32, M x K)
-//   B[8 * (l / 16) + i][l % 16], i < 8      (32 x 16, K x N)
-// and receives D[4 * (l / 16) + i][l % 16], i < 4.
-// ---------------------------------------------------------------------------
-enum { kEpStoreF32 = 0, kEpBiasRelu = 1, kEpReluMask = 2 };
-
-struct GemmArgs {
-    const uint16_t* A;
-    int64_t sam, sak;        // A(m, k) = A[m * sam + k * sak]
-    const uint16_t* B;
-    int64_t sbk, sbn;        // B(k, n) = B[k * sbk + n * sbn]
-    int M, N, K;
-    int epilogue;
-    float* C32;              // kEpStoreF32: C[m * N + n]
-    uint16_t* C16;           // kEpBiasRelu / kEpReluMask: bf16 C[m * N + n]
-    const float* bias;       // kEpBiasRelu: bias[n]
-    const uint16_t* mask;    // kEpReluMask: keep where mask[m * N + n] > 0
-    int splits;              // K split across this many workgroups (kEpStoreF32 only)
-    float* partial;          // splits > 1: [splits][M][N] fp32 partial sums
-};
-
-__device__ __forceinline__ int lane16() { return (int)(__lane_id() & 15); }
-__device__ __forceinline__ int quad() { return (int)(__lane_id() >> 4); }
-
-// Block tile of the GEMM: 64 x 64 outputs per workgroup of 4 waves, each
-// wave a 32 x 32 quarter (2 x 2 MFMA tiles), K in steps of 32.  Both operand
-// tiles are staged in LDS with k contiguous, so every MFMA fragment is one
-// 16-byte LDS read; the global loads are 16 bytes along whichever of the two
-// dimensions is contiguous in memory (a transposed operand is scattered into
-// LDS).  With splits > 1 the K range is split across workgroups and each
-// writes fp32 partial sums, added in split order by mlp_reduce_kernel.
-constexpr int kBM = 64, kBN = 64, kBK = 32, kLdsPitch = kBK + 8;
-
-// One 64 x 32 operand tile into LDS (rows r0.., k k0..): element (r, k) of
-// the operand is src[r * s_row + k * s_k]; rows >= R are zero.  Needs R a
-// multiple of 8 and, for s_k != 1, s_row == 1.
-__device__ __forceinline__ void load_tile(const uint16_t* __restrict__ src, int64_t s_row,
-                                          int64_t s_k, int r0, int k0, int R,
-                                          uint16_t (*dst)[kLdsPitch])
-{
-    const int tid = (int)threadIdx.x;
-    if (s_k == 1) {
-        const int r = tid >> 2, kc = (tid & 3) * 8;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (r0 + r < R)
-            v = *reinterpret_cast<const uint4*>(src + (int64_t)(r0 + r) * s_row + k0 + kc);
-        *reinterpret_cast<uint4*>(&dst[r][kc]) = v;
-    } else {
-        const int k = tid >> 3, rc = (tid & 7) * 8;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (r0 + rc < R)
-            v = *reinterpret_cast<const uint4*>(src + (int64_t)(k0 + k) * s_k + r0 + rc);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            dst[rc + e][k] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-    }
-}
-
-__global__ __launch_bounds__(256) void mlp_gemm_kernel(GemmArgs g)
-{
-    __shared__ __attribute__((aligned(16))) uint16_t As[kBM][kLdsPitch];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[kBN][kLdsPitch];
-    const int wave = (int)(threadIdx.x >> 6), l = (int)(threadIdx.x & 63);
-    const int tiles_n = (g.N + kBN - 1) / kBN;
-    const int m0 = ((int)blockIdx.x / tiles_n) * kBM, n0 = ((int)blockIdx.x % tiles_n) * kBN;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    const int split = (int)blockIdx.y;
-    const int kper = ((g.K / kBK + g.splits - 1) / g.splits) * kBK;
-    const int kbeg = split * kper, kend = min(g.K, kbeg + kper);
-    floatx4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = kbeg; k0 < kend; k0 += kBK) {
-        load_tile(g.A, g.sam, g.sak, m0, k0, g.M, As);
-        load_tile(g.B, g.sbn, g.sbk, n0, k0, g.N, Bs);
-        __syncthreads();
-        bf16x8 af[2], bf[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            af[i] = *reinterpret_cast<const bf16x8*>(&As[wm + 16 * i + (l & 15)][8 * (l >> 4)]);
-            bf[i] = *reinterpret_cast<const bf16x8*>(&Bs[wn + 16 * i + (l & 15)][8 * (l >> 4)]);
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0,
-                                                                     0);
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int m = m0 + wm + 16 * i + 4 * (l >> 4) + e;
-                const int n = n0 + wn + 16 * j + (l & 15);
-                if (m >= g.M || n >= g.N)
-                    continue;
-                const float v = acc[i][j][e];
-                const int64_t o = (int64_t)m * g.N + n;
-                if (g.splits > 1) {
-                    g.partial[(int64_t)split * g.M * g.N + o] = v;
-                } else if (g.epilogue == kEpStoreF32) {
-                    g.C32[o] = v;
-                } else if (g.epilogue == kEpBiasRelu) {
-                    const float z = v + g.bias[n];
-                    g.C16[o] = bf16_bits(z > 0.f ? z : 0.f);
-                } else {
-                    g.C16[o] = bf16_bits(g.mask[o] != 0 ? v : 0.f);
-                }
-            }
-        }
-    }
-}
-
-// out[i] = sum over s < parts of partial[s * count + i], in that order.
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict__ partial,
-                                                         int parts, int64_t count, float* out)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= count)
-        return;
-    float s = 0.f;
-    for (int p = 0; p < parts; ++p)
-        s += partial[(int64_t)p * count + i];
-    out[i] = s;
-}
 
 // ---------------------------------------------------------------------------
 // Scoring in one pass: a wave takes 16 NB samples through the whole network by
@@ -364,12 +201,10 @@ __global__ __launch_bounds__(512) void mlp_score_kernel(MlpArgs a, const uint64_
     const uint32_t cmask = (uint32_t)a.c - 1u;
     for (int f = wave; f < 8 * 8 * 2; f += kScoreWaves)
         w2s[f * 64 + l] =
-            load_bf16x8(a.w2t + (size_t)(32 * (f >> 4) + 16 * (f & 1) + r16) * kMlpHidden +
-                        32 * ((f >> 1) & 7) + 8 * q);
+            load_bf16x8(a.w2t + ((2 * (f >> 4) + (f & 1)) * 8 + ((f >> 1) & 7)) * 512 + 8 * l);
     for (int f = wave; f < 8 * kW1 * 2; f += kScoreWaves)
-        w1s[f * 64 + l] =
-            load_bf16x8(a.w1t + (size_t)(32 * (f / (2 * kW1)) + 16 * (f & 1) + r16) * kMlpIn +
-                        32 * ((f >> 1) % kW1) + 8 * q);
+        w1s[f * 64 + l] = load_bf16x8(
+            a.w1t + ((2 * (f / (2 * kW1)) + (f & 1)) * 3 + (f >> 1) % kW1) * 512 + 8 * l);
     __syncthreads();
     const float b3v[4] = {a.p.b3[0], a.p.b3[1], a.p.b3[2], a.p.b3[3]};
     const uint32_t tiles = (n + kRows - 1) / kRows;
@@ -424,9 +259,7 @@ __global__ __launch_bounds__(512) void mlp_score_kernel(MlpArgs a, const uint64_
                     for (int m = 0; m < 2; ++m) {
                         const bf16x8 w =
                             kb < kW1 ? w1s[((fb * kW1 + kb) * 2 + m) * 64 + l]
-                                     : load_bf16x8(a.w1t +
-                                                   (size_t)(32 * fb + 16 * m + r16) * kMlpIn +
-                                                   32 * kb + 8 * q);
+                                     : load_bf16x8(a.w1t + ((2 * fb + m) * 3 + kb) * 512 + 8 * l);
 #pragma unroll
                         for (int nb = 0; nb < kHalf; ++nb)
                             acc[m][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
@@ -506,145 +339,427 @@ __global__ __launch_bounds__(512) void mlp_score_kernel(MlpArgs a, const uint64_
 }
 
 // ---------------------------------------------------------------------------
-// Head and loss: out = h2 W3 + b3 per sample; with labels, the per-sample loss
-// and dout = d(mean loss)/d(out).
+// Training and the plain forward pass.  A step of 4,096 samples is 2 GFLOP, a
+// few microseconds of the matrix cores, so what bounds it is latency: launches,
+// and the chains of loads and sums in each.  Twenty kernels, one per layer and
+// gradient, took 239 us; now three, 34 us:
+//   samples     forward, loss and the gradients of the activations, sixteen
+//               samples a workgroup, everything between the layers in LDS (17 us)
+//   gradients   the products over the batch, split across it, and the chunk
+//               sums of the head and the biases, side by side (14 us)
+//   update      the splits and chunks of each parameter added, Adam, and the
+//               bf16 copies (4 us)
+// Every sum keeps a fixed order, so a step has one result.
+//
+// Activations and their gradients go between the kernels in the order of the
+// matrix cores' operands: [32 samples][16 features] blocks of 1 KB, in which
+// lane (feature % 16) + 16 (sample % 32 / 8) holds 8 samples of one feature.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void mlp_head_kernel(MlpArgs a, uint32_t n,
-                                                       const jatam_result_t* labels,
-                                                       float* out4, float* scores)
+constexpr int kSampleRows = 16;
+constexpr int kRowPitch = kMlpHidden + 8;   // bf16 of an LDS row: 16-lane reads conflict-free
+
+__device__ __forceinline__ size_t operand_at(uint32_t sample, int feature, int features)
 {
-    const uint32_t b = blockIdx.x * 256 + threadIdx.x;
-    if (b >= n)
-        return;
-    float o[kMlpOut];
+    return ((size_t)(sample / 32) * (features / 16) + feature / 16) * 512 +
+           (sample % 32 / 8 * 16 + feature % 16) * 8 + sample % 8;
+}
+
+// Eight bf16 (16 bytes).
+__device__ __forceinline__ uint4 pack8(const uint16_t* v)
+{
+    uint4 u;
+    __builtin_memcpy(&u, v, sizeof(u));
+    return u;
+}
+
+// Samples 16 blockIdx.x ..: with kTrain the loss, dout and the operands of the
+// batch products, from n on as zeros (n_pad, a multiple of 32, rows are
+// written); else out4.
+//
+// Wave w owns hidden columns 32w .. 32w + 31 of both products and loads its
+// slices of W2 at the start, behind layer 1: with one tile a workgroup the
+// weights (256 KB a workgroup, from L2) are most of its traffic (in rows instead
+// of operand order they took 6 us more).  Layer 1 is a
+// gather, the sum of 4t rows of W1, a sample and 8 columns a thread.  Sixteen
+// rows, the matrix cores' least, give 4,096 samples a workgroup on each CU.
+template <bool kTrain>
+__global__ __launch_bounds__(512) void mlp_sample_kernel(MlpArgs a, const uint64_t* genomes,
+                                                         const uint8_t* tvec, int t_all,
+                                                         uint32_t n, const jatam_result_t* labels,
+                                                         float* out4)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t h1s[kSampleRows][kRowPitch];
+    __shared__ __attribute__((aligned(16))) uint16_t h2s[kSampleRows][kRowPitch];   // then dh2
+    __shared__ __attribute__((aligned(16))) float w3s[kMlpOut][kMlpHidden + 4];
+    __shared__ __attribute__((aligned(16))) float douts[kSampleRows][kMlpOut];
+    __shared__ uint64_t gs[kSampleRows];
+    __shared__ int ts[kSampleRows];
+    const int tid = (int)threadIdx.x, wave = tid >> 6, l = tid & 63;
+    const int r16 = l & 15, q = l >> 4, col0 = 32 * wave;
+    const uint32_t s0 = blockIdx.x * kSampleRows;
+    // Everything the workgroup needs from memory is asked for at the start, in the
+    // order of its use (waits are in that order): one round trip instead of six.
+    // a thread's sample and 8 columns of layer 1
+    const int row = tid >> 5, c8 = (tid & 31) * 8;
+    const bool real = s0 + (uint32_t)row < n;
+    const uint32_t cmask = (uint32_t)a.c - 1u;
+    uint64_t genome = 0;
+    int tiles = 0;
+    if (real) {
+        genome = genomes[s0 + row];
+        tiles = mlp_tiles(tvec != nullptr ? tvec[s0 + row] : t_all);
+    }
+    const float4 b1a = *reinterpret_cast<const float4*>(a.p.b1 + c8);
+    const float4 b1b = *reinterpret_cast<const float4*>(a.p.b1 + c8 + 4);
+    uint4 w1[kMlpEdges];   // its rows of W1 (of an edge that is absent: some row)
 #pragma unroll
-    for (int k = 0; k < kMlpOut; ++k)
-        o[k] = a.p.b3[k];
-    const uint16_t* h = a.h2 + (size_t)b * kMlpHidden;
-    for (int j = 0; j < kMlpHidden; ++j) {
-        const float hj = bf16_float(h[j]);
+    for (int e = 0; e < kMlpEdges; ++e) {
+        const int shift = a.bits * max(4 * tiles - 1 - e, 0);
+        const uint32_t colour = (uint32_t)(genome >> shift) & cmask;
+        w1[e] = *reinterpret_cast<const uint4*>(a.w1b + (size_t)(e * 8 + colour) * kMlpHidden + c8);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const float b2v[2] = {a.p.b2[col0 + r16], a.p.b2[col0 + 16 + r16]};
+    const uint64_t w3v = tid < kMlpHidden ? reinterpret_cast<const uint64_t*>(a.w3b)[tid] : 0;
+    const float b3v = a.p.b3[l & 3];
+    jatam_result_t label{JATAM_INVALID, 0, 0u, 0};
+    if (kTrain && wave == 0 && s0 + (uint32_t)(l >> 2) < n)
+        label = labels[s0 + (uint32_t)(l >> 2)];
+    bf16x8 w2f[8][2], w2r[kTrain ? 8 : 1][2];
+#pragma unroll
+    for (int kb = 0; kb < 8; ++kb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+            w2f[kb][nb] = load_bf16x8(a.w2t + ((2 * wave + nb) * 8 + kb) * 512 + 8 * l);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kTrain)
+#pragma unroll
+        for (int kb = 0; kb < 8; ++kb)
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+                w2r[kb][nb] = load_bf16x8(a.w2b + ((2 * wave + nb) * 8 + kb) * 512 + 8 * l);
+    __builtin_amdgcn_sched_barrier(0);
+    // -- layer 1 -------------------------------------------------------------------
+    {
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < kMlpEdges; ++e) {
+            const uint32_t ww[4] = {w1[e].x, w1[e].y, w1[e].z, w1[e].w};
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float sum = acc[i] + bf16_float((uint16_t)(ww[i >> 1] >> (16 * (i & 1))));
+                acc[i] = e < 4 * tiles ? sum : acc[i];
+            }
+        }
+        const float b1v[8] = {b1a.x, b1a.y, b1a.z, b1a.w, b1b.x, b1b.y, b1b.z, b1b.w};
+        uint16_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float z = acc[i] + b1v[i];
+            v[i] = real && z > 0.f ? bf16_bits(z) : (uint16_t)0;   // +0, never -0
+        }
+        *reinterpret_cast<uint4*>(&h1s[row][c8]) = pack8(v);
+    }
+    if (kTrain && (tid & 31) == 0) {
+        gs[row] = genome;
+        ts[row] = tiles;   // none past the samples' end
+    }
+    if (tid < kMlpHidden)
 #pragma unroll
         for (int k = 0; k < kMlpOut; ++k)
-            o[k] = fmaf(hj, bf16_float(a.w3b[j * kMlpOut + k]), o[k]);
-    }
-    if (out4 != nullptr)
-#pragma unroll
-        for (int k = 0; k < kMlpOut; ++k)
-            out4[(size_t)b * kMlpOut + k] = o[k];
-    if (scores != nullptr) {
-        // expected size of a deterministic structure: P(DET) e^pred - 1
-        const float mx = fmaxf(o[0], fmaxf(o[1], o[2]));
-        const float e0 = expf(o[0] - mx), e1 = expf(o[1] - mx), e2 = expf(o[2] - mx);
-        scores[b] = e2 / (e0 + e1 + e2) * expf(o[3]) - 1.f;
-    }
-    if (labels == nullptr)
-        return;
-    const jatam_result_t rec = labels[b];
-    const int y = rec.cls == JATAM_UNBOUND ? 0 : rec.cls == JATAM_DET ? 2 : 1;
-    const float mx = fmaxf(o[0], fmaxf(o[1], o[2]));
-    const float e0 = expf(o[0] - mx), e1 = expf(o[1] - mx), e2 = expf(o[2] - mx);
-    const float s = e0 + e1 + e2;
-    const float py = (y == 0 ? e0 : y == 1 ? e1 : e2) / s;
-    const float target = log1pf((float)rec.size);
-    const float err = o[3] - target;
-    a.loss[b] = -logf(py) + err * err;
-    const float inv = 1.f / (float)n;
-    a.dout[(size_t)b * kMlpOut + 0] = (e0 / s - (y == 0 ? 1.f : 0.f)) * inv;
-    a.dout[(size_t)b * kMlpOut + 1] = (e1 / s - (y == 1 ? 1.f : 0.f)) * inv;
-    a.dout[(size_t)b * kMlpOut + 2] = (e2 / s - (y == 2 ? 1.f : 0.f)) * inv;
-    a.dout[(size_t)b * kMlpOut + 3] = 2.f * err * inv;
-}
-
-// dh2 = bf16((dout W3^T) * (h2 > 0)), one thread per (sample, unit); zero on
-// padding rows (b >= n).
-__global__ __launch_bounds__(256) void mlp_dh2_kernel(MlpArgs a, uint32_t n)
-{
-    const uint32_t b = blockIdx.x;
-    const int j = threadIdx.x;
-    if (b >= n) {
-        a.dh2[(size_t)b * kMlpHidden + j] = 0;
-        return;
-    }
-    float v = 0.f;
-#pragma unroll
-    for (int k = 0; k < kMlpOut; ++k)
-        v = fmaf(a.dout[(size_t)b * kMlpOut + k], bf16_float(a.w3b[j * kMlpOut + k]), v);
-    const size_t o = (size_t)b * kMlpHidden + j;
-    a.dh2[o] = bf16_bits(a.h2[o] != 0 ? v : 0.f);
-}
-
-// Row chunks of the batch reductions below: each block sums one chunk of
-// rows into partial[chunk][...]; mlp_reduce_kernel adds the chunks in order.
-constexpr int kRedRows = 128;
-
-// Column sums of [n][cols] rows (bf16 or fp32): partial[chunk][j].
-__global__ __launch_bounds__(256) void mlp_colsum_kernel(const uint16_t* src16, const float* src32,
-                                                         uint32_t n, int cols, float* partial)
-{
-    const uint32_t b0 = blockIdx.y * kRedRows, b1 = min(n, b0 + kRedRows);
-    for (int j = blockIdx.x * 256 + threadIdx.x; j < cols; j += gridDim.x * 256) {
-        float s = 0.f;
-        for (uint32_t b = b0; b < b1; ++b)
-            s += src16 != nullptr ? bf16_float(src16[(size_t)b * cols + j])
-                                  : src32[(size_t)b * cols + j];
-        partial[(size_t)blockIdx.y * cols + j] = s;
-    }
-}
-
-// dW3[j][k] = sum_b h2[b][j] dout[b][k]: partial[chunk][j * 4 + k].
-__global__ __launch_bounds__(256) void mlp_dw3_kernel(MlpArgs a, uint32_t n, float* partial)
-{
-    const int j = threadIdx.x;
-    const uint32_t b0 = blockIdx.x * kRedRows, b1 = min(n, b0 + kRedRows);
-    float s[kMlpOut] = {0.f, 0.f, 0.f, 0.f};
-    for (uint32_t b = b0; b < b1; ++b) {
-        const float h = bf16_float(a.h2[(size_t)b * kMlpHidden + j]);
-#pragma unroll
-        for (int k = 0; k < kMlpOut; ++k)
-            s[k] = fmaf(h, a.dout[(size_t)b * kMlpOut + k], s[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < kMlpOut; ++k)
-        partial[(size_t)blockIdx.x * kMlpHidden * kMlpOut + j * kMlpOut + k] = s[k];
-}
-
-// Per-chunk loss sums: partial[chunk].
-__global__ __launch_bounds__(256) void mlp_loss_kernel(MlpArgs a, uint32_t n, float* partial)
-{
-    __shared__ float part[256];
-    const uint32_t b0 = blockIdx.x * kRedRows, b1 = min(n, b0 + kRedRows);
-    const uint32_t b = b0 + threadIdx.x;
-    part[threadIdx.x] = b < b1 ? a.loss[b] : 0.f;
+            w3s[k][tid] = bf16_float((uint16_t)(w3v >> (16 * k)));
     __syncthreads();
+    // eight samples of one feature as the batch products take them
+    const int feature = tid & 255, half = 8 * (tid >> 8);
+    if constexpr (kTrain) {
+        uint16_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            v[i] = h1s[half + i][feature];
+        *reinterpret_cast<uint4*>(a.h1 + operand_at(s0 + half, feature, kMlpHidden)) = pack8(v);
+        if (feature < kMlpIn) {
+            const int e = feature >> 3;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int shift = a.bits * max(4 * ts[half + i] - 1 - e, 0);
+                const uint32_t colour = (uint32_t)(gs[half + i] >> shift) & cmask;
+                v[i] = e < 4 * ts[half + i] && colour == (uint32_t)(feature & 7) ? 0x3F80u : 0u;
+            }
+            *reinterpret_cast<uint4*>(a.x + operand_at(s0 + half, feature, kMlpIn)) = pack8(v);
+        }
+    }
+    // -- layer 2: samples x features, a lane with samples 4q + i of feature r16 ---
+    floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int kb = 0; kb < 8; ++kb) {
+        const bf16x8 af = load_bf16x8(&h1s[r16][32 * kb + 8 * q]);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2f[kb][nb], acc[nb], 0, 0, 0);
+    }
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+        const int col = col0 + 16 * nb + r16;
+        uint16_t v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float z = acc[nb][i] + b2v[nb];
+            v[i] = bf16_bits(z > 0.f ? z : 0.f);
+            h2s[4 * q + i][col] = v[i];
+        }
+        if constexpr (kTrain)
+            __builtin_memcpy(a.h2 + operand_at(s0 + 4 * q, col, kMlpHidden), v, sizeof(v));
+    }
+    __syncthreads();
+    // -- head and loss: a lane per output, its sum in the order of the features ---
+    if (wave == 0) {
+        const int s = l >> 2, k = l & 3;
+        const uint32_t b = s0 + (uint32_t)s;
+        float o = b3v;
+#pragma unroll 4
+        for (int j = 0; j < kMlpHidden; j += 8) {
+            const uint4 h = *reinterpret_cast<const uint4*>(&h2s[s][j]);
+            const uint32_t hw[4] = {h.x, h.y, h.z, h.w};
+            const float4 wa = *reinterpret_cast<const float4*>(&w3s[k][j]);
+            const float4 wb = *reinterpret_cast<const float4*>(&w3s[k][j + 4]);
+            const float w[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                o = fmaf(bf16_float((uint16_t)(hw[i >> 1] >> (16 * (i & 1)))), w[i], o);
+        }
+        if (b < n && out4 != nullptr)
+            out4[(size_t)b * kMlpOut + k] = o;
+        if constexpr (kTrain) {
+            const float o0 = __shfl(o, (l & ~3) + 0), o1 = __shfl(o, (l & ~3) + 1);
+            const float o2 = __shfl(o, (l & ~3) + 2), o3 = __shfl(o, (l & ~3) + 3);
+            float d = 0.f;
+            if (b < n) {
+                const int y = label.cls == JATAM_UNBOUND ? 0 : label.cls == JATAM_DET ? 2 : 1;
+                const float mx = fmaxf(o0, fmaxf(o1, o2));
+                const float e0 = expf(o0 - mx), e1 = expf(o1 - mx), e2 = expf(o2 - mx);
+                const float sum = e0 + e1 + e2;
+                const float py = (y == 0 ? e0 : y == 1 ? e1 : e2) / sum;
+                const float err = o3 - log1pf((float)label.size);
+                const float inv = 1.f / (float)n;
+                if (k == 0)
+                    a.loss[b] = -logf(py) + err * err;
+                d = k == 3 ? 2.f * err * inv
+                           : ((k == 0 ? e0 : k == 1 ? e1 : e2) / sum - (y == k ? 1.f : 0.f)) * inv;
+                a.dout[(size_t)b * kMlpOut + k] = d;
+            }
+            douts[s][k] = d;
+        }
+    }
+    if constexpr (!kTrain)
+        return;
+    __syncthreads();
+    // -- dh2 = bf16((dout W3^T) * (h2 > 0)), over h2 in LDS ------------------------
+    {
+        uint16_t v[8];
+        const float4 d = *reinterpret_cast<const float4*>(&douts[row][0]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            float z = fmaf(d.x, w3s[0][c8 + i], 0.f);
+            z = fmaf(d.y, w3s[1][c8 + i], z);
+            z = fmaf(d.z, w3s[2][c8 + i], z);
+            z = fmaf(d.w, w3s[3][c8 + i], z);
+            v[i] = real && h2s[row][c8 + i] != 0 ? bf16_bits(z) : (uint16_t)0;
+        }
+        *reinterpret_cast<uint4*>(&h2s[row][c8]) = pack8(v);
+    }
+    __syncthreads();
+    {
+        uint16_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            v[i] = h2s[half + i][feature];
+        *reinterpret_cast<uint4*>(a.dh2 + operand_at(s0 + half, feature, kMlpHidden)) = pack8(v);
+    }
+    // -- dh1 = bf16((dh2 W2^T) * (h1 > 0)) ------------------------------------------
+    acc[0] = acc[1] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = 0; kb < (kTrain ? 8 : 1); ++kb) {
+        const bf16x8 af = load_bf16x8(&h2s[r16][32 * kb + 8 * q]);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, w2r[kb][nb], acc[nb], 0, 0, 0);
+    }
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+        const int col = col0 + 16 * nb + r16;
+        uint16_t v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v[i] = bf16_bits(h1s[4 * q + i][col] != 0 ? acc[nb][i] : 0.f);
+        __builtin_memcpy(a.dh1 + operand_at(s0 + 4 * q, col, kMlpHidden), v, sizeof(v));
+    }
+}
+
+// Row chunks of the head's and the biases' batch sums: partial sums per chunk,
+// added in chunk order.
+constexpr int kRedRows = 128;
+constexpr int kGradTiles = (kMlpHidden / 32) * (kMlpHidden / 32) + (kMlpIn / 32) * (kMlpHidden / 32);
+
+// Where the batch products' and sums' parts lie in MlpArgs::partial.
+struct GradParts {
+    int splits, chunks;
+    float *w2, *w1, *w3, *b2, *b1, *b3, *loss;
+};
+
+constexpr int kMaxSplits = 16;
+
+static GradParts grad_parts(float* base, uint32_t n, uint32_t n_pad)
+{
+    GradParts g;
+    const int want = (int)(n_pad / 256);
+    g.splits = want < 1 ? 1 : want > kMaxSplits ? kMaxSplits : want;
+    g.chunks = (int)((n + kRedRows - 1) / kRedRows);
+    g.w2 = base;
+    g.w1 = g.w2 + (size_t)kMaxSplits * kMlpHidden * kMlpHidden;
+    g.w3 = g.w1 + (size_t)kMaxSplits * kMlpIn * kMlpHidden;
+    g.b2 = g.w3 + (size_t)g.chunks * kMlpHidden * kMlpOut;
+    g.b1 = g.b2 + (size_t)g.chunks * kMlpHidden;
+    g.b3 = g.b1 + (size_t)g.chunks * kMlpHidden;
+    g.loss = g.b3 + (size_t)g.chunks * kMlpOut;
+    return g;
+}
+
+size_t mlp_partial_floats(size_t max_batch)
+{
+    const size_t chunks = (max_batch + kRedRows - 1) / kRedRows;
+    return (size_t)kMaxSplits * (kMlpHidden + kMlpIn) * kMlpHidden +
+           chunks * (kMlpHidden * kMlpOut + 2 * kMlpHidden + kMlpOut + 1);
+}
+
+// Batch sums of feature j's values over chunk rows: f(row, value) in row order.
+template <class F>
+__device__ __forceinline__ void each_row(const uint16_t* src, uint32_t b0, uint32_t rows, int j, F f)
+{
+    // 128 rows of one feature are 16 reads of 16 bytes, all under way at once
+    uint4 v[kRedRows / 8];
+#pragma unroll
+    for (int r = 0; r < kRedRows / 8; ++r)
+        if ((uint32_t)(8 * r) < rows)
+            v[r] = *reinterpret_cast<const uint4*>(src + operand_at(b0 + 8 * r, j, kMlpHidden));
+#pragma unroll
+    for (int r = 0; r < kRedRows / 8; ++r) {
+        const uint32_t w[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if ((uint32_t)(8 * r + i) < rows)
+                f(8 * r + i, bf16_float((uint16_t)(w[i >> 1] >> (16 * (i & 1)))));
+    }
+}
+
+// dW2 = h1^T dh2 and dW1 = x^T dh1, a 32 x 32 tile and a split of the batch per
+// wave, its operands straight from memory; from block `products` on, the chunk
+// sums: dW3, db3 and the loss, then db2, then db1.
+__global__ __launch_bounds__(256) void mlp_grad_kernel(MlpArgs a, GradParts g, uint32_t n,
+                                                       uint32_t n_pad, uint32_t products)
+{
+    const int tid = (int)threadIdx.x, l = tid & 63;
+    if (blockIdx.x < products) {
+        const uint32_t task = blockIdx.x * 4 + (uint32_t)(tid >> 6);
+        const uint32_t split = task / kGradTiles;
+        int tile = (int)(task % kGradTiles);
+        constexpr int kTiles2 = (kMlpHidden / 32) * (kMlpHidden / 32);
+        const bool second = tile < kTiles2;
+        tile -= second ? 0 : kTiles2;
+        const int m = tile / (kMlpHidden / 32), c = tile % (kMlpHidden / 32);
+        const uint16_t* const left = (second ? a.h1 : a.x) + (2 * m) * 512 + l * 8;
+        const uint16_t* const right = (second ? a.dh2 : a.dh1) + (2 * c) * 512 + l * 8;
+        const size_t lstep = (second ? kMlpHidden : kMlpIn) * 32, rstep = kMlpHidden * 32;
+        const uint32_t blocks = n_pad / 32, per = (blocks + g.splits - 1) / g.splits;
+        const uint32_t from = split * per, to = min(blocks, from + per);
+        floatx4 acc[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        // eight k blocks' operands under way at once
+        constexpr int kAhead = 8;
+        for (uint32_t k0 = from; k0 < to; k0 += kAhead) {
+            bf16x8 af[kAhead][2], bf[kAhead][2];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const size_t kb = min(k0 + k, to - 1);
+                    af[k][i] = load_bf16x8(left + kb * lstep + i * 512);
+                    bf[k][i] = load_bf16x8(right + kb * rstep + i * 512);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k)
+                if (k0 + k < to)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                af[k][i], bf[k][j], acc[i][j], 0, 0, 0);
+        }
+        float* const out = second ? g.w2 + (size_t)split * kMlpHidden * kMlpHidden
+                                  : g.w1 + (size_t)split * kMlpIn * kMlpHidden;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    out[(32 * m + 16 * i + 4 * (l >> 4) + e) * kMlpHidden + 32 * c + 16 * j +
+                        (l & 15)] = acc[i][j][e];
+        return;
+    }
+    __shared__ float4 douts[kRedRows];
+    __shared__ float part[256];
+    const uint32_t chunk = (blockIdx.x - products) % (uint32_t)g.chunks;
+    const uint32_t what = (blockIdx.x - products) / (uint32_t)g.chunks;
+    const uint32_t b0 = chunk * kRedRows;
+    if (what > 0) {
+        float s = 0.f;
+        each_row(what == 1 ? a.dh2 : a.dh1, b0, min(n_pad - b0, (uint32_t)kRedRows), tid,
+                 [&](int, float v) { s += v; });
+        (what == 1 ? g.b2 : g.b1)[(size_t)chunk * kMlpHidden + tid] = s;
+        return;
+    }
+    const uint32_t rows = min(n - b0, (uint32_t)kRedRows);
+    if ((uint32_t)tid < rows)
+        douts[tid] = reinterpret_cast<const float4*>(a.dout)[b0 + tid];
+    part[tid] = (uint32_t)tid < rows ? a.loss[b0 + tid] : 0.f;
+    __syncthreads();
+    float s[kMlpOut] = {0.f, 0.f, 0.f, 0.f};
+    each_row(a.h2, b0, rows, tid, [&](int r, float h) {
+        const float4 d = douts[r];
+        s[0] = fmaf(h, d.x, s[0]);
+        s[1] = fmaf(h, d.y, s[1]);
+        s[2] = fmaf(h, d.z, s[2]);
+        s[3] = fmaf(h, d.w, s[3]);
+    });
+    reinterpret_cast<float4*>(g.w3)[(size_t)chunk * kMlpHidden + tid] =
+        make_float4(s[0], s[1], s[2], s[3]);
+    if (tid < kMlpOut) {
+        float b = 0.f;
+#pragma unroll 16
+        for (uint32_t r = 0; r < rows; ++r)
+            b += reinterpret_cast<const float*>(&douts[r])[tid];
+        g.b3[(size_t)chunk * kMlpOut + tid] = b;
+    }
     for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off)
-            part[threadIdx.x] += part[threadIdx.x + off];
+        if (tid < off)
+            part[tid] += part[tid + off];
         __syncthreads();
     }
-    if (threadIdx.x == 0)
-        partial[blockIdx.x] = part[0];
+    if (tid == 0)
+        g.loss[chunk] = part[0];
 }
 
-// loss_out = (sum of the chunk sums) / n.
-__global__ void mlp_loss_final_kernel(const float* partial, int chunks, uint32_t n,
-                                      float* loss_out)
+// Adam on a parameter; refreshes its bf16 copies.
+__device__ __forceinline__ void adam_step(const MlpArgs& a, int i, float gi, float lr, float bc1,
+                                          float bc2)
 {
-    if (threadIdx.x != 0)
-        return;
-    float s = 0.f;
-    for (int c = 0; c < chunks; ++c)
-        s += partial[c];
-    loss_out[0] = s / (float)n;
-}
-
-// Adam on the flat fp32 parameter vector; refreshes the bf16 weight copies.
-__global__ __launch_bounds__(256) void mlp_adam_kernel(MlpArgs a, float lr, float bc1, float bc2)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= kMlpParams)
-        return;
     const float beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f;
-    const float gi = a.g.flat[i];
     const float m = beta1 * a.m[i] + (1.f - beta1) * gi;
     const float v = beta2 * a.v[i] + (1.f - beta2) * gi * gi;
     a.m[i] = m;
@@ -652,6 +767,61 @@ __global__ __launch_bounds__(256) void mlp_adam_kernel(MlpArgs a, float lr, floa
     const float w = a.p.flat[i] - lr * (m / bc1) / (sqrtf(v / bc2) + eps);
     a.p.flat[i] = w;
     refresh_bf16(a, i, w);
+}
+
+// Every parameter's gradient from its parts, in their order, and with lr > 0 an
+// Adam step on it; the block past the parameters: the mean loss.
+__global__ __launch_bounds__(256) void mlp_update_kernel(MlpArgs a, GradParts g, uint32_t n,
+                                                         float* loss_out, float lr, float bc1,
+                                                         float bc2)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.x == gridDim.x - 1) {
+        if (threadIdx.x == 0 && loss_out != nullptr) {
+            float s = 0.f;
+#pragma unroll 16
+            for (int c = 0; c < g.chunks; ++c)
+                s += g.loss[c];
+            loss_out[0] = s / (float)n;
+        }
+        return;
+    }
+    if (i >= kMlpParams)
+        return;
+    const float* part;
+    int count, parts;
+    if (i < kMlpOffB1) {
+        part = g.w1 + i;
+        count = kMlpIn * kMlpHidden;
+        parts = g.splits;
+    } else if (i < kMlpOffW2) {
+        part = g.b1 + (i - kMlpOffB1);
+        count = kMlpHidden;
+        parts = g.chunks;
+    } else if (i < kMlpOffB2) {
+        part = g.w2 + (i - kMlpOffW2);
+        count = kMlpHidden * kMlpHidden;
+        parts = g.splits;
+    } else if (i < kMlpOffW3) {
+        part = g.b2 + (i - kMlpOffB2);
+        count = kMlpHidden;
+        parts = g.chunks;
+    } else if (i < kMlpOffB3) {
+        part = g.w3 + (i - kMlpOffW3);
+        count = kMlpHidden * kMlpOut;
+        parts = g.chunks;
+    } else {
+        part = g.b3 + (i - kMlpOffB3);
+        count = kMlpOut;
+        parts = g.chunks;
+    }
+    float s = 0.f;
+#pragma unroll 16
+    for (int p = 0; p < parts; ++p)
+        s += part[(size_t)p * count];
+    a.g.flat[i] = s;
+    if (lr > 0.f)
+        adam_step(a, i, s, lr, bc1, bc2);
 }
 
 // bf16 copies of all weights from the fp32 masters.
@@ -691,42 +861,6 @@ __global__ __launch_bounds__(256) void mlp_init_kernel(MlpArgs a, uint32_t k0, u
 // ---------------------------------------------------------------------------
 // Host side.
 // ---------------------------------------------------------------------------
-// C = A B (M x N, K a multiple of 32, M and N multiples of 8).  Store
-// epilogues with a long K are split across workgroups (fp32 partials in
-// `partial`, added in split order).
-static int gemm(GemmArgs g, float* partial, hipStream_t s)
-{
-    const int tiles = ((g.M + kBM - 1) / kBM) * ((g.N + kBN - 1) / kBN);
-    g.splits = 1;
-    if (g.epilogue == kEpStoreF32) {
-        const int want = g.K / 256;
-        g.splits = want < 1 ? 1 : want > 16 ? 16 : want;
-    }
-    g.partial = partial;
-    hipLaunchKernelGGL(mlp_gemm_kernel, dim3(tiles, g.splits), dim3(256), 0, s, g);
-    if (g.splits > 1) {
-        const int64_t count = (int64_t)g.M * g.N;
-        hipLaunchKernelGGL(mlp_reduce_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
-                           s, (const float*)partial, g.splits, count, g.C32);
-    }
-    return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
-}
-
-size_t mlp_partial_floats(size_t max_batch)
-{
-    const size_t chunks = (max_batch + kRedRows - 1) / kRedRows;
-    const size_t split = (size_t)16 * kMlpHidden * kMlpHidden;       // dW2, 16 splits
-    const size_t rows = chunks * (size_t)(kMlpHidden * kMlpOut);      // dW3 chunk sums
-    return split > rows ? split : rows;
-}
-
-// Sum of `chunks` partial rows of `cols` floats into out (fixed order).
-static void reduce_rows(const float* partial, int chunks, int cols, float* out, hipStream_t s)
-{
-    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((unsigned)((cols + 255) / 256)), dim3(256), 0, s,
-                       partial, chunks, (int64_t)cols, out);
-}
-
 int mlp_launch_init(const MlpArgs& a, uint64_t seed, hipStream_t s)
 {
     hipLaunchKernelGGL(mlp_init_kernel, dim3((kMlpParams + 255) / 256), dim3(256), 0, s, a,
@@ -740,33 +874,13 @@ int mlp_launch_refresh(const MlpArgs& a, hipStream_t s)
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }
 
-// Forward pass over n samples (n a multiple of 16); out4 may be null.
-// Forward pass over n samples padded to n_pad (a multiple of 32): padding rows
-// carry zero inputs and are never read back; out4 may be null.
+// Outputs of n samples.
 int mlp_launch_forward(const MlpArgs& a, const uint64_t* genomes, const uint8_t* tvec, int t_all,
-                       uint32_t n, uint32_t n_pad, const jatam_result_t* labels, float* out4,
-                       hipStream_t s)
+                       uint32_t n, float* out4, hipStream_t s)
 {
-    hipLaunchKernelGGL(mlp_layer1_kernel, dim3(n_pad), dim3(256), 0, s, a, genomes, tvec, t_all,
-                       n);
-    GemmArgs g{};
-    g.A = a.h1;
-    g.sam = kMlpHidden;
-    g.sak = 1;
-    g.B = a.w2b;
-    g.sbk = kMlpHidden;
-    g.sbn = 1;
-    g.M = (int)n_pad;
-    g.N = kMlpHidden;
-    g.K = kMlpHidden;
-    g.epilogue = kEpBiasRelu;
-    g.C16 = a.h2;
-    g.bias = a.p.b2;
-    int rc = gemm(g, a.partial, s);
-    if (rc != JATAM_OK)
-        return rc;
-    hipLaunchKernelGGL(mlp_head_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a, n, labels,
-                       out4, (float*)nullptr);
+    hipLaunchKernelGGL(mlp_sample_kernel<false>, dim3((n + kSampleRows - 1) / kSampleRows),
+                       dim3(512), 0, s, a, genomes, tvec, t_all, n,
+                       (const jatam_result_t*)nullptr, out4);
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }
 
@@ -801,85 +915,22 @@ int mlp_launch_score(const MlpArgs& a, const uint64_t* genomes, const uint8_t* t
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }
 
-// Backward pass of the last forward (with labels).
-int mlp_launch_backward(const MlpArgs& a, uint32_t n, uint32_t n_pad, float* loss_out,
-                        hipStream_t s)
+// Loss and gradients of n samples, padded to n_pad (a multiple of 32) in the
+// workspace; with lr > 0 Adam step number `step`.
+int mlp_launch_train(const MlpArgs& a, const uint64_t* genomes, const uint8_t* tvec, int t_all,
+                     const jatam_result_t* labels, uint32_t n, uint32_t n_pad, float lr, int step,
+                     float* loss_out, hipStream_t s)
 {
-    const int chunks = (int)((n + kRedRows - 1) / kRedRows);
-    const int chunks_pad = (int)((n_pad + kRedRows - 1) / kRedRows);
-    if (loss_out != nullptr) {
-        hipLaunchKernelGGL(mlp_loss_kernel, dim3(chunks), dim3(256), 0, s, a, n, a.partial);
-        hipLaunchKernelGGL(mlp_loss_final_kernel, dim3(1), dim3(64), 0, s, (const float*)a.partial,
-                           chunks, n, loss_out);
-    }
-    hipLaunchKernelGGL(mlp_dw3_kernel, dim3(chunks), dim3(kMlpHidden), 0, s, a, n, a.partial);
-    reduce_rows(a.partial, chunks, kMlpHidden * kMlpOut, a.g.w3, s);
-    hipLaunchKernelGGL(mlp_colsum_kernel, dim3(1, chunks), dim3(256), 0, s,
-                       (const uint16_t*)nullptr, (const float*)a.dout, n, kMlpOut, a.partial);
-    reduce_rows(a.partial, chunks, kMlpOut, a.g.b3, s);
-    hipLaunchKernelGGL(mlp_dh2_kernel, dim3(n_pad), dim3(256), 0, s, a, n);
-    // dW2 = h1^T dh2 (M = K_hidden rows of h1^T, K = batch)
-    GemmArgs g{};
-    g.A = a.h1;
-    g.sam = 1;
-    g.sak = kMlpHidden;
-    g.B = a.dh2;
-    g.sbk = kMlpHidden;
-    g.sbn = 1;
-    g.M = kMlpHidden;
-    g.N = kMlpHidden;
-    g.K = (int)n_pad;
-    g.epilogue = kEpStoreF32;
-    g.C32 = a.g.w2;
-    int rc = gemm(g, a.partial, s);
-    if (rc != JATAM_OK)
-        return rc;
-    hipLaunchKernelGGL(mlp_colsum_kernel, dim3(1, chunks_pad), dim3(256), 0, s,
-                       (const uint16_t*)a.dh2, (const float*)nullptr, n_pad, kMlpHidden,
-                       a.partial);
-    reduce_rows(a.partial, chunks_pad, kMlpHidden, a.g.b2, s);
-    // dh1 = bf16((dh2 W2^T) * (h1 > 0))
-    g = GemmArgs{};
-    g.A = a.dh2;
-    g.sam = kMlpHidden;
-    g.sak = 1;
-    g.B = a.w2b;
-    g.sbk = 1;
-    g.sbn = kMlpHidden;
-    g.M = (int)n_pad;
-    g.N = kMlpHidden;
-    g.K = kMlpHidden;
-    g.epilogue = kEpReluMask;
-    g.C16 = a.dh1;
-    g.mask = a.h1;
-    if ((rc = gemm(g, a.partial, s)) != JATAM_OK)
-        return rc;
-    hipLaunchKernelGGL(mlp_colsum_kernel, dim3(1, chunks_pad), dim3(256), 0, s,
-                       (const uint16_t*)a.dh1, (const float*)nullptr, n_pad, kMlpHidden,
-                       a.partial);
-    reduce_rows(a.partial, chunks_pad, kMlpHidden, a.g.b1, s);
-    // dW1 = x^T dh1
-    g = GemmArgs{};
-    g.A = a.x;
-    g.sam = 1;
-    g.sak = kMlpIn;
-    g.B = a.dh1;
-    g.sbk = kMlpHidden;
-    g.sbn = 1;
-    g.M = kMlpIn;
-    g.N = kMlpHidden;
-    g.K = (int)n_pad;
-    g.epilogue = kEpStoreF32;
-    g.C32 = a.g.w1;
-    return gemm(g, a.partial, s);
-}
-
-int mlp_launch_adam(const MlpArgs& a, float lr, int step, hipStream_t s)
-{
+    const GradParts g = grad_parts(a.partial, n, n_pad);
+    hipLaunchKernelGGL(mlp_sample_kernel<true>, dim3(n_pad / kSampleRows), dim3(512), 0, s, a,
+                       genomes, tvec, t_all, n, labels, (float*)nullptr);
+    const uint32_t products = (uint32_t)(kGradTiles * g.splits / 4);
+    hipLaunchKernelGGL(mlp_grad_kernel, dim3(products + 3u * (uint32_t)g.chunks), dim3(256), 0, s,
+                       a, g, n, n_pad, products);
     const float bc1 = 1.f - powf(0.9f, (float)step);
     const float bc2 = 1.f - powf(0.999f, (float)step);
-    hipLaunchKernelGGL(mlp_adam_kernel, dim3((kMlpParams + 255) / 256), dim3(256), 0, s, a, lr,
-                       bc1, bc2);
+    hipLaunchKernelGGL(mlp_update_kernel, dim3((kMlpParams + 255) / 256 + 1), dim3(256), 0, s, a,
+                       g, n, loss_out, lr, bc1, bc2);
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }
 
