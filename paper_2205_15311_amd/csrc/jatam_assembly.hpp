@@ -626,6 +626,182 @@ __device__ __forceinline__ int run_four(const Src& m, Grid& g, RunState& st, int
     return event_of(ev);
 }
 
+// The wave's last running lane `t` to the end of its run, by the whole wave: the
+// grid in registers, lane W/16 y + x/16 with 16 cells of row y (frontier bits and
+// PEND nibbles), everything else uniform.  Called by the whole wave, with lane
+// t's run between groups of four steps and not over; returns its event.
+//
+// A lone lane's step is a chain of 200 (16 x 16) to 250 (32 x 32) instructions
+// and three LDS round trips, 0.7 us, and where every wave has few runs the
+// longest one is the call's time.  Here the frontier site's row comes from a
+// prefix sum over the lanes and a ballot instead of from two levels of words, its
+// neighbours by reading lanes, and 64 Philox blocks are computed at once: about
+// 170 instructions and no LDS, 0.48 us.  A GA generation of 65,536 three-tile
+// genotypes at G = 32, whose longest run has 462 steps, 0.40 -> 0.32 ms; 1,000
+// two-tile genotypes 53 -> 43 us.  Two running lanes are faster side by side in
+// their own grids.
+template <class Grid, class Src>
+__device__ __forceinline__ int lone_run(const Src& src, Grid& g, RunState& st, int grid,
+                                        const RunKey& key, uint32_t t)
+{
+    static_assert(Grid::kLean, "the layout of LeanGrid");
+    constexpr uint32_t W = Grid::kW, R = W / 16;
+    const uint32_t lane = __lane_id();
+    auto of = [](uint32_t v, uint32_t l) -> uint32_t {
+        return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
+    };
+    wave_lds_sync();
+    uint32_t* const col = g.base - lane + t;
+    const bool mine = lane < (W - 1) * R;   // row W-1 is not the run's
+    uint32_t f = 0, plo = 0, phi = 0;
+    if (mine) {
+        f = (col[(Grid::kFr + lane / 2) * 64] >> (16 * (lane & 1))) & 0xFFFFu;
+        plo = col[(Grid::kPend + 2 * lane) * 64];
+        phi = col[(Grid::kPend + 2 * lane + 1) * 64];
+    }
+    Src m = src;
+    m.t0 = of(src.t0, t);
+    m.t1 = of(src.t1, t);
+    if constexpr (Src::kManyIds) {
+        m.t2 = of(src.t2, t);
+        m.t3 = of(src.t3, t);
+    }
+    m.lo = of(src.lo, t);
+    m.hi = of(src.hi, t);
+    if constexpr (BondsTraits<Src>::kWide) {
+        m.lo2 = of(src.lo2, t);
+        m.hi2 = of(src.hi2, t);
+    }
+    const int G = (int)of((uint32_t)grid, t);
+    const uint32_t rid_lo = of(key.rid_lo, t), rid_hi = of(key.rid_hi, t);
+    const uint32_t run = of((uint32_t)key.run, t);
+    uint32_t nf = of(st.nf, t), lost = of(st.lost, t);
+    uint32_t steps = of((uint32_t)st.steps, t);
+    uint32_t choice = of(st.choice ? 2u : 0u, t);
+    const uint32_t limit = (uint32_t)((G - 1) * (G - 1));
+
+    // one step, as run_step
+    auto step = [&](uint32_t u) -> uint32_t {
+        const uint32_t j = __umulhi(u, nf);
+        choice |= nf & ~1u;
+        // inclusive prefix sums of the lanes' frontier sites
+        uint32_t sum = (uint32_t)__popc(f);
+        sum += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sum, 0x111, 0xf, 0xf, false);
+        sum += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sum, 0x112, 0xf, 0xf, false);
+        sum += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sum, 0x114, 0xf, 0xf, false);
+        sum += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sum, 0x118, 0xf, 0xf, false);
+        if constexpr (W == 32) {
+            sum += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sum, 0x142, 0xa, 0xf, false);
+            sum += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sum, 0x143, 0xc, 0xf, false);
+        }
+        const uint64_t above = __ballot(sum > j);
+        if (above == 0)
+            return 1u;   // corrupt: never, the frontier's count is nf
+        const uint32_t L = (uint32_t)__builtin_ctzll(above);
+        uint32_t rest = of(f, L);
+        for (uint32_t rank = j - (of(sum, L) - (uint32_t)__popc(rest)); rank > 0; --rank)
+            rest &= rest - 1u;
+        const uint32_t xi = (uint32_t)__builtin_ctz(rest | 0x10000u) & 15u;
+        // the cells around as (lane, index): N and S share the cell's index; E and W
+        // may lie in the next lane, or outside (a lane without cells, then)
+        const uint32_t at = 16 * L + xi, x = at % W, y = at / W;
+        const uint32_t up = (L - R) & 63u, down = (L + R) & 63u;
+        const uint32_t at_e = at + 1, at_w = at - 1;
+        const uint32_t le = (at_e >> 4) & 63u, lw = (at_w >> 4) & 63u;
+        const uint32_t xe = at_e & 15u, xw = at_w & 15u;
+        // every lane's PEND nibble at an index, with bit 7 set if on the frontier
+        const uint64_t pend64 = ((uint64_t)phi << 32) | plo;
+        const uint32_t f7 = f << 7;
+        const uint32_t cells = ((uint32_t)(pend64 >> (4 * xi)) & 15u) | ((f7 >> xi) & 0x80u);
+        const uint32_t cells_e = ((uint32_t)(pend64 >> (4 * xe)) & 15u) | ((f7 >> xe) & 0x80u);
+        const uint32_t cells_w = ((uint32_t)(pend64 >> (4 * xw)) & 15u) | ((f7 >> xw) & 0x80u);
+        const uint32_t around = of(cells, up) | (of(cells_e, le) << 8) | (of(cells, down) << 16) |
+                                (of(cells_w, lw) << 24);
+        const uint32_t own = of(cells, L) & 15u;
+        const uint32_t pend = around & 0x0F0F0F0Fu, fr = around & 0x80808080u;
+        const uint32_t occ = (pend + 0x7F7F7F7Fu) & ~fr;
+        const uint32_t codes =
+            (uint32_t)__builtin_amdgcn_readfirstlane((int)m.codes(m.oriented(own - 1u)));
+        const uint32_t tags = codes + 0x01010101u;
+        uint32_t fresh;
+        const uint32_t ev = check_sites(codes, inside_box(x, y, G), occ, fr, pend, tags, fresh);
+        const uint32_t ones = fresh >> 7, ids = tags & ((ones << 4) - ones);
+        // the cell leaves the frontier, fresh sites join
+        const bool is_n = lane == up, is_s = lane == down, is_e = lane == le, is_w = lane == lw;
+        f ^= ((is_n ? ones & 1u : is_s ? (ones >> 16) & 1u : lane == L ? 1u : 0u) << xi) |
+             (is_e ? ((ones >> 8) & 1u) << xe : 0u) | (is_w ? (ones >> 24) << xw : 0u);
+        uint32_t id = is_n ? ids & 15u : is_s ? (ids >> 16) & 15u : 0u;
+        if constexpr (Src::kManyIds) {   // id 15: see LeanGrid
+            const uint32_t mark = (own - 1u) >> 31;
+            lost |= mark;
+            id |= lane == L ? mark : 0u;
+        }
+        const uint64_t id_e = (uint64_t)((ids >> 8) & 15u) << (4 * xe);
+        const uint64_t id_w = (uint64_t)(ids >> 24) << (4 * xw);
+        const uint64_t id_v = (uint64_t)id << (4 * xi);
+        plo |= (uint32_t)id_v | (is_e ? (uint32_t)id_e : 0u) | (is_w ? (uint32_t)id_w : 0u);
+        phi |= (uint32_t)(id_v >> 32) | (is_e ? (uint32_t)(id_e >> 32) : 0u) |
+               (is_w ? (uint32_t)(id_w >> 32) : 0u);
+        nf = nf + (uint32_t)__popc(fresh) - 1u;
+        steps += 1;
+        return ev;
+    };
+
+    uint32_t ev = 0;
+    while (ev == 0 && nf != 0 && steps < limit) {
+        // the words of the next 256 steps, four a lane
+        const Words4 u = philox4x32_10((steps >> 2) + lane, run, rid_lo, rid_hi, key.key0, key.key1);
+        for (uint32_t block = 0; block < 64 && ev == 0 && nf != 0 && steps < limit; ++block) {
+            ev = step(of(u.w[0], block));
+            if (ev == 0 && nf != 0)
+                ev = step(of(u.w[1], block));
+            if (ev == 0 && nf != 0)
+                ev = step(of(u.w[2], block));
+            if (ev == 0 && nf != 0)
+                ev = step(of(u.w[3], block));
+        }
+    }
+    if (mine) {
+        col[(Grid::kPend + 2 * lane) * 64] = plo;
+        col[(Grid::kPend + 2 * lane + 1) * 64] = phi;
+    }
+    const uint32_t pair = f | ((uint32_t)__shfl((int)f, (int)(lane + 1) & 63) << 16);
+    if ((lane & 1u) == 0 && lane < (W == 16 ? 16u : 62u))
+        col[(Grid::kFr + lane / 2) * 64] = pair;
+    // what the run's state says of its grid: the words with a cell, and the cells
+    // in the window at the seed (all occupied unless the run met an event)
+    // (every lane takes part in the exchange)
+    const int any = __shfl((int)(plo | phi), (int)(2 * lane) & 63) |
+                    __shfl((int)(plo | phi), (int)(2 * lane + 1) & 63);
+    const uint32_t touched = (uint32_t)__ballot(any != 0);
+    uint64_t v = ((uint64_t)phi << 32) | plo;
+    v |= v >> 2;
+    v = (v | (v >> 1)) & 0x1111111111111111ull;
+    v = (v | (v >> 3)) & 0x0303030303030303ull;
+    v = (v | (v >> 6)) & 0x000F000F000F000Full;
+    v = (v | (v >> 12)) & 0x000000FF000000FFull;
+    const uint32_t cells = (uint32_t)(v | (v >> 24)) & 0xFFFFu;
+    uint64_t near = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < 8; ++r) {
+        const uint32_t first = ((uint32_t)(G / 2 - 4) + r) * R;
+        uint32_t row = of(cells, first);
+        if constexpr (R == 2)
+            row |= of(cells, first + 1) << 16;
+        near |= (uint64_t)((row >> (G / 2 - 4)) & 0xFFu) << (8 * r);
+    }
+    if (lane == t) {
+        st.nf = nf;
+        st.osum |= touched;
+        st.lost = lost;
+        st.steps = (int)steps;
+        st.choice = choice != 0;
+        st.near = near;
+    }
+    wave_lds_sync();
+    return event_of(ev);
+}
+
 // One run from the seed to completion or to an event.
 template <class Grid, class Src>
 __device__ __forceinline__ int run_assembly(const Src& m, Grid& g, RunState& st, int G,

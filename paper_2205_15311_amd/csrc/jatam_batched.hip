@@ -288,8 +288,16 @@ __global__ __launch_bounds__(64) void first_run_kernel(const BatchArgs a, int kl
         const uint32_t enough = queued == 0 && starved ? 65u : (uint32_t)a.refill;
         for (;;) {
             const bool stepping = busy && !run_over(ev, st, gd.grid);
-            if (__ballot(stepping) == 0)
+            const uint64_t still = __ballot(stepping);
+            if (still == 0)
                 break;
+            if (enough > 64u && (still & (still - 1)) == 0) {
+                const uint32_t last = (uint32_t)__builtin_ctzll(still);
+                const int end = lone_run(m, g, st, gd.grid, run_key(a, gd, 0), last);
+                if (stepping)
+                    ev = end;
+                break;
+            }
             if (stepping)
                 ev = run_four(m, g, st, gd.grid, run_key(a, gd, 0));
             const uint64_t waiting = __ballot(!busy || run_over(ev, st, gd.grid));

@@ -25,8 +25,10 @@ namespace jatam {
 constexpr int kSoloPend = 128;    // unproven candidates: drained above 64
 constexpr int kSoloShapes = 64;   // packed shapes waiting for a proof
 
+// Three waves a SIMD in the 16 x 16 layout: twelve a CU, where LDS holds eleven
+// (with 177 registers two: an enumeration of S_{2,8} 1.27 instead of 1.21 ms).
 template <int W, class M, int kIn, bool kOpen>
-__global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
+__global__ __launch_bounds__(64, W == 16 ? 3 : 1) void solo_kernel(const BatchArgs a, int klass,
                                                   uint32_t chunk_items, bool direct_tally,
                                                   ShapeTable table, OpenList open)
 {
@@ -265,8 +267,16 @@ __global__ __launch_bounds__(64) void solo_kernel(const BatchArgs a, int klass,
         const uint32_t enough = full || (queued == 0 && starved) ? 65u : (uint32_t)a.refill;
         for (;;) {
             const bool stepping = busy && !run_over(ev, st, gd.grid);
-            if (__ballot(stepping) == 0)
+            const uint64_t still = __ballot(stepping);
+            if (still == 0)
                 break;
+            if (enough > 64u && (still & (still - 1)) == 0) {
+                const uint32_t last = (uint32_t)__builtin_ctzll(still);
+                const int end = lone_run(m, g, st, gd.grid, run_key(a, gd, 0), last);
+                if (stepping)
+                    ev = end;
+                break;
+            }
             if (stepping)
                 ev = run_four(m, g, st, gd.grid, run_key(a, gd, 0));
             const uint64_t waiting = __ballot(!busy || run_over(ev, st, gd.grid));
