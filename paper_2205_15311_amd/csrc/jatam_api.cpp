@@ -1039,10 +1039,9 @@ int jatam_mlp_create(int64_t max_batch, int c, jatam_mlp_t** mlp)
     jatam::MlpArgs& a = m->a;
     bool ok = mlp_alloc(m, P * 4, (void**)&p) && mlp_alloc(m, P * 4, (void**)&g) &&
               mlp_alloc(m, P * 4, (void**)&a.m) && mlp_alloc(m, P * 4, (void**)&a.v) &&
-              mlp_alloc(m, (size_t)jatam::kMlpIn * Hd * 2, (void**)&a.w1b) &&
+              mlp_alloc(m, 2 * (size_t)jatam::kMlpIn * Hd * 2, (void**)&a.w1b) &&
               mlp_alloc(m, Hd * Hd * 2, (void**)&a.w2b) &&
               mlp_alloc(m, Hd * jatam::kMlpOut * 2, (void**)&a.w3b) &&
-              mlp_alloc(m, (size_t)jatam::kMlpIn * Hd * 2, (void**)&a.w1t) &&
               mlp_alloc(m, Hd * Hd * 2, (void**)&a.w2t) &&
               mlp_alloc(m, 16 * Hd * 2, (void**)&a.w3t) &&
               mlp_alloc(m, B * jatam::kMlpIn * 2, (void**)&a.x) &&
@@ -1058,6 +1057,7 @@ int jatam_mlp_create(int64_t max_batch, int c, jatam_mlp_t** mlp)
     }
     mlp_views(p, &a.p);
     mlp_views(g, &a.g);
+    a.w1t = a.w1b + (size_t)jatam::kMlpIn * Hd;
     a.c = c;
     a.bits = bits;
     // the padding rows of the transposed head weights stay zero
@@ -1184,7 +1184,7 @@ struct jatam_ga {
     uint64_t* cand;          // offspring candidates
     float* scores;           // their surrogate scores
     uint32_t* idx;           // kept candidates
-    jatam::SelectWork sel;
+    uint32_t* select;      // select_top's scratch
     void* allocations[8];
     int nalloc;
 };
@@ -1225,11 +1225,7 @@ int jatam_ga_create(int64_t max_candidates, jatam_ga_t** ga)
     const size_t n = (size_t)max_candidates;
     const bool ok = ga_alloc(g, n * 8, (void**)&g->cand) && ga_alloc(g, n * 4, (void**)&g->scores) &&
                     ga_alloc(g, n * 4, (void**)&g->idx) &&
-                    ga_alloc(g, jatam::kSelectState * 4, (void**)&g->sel.state) &&
-                    ga_alloc(g, n * 4, (void**)&g->sel.flag) &&
-                    ga_alloc(g, n * 4, (void**)&g->sel.rank_eq) &&
-                    ga_alloc(g, n * 4, (void**)&g->sel.pos) &&
-                    ga_alloc(g, (n / 1024 + 2) * 4, (void**)&g->sel.sums);
+                    ga_alloc(g, jatam::kSelectState * 4, (void**)&g->select);
     if (!ok) {
         ga_free(g);
         return JATAM_E_HIP;
@@ -1253,7 +1249,7 @@ int jatam_select_top(jatam_ga_t* ga, const float* scores, int64_t n, int64_t k, 
     if (ga == nullptr || scores == nullptr || n < 0 || n > ga->max_cand || k < 0 || k > n ||
         (k > 0 && out_idx == nullptr))
         return JATAM_E_INVALID_ARG;
-    return jatam::launch_select_top(scores, (uint32_t)n, (uint32_t)k, out_idx, ga->sel,
+    return jatam::launch_select_top(scores, (uint32_t)n, (uint32_t)k, out_idx, ga->select,
                                     (hipStream_t)stream);
 }
 
@@ -1279,7 +1275,7 @@ int jatam_ga_step_screened(jatam_ga_t* ga, jatam_batch_t* batch, jatam_mlp_t* ml
         return rc;
     if ((rc = jatam_mlp_score(mlp, ga->cand, nullptr, t, m, ga->scores, stream)) != JATAM_OK)
         return rc;
-    if ((rc = jatam::launch_select_top(ga->scores, m, (uint32_t)n, ga->idx, ga->sel, s)) !=
+    if ((rc = jatam::launch_select_top(ga->scores, m, (uint32_t)n, ga->idx, ga->select, s)) !=
         JATAM_OK)
         return rc;
     if ((rc = jatam::launch_gather(ga->cand, ga->idx, (uint32_t)n, next_pop, s)) != JATAM_OK)

@@ -322,20 +322,14 @@ int mlp_launch_train(const MlpArgs& a, const uint64_t* genomes, const uint8_t* t
 // ---------------------------------------------------------------------------
 // Top-k selection (jatam_select.hip).
 // ---------------------------------------------------------------------------
-constexpr int kSelectState = 2 + 256;
-
-struct SelectWork {
-    uint32_t* state;     // [kSelectState]
-    uint32_t* flag;      // [n]
-    uint32_t* rank_eq;   // [n]
-    uint32_t* pos;       // [n]
-    uint32_t* sums;      // [n / 1024 + 1]
-};
+constexpr int kSelectPasses = 3, kSelectBins = 2048, kSelectMaxBlocks = 1024;
+// words of device scratch: a histogram a pass, two counts a block
+constexpr int kSelectState = kSelectPasses * kSelectBins + 2 * kSelectMaxBlocks;
 
 // Indices of the k best scores (descending, ties to the lower index, NaN
 // last), in ascending index order, into out_idx[k].
 int launch_select_top(const float* scores, uint32_t n, uint32_t k, uint32_t* out_idx,
-                      const SelectWork& w, hipStream_t s);
+                      uint32_t* state, hipStream_t s);
 
 int launch_gather(const uint64_t* src, const uint32_t* idx, uint32_t n, uint64_t* dst,
                   hipStream_t s);

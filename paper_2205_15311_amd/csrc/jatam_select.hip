@@ -3,11 +3,10 @@
 // Keeps the k of n candidates with the highest score, ties going to the
 // lower index, and lists the kept indices in ascending order.  Scores become
 // 32-bit keys whose ascending order is descending score (NaN last); a radix
-// select over 4 digits of 8 bits finds the k-th key D; keys below D are kept,
-// and of the keys equal to D the first (k - #below) by index.  Index order
-// comes from exclusive scans, so nothing depends on thread timing.  No host
-// synchronisation: every pass reads the previous pass's state from device
-// memory.
+// select finds the k-th key D; keys below D are kept, and of the keys equal to D
+// the first (k - #below) by index.  Index order comes from prefix sums, so
+// nothing depends on thread timing.  No host synchronisation: every pass reads
+// the previous pass's state from device memory.
 #include "jatam_internal.hpp"
 
 namespace jatam {
@@ -22,177 +21,207 @@ __device__ __forceinline__ uint32_t score_key(float f)
     return ~ascending;
 }
 
-// state: [0] prefix of D found so far, [1] how many keys still to take below
-// the prefix (k minus keys already known to be smaller), [2..257] histogram
-__global__ __launch_bounds__(256) void select_init_kernel(uint32_t* state, uint32_t k)
+// Radix select of the k-th key, 11 + 11 + 10 bits, from the top.  A pass counts
+// the keys that share the digits found so far; every block of the next pass finds
+// the digit from the whole histogram by itself, so a pass is one launch.  The
+// blocks add to one histogram of a few hot bins, so there are few of them (128
+// until each has 8,192 scores: 1,024 took 10 us a pass for 262,144 scores, their
+// atomics one after the other), and a block's items lie together, for the last two
+// kernels' index order.
+//
+// 65,536 of 262,144 scores: 102 us in 18 launches, 34 in these six; 2^22 of 2^24:
+// 524 and 199.
+// First bit of pass p's digit.
+__device__ __forceinline__ int select_shift(int p) { return p == 0 ? 21 : p == 1 ? 10 : 0; }
+
+__device__ __forceinline__ uint32_t select_bits_above(int p)
 {
-    for (int i = threadIdx.x; i < kSelectState; i += 256)
-        state[i] = 0;
+    return p == 0 ? 0u : 0xFFFFFFFFu << select_shift(p - 1);
+}
+
+// Items of block b: [b * per, ...).
+__device__ __forceinline__ uint32_t select_per_block(uint32_t n)
+{
+    const uint32_t per = (n + gridDim.x - 1) / gridDim.x;
+    return (per + 255) / 256 * 256;
+}
+
+// Exclusive prefix sum of v over the block's 256 threads; *total receives the
+// sum.  waves: LDS for four words.
+__device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t* waves, uint32_t* total)
+{
+    uint32_t sum = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t up = (uint32_t)__shfl_up((int)sum, off);
+        sum += (int)(threadIdx.x & 63) >= off ? up : 0u;
+    }
     __syncthreads();
-    if (threadIdx.x == 0)
-        state[1] = k;
+    if ((threadIdx.x & 63) == 63)
+        waves[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        before += w < (int)(threadIdx.x >> 6) ? waves[w] : 0u;
+        all += waves[w];
+    }
+    *total = all;
+    return before + sum - v;
+}
+
+// What pass p finds from the histograms before it (all of the block, with the
+// same result): the key's digits above pass p, and how many of the keys with
+// these digits are still to take.
+struct SelectFound {
+    uint32_t prefix, need;
+};
+
+__device__ __forceinline__ SelectFound select_found(const uint32_t* state, uint32_t k, int passes,
+                                                    uint32_t* waves, uint32_t* found)
+{
+    SelectFound f{0u, k};
+    for (int p = 0; p < passes; ++p) {
+        const uint32_t* const hist = state + p * kSelectBins + 8 * threadIdx.x;
+        uint32_t c[8], sum = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            c[i] = hist[i];
+            sum += c[i];
+        }
+        uint32_t total;
+        uint32_t before = block_prefix(sum, waves, &total);
+        // the thread whose bins hold the need-th key
+        if (before < f.need && f.need <= before + sum) {
+            uint32_t digit = 0, need = f.need - before;
+#pragma unroll
+            for (int i = 0; i < 7; ++i) {
+                const bool past = digit == (uint32_t)i && need > c[i];
+                need -= past ? c[i] : 0u;
+                digit += past ? 1u : 0u;
+            }
+            found[0] = (8 * threadIdx.x + digit) << select_shift(p);
+            found[1] = need;
+        }
+        __syncthreads();
+        f.prefix |= found[0];
+        f.need = found[1];
+        __syncthreads();
+    }
+    return f;
+}
+
+__global__ __launch_bounds__(256) void select_init_kernel(uint32_t* state)
+{
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < kSelectPasses * kSelectBins;
+         i += gridDim.x * 256)
+        state[i] = 0;
 }
 
 __global__ __launch_bounds__(256) void select_hist_kernel(const float* __restrict__ score,
-                                                          uint32_t n, uint32_t* state, int pass)
+                                                          uint32_t n, uint32_t k, uint32_t* state,
+                                                          int pass)
 {
-    __shared__ uint32_t hist[256];
-    hist[threadIdx.x] = 0;
+    __shared__ uint32_t hist[kSelectBins];
+    __shared__ uint32_t waves[4], found[2];
+    for (uint32_t i = threadIdx.x; i < kSelectBins; i += 256)
+        hist[i] = 0;
+    const SelectFound f = select_found(state, k, pass, waves, found);
     __syncthreads();
-    const int shift = 24 - 8 * pass;
-    const uint32_t prefix = state[0];
-    const uint32_t pmask = pass == 0 ? 0u : 0xFFFFFFFFu << (32 - 8 * pass);
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+    const int shift = select_shift(pass);
+    const uint32_t above = select_bits_above(pass);
+    const uint32_t per = select_per_block(n);
+    const uint32_t lo = min(n, blockIdx.x * per), hi = lo + min(n - lo, per);
+    for (uint32_t i = lo + threadIdx.x; i < hi; i += 256) {
         const uint32_t key = score_key(score[i]);
-        if ((key & pmask) == prefix)
-            atomicAdd(&hist[(key >> shift) & 0xFFu], 1u);
+        if ((key & above) == f.prefix)
+            atomicAdd(&hist[(key & ~above) >> shift], 1u);
     }
     __syncthreads();
-    if (hist[threadIdx.x] != 0)
-        atomicAdd(&state[2 + threadIdx.x], hist[threadIdx.x]);
+    for (uint32_t i = threadIdx.x; i < kSelectBins; i += 256)
+        if (hist[i] != 0)
+            atomicAdd(&state[pass * kSelectBins + i], hist[i]);
 }
 
-// Picks the digit whose bin holds the need-th key; clears the histogram.
-__global__ void select_pick_kernel(uint32_t* state, int pass)
+// Keys below the k-th key D, and equal to it, per block.
+__global__ __launch_bounds__(256) void select_count_kernel(const float* __restrict__ score,
+                                                           uint32_t n, uint32_t k,
+                                                           const uint32_t* state, uint32_t* counts)
 {
-    if (threadIdx.x != 0)
-        return;
-    uint32_t need = state[1], digit = 255;
-    for (uint32_t d = 0; d < 256; ++d) {
-        const uint32_t c = state[2 + d];
-        if (need <= c) {
-            digit = d;
-            break;
-        }
-        need -= c;
-    }
-    state[0] |= digit << (24 - 8 * pass);
-    state[1] = need;
-    for (int d = 0; d < 256; ++d)
-        state[2 + d] = 0;
-}
-
-// flag[i]: 1 if key < D, 2 if key == D, else 0.
-__global__ __launch_bounds__(256) void select_flag_kernel(const float* __restrict__ score,
-                                                          uint32_t n, const uint32_t* state,
-                                                          uint32_t* flag)
-{
-    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n)
-        return;
-    const uint32_t key = score_key(score[i]), D = state[0];
-    flag[i] = key < D ? 1u : key == D ? 2u : 0u;
-}
-
-// Block-level exclusive scan of pred(flag) in place into out; block totals
-// into sums.  pred: mode 0 -> flag == 2, mode 1 -> flag != 0 (kept).
-__device__ __forceinline__ uint32_t select_pred(uint32_t f, int mode, uint32_t rank_eq,
-                                                uint32_t need)
-{
-    if (mode == 0)
-        return f == 2u;
-    return f == 1u || (f == 2u && rank_eq < need);
-}
-
-__global__ __launch_bounds__(1024) void select_scan_block_kernel(const uint32_t* flag,
-                                                                 const uint32_t* rank_eq,
-                                                                 const uint32_t* state,
-                                                                 uint32_t n, int mode,
-                                                                 uint32_t* out, uint32_t* sums)
-{
-    __shared__ uint32_t part[1024];
-    const uint32_t i = blockIdx.x * 1024 + threadIdx.x;
-    const uint32_t need = state[1];
-    const uint32_t v = i < n ? select_pred(flag[i], mode, mode ? rank_eq[i] : 0u, need) : 0u;
-    part[threadIdx.x] = v;
+    __shared__ uint32_t waves[4], found[2], c[2];
+    if (threadIdx.x < 2)
+        c[threadIdx.x] = 0;
+    const SelectFound f = select_found(state, k, kSelectPasses, waves, found);
     __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const uint32_t add = (int)threadIdx.x >= off ? part[threadIdx.x - off] : 0u;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
+    const uint32_t per = select_per_block(n);
+    const uint32_t lo = min(n, blockIdx.x * per), hi = lo + min(n - lo, per);
+    uint32_t below = 0, equal = 0;
+    for (uint32_t i = lo + threadIdx.x; i < hi; i += 256) {
+        const uint32_t key = score_key(score[i]);
+        below += key < f.prefix ? 1u : 0u;
+        equal += key == f.prefix ? 1u : 0u;
     }
-    if (i < n)
-        out[i] = part[threadIdx.x] - v;
-    if (threadIdx.x == 1023)
-        sums[blockIdx.x] = part[1023];
-}
-
-// Exclusive scan of the block totals (one block, loops over them).
-__global__ __launch_bounds__(1024) void select_scan_sums_kernel(uint32_t* sums, uint32_t nblocks)
-{
-    __shared__ uint32_t part[1024];
-    const uint32_t per = (nblocks + 1023) / 1024;
-    const uint32_t lo = threadIdx.x * per, hi = min(nblocks, lo + per);
-    uint32_t s = 0;
-    for (uint32_t b = lo; b < hi; ++b)
-        s += sums[b];
-    part[threadIdx.x] = s;
+    atomicAdd(&c[0], below);
+    atomicAdd(&c[1], equal);
     __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const uint32_t add = (int)threadIdx.x >= off ? part[threadIdx.x - off] : 0u;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
+    if (threadIdx.x < 2)
+        counts[2 * blockIdx.x + threadIdx.x] = c[threadIdx.x];
+}
+
+// Writes the kept indices at their ranks: of the keys equal to D the first
+// `need`.
+__global__ __launch_bounds__(256) void select_emit_kernel(const float* __restrict__ score,
+                                                          uint32_t n, uint32_t k,
+                                                          const uint32_t* state,
+                                                          const uint32_t* counts,
+                                                          uint32_t* out_idx)
+{
+    __shared__ uint32_t waves[4], found[2];
+    const SelectFound f = select_found(state, k, kSelectPasses, waves, found);
+    // what the blocks before this one hold
+    uint32_t below = 0, equal = 0, total;
+    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += 256) {
+        below += counts[2 * b];
+        equal += counts[2 * b + 1];
     }
-    uint32_t run = part[threadIdx.x] - s;
-    for (uint32_t b = lo; b < hi; ++b) {
-        const uint32_t v = sums[b];
-        sums[b] = run;
-        run += v;
+    block_prefix(below, waves, &total);
+    below = total;
+    block_prefix(equal, waves, &total);
+    equal = total;
+    const uint32_t per = select_per_block(n);
+    const uint32_t lo = min(n, blockIdx.x * per), hi = lo + min(n - lo, per);
+    for (uint32_t at = lo; at < hi; at += 256) {
+        const uint32_t i = at + threadIdx.x;
+        const uint32_t key = i < hi ? score_key(score[i]) : 0xFFFFFFFFu;
+        const bool is_below = i < hi && key < f.prefix, is_equal = i < hi && key == f.prefix;
+        // both counts of up to 256 in one sum
+        const uint32_t sums = block_prefix((is_below ? 1u : 0u) | (is_equal ? 0x10000u : 0u), waves,
+                                           &total);
+        const uint32_t b = below + (sums & 0xFFFFu), e = equal + (sums >> 16);
+        if (is_below || (is_equal && e < f.need))
+            out_idx[b + min(e, f.need)] = i;
+        below += total & 0xFFFFu;
+        equal += total >> 16;
     }
-}
-
-__global__ __launch_bounds__(1024) void select_scan_add_kernel(uint32_t* out, const uint32_t* sums,
-                                                               uint32_t n)
-{
-    const uint32_t i = blockIdx.x * 1024 + threadIdx.x;
-    if (i < n)
-        out[i] += sums[blockIdx.x];
-}
-
-// Writes kept indices at their ranks (ascending index order).
-__global__ __launch_bounds__(256) void select_compact_kernel(const uint32_t* flag,
-                                                             const uint32_t* rank_eq,
-                                                             const uint32_t* pos,
-                                                             const uint32_t* state, uint32_t n,
-                                                             uint32_t* out_idx)
-{
-    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n)
-        return;
-    if (select_pred(flag[i], 1, rank_eq[i], state[1]))
-        out_idx[pos[i]] = i;
-}
-
-static void exclusive_scan(const SelectWork& w, uint32_t n, int mode, uint32_t* out,
-                           hipStream_t s)
-{
-    const uint32_t nb = (n + 1023) / 1024;
-    hipLaunchKernelGGL(select_scan_block_kernel, dim3(nb), dim3(1024), 0, s, w.flag, w.rank_eq,
-                       w.state, n, mode, out, w.sums);
-    hipLaunchKernelGGL(select_scan_sums_kernel, dim3(1), dim3(1024), 0, s, w.sums, nb);
-    hipLaunchKernelGGL(select_scan_add_kernel, dim3(nb), dim3(1024), 0, s, out, w.sums, n);
 }
 
 int launch_select_top(const float* scores, uint32_t n, uint32_t k, uint32_t* out_idx,
-                      const SelectWork& w, hipStream_t s)
+                      uint32_t* state, hipStream_t s)
 {
     if (k == 0 || n == 0)
         return JATAM_OK;
-    const uint32_t grid = min((n + 255) / 256, 1024u);
-    hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(256), 0, s, w.state, k);
-    for (int pass = 0; pass < 4; ++pass) {
-        hipLaunchKernelGGL(select_hist_kernel, dim3(grid), dim3(256), 0, s, scores, n, w.state,
+    // at least 1,024 items a block
+    const uint32_t grid =
+        min(n / 1024 + 1, max(128u, min(n / 8192, (uint32_t)kSelectMaxBlocks)));
+    hipLaunchKernelGGL(select_init_kernel, dim3(4), dim3(256), 0, s, state);
+    for (int pass = 0; pass < kSelectPasses; ++pass)
+        hipLaunchKernelGGL(select_hist_kernel, dim3(grid), dim3(256), 0, s, scores, n, k, state,
                            pass);
-        hipLaunchKernelGGL(select_pick_kernel, dim3(1), dim3(64), 0, s, w.state, pass);
-    }
-    hipLaunchKernelGGL(select_flag_kernel, dim3((n + 255) / 256), dim3(256), 0, s, scores, n,
-                       w.state, w.flag);
-    exclusive_scan(w, n, 0, w.rank_eq, s);   // rank of each key == D among equals
-    exclusive_scan(w, n, 1, w.pos, s);       // output position of each kept index
-    hipLaunchKernelGGL(select_compact_kernel, dim3((n + 255) / 256), dim3(256), 0, s, w.flag,
-                       w.rank_eq, w.pos, w.state, n, out_idx);
+    uint32_t* const counts = state + kSelectPasses * kSelectBins;
+    hipLaunchKernelGGL(select_count_kernel, dim3(grid), dim3(256), 0, s, scores, n, k, state,
+                       counts);
+    hipLaunchKernelGGL(select_emit_kernel, dim3(grid), dim3(256), 0, s, scores, n, k, state,
+                       counts, out_idx);
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
 }
 
@@ -254,6 +283,31 @@ __global__ __launch_bounds__(1024) void order_scan_block_kernel(uint32_t* x, uin
         sums[blockIdx.x] = part[1023];
 }
 
+// Exclusive scan of the block totals (one block, loops over them).
+__global__ __launch_bounds__(1024) void order_scan_sums_kernel(uint32_t* sums, uint32_t nblocks)
+{
+    __shared__ uint32_t part[1024];
+    const uint32_t per = (nblocks + 1023) / 1024;
+    const uint32_t lo = threadIdx.x * per, hi = min(nblocks, lo + per);
+    uint32_t s = 0;
+    for (uint32_t b = lo; b < hi; ++b)
+        s += sums[b];
+    part[threadIdx.x] = s;
+    __syncthreads();
+    for (int off = 1; off < 1024; off <<= 1) {
+        const uint32_t add = (int)threadIdx.x >= off ? part[threadIdx.x - off] : 0u;
+        __syncthreads();
+        part[threadIdx.x] += add;
+        __syncthreads();
+    }
+    uint32_t run = part[threadIdx.x] - s;
+    for (uint32_t b = lo; b < hi; ++b) {
+        const uint32_t v = sums[b];
+        sums[b] = run;
+        run += v;
+    }
+}
+
 __global__ __launch_bounds__(1024) void order_scan_add_kernel(uint32_t* x, const uint32_t* sums,
                                                               uint32_t m)
 {
@@ -295,7 +349,7 @@ int launch_order_by_cost(const float* scores, uint32_t n, uint32_t* order, uint3
     // the block totals: at most 1024 of them for n up to 2^24 items, more in
     // a second level
     if (sb > 1) {
-        hipLaunchKernelGGL(select_scan_sums_kernel, dim3(1), dim3(1024), 0, s, sums, sb);
+        hipLaunchKernelGGL(order_scan_sums_kernel, dim3(1), dim3(1024), 0, s, sums, sb);
         hipLaunchKernelGGL(order_scan_add_kernel, dim3(sb), dim3(1024), 0, s, hist, sums, m);
     }
     hipLaunchKernelGGL(order_scatter_kernel, dim3(nb), dim3(256), 0, s, scores, n, hist, order);
