@@ -82,7 +82,7 @@ def stage_ops(gold):
 
 COUNTER_PROFILE = os.path.join(ROOT, "profiles", "batched_pipeline_s28_g16_r20_counters.md")
 KERNEL_SOURCES = ("jatam_batched.hip", "jatam_assembly.hpp", "jatam_device.hpp",
-                  "jatam_internal.hpp")
+                  "jatam_internal.hpp", "jatam_waves.hpp", "jatam_shapes.hpp")
 
 
 def code_text(src):
@@ -756,10 +756,9 @@ def main():
     tuning, tune_log = (batch.get_tuning(GRID), []) if args.no_autotune else \
         batch.autotune(0, TOTAL, T, C, GRID, RUNS, TUNE_SEED)
 
-    # graph paths: one captured slice pipeline (2^20 or 2^22 genotypes),
-    # replayed 16 or 4 times; the workspace is tuned for the slice it
-    # replays (a 2^20 slice leaves each of the one-call grid's waves only a
-    # few chunks)
+    # graph paths: an enumeration in slices of 2^20 or 2^22 genotypes (one
+    # launch on this grid; above 16 a captured slice pipeline replayed per
+    # slice, for which the workspace is tuned)
     if "graph" in paths:
         for slice_n in (SLICE, 4 * SLICE):
             reps = TOTAL // slice_n
@@ -778,8 +777,8 @@ def main():
                 "value": TOTAL * args.steps / (graph_total_ms / 1e3),
                 "ms_per_step": graph_total_ms / args.steps, "bit_exact": graph_ok,
                 "tuning": graph_tuning,
-                "kernel": f"one captured 2^{slice_n.bit_length() - 1}-genotype slice pipeline, "
-                          f"{reps} hipGraph replays"}
+                "kernel": f"enumeration in {reps} slices of 2^{slice_n.bit_length() - 1} "
+                          f"genotypes: solo_kernel<16>, all slices in one launch"}
     graph_batch.close()
 
     # batched + surrogate path: the network (trained untimed, on genotypes

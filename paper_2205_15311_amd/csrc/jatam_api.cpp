@@ -525,9 +525,12 @@ int jatam_batch_enumerate(jatam_batch_t* batch, uint64_t first, int64_t slice, i
                 batch, p, (int64_t)(total - at < kPiece ? total - at : kPiece),
                 out != nullptr ? out + at : nullptr, tally);
             a.first = first + at;
-            a.refill = batch->tune[0].refill;
-            a.dyn16 = batch->tune[0].claim_share;
-            a.claim_chunks = batch->tune[0].claim_chunks;
+            // the default refill and claims: a workspace's own are the pipeline's
+            // (tuned for it on a slice, an enumeration took 1.8 instead of 1.2 ms)
+            const jatam_tuning_t tuning = jatam::default_tuning(0);
+            a.refill = tuning.refill;
+            a.dyn16 = tuning.claim_share;
+            a.claim_chunks = tuning.claim_chunks;
             if ((rc = jatam::launch_solo(a, classes, waves, geno, shapes, log2cap, s)) != JATAM_OK)
                 return rc;
         }
