@@ -4,9 +4,8 @@
 One step = classification of all 2^24 two-tile genotypes (c=8, G=16, R=20,
 seed 1), no input read from HBM, 256 MiB of records written to HBM.  Four
 paths are timed on the same stream:
-  plain      16 launches of the plain kernel over 2^20-genotype ranges,
-  graph      one captured pipeline of a 2^20-genotype slice, replayed 16 times
-             (and of a 2^22 slice, replayed 4 times),
+  plain      16 plain calls over 2^20-genotype ranges (one launch each),
+  graph      an enumeration in 16 slices of 2^20 genotypes (and in 4 of 2^22),
   surrogate  the trained network's predicted cost of every genotype, the
              queue ordered by it, the pipelined call in that order (scoring
              and ordering inside the timed step),

@@ -625,7 +625,7 @@ int jatam_true_class_range(jatam_truth_t* w, uint64_t first, int64_t n, int t, i
                            int grid_limit, int64_t cap, jatam_result_t* out, void* stream);
 
 /* ------------------------------------------------------------------------
- * Classification variants, by the plain kernel (one lane per genotype):
+ * Classification variants (one lane per genotype, all of its runs):
  *   JATAM_VARIANT_C4    DET shapes hashed up to rotation only (§3.3 names the
  *                       four rotations): the four rotation hashes sorted
  *                       ascending and hashed again as 16 little-endian bytes

@@ -1,7 +1,7 @@
 // jatam_batched.hip - pipelined classification without global queues.
 //
-// The plain kernel gives each lane a whole genotype, so a wave lasts as long
-// as its slowest genotype: on S_{2,8} the sum over waves of the slowest lane's
+// With a whole genotype to each lane a wave lasts as long as its slowest
+// genotype: on S_{2,8} the sum over waves of the slowest lane's
 // work is ~7x the total work.  Here the classification is split by what the
 // work actually is, into three stages per grid class (W = 16 or 32):
 //
@@ -49,7 +49,7 @@
 // every wave serialise); and the second repeat queue's counter, one atomic
 // per wave and round of the first pass.  Every other queue is a per-wave
 // segment or a scan.  Records are identical
-// to the plain kernel's: each is a pure function of the genotype, never of
+// on every route: each is a pure function of the genotype, never of
 // the schedule.
 #include "jatam_waves.hpp"
 

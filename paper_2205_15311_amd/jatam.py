@@ -699,8 +699,9 @@ class Batch:
                   grid_limit: int = 16, runs: int = 20, seed: int = 1,
                   out: torch.Tensor | None = None, tally: torch.Tensor | None = None,
                   shapes: torch.Tensor | None = None, stream=None):
-        """jatam_batch_enumerate: `slices` graph replays of one slice's
-        pipeline over [first, first + slice_n * slices).  out: None or an
+        """jatam_batch_enumerate over [first, first + slice_n * slices): one
+        launch for grid_limit <= 16, `slices` graph replays of one slice's
+        pipeline above.  out: None or an
         int32 (slice_n * slices, 4) tensor; shapes: None or a table as for
         shape_histogram (int64 (capacity, 2))."""
         if out is not None:
