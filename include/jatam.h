@@ -222,8 +222,12 @@ int jatam_batch_set_refill(jatam_batch_t* batch, int idle_lanes);
 /*
  * Launch parameters of the pipeline for one grid class (G <= 16 or
  * 16 < G <= 32).  None of them changes a record.  Calls of up to 2^20 items
- * with the default parameters of both classes and without the timing hook are
- * made by one launch that does the whole classification instead.
+ * without the timing hook are made by one launch that does the whole
+ * classification, not by the pipeline, unless the caller has set other
+ * parameters than the defaults for a grid class that the call may use (its G's;
+ * both for mixed items) with jatam_batch_set_tuning, jatam_batch_set_refill or
+ * jatam_classify_batch's `tune`.  What the autotuner finds is used wherever the
+ * pipeline runs and does not change which calls it makes.
  *   refill        first runs: a wave refills once this many of its 64 lanes
  *                 are idle, 1..64 (default 24)
  *   first_waves   persistent one-wave workgroups per CU of the first-run
@@ -334,7 +338,8 @@ int jatam_batch_set_tuning(jatam_batch_t* batch, int grid_limit, const jatam_tun
  * {0, 4, 8, 12, 16}, claim_chunks in {1, 2, 4, 8} and the three
  * repeat_mapping values, keeping a
  * value when the median of three timed calls improves by more than 1%
- * (less is within run-to-run noise).  Every candidate's records are
+ * (less is within run-to-run noise).  Every timed call runs the pipeline,
+ * whatever n is.  Every candidate's records are
  * compared with the starting configuration's, bit for bit: a difference
  * stops the search with JATAM_E_MISMATCH.  The best parameters found are
  * set on the workspace and written to *best (if not NULL).
@@ -352,7 +357,7 @@ int jatam_batch_autotune(jatam_batch_t* batch, uint64_t first, int64_t n, int t,
  *    "refill": .., "first_waves": .., "repeat_waves": .., "wide_layout": ..,
  *    "claim_share": .., "claim_chunks": .., "repeat_mapping": ..}
  * keyed by the device, grid_limit's class, t, c and runs.  A valid entry
- * for the key is applied (jatam_batch_set_tuning) and *from_cache = 1;
+ * for the key is set on the workspace, as if just found, and *from_cache = 1;
  * otherwise jatam_batch_autotune runs (arguments as there) and the file is
  * rewritten with the new entry added (other keys kept, a broken line of this
  * key dropped; written to path.tmp, then renamed), *from_cache = 0.

@@ -20,7 +20,9 @@ struct jatam_batch {
     int64_t max_n;
     int cus;                       // compute units of the device
     jatam::BatchOccupancy occ;     // resident blocks per CU
-    jatam_tuning_t tune[2];        // launch parameters per grid class
+    jatam_tuning_t tune[2];        // the pipeline's launch parameters per grid class
+    bool chosen[2];                // set by the caller (set_tuning, set_refill) to others
+                                   // than the defaults: the class's calls run the pipeline
     std::vector<std::pair<jatam_tuning_t, double>> tune_log;   // last autotune
     jatam::DeviceWorkspace ws;
     void* allocations[24];
@@ -241,27 +243,41 @@ static int next_marks(jatam_batch_t* b, hipEvent_t** marks, uint8_t** launched)
     return JATAM_OK;
 }
 
-// Launches the pipeline with the workspace's parameters, or `tune` for this
-// call.  grid_limit: the uniform G of the call, or 0 for mixed items (both
-// grid classes).  marks/launched: timing hook or nullptr.
+// Whether a call takes the one launch or the pipeline: by its size, or always the
+// pipeline.
+enum class Route { kBySize, kPipeline };
 
-static int launch_pipeline(jatam_batch_t* b, const jatam::BatchArgs& a, int grid_limit,
-                           int max_t, hipStream_t stream, hipEvent_t* marks, uint8_t* launched,
-                           const jatam_tuning_t* tune = nullptr)
+// Sets a class's parameters.  Those a caller chose are meant for its calls, which
+// then run the pipeline; those the autotuner found are the pipeline's wherever it
+// runs, and the calls that the one launch makes faster than any of them keep it
+// (1,000 two-tile items 50 us, the pipeline 123; 2^20 215 and 255).
+static void set_class_tuning(jatam_batch_t* b, int k, const jatam_tuning_t& t, bool by_caller)
 {
-    return jatam::launch_tuned(tune != nullptr ? tune : b->tune, b->occ, b->cus, a, grid_limit,
-                               max_t, stream, marks, launched);
+    b->tune[k] = t;
+    b->chosen[k] = by_caller && !jatam::same_tuning(t, jatam::default_tuning(k));
 }
 
-static int launch_timed(jatam_batch_t* b, const jatam::BatchArgs& a, int grid_limit, int max_t,
-                        hipStream_t stream)
+// The route of a call on the workspace's own parameters (grid_limit 0: mixed items).
+static Route route_of(const jatam_batch_t* b, int grid_limit)
+{
+    const bool narrow = b->chosen[0] && grid_limit <= 16;
+    const bool wide = b->chosen[1] && (grid_limit == 0 || grid_limit > 16);
+    return narrow || wide ? Route::kPipeline : Route::kBySize;
+}
+
+// Launches a classification with the workspace's parameters, or `tune` for this
+// call.  grid_limit: the uniform G of the call, or 0 for mixed items (both
+// grid classes).
+static int launch_call(jatam_batch_t* b, const jatam::BatchArgs& a, int grid_limit, int max_t,
+                       hipStream_t stream, Route route, const jatam_tuning_t* tune = nullptr)
 {
     hipEvent_t* marks;
     uint8_t* launched;
     const int rc = next_marks(b, &marks, &launched);
     if (rc != JATAM_OK)
         return rc;
-    return launch_pipeline(b, a, grid_limit, max_t, stream, marks, launched);
+    return jatam::launch_tuned(tune != nullptr ? tune : b->tune, b->occ, b->cus, a, grid_limit,
+                               max_t, stream, marks, launched, route == Route::kPipeline);
 }
 
 static bool batch_alloc(jatam_batch_t* b, size_t bytes, void** out)
@@ -290,7 +306,7 @@ int jatam_batch_create(int64_t max_n, jatam_batch_t** batch)
     b->graph_exec = nullptr;
     b->graph_stream = nullptr;
     for (int k = 0; k < 2; ++k)
-        b->tune[k] = jatam::default_tuning(k);
+        set_class_tuning(b, k, jatam::default_tuning(k), false);
     hipDeviceProp_t prop;
     if (hipGetDevice(&b->device) != hipSuccess ||
         hipGetDeviceProperties(&prop, b->device) != hipSuccess) {
@@ -365,12 +381,12 @@ int jatam_batch_classify(jatam_batch_t* batch, const uint64_t* genotypes, int64_
         return JATAM_E_INVALID_ARG;
     jatam::BatchArgs a = batch_args(batch, p, n, out, tally);
     a.genomes = genotypes;
-    return launch_timed(batch, a, grid_limit, t, (hipStream_t)stream);
+    return launch_call(batch, a, grid_limit, t, (hipStream_t)stream, route_of(batch, grid_limit));
 }
 
-int jatam_batch_classify_range(jatam_batch_t* batch, uint64_t first, int64_t n, int t, int c,
-                               int grid_limit, int runs, uint64_t seed, jatam_result_t* out,
-                               uint64_t* tally, void* stream)
+static int classify_range(jatam_batch_t* batch, uint64_t first, int64_t n, int t, int c,
+                          int grid_limit, int runs, uint64_t seed, jatam_result_t* out,
+                          uint64_t* tally, hipStream_t stream, const Route* route)
 {
     jatam::Params p;
     int rc = jatam::make_params(t, c, grid_limit, runs, seed, &p);
@@ -385,7 +401,16 @@ int jatam_batch_classify_range(jatam_batch_t* batch, uint64_t first, int64_t n, 
     }
     jatam::BatchArgs a = batch_args(batch, p, n, out, tally);
     a.first = first;
-    return launch_timed(batch, a, grid_limit, t, (hipStream_t)stream);
+    return launch_call(batch, a, grid_limit, t, stream,
+                       route != nullptr ? *route : route_of(batch, grid_limit));
+}
+
+int jatam_batch_classify_range(jatam_batch_t* batch, uint64_t first, int64_t n, int t, int c,
+                               int grid_limit, int runs, uint64_t seed, jatam_result_t* out,
+                               uint64_t* tally, void* stream)
+{
+    return classify_range(batch, first, n, t, c, grid_limit, runs, seed, out, tally,
+                          (hipStream_t)stream, nullptr);
 }
 
 int jatam_batch_classify_range_ordered(jatam_batch_t* batch, uint64_t first, int64_t n, int t,
@@ -408,7 +433,7 @@ int jatam_batch_classify_range_ordered(jatam_batch_t* batch, uint64_t first, int
     jatam::BatchArgs a = batch_args(batch, p, n, out, tally);
     a.first = first;
     a.order = order;
-    return launch_timed(batch, a, grid_limit, t, (hipStream_t)stream);
+    return launch_call(batch, a, grid_limit, t, (hipStream_t)stream, route_of(batch, grid_limit));
 }
 
 int64_t jatam_order_work_words(int64_t n)
@@ -450,7 +475,7 @@ int jatam_batch_classify_items_ordered(jatam_batch_t* batch, const jatam_item_t*
     jatam::BatchArgs a = batch_args(batch, p, n, out, tally);
     a.items = items;
     a.order = order;
-    return launch_timed(batch, a, 0, 4, (hipStream_t)stream);
+    return launch_call(batch, a, 0, 4, (hipStream_t)stream, route_of(batch, 0));
 }
 
 int jatam_classify_batch(jatam_batch_t* batch, const jatam_item_t* items, int64_t n, int c,
@@ -470,11 +495,12 @@ int jatam_classify_batch(jatam_batch_t* batch, const jatam_item_t* items, int64_
     jatam::BatchArgs a = batch_args(batch, p, n, out, tally);
     a.items = items;
     a.order = order;
-    hipEvent_t* marks;
-    uint8_t* launched;
-    if ((rc = next_marks(batch, &marks, &launched)) != JATAM_OK)
-        return rc;
-    return launch_pipeline(batch, a, 0, 4, (hipStream_t)stream, marks, launched, tune);
+    // parameters for this call are the caller's choice too
+    const bool given = tune != nullptr && !(jatam::same_tuning(tune[0], jatam::default_tuning(0)) &&
+                                            jatam::same_tuning(tune[1], jatam::default_tuning(1)));
+    const Route route = given ? Route::kPipeline
+                      : tune != nullptr ? Route::kBySize : route_of(batch, 0);
+    return launch_call(batch, a, 0, 4, (hipStream_t)stream, route, tune);
 }
 
 int jatam_batch_enumerate(jatam_batch_t* batch, uint64_t first, int64_t slice, int64_t slices,
@@ -545,7 +571,8 @@ int jatam_batch_enumerate(jatam_batch_t* batch, uint64_t first, int64_t slice, i
     hipStream_t cs = batch->capture_stream;
     if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess)
         return JATAM_E_HIP;
-    rc = launch_pipeline(batch, a, grid_limit, t, cs, nullptr, nullptr);
+    rc = jatam::launch_tuned(batch->tune, batch->occ, batch->cus, a, grid_limit, t, cs, nullptr,
+                             nullptr, true);
     if (rc == JATAM_OK && shapes != nullptr)
         rc = jatam::launch_shape_hist(a.out, (uint64_t)slice, shapes, log2cap, nullptr,
                                       batch->cus, out != nullptr ? a.slice : nullptr, cs);
@@ -578,8 +605,11 @@ int jatam_batch_set_refill(jatam_batch_t* batch, int idle_lanes)
 {
     if (batch == nullptr || idle_lanes < 1 || idle_lanes > 64)
         return JATAM_E_INVALID_ARG;
-    batch->tune[0].refill = idle_lanes;
-    batch->tune[1].refill = idle_lanes;
+    for (int k = 0; k < 2; ++k) {
+        jatam_tuning_t t = batch->tune[k];
+        t.refill = idle_lanes;
+        set_class_tuning(batch, k, t, true);
+    }
     return JATAM_OK;
 }
 
@@ -596,7 +626,7 @@ int jatam_batch_set_tuning(jatam_batch_t* batch, int grid_limit, const jatam_tun
     if (batch == nullptr || tuning == nullptr || grid_limit < 8 || grid_limit > 32 ||
         !tuning_valid(grid_limit, tuning))
         return JATAM_E_INVALID_ARG;
-    batch->tune[grid_limit <= 16 ? 0 : 1] = *tuning;
+    set_class_tuning(batch, grid_limit <= 16 ? 0 : 1, *tuning, true);
     return JATAM_OK;
 }
 
@@ -621,14 +651,17 @@ int jatam_batch_autotune(jatam_batch_t* batch, uint64_t first, int64_t n, int t,
     }
     batch->tune_log.clear();
     int rc = JATAM_OK;
-    // median of three timed calls after one warm-up; records into `dst`
+    // median of three timed calls after one warm-up, on the pipeline whatever the
+    // sample's size (the parameters are its, and the one launch of a small sample
+    // would be timed against it); records into `dst`
+    const Route pipeline = Route::kPipeline;
     auto measure = [&](jatam_result_t* dst, double* ms) -> int {
         float v[3];
         for (int r = 0; r < 4; ++r) {
             if (r > 0 && hipEventRecord(e0, s) != hipSuccess)
                 return JATAM_E_HIP;
-            const int q = jatam_batch_classify_range(batch, first, n, t, c, grid_limit, runs,
-                                                     seed, dst, nullptr, stream);
+            const int q = classify_range(batch, first, n, t, c, grid_limit, runs, seed, dst,
+                                         nullptr, s, &pipeline);
             if (q != JATAM_OK)
                 return q;
             if (r > 0) {
@@ -709,7 +742,7 @@ int jatam_batch_autotune(jatam_batch_t* batch, uint64_t first, int64_t n, int t,
         }
     }
 done:
-    batch->tune[k] = cur;
+    set_class_tuning(batch, k, cur, false);
     if (best != nullptr)
         *best = cur;
     (void)hipEventDestroy(e0);
@@ -830,9 +863,7 @@ int jatam_batch_autotune_cached(jatam_batch_t* batch, const char* path, uint64_t
         fclose(f);
     }
     if (have) {
-        const int rc = jatam_batch_set_tuning(batch, grid_limit, &found);
-        if (rc != JATAM_OK)
-            return rc;
+        set_class_tuning(batch, grid_limit <= 16 ? 0 : 1, found, false);
         if (best != nullptr)
             *best = found;
         if (from_cache != nullptr)
@@ -1393,7 +1424,7 @@ constexpr int64_t kWindowMinItems = 1 << 20;
 // 382 : 465, 540 : 743 (the pipeline's window), 1448 : 925.
 constexpr int64_t kSoloItems = 1 << 20;
 
-static bool same_tuning(const jatam_tuning_t& x, const jatam_tuning_t& y)
+bool same_tuning(const jatam_tuning_t& x, const jatam_tuning_t& y)
 {
     return x.refill == y.refill && x.first_waves == y.first_waves &&
            x.repeat_waves == y.repeat_waves && x.wide_layout == y.wide_layout &&
@@ -1403,14 +1434,12 @@ static bool same_tuning(const jatam_tuning_t& x, const jatam_tuning_t& y)
 
 int launch_tuned(const jatam_tuning_t tn[2], const BatchOccupancy& occ, int cus, BatchArgs a,
                  int grid_limit, int max_t, hipStream_t stream, hipEvent_t* marks,
-                 uint8_t* launched)
+                 uint8_t* launched, bool pipeline)
 {
     const int geno = geno_kind(max_t, a.c);
-    // Small calls: one launch instead of the pipeline's eight.  Only with the
-    // default parameters and without the timing hook, which are about the
-    // pipeline's stages.
-    if (a.n <= kSoloItems && marks == nullptr && a.slice == nullptr && same_tuning(tn[0], default_tuning(0)) &&
-        same_tuning(tn[1], default_tuning(1))) {
+    // Small calls: one launch instead of the pipeline's eight, but not with the
+    // timing hook, which is about the pipeline's stages.
+    if (!pipeline && a.n <= kSoloItems && marks == nullptr) {
         const bool one[2] = {grid_limit <= 16, grid_limit == 0 || grid_limit > 16};
         const int waves[2] = {occ.solo[0][geno] * cus, occ.solo[1][geno] * cus};
         return launch_solo(a, one, waves, geno, nullptr, 0, stream);

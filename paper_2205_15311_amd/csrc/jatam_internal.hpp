@@ -159,6 +159,7 @@ struct BatchOccupancy {
 void batch_occupancy(BatchOccupancy& occ);
 // Default launch parameters of a grid class.
 jatam_tuning_t default_tuning(int klass);
+bool same_tuning(const jatam_tuning_t& x, const jatam_tuning_t& y);
 // Largest first-run grid (one-wave blocks) over the classes and tile bounds.
 int max_first_blocks(const BatchOccupancy& occ, int cus);
 // Whether the size scan can cover that many first-run blocks.
@@ -215,12 +216,13 @@ int launch_neighbourhood_space(const jatam_result_t* space, uint64_t first, int6
 // Arguments of a pipelined call over a workspace (range mode, no order).
 BatchArgs batch_args_for(const Params& p, int64_t n, jatam_result_t* out, uint64_t* tally,
                          const DeviceWorkspace& ws);
-// Launches the pipeline with launch parameters tn[grid class], capped by the
-// residency limits occ on a device of `cus` compute units.  grid_limit: the
-// call's uniform G, or 0 for mixed items (both classes).
+// Launches a call: the one-launch kernel for a small one, unless `pipeline` or
+// `marks` is set; else the pipeline with launch parameters tn[grid class], capped
+// by the residency limits occ on a device of `cus` compute units.  grid_limit:
+// the call's uniform G, or 0 for mixed items (both classes).
 int launch_tuned(const jatam_tuning_t tn[2], const BatchOccupancy& occ, int cus, BatchArgs a,
                  int grid_limit, int max_t, hipStream_t stream, hipEvent_t* marks,
-                 uint8_t* launched);
+                 uint8_t* launched, bool pipeline);
 // When `marks` is not null, an event is recorded on the stream before stage
 // s (marks[2s]) and after it (marks[2s+1]), and launched[s] is set.
 // The one-launch classification (jatam_solo.hip) of the grid classes `classes`,
