@@ -178,8 +178,10 @@ int jatam_batch_classify_items(jatam_batch_t* batch, const jatam_item_t* items, 
  * Enumeration of a lexicographic range in slices: genotypes first .. first +
  * slice*slices - 1 (§3.4: the paper's slice-by-slice enumeration, here
  * without host work per slice).  For G <= 16 the slices are classified
- * together by the one-launch kernel, which needs no room per genotype.  Above,
- * with HIP graphs: the pipeline of one slice of `slice` genotypes (and, if
+ * together by the one-launch kernel, which needs no room per genotype and reads
+ * no launch parameters, unless the caller has set the class's parameters to
+ * others than the defaults (see jatam_tuning_t).  Else, and for G > 16, with HIP
+ * graphs and the workspace's launch parameters: the pipeline of one slice of `slice` genotypes (and, if
  * `shapes` is given, the shape histogram of its records) is captured once into
  * a graph whose kernels read the slice number from a device counter, then the
  * graph is launched `slices` times on `stream`, the counter advancing by one

@@ -538,7 +538,7 @@ int jatam_batch_enumerate(jatam_batch_t* batch, uint64_t first, int64_t slice, i
             return JATAM_E_HIP;
         drop_graph(batch);
     }
-    if (grid_limit <= 16) {
+    if (grid_limit <= 16 && route_of(batch, grid_limit) != Route::kPipeline) {
         // the one-launch kernel needs no staging, so the slices are taken
         // together, and counts shapes itself, so records that nobody asked
         // for are not written at all

@@ -64,6 +64,12 @@ class Batch:
             self.h, self.mem, ctypes.c_int64(n), 8, 20, ctypes.c_uint64(1), None, pair, self.mem,
             None, None))
 
+    def enumerate_(self, slice_n, slices, grid, shapes=True):
+        return self.host.count(lambda: self.lib.jatam_batch_enumerate(
+            self.h, ctypes.c_uint64(0), ctypes.c_int64(slice_n), ctypes.c_int64(slices), 2, 8,
+            grid, 20, ctypes.c_uint64(1), None, self.mem, self.mem if shapes else None,
+            ctypes.c_int64(64 if shapes else 0), None))
+
     def autotune(self, n, grid=16):
         best = Tuning()
         got = self.host.count(lambda: self.lib.jatam_batch_autotune(
@@ -138,3 +144,20 @@ def test_parameters_of_one_call(batch, host):
     assert batch.items(SMALL, other) == PIPE
     batch.set_tuning(16, refill=25)
     assert batch.items(SMALL, default) == ONE and batch.items(SMALL) == PIPE
+
+
+@pytest.mark.parametrize("grid", [16, 32])
+def test_enumeration_runs_on_the_parameters_the_caller_chose(batch, host, grid):
+    """One launch over all slices for G <= 16, or with chosen parameters of its
+    class the slice pipeline, captured once and replayed."""
+    one = ONE if grid == 16 else (0, 1, 1, 8)
+    assert batch.enumerate_(SMALL, 8, grid) == one
+    batch.set_tuning(48 - grid, refill=8)        # the other class's parameters
+    assert batch.enumerate_(SMALL, 8, grid) == one
+    host.fast_refill = 32
+    batch.autotune(SMALL, grid)
+    assert batch.enumerate_(SMALL, 8, grid) == one
+    batch.set_tuning(grid, refill=25, repeat_mapping=1)
+    assert batch.enumerate_(SMALL, 8, grid) == (0, 1, 1, 8)
+    assert (host.last_refill, host.last_mapping, host.last_n) == (25, 1, SMALL)
+    assert batch.enumerate_(SMALL, 8, grid, shapes=False) == (0, 1, 0, 8)
