@@ -42,6 +42,7 @@ __global__ __launch_bounds__(64, W == 16 ? 3 : 1) void solo_kernel(const BatchAr
     __shared__ uint32_t orient[8 * kSoloGroups];
     __shared__ uint4 cache_mem[kShapeCache];
     __shared__ uint32_t small_count[2];
+    __shared__ uint4 other_shapes[WaveShapeCache::kOther];
     uint32_t* const ring = smem + Grid::kSpare;   // survivor indices
     // the second list of a drain: the shapes are all proven then
     uint32_t* const undecided = reinterpret_cast<uint32_t*>(shapes);
@@ -50,10 +51,12 @@ __global__ __launch_bounds__(64, W == 16 ? 3 : 1) void solo_kernel(const BatchAr
     const uint32_t lane = (uint32_t)lane_id();
     Grid g{smem + threadIdx.x};
     g.clear_all();
-    WaveShapeCache cache{cache_mem, small_count};
+    WaveShapeCache cache{cache_mem, small_count, other_shapes};
     cache.clear((int)lane);
     if (lane < 2)
         small_count[lane] = 0;
+    if (lane < WaveShapeCache::kOther)
+        other_shapes[lane] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     RunState st{};
     WaveTally tally{{0, 0, 0, 0}};

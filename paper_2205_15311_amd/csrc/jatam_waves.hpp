@@ -191,14 +191,13 @@ __device__ __forceinline__ void count_shapes(const ShapeTable& table, WaveShapeC
                                              bool want, int size, bool fits, uint64_t key,
                                              uint32_t hash)
 {
-    if (table.entries == nullptr || !want)
+    if (table.entries == nullptr)
         return;
     // (monomers and dominoes have bitmaps like the rest)
-    if (size <= 2) {
+    const bool small = size <= 2;
+    if (want && small)
         atomicAdd(&cache.small_count[size - 1], 1u);
-    } else if (!fits || !cache.count(key)) {
-        table.add(shape_key(hash, size), 1);
-    }
+    cache.count_other(want && !small && (!fits || !cache.count(key)), hash, size, lane_id(), table);
 }
 
 // ---------------------------------------------------------------------------
