@@ -39,17 +39,18 @@ __global__ __launch_bounds__(256) void mutants_kernel(const uint64_t* __restrict
 
 constexpr int kNbLanes = 64;   // one-wave blocks: 64 lanes x up to 64 keys in LDS
 
-// Counts for genotype i, its mutants' keys already in keys[k * 64 + lane].
+// Counts for a genotype, its mutants' keys already in keys[k * lanes].
 __device__ __forceinline__ jatam_neighbourhood_t count_neighbourhood(const uint64_t* keys,
-                                                                     uint64_t own, int nbits)
+                                                                     uint64_t own, int nbits,
+                                                                     uint32_t lanes = kNbLanes)
 {
     int robust = 0, evolv = 0;
     for (int k = 0; k < nbits; ++k) {
-        const uint64_t kk = keys[k * kNbLanes];
+        const uint64_t kk = keys[(uint32_t)k * lanes];
         robust += kk == own;
         bool fresh = kk != own;
         for (int j = 0; j < k && fresh; ++j)
-            fresh = keys[j * kNbLanes] != kk;
+            fresh = keys[(uint32_t)j * lanes] != kk;
         evolv += fresh;
     }
     return jatam_neighbourhood_t{robust, evolv};
@@ -88,10 +89,12 @@ __global__ __launch_bounds__(kNbLanes) void neighbourhood_kernel(
 // compared their keys in pairs took 5.86 ms over S_{2,8}; this takes 0.32 ms.
 // ---------------------------------------------------------------------------
 constexpr int kNbSlots = 64;
-constexpr uint32_t kNbUnknown = 0xFFu;   // no number: the table was full
+constexpr uint32_t kNbLds = 1u << 16;    // bytes of LDS, a window's numbers or a recount's keys
 
-// The number of phenotype `key` in the window's table, entered if new.
-__device__ __forceinline__ uint32_t phenotype_number(unsigned long long* table, uint64_t key)
+// The number of phenotype `key` in the window's table, entered if new; `full` is
+// set (and any number returned) if it has no room left.
+__device__ __forceinline__ uint32_t phenotype_number(unsigned long long* table, uint64_t key,
+                                                     uint32_t& full)
 {
     if (key <= 2ull)
         return (uint32_t)key - 1u;   // UNBOUND, non-deterministic: entries 0 and 1
@@ -104,25 +107,8 @@ __device__ __forceinline__ uint32_t phenotype_number(unsigned long long* table, 
         if (seen == 0ull || seen == key)
             return s;
     }
-    return kNbUnknown;
-}
-
-// Counts of one genotype by reading its mutants' records in pairs: where the
-// window met more phenotypes than the table holds.
-__device__ jatam_neighbourhood_t count_from_space(const jatam_result_t* space, uint64_t g,
-                                                  int nbits)
-{
-    const uint64_t own = phenotype_key(space[g]);
-    int robust = 0, evolv = 0;
-    for (int k = 0; k < nbits; ++k) {
-        const uint64_t kk = phenotype_key(space[g ^ (1ull << k)]);
-        robust += kk == own;
-        bool fresh = kk != own;
-        for (int j = 0; j < k && fresh; ++j)
-            fresh = phenotype_key(space[g ^ (1ull << j)]) != kk;
-        evolv += fresh;
-    }
-    return jatam_neighbourhood_t{robust, evolv};
+    full = 1u;
+    return 0u;
 }
 
 // Four neighbouring genotypes' records.
@@ -136,12 +122,12 @@ struct Quad {
             r[q] = p[q];
     }
     // their phenotypes' numbers, one byte each
-    __device__ __forceinline__ uint32_t numbers(unsigned long long* table) const
+    __device__ __forceinline__ uint32_t numbers(unsigned long long* table, uint32_t& full) const
     {
         uint32_t v = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            v |= phenotype_number(table, phenotype_key(r[q])) << (8 * q);
+            v |= phenotype_number(table, phenotype_key(r[q]), full) << (8 * q);
         return v;
     }
 };
@@ -150,7 +136,6 @@ struct Quad {
 struct MutantSets {
     uint64_t set[4];
     uint32_t other;     // byte q: mutants with another phenotype than genotype q
-    uint32_t unknown;   // bit 7 of byte q: one of them has no number
     uint32_t own;       // byte q: genotype q's number
 
     // one mutant of each genotype, byte q the number of genotype q's
@@ -160,8 +145,7 @@ struct MutantSets {
         for (int q = 0; q < 4; ++q)
             set[q] |= 1ull << ((ids >> (8 * q)) & 63u);
         // numbers are below 64, so their XOR plus 0x7F has bit 7 iff they differ
-        other += ((((ids ^ own) & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) >> 7) & 0x01010101u;
-        unknown |= ids;
+        other += (((ids ^ own) + 0x7F7F7F7Fu) >> 7) & 0x01010101u;
     }
 };
 
@@ -169,8 +153,10 @@ __global__ __launch_bounds__(1024) void neighbourhood_space_kernel(
     const jatam_result_t* __restrict__ space, uint64_t first, uint64_t n, int nbits, int b,
     uint64_t window0, uint32_t windows, jatam_neighbourhood_t* __restrict__ out)
 {
-    extern __shared__ uint32_t ids[];   // 2^b numbers, four to a word
+    // 2^b numbers, four to a word (kNbLds bytes)
+    extern __shared__ __attribute__((aligned(16))) uint32_t ids[];
     __shared__ unsigned long long table[kNbSlots];
+    __shared__ uint32_t crowded;   // a phenotype found no room in the table
     const uint32_t tid = threadIdx.x, threads = blockDim.x;
     // workgroups go to the XCDs in turn: each XCD takes neighbouring windows
     const uint32_t per_xcd = (windows + 7u) / 8u;
@@ -180,7 +166,10 @@ __global__ __launch_bounds__(1024) void neighbourhood_space_kernel(
     const uint64_t base = (window0 + wi) << b;
     for (uint32_t s = tid; s < (uint32_t)kNbSlots; s += threads)
         table[s] = s < 2u ? s + 1ull : 0ull;
+    if (tid == 0)
+        crowded = 0u;
     __syncthreads();
+    uint32_t full = 0;
     const uint32_t words = (1u << b) / 4u;
     // records are loaded a round ahead of their lookups: the loads of one
     // round, four a lane, are what hides their own latency
@@ -189,17 +178,20 @@ __global__ __launch_bounds__(1024) void neighbourhood_space_kernel(
     for (uint32_t i = tid; i < words; i += threads) {
         const Quad cur = next;
         next.load(space + base + 4u * (i + threads < words ? i + threads : i));
-        ids[i] = cur.numbers(table);
+        ids[i] = cur.numbers(table, full);
     }
+    if (full != 0)
+        crowded = 1u;
     __syncthreads();
-    for (uint32_t i = tid; i < words; i += threads) {
+    const uint32_t sets = crowded == 0u ? words : 0u;
+    for (uint32_t i = tid; i < sets; i += threads) {
         const uint64_t g0 = base + 4u * i;
         if (g0 + 3u < first || g0 >= first + n)
             continue;
         if (b < nbits)
             next.load(space + (g0 ^ (1ull << b)));
         const uint32_t own = ids[i];
-        MutantSets m{{0ull, 0ull, 0ull, 0ull}, 0u, own, own};
+        MutantSets m{{0ull, 0ull, 0ull, 0ull}, 0u, own};
         // bits 0 and 1: the other genotypes of the word
         m.add(((own >> 8) & 0x00FF00FFu) | ((own << 8) & 0xFF00FF00u));
         m.add((own >> 16) | (own << 16));
@@ -208,7 +200,7 @@ __global__ __launch_bounds__(1024) void neighbourhood_space_kernel(
         for (int k = b; k < nbits; ++k) {
             const Quad cur = next;
             next.load(space + (g0 ^ (1ull << (k + 1 < nbits ? k + 1 : k))));
-            m.add(cur.numbers(table));
+            m.add(cur.numbers(table, full));
         }
 #pragma unroll
         for (uint32_t q = 0; q < 4; ++q) {
@@ -218,10 +210,25 @@ __global__ __launch_bounds__(1024) void neighbourhood_space_kernel(
             jatam_neighbourhood_t c;
             c.robust = nbits - (int)((m.other >> (8 * q)) & 0xFFu);
             c.evolv = __popcll(m.set[q] & ~(1ull << ((own >> (8 * q)) & 63u)));
-            if ((m.unknown >> (8 * q)) & 0x80u)
-                c = count_from_space(space, g, nbits);
             out[g - first] = c;
         }
+    }
+    if (full != 0)
+        crowded = 1u;
+    __syncthreads();
+    if (crowded == 0u)
+        return;
+    // More phenotypes than the table holds: the window's counts once more, a
+    // genotype a lane, its mutants' keys in LDS in place of the numbers and
+    // compared in pairs.  2^24 genotypes of 200 phenotypes 6.3 ms (13 of them, which
+    // the table holds, 0.28); with the pairs' records read from memory 20.3.
+    uint64_t* const keys = reinterpret_cast<uint64_t*>(ids);
+    const uint32_t lanes = min(threads, kNbLds / 8u / (uint32_t)nbits / 64u * 64u);
+    const uint64_t last = min(first + n, base + (1ull << b));
+    for (uint64_t g = max(first, base) + tid; tid < lanes && g < last; g += lanes) {
+        for (int k = 0; k < nbits; ++k)
+            keys[(uint32_t)k * lanes + tid] = phenotype_key(space[g ^ (1ull << k)]);
+        out[g - first] = count_neighbourhood(keys + tid, phenotype_key(space[g]), nbits, lanes);
     }
 }
 
@@ -258,7 +265,9 @@ int launch_neighbourhood_space(const jatam_result_t* space, uint64_t first, int6
                                jatam_neighbourhood_t* out, hipStream_t s)
 {
     // windows of 2^16 genotypes (a byte each in LDS), smaller ones while they
-    // would leave compute units idle; at least one thread's four genotypes
+    // would leave compute units idle; at least one thread's four genotypes.  All
+    // with the LDS of the largest: of the smaller ones there are at most two a
+    // compute unit, and a crowded window needs it for its keys.
     int b = nbits < 16 ? nbits : 16;
     while (b > 10 && (n >> b) < 256)
         --b;
@@ -269,7 +278,7 @@ int launch_neighbourhood_space(const jatam_result_t* space, uint64_t first, int6
     for (uint64_t w = w0; w <= w1; w += per_launch) {
         const uint32_t windows = (uint32_t)(w1 - w + 1u < per_launch ? w1 - w + 1u : per_launch);
         hipLaunchKernelGGL(neighbourhood_space_kernel, dim3((windows + 7u) / 8u * 8u),
-                           dim3(threads), (size_t)1 << b, s, space, first, (uint64_t)n, nbits, b,
+                           dim3(threads), (size_t)kNbLds, s, space, first, (uint64_t)n, nbits, b,
                            w, windows, out);
     }
     return hipGetLastError() == hipSuccess ? JATAM_OK : JATAM_E_HIP;
