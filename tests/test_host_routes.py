@@ -86,10 +86,13 @@ def batch(host):
 
 
 def test_size_decides_by_default(batch):
-    for grid in (8, 16, 18, 32):
-        assert batch.range_(SMALL, grid) == ONE and batch.list_(1 << 20, grid) == ONE
-        assert batch.range_(LARGE, grid) == PIPE and batch.list_(LARGE, grid) == PIPE
-    assert batch.items(SMALL) == ONE and batch.items(LARGE) == PIPE
+    for grid, most in ((8, 1 << 20), (16, 1 << 20), (18, 1 << 19), (32, 1 << 19)):
+        for n in (1, SMALL, most):
+            assert batch.range_(n, grid) == ONE and batch.list_(n, grid) == ONE
+        for n in (most + 1, LARGE):
+            assert batch.range_(n, grid) == PIPE and batch.list_(n, grid) == PIPE
+    assert batch.items(SMALL) == ONE and batch.items((1 << 20) - 1) == ONE
+    assert batch.items(1 << 20) == PIPE and batch.items(LARGE) == PIPE
 
 
 @pytest.mark.parametrize("n", [SMALL, 1 << 20, LARGE])
