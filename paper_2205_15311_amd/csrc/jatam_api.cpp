@@ -1176,9 +1176,14 @@ int jatam_mlp_train_step(jatam_mlp_t* mlp, const uint64_t* genomes, const uint8_
         labels == nullptr || !(lr >= 0.f) ||
         (t == nullptr && (t_all < 1 || t_all > 3)))
         return JATAM_E_INVALID_ARG;
-    const int step = lr > 0.f ? ++mlp->step : mlp->step;
-    return jatam::mlp_launch_train(mlp->a, genomes, t, t_all, labels, (uint32_t)n, pad32(n), lr,
-                                   step, loss_out, (hipStream_t)stream);
+    // a step that fails leaves the step count, and so Adam's bias correction, as
+    // they were
+    const int step = mlp->step + (lr > 0.f ? 1 : 0);
+    const int rc = jatam::mlp_launch_train(mlp->a, genomes, t, t_all, labels, (uint32_t)n, pad32(n),
+                                           lr, step, loss_out, (hipStream_t)stream);
+    if (rc == JATAM_OK)
+        mlp->step = step;
+    return rc;
 }
 
 int jatam_mlp_predict(jatam_mlp_t* mlp, int kind, const uint64_t* genomes, const uint8_t* t,

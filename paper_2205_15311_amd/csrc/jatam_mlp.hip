@@ -927,6 +927,9 @@ int mlp_launch_train(const MlpArgs& a, const uint64_t* genomes, const uint8_t* t
     const uint32_t products = (uint32_t)(kGradTiles * g.splits / 4);
     hipLaunchKernelGGL(mlp_grad_kernel, dim3(products + 3u * (uint32_t)g.chunks), dim3(256), 0, s,
                        a, g, n, n_pad, products);
+    // without both of these the parameters stay as they are
+    if (hipGetLastError() != hipSuccess)
+        return JATAM_E_HIP;
     const float bc1 = 1.f - powf(0.9f, (float)step);
     const float bc2 = 1.f - powf(0.999f, (float)step);
     hipLaunchKernelGGL(mlp_update_kernel, dim3((kMlpParams + 255) / 256 + 1), dim3(256), 0, s, a,
