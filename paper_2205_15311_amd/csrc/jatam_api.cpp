@@ -71,30 +71,6 @@ std::vector<int> wave_choices(int occ)
     return v;
 }
 
-// Compute units and residency limits of a device, queried once per device.
-struct DeviceLimits {
-    std::once_flag once;
-    int cus = 0;
-    int solo[2][jatam::kGenoKinds] = {};
-};
-
-// The current device's limits; nullptr if they cannot be had.
-const DeviceLimits* device_limits()
-{
-    static DeviceLimits limits[64];
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
-        return nullptr;
-    DeviceLimits& d = limits[dev];
-    std::call_once(d.once, [&d, dev] {
-        if (hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-            hipSuccess)
-            d.cus = 0;
-        jatam::solo_occupancy(d.solo);
-    });
-    return d.cus > 0 ? &d : nullptr;
-}
-
 // Classification without a workspace: the one-launch kernel, every chunk dealt
 // out (there is nowhere to keep claim counters).
 int classify_solo(const uint64_t* genotypes, uint64_t first, int64_t n, const jatam::Params& p,
@@ -102,7 +78,7 @@ int classify_solo(const uint64_t* genotypes, uint64_t first, int64_t n, const ja
 {
     if (n == 0)
         return JATAM_OK;
-    const DeviceLimits* d = device_limits();
+    const jatam::DeviceLimits* d = jatam::device_limits();
     if (d == nullptr)
         return JATAM_E_HIP;
     const int geno = jatam::geno_kind(p.t, p.c);
@@ -1353,6 +1329,26 @@ extern "C" int jatam_shape_histogram(const jatam_result_t* recs, int64_t n,
 // the call without a workspace.
 // ---------------------------------------------------------------------------
 namespace jatam {
+
+const DeviceLimits* device_limits()
+{
+    static DeviceLimits limits[64];
+    static std::mutex mutex;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
+        return nullptr;
+    DeviceLimits& d = limits[dev];
+    std::lock_guard<std::mutex> lock(mutex);
+    if (d.cus <= 0) {
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
+                hipSuccess || cus <= 0)
+            return nullptr;   // asked again by the next call
+        solo_occupancy(d.solo);
+        d.cus = cus;
+    }
+    return &d;
+}
 
 // Class 0 (G <= 16) makes its repeat runs in two passes (on S_2,8 most
 // candidates left after the proofs are non-deterministic and decided by run

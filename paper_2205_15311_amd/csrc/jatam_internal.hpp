@@ -157,6 +157,13 @@ struct BatchOccupancy {
     int solo[2][kGenoKinds];
 };
 void batch_occupancy(BatchOccupancy& occ);
+// Compute units of a device and the one-launch kernel's residency there, kept once
+// they are known.  device_limits: the current device's; nullptr if they cannot be had.
+struct DeviceLimits {
+    int cus = 0;
+    int solo[2][kGenoKinds] = {};
+};
+const DeviceLimits* device_limits();
 // Default launch parameters of a grid class.
 jatam_tuning_t default_tuning(int klass);
 bool same_tuning(const jatam_tuning_t& x, const jatam_tuning_t& y);

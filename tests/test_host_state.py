@@ -29,3 +29,18 @@ def test_failed_training_step_keeps_the_step_count(host):
     assert train(0.0) == 0 and host.last_step == 2      # gradients only
     assert train(1e-3) == 0 and host.last_step == 3
     lib.jatam_mlp_destroy(net)
+
+
+def test_failed_device_query_is_asked_again(host):
+    mem = ctypes.create_string_buffer(64)
+
+    def classify():
+        return host.lib.jatam_classify(mem, ctypes.c_int64(8), 2, 8, 16, 20, ctypes.c_uint64(1), mem,
+                                       None)
+
+    host.fail_attribute = 2
+    assert classify() == host_api.E_HIP and classify() == host_api.E_HIP
+    assert host.solo_launches == 0
+    assert classify() == 0 and host.solo_launches == 1
+    host.fail_attribute = 1          # known by now
+    assert classify() == 0 and host.solo_launches == 2
