@@ -303,13 +303,13 @@ int jatam_batch_create(int64_t max_n, jatam_batch_t** batch)
         return JATAM_E_UNSUPPORTED;
     }
     // one region, laid out by carve_workspace
-    const size_t bytes = jatam::carve_workspace(nullptr, (size_t)max_n, max_blocks, true, nullptr);
+    const size_t bytes = jatam::carve_workspace(nullptr, (size_t)max_n, max_blocks, nullptr);
     uint8_t* base = nullptr;
     if (!batch_alloc(b, bytes, (void**)&base)) {
         free_batch(b);
         return JATAM_E_HIP;
     }
-    jatam::carve_workspace(base, (size_t)max_n, max_blocks, true, &b->ws);
+    jatam::carve_workspace(base, (size_t)max_n, max_blocks, &b->ws);
     *batch = b;
     return JATAM_OK;
 }
@@ -1325,8 +1325,7 @@ extern "C" int jatam_shape_histogram(const jatam_result_t* recs, int64_t n,
 }
 
 // ---------------------------------------------------------------------------
-// Workspace layout and launch parameters, shared by the workspace calls and
-// the call without a workspace.
+// Workspace layout, launch parameters and routes.
 // ---------------------------------------------------------------------------
 namespace jatam {
 
@@ -1374,8 +1373,7 @@ bool scan_fits(int max_blocks)
     return (size_t)kSizeBuckets * max_blocks <= (size_t)kScanBlock * kMaxScanBlocks;
 }
 
-size_t carve_workspace(uint8_t* base, size_t max_n, int max_blocks, bool records,
-                       DeviceWorkspace* ws)
+size_t carve_workspace(uint8_t* base, size_t max_n, int max_blocks, DeviceWorkspace* ws)
 {
     size_t at = 0;
     auto take = [&](size_t bytes) -> void* {
@@ -1393,7 +1391,7 @@ size_t carve_workspace(uint8_t* base, size_t max_n, int max_blocks, bool records
     w.tally_slots =
         (unsigned long long*)take(kTallySlots * kTallyStride * sizeof(unsigned long long));
     w.seg_left = (uint32_t*)take(mb * sizeof(uint32_t));
-    w.records = records ? (jatam_result_t*)take(n * sizeof(jatam_result_t)) : nullptr;
+    w.records = (jatam_result_t*)take(n * sizeof(jatam_result_t));
     for (int k = 0; k < 2; ++k) {
         w.seg_count[k] = (uint32_t*)take(mb * sizeof(uint32_t));
         w.seg_hist[k] = (uint32_t*)take((size_t)kSizeBuckets * mb * sizeof(uint32_t));

@@ -173,10 +173,9 @@ int max_first_blocks(const BatchOccupancy& occ, int cus);
 bool scan_fits(int max_blocks);
 // Lays out a DeviceWorkspace for calls of up to max_n genotypes and first-run
 // grids of up to max_blocks blocks in one region at `base` (pieces aligned to
-// 256 bytes); `records` includes the GA generation's record array.  Returns
-// the region's size in bytes; with base == nullptr only the size.
-size_t carve_workspace(uint8_t* base, size_t max_n, int max_blocks, bool records,
-                       DeviceWorkspace* ws);
+// 256 bytes).  Returns the region's size in bytes; with base == nullptr only the
+// size.
+size_t carve_workspace(uint8_t* base, size_t max_n, int max_blocks, DeviceWorkspace* ws);
 // Validates and digests the arguments shared by every classification call.
 int make_params(int t, int c, int grid, int runs, uint64_t seed, Params* p);
 

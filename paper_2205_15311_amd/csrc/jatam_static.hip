@@ -1,15 +1,15 @@
-// jatam_static.hip - the pipelined classification for callers that cannot
-// allocate device memory (code under HIP graph capture, tight serving loops,
-// harnesses that forbid hipMalloc): the pipeline's queues live in a static
-// device array of the library instead of a jatam_batch_t workspace.
+// jatam_static.hip - classification for callers that cannot allocate device
+// memory (code under HIP graph capture, tight serving loops, harnesses that
+// forbid hipMalloc): the one-launch kernel, with the counter sets of a call's
+// tally in a static device array of the library instead of a jatam_batch_t
+// workspace.  It needs no other memory.
 //
-// `scratch` below is a host-side stand-in in host code: its device address
+// `counters` below is a host-side stand-in in host code: its device address
 // is taken once per device with hipGetSymbolAddress (with that device
 // current) and only that address is ever handed to kernels.  Every call on a
 // device shares the device's copy of the array, so calls that overlap on one
-// GPU race; the pipeline writes every queue entry and counter it reads
-// (counters by kernels, never by a memset), so nothing carries over from the
-// previous call.
+// GPU mix their tallies; each clears its counter sets first (by a kernel, never
+// a memset), so nothing carries over from the previous call.
 #include <mutex>
 
 #include "jatam_internal.hpp"
@@ -17,51 +17,34 @@
 namespace {
 
 constexpr int64_t kStaticMaxN = int64_t(1) << 18;   // genotypes per call
-constexpr size_t kStaticBytes = size_t(32) << 20;   // 32 MiB per device
 constexpr int kMaxDevices = 64;
 
-struct StaticDevice {
-    bool ready;
-    int cus;
-    jatam::BatchOccupancy occ;
-    jatam::DeviceWorkspace ws;
+struct StaticCounters {
+    unsigned long long tally[jatam::kTallySlots * jatam::kTallyStride];
+    uint32_t claims[2 * jatam::kClaimCounters * jatam::kClaimStride];   // cleared, not used
 };
 
-StaticDevice g_devices[kMaxDevices];
+StaticCounters* g_counters[kMaxDevices];
 std::mutex g_setup;
 
 }  // namespace
 
-__device__ __align__(256) uint8_t scratch[kStaticBytes];
+__device__ __align__(256) uint8_t counters[sizeof(StaticCounters)];
 
 namespace {
 
-// Set-up on the current device, once: the array's device address, the
-// residency limits and the workspace layout (runtime queries, so the first
-// call on a device must not be under graph capture).
-int static_setup(int dev, StaticDevice** out)
+// The array's address on the current device (a runtime query, so the first call on
+// a device must not be under graph capture).
+StaticCounters* static_counters(int dev)
 {
     std::lock_guard<std::mutex> lock(g_setup);
-    StaticDevice& d = g_devices[dev];
-    if (!d.ready) {
-        uint8_t* ptr = nullptr;
-        if (hipGetSymbolAddress((void**)&ptr, HIP_SYMBOL(scratch)) != hipSuccess ||
-            ptr == nullptr)
-            return JATAM_E_HIP;
-        if (hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-            hipSuccess)
-            return JATAM_E_HIP;
-        jatam::batch_occupancy(d.occ);
-        const int max_blocks = jatam::max_first_blocks(d.occ, d.cus);
-        if (!jatam::scan_fits(max_blocks) ||
-            jatam::carve_workspace(nullptr, (size_t)kStaticMaxN, max_blocks, false, nullptr) >
-                kStaticBytes)
-            return JATAM_E_UNSUPPORTED;
-        jatam::carve_workspace(ptr, (size_t)kStaticMaxN, max_blocks, false, &d.ws);
-        d.ready = true;
+    void* ptr = g_counters[dev];
+    if (ptr == nullptr) {
+        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(counters)) != hipSuccess)
+            return nullptr;
+        g_counters[dev] = (StaticCounters*)ptr;
     }
-    *out = &d;
-    return JATAM_OK;
+    return g_counters[dev];
 }
 
 }  // namespace
@@ -81,13 +64,17 @@ extern "C" int jatam_classify_static(const uint64_t* genotypes, int64_t n, int t
         return JATAM_E_HIP;
     if (dev >= kMaxDevices)
         return JATAM_E_UNSUPPORTED;
-    StaticDevice* d = nullptr;
-    const int sc = static_setup(dev, &d);
-    if (sc != JATAM_OK)
-        return sc;
-    jatam::BatchArgs a = jatam::batch_args_for(p, n, out, tally, d->ws);
+    const jatam::DeviceLimits* d = jatam::device_limits();
+    StaticCounters* const k = static_counters(dev);
+    if (d == nullptr || k == nullptr)
+        return JATAM_E_HIP;
+    jatam::DeviceWorkspace ws{};
+    ws.tally_slots = k->tally;
+    ws.run_claim = k->claims;
+    jatam::BatchArgs a = jatam::batch_args_for(p, n, out, tally, ws);
     a.genomes = genotypes;
-    const jatam_tuning_t tune[2] = {jatam::default_tuning(0), jatam::default_tuning(1)};
-    return jatam::launch_tuned(tune, d->occ, d->cus, a, grid_limit, t, (hipStream_t)stream,
-                               nullptr, nullptr, false);
+    const int geno = jatam::geno_kind(t, c);
+    const bool classes[2] = {grid_limit <= 16, grid_limit > 16};
+    const int waves[2] = {d->solo[0][geno] * d->cus, d->solo[1][geno] * d->cus};
+    return jatam::launch_solo(a, classes, waves, geno, nullptr, 0, (hipStream_t)stream);
 }

@@ -240,9 +240,8 @@ STATIC_MAX_N = 1 << 18
 def classify_static(genotypes: torch.Tensor, t: int, c: int = 8, grid_limit: int = 16,
                     runs: int = 20, seed: int = 1, out: torch.Tensor | None = None,
                     tally: torch.Tensor | None = None, stream=None) -> torch.Tensor:
-    """jatam_classify_static: the pipelined path with the library's static
-    device array as its workspace (n <= 2^18; no device allocation by the
-    library)."""
+    """jatam_classify_static: the one-launch classification with a tally and
+    without a workspace (n <= 2^18; no device allocation by the library)."""
     if genotypes.dtype not in (torch.int64, torch.uint64) or genotypes.dim() != 1:
         raise ValueError("genotypes must be a 1-D int64/uint64 tensor")
     if not genotypes.is_cuda or not genotypes.is_contiguous():
