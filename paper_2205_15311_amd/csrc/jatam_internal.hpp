@@ -334,6 +334,19 @@ constexpr int kSelectPasses = 3, kSelectBins = 2048, kSelectMaxBlocks = 1024;
 // words of device scratch: a histogram a pass, two counts a block
 constexpr int kSelectState = kSelectPasses * kSelectBins + 2 * kSelectMaxBlocks;
 
+// The scores of a block: whole rounds of 256, without a sum past 2^32 for any n.
+struct SelectRange {
+    uint32_t first, count;
+};
+__host__ __device__ inline SelectRange select_range(uint32_t n, uint32_t blocks, uint32_t block)
+{
+    const uint64_t per = ((uint64_t)n + 256ull * blocks - 1u) / (256ull * blocks) * 256u;
+    const uint64_t first = block * per;
+    if (first >= n)
+        return SelectRange{n, 0u};
+    return SelectRange{(uint32_t)first, (uint32_t)(n - first < per ? n - first : per)};
+}
+
 // Indices of the k best scores (descending, ties to the lower index, NaN
 // last), in ascending index order, into out_idx[k].
 int launch_select_top(const float* scores, uint32_t n, uint32_t k, uint32_t* out_idx,

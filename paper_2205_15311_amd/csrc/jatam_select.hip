@@ -39,13 +39,6 @@ __device__ __forceinline__ uint32_t select_bits_above(int p)
     return p == 0 ? 0u : 0xFFFFFFFFu << select_shift(p - 1);
 }
 
-// Items of block b: [b * per, ...).
-__device__ __forceinline__ uint32_t select_per_block(uint32_t n)
-{
-    const uint32_t per = (n + gridDim.x - 1) / gridDim.x;
-    return (per + 255) / 256 * 256;
-}
-
 // Exclusive prefix sum of v over the block's 256 threads; *total receives the
 // sum.  waves: LDS for four words.
 __device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t* waves, uint32_t* total)
@@ -130,10 +123,9 @@ __global__ __launch_bounds__(256) void select_hist_kernel(const float* __restric
     __syncthreads();
     const int shift = select_shift(pass);
     const uint32_t above = select_bits_above(pass);
-    const uint32_t per = select_per_block(n);
-    const uint32_t lo = min(n, blockIdx.x * per), hi = lo + min(n - lo, per);
-    for (uint32_t i = lo + threadIdx.x; i < hi; i += 256) {
-        const uint32_t key = score_key(score[i]);
+    const SelectRange r = select_range(n, gridDim.x, blockIdx.x);
+    for (uint32_t i = threadIdx.x; i < r.count; i += 256) {
+        const uint32_t key = score_key(score[r.first + i]);
         if ((key & above) == f.prefix)
             atomicAdd(&hist[(key & ~above) >> shift], 1u);
     }
@@ -153,11 +145,10 @@ __global__ __launch_bounds__(256) void select_count_kernel(const float* __restri
         c[threadIdx.x] = 0;
     const SelectFound f = select_found(state, k, kSelectPasses, waves, found);
     __syncthreads();
-    const uint32_t per = select_per_block(n);
-    const uint32_t lo = min(n, blockIdx.x * per), hi = lo + min(n - lo, per);
+    const SelectRange r = select_range(n, gridDim.x, blockIdx.x);
     uint32_t below = 0, equal = 0;
-    for (uint32_t i = lo + threadIdx.x; i < hi; i += 256) {
-        const uint32_t key = score_key(score[i]);
+    for (uint32_t i = threadIdx.x; i < r.count; i += 256) {
+        const uint32_t key = score_key(score[r.first + i]);
         below += key < f.prefix ? 1u : 0u;
         equal += key == f.prefix ? 1u : 0u;
     }
@@ -188,12 +179,12 @@ __global__ __launch_bounds__(256) void select_emit_kernel(const float* __restric
     below = total;
     block_prefix(equal, waves, &total);
     equal = total;
-    const uint32_t per = select_per_block(n);
-    const uint32_t lo = min(n, blockIdx.x * per), hi = lo + min(n - lo, per);
-    for (uint32_t at = lo; at < hi; at += 256) {
-        const uint32_t i = at + threadIdx.x;
-        const uint32_t key = i < hi ? score_key(score[i]) : 0xFFFFFFFFu;
-        const bool is_below = i < hi && key < f.prefix, is_equal = i < hi && key == f.prefix;
+    const SelectRange r = select_range(n, gridDim.x, blockIdx.x);
+    for (uint32_t at = 0; at < r.count; at += 256) {
+        const bool mine = at + threadIdx.x < r.count;
+        const uint32_t i = r.first + at + threadIdx.x;
+        const uint32_t key = mine ? score_key(score[i]) : 0xFFFFFFFFu;
+        const bool is_below = mine && key < f.prefix, is_equal = mine && key == f.prefix;
         // both counts of up to 256 in one sum
         const uint32_t sums = block_prefix((is_below ? 1u : 0u) | (is_equal ? 0x10000u : 0u), waves,
                                            &total);
@@ -210,9 +201,9 @@ int launch_select_top(const float* scores, uint32_t n, uint32_t k, uint32_t* out
 {
     if (k == 0 || n == 0)
         return JATAM_OK;
-    // at least 1,024 items a block
-    const uint32_t grid =
-        min(n / 1024 + 1, max(128u, min(n / 8192, (uint32_t)kSelectMaxBlocks)));
+    // 1,024 items a block, more once there are 128, 8,192 once those have as many
+    const uint32_t grid = min((n - 1u) / 1024u + 1u,
+                              max(128u, min(n / 8192u, (uint32_t)kSelectMaxBlocks)));
     hipLaunchKernelGGL(select_init_kernel, dim3(4), dim3(256), 0, s, state);
     for (int pass = 0; pass < kSelectPasses; ++pass)
         hipLaunchKernelGGL(select_hist_kernel, dim3(grid), dim3(256), 0, s, scores, n, k, state,
