@@ -86,8 +86,9 @@ struct LaneGrid {
 // nibble holds tag = id + 1 (mod 16), and a cell off the frontier is occupied
 // exactly when its nibble is not zero: so a step reads, tests and writes three
 // words less too.  Id 15 has tag 0, which is fine on the frontier (FR tells);
-// a cell placed with it takes the tag 1 instead, and the run's tiles count as
-// lost (its shape is then replayed rather than unpacked by the proof stage).
+// a cell placed with it takes the tag 1 instead, that of id 0, and the run's tiles
+// count as lost: its shape waits for a proof of its own, in which shape_ids tells
+// the two apart from their neighbours.
 // The occupied cells near the seed are kept as a bitmap in a register
 // (RunState::near) for the shape at the run's end.
 //
@@ -1244,7 +1245,7 @@ __device__ __forceinline__ bool same_cells(LeanGrid<W>& g, LeanGrid<W>& h, int G
 // without replaying the run: .x/.y the anchored 8 x 8 bitmap (bit 8y + x),
 // .z/.w a 64-bit word holding the tile nibble of every cell in ascending bit
 // order (at most kPackedCells cells) and, in bits 58..63, the seed's bit.
-// All ones in .z/.w: the shape does not fit (larger box or more cells).
+// All ones in .z/.w: no packed shape (larger box, more cells, or tiles' ids lost).
 // ---------------------------------------------------------------------------
 constexpr int kPackedCells = 14;
 
@@ -1257,6 +1258,74 @@ __device__ __forceinline__ bool packed_shape_valid(const uint4& v)
 __device__ __forceinline__ uint4 packed_none()
 {
     return make_uint4(0u, 0u, 0xFFFFFFFFu, 0xFFFFFFFFu);
+}
+
+// What a clean run's grid says of its tiles' ids: with `known`, the id of a cell is
+// tile_id's, or 15 in the cells of `last` (anchored 8 x 8 bitmap).
+struct TileIds {
+    bool known;
+    uint64_t last;
+
+    template <class Grid>
+    __device__ __forceinline__ uint32_t at(Grid& g, int x0, int y0, int b) const
+    {
+        return ((last >> b) & 1ull) != 0 ? 15u
+                                         : g.tile_id((y0 + (b >> 3)) * Grid::kW + x0 + (b & 7));
+    }
+};
+
+// The ids of the shape (shape_key8, if it `fits`) that a run without an event left.
+// Only a lean grid of a run that placed the sixteenth oriented tile is in doubt, in
+// the cells with id 0's tag.  Such a cell was placed because a neighbour placed before
+// it admits its tile there, and nothing else: so if its neighbours, each with any id
+// that it may have itself, admit only one of the two, that one it is.  (Not for
+// shapes beyond 8 x 8, which stay unproven with such a tile.)
+template <class Grid, class Src>
+__device__ __forceinline__ TileIds shape_ids(const Src& m, Grid& g, const RunState& st, int G,
+                                             bool fits, uint64_t shape, int x0, int y0)
+{
+    TileIds ids{true, 0ull};
+    if constexpr (Grid::kLean && Src::kManyIds) {
+        if (st.lost != 0) {
+            const int s = G / 2 - 1;
+            uint64_t doubt = 0;
+            if (fits)
+                for (uint64_t cells = shape & ~(1ull << ((s - y0) * 8 + (s - x0))); cells != 0;
+                     cells &= cells - 1) {
+                    const int b = __builtin_ctzll(cells);
+                    doubt |= (uint64_t)(ids.at(g, x0, y0, b) == 0u ? 1u : 0u) << b;
+                }
+            ids.known = fits;
+            const uint32_t zero = m.codes(m.oriented(0u)), last = m.codes(m.oriented(15u));
+            for (uint64_t cells = doubt; cells != 0; cells &= cells - 1) {
+                const int b = __builtin_ctzll(cells);
+                bool is_zero = false, is_last = false;
+                auto admits = [&](uint32_t code) {   // one tile only
+                    const bool one = (code & 0xC0u) == 0x80u;
+                    is_zero = is_zero | (one & ((code & 15u) == 0u));
+                    is_last = is_last | (one & ((code & 15u) == 15u));
+                };
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const bool inside = d == 0   ? b >= 8
+                                        : d == 1 ? (b & 7) < 7
+                                        : d == 2 ? b < 56
+                                                 : (b & 7) > 0;
+                    const int q = (b + (d == 0 ? -8 : d == 1 ? 1 : d == 2 ? 8 : -1)) & 63;
+                    const int from = 8 * ((d + 2) & 3);   // the neighbour's side
+                    if (inside && ((doubt >> q) & 1ull) != 0) {
+                        admits(zero >> from);
+                        admits(last >> from);
+                    } else if (inside && ((shape >> q) & 1ull) != 0) {
+                        admits(m.codes(m.oriented(TileIds{true, 0ull}.at(g, x0, y0, q))) >> from);
+                    }
+                }
+                ids.known = ids.known && is_zero != is_last;
+                ids.last |= (uint64_t)(is_last ? 1u : 0u) << b;
+            }
+        }
+    }
+    return ids;
 }
 
 // Packs the shape m (shape_key8) whose box starts at (x0, y0).
@@ -1290,20 +1359,19 @@ __device__ __forceinline__ bool packed_shape_is_guarded(const Src& src, const ui
                              [tiles](int, int k) { return (uint32_t)(tiles >> (4 * k)) & 15u; });
 }
 
-// Whether the shape left by a finished run is guarded; false, too, if one of
-// its tiles' ids was lost (LeanGrid).  key, x0, y0: shape_key8's, if it `fits`.
+// Whether the shape left by a finished run is guarded; false, too, if its tiles' ids
+// are not known.  key, x0, y0: shape_key8's, if it `fits`.
 template <class Grid, class Src>
-__device__ __forceinline__ bool shape_is_guarded(const Src& m, Grid& g, const RunState& st,
-                                                 int G, bool fits, uint64_t key, int x0, int y0)
+__device__ __forceinline__ bool shape_is_guarded(const Src& m, Grid& g, const TileIds& ids, int G,
+                                                 bool fits, uint64_t key, int x0, int y0)
 {
-    if (Grid::kLean && st.lost != 0)
+    if (!ids.known)
         return false;
     if (!fits)
         return shape_is_forced(m, g, G);
     const int s = G / 2 - 1;
-    return bitmap_is_guarded(m, key, 1ull << ((s - y0) * 8 + (s - x0)), [&](int b, int) {
-        return g.tile_id((y0 + (b >> 3)) * Grid::kW + x0 + (b & 7));
-    });
+    return bitmap_is_guarded(m, key, 1ull << ((s - y0) * 8 + (s - x0)),
+                             [&](int b, int) { return ids.at(g, x0, y0, b); });
 }
 
 // D4 hash of a shape given as an anchored 8 x 8 bitmap, by one lane.

@@ -458,7 +458,7 @@ __global__ __launch_bounds__(256) void sort_scatter_kernel(BatchArgs a, int klas
 // ---------------------------------------------------------------------------
 // prove<W>: one lane per candidate (in size order) takes its run-0 shape as
 // the first-run stage packed it (the sort moved it beside the candidate), or
-// replays run 0 where it did not fit, and checks whether the shape is guarded
+// replays run 0 where it did not fit or its ids were lost, and checks whether the shape is guarded
 // (shape_is_guarded; forced shapes are the case without conflicts): then
 // every run ends in it and the record is final without the repeat runs --
 // DET, run 0's size and hash, (size - 1) * R placements.  The other
@@ -501,7 +501,9 @@ __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
             size = st.size();
             int x0 = 0, y0 = 0;
             packed = ev == kEvNone && shape_key8(g, st, gd.grid, size, key, x0, y0);
-            forced = ev == kEvNone && shape_is_guarded(src, g, st, gd.grid, packed, key, x0, y0);
+            forced = ev == kEvNone &&
+                     shape_is_guarded(src, g, shape_ids(src, g, st, gd.grid, packed, key, x0, y0),
+                                      gd.grid, packed, key, x0, y0);
         }
     }
     // the hash of a packed or replayed shape from its bitmap, if it has one

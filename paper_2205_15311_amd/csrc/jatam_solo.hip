@@ -24,6 +24,13 @@ namespace jatam {
 
 constexpr int kSoloPend = 128;    // unproven candidates: drained above 64
 constexpr int kSoloShapes = 64;   // packed shapes waiting for a proof
+// An unproven candidate (positions are below 2^31) whose tiles' ids were lost, so that
+// it has had no proof; from this many of them in a wave's list on they get one, with a
+// run 0 of their own.  (Uniform four-tile lists have a few a wave: 2^20 of them 200
+// instead of 163 us with a proof for each.  Lists of such shapes only: 2^20 at G = 16
+// 189 us, 934 with all runs made.)
+constexpr uint32_t kLost = 1u << 31;
+constexpr uint32_t kLostProof = 16;
 
 // Three waves a SIMD in the 16 x 16 layout: twelve a CU, where LDS holds eleven
 // (with 177 registers two: an enumeration of S_{2,8} 1.27 instead of 1.21 ms).
@@ -63,7 +70,7 @@ __global__ __launch_bounds__(64, W == 16 ? 3 : 1) void solo_kernel(const BatchAr
     const uint32_t n_items = (uint32_t)a.n;
     ChunkSource chunks;
     chunks.init(a, klass, (n_items + chunk_items - 1) / chunk_items);
-    uint32_t head = 0, queued = 0, nshapes = 0, npend = 0;   // wave-uniform
+    uint32_t head = 0, queued = 0, nshapes = 0, npend = 0, nlost = 0;   // wave-uniform
     bool busy = false, starved = false;
     uint32_t idx = 0;
     Geno gd{};
@@ -107,29 +114,66 @@ __global__ __launch_bounds__(64, W == 16 ? 3 : 1) void solo_kernel(const BatchAr
             at = atomicAdd(open.count, npend);
         at = (uint32_t)__shfl((int)at, 0);
         for (uint32_t j = lane; j < npend; j += 64)
-            open.items[at + j] = open.base + pend[j];
+            open.items[at + j] = open.base + (pend[j] & ~kLost);
         npend = 0;
         wave_lds_sync();
     };
-    // Repeat rounds of rpass lanes per candidate over a list of indices; what
-    // they leave undecided to the second list.  Returns its length.
-    auto rounds = [&](int rpass, uint32_t* list, uint32_t count) -> uint32_t {
-        RepeatWave<W, M, true> rw(a, smem, orient, cache, st, tally, rpass, 0, false, undecided,
-                                  nullptr, table);
-        const uint32_t groups = (uint32_t)rw.groups, grp = (uint32_t)rw.grp;
-        for (uint32_t at = 0; at < count; at += groups) {
-            const bool active = grp < groups && at + grp < count;
-            rw.round(active, active ? list[at + grp] : 0u, 0u);
+    // Repeat rounds over the unproven candidates, in passes of ever more lanes each.
+    // A pass lists the candidates it leaves undecided for the next one, in the second
+    // list, which can be the one it reads: a round's candidates are read before it
+    // appends any, and are no fewer.
+    auto drain = [&]() {
+        uint32_t* list = pend;
+        uint32_t count = npend, kept = 0;
+        // runs 0-3 first
+        auto pass_after = [&](int runs) {
+            return runs < kRepeatFirstRuns && a.runs > 2 * kRepeatFirstRuns ? kRepeatFirstRuns
+                                                                            : a.runs;
+        };
+        int rpass = pass_after(0);
+        if (M::kManyIds && nlost >= kLostProof) {
+            wave_lds_sync();
+            uint32_t lost = 0;
+            for (uint32_t at = 0; at < npend; at += 64) {
+                const uint32_t i = at + lane < npend ? pend[at + lane] : 0u;
+                const bool there = at + lane < npend, is_lost = (i & kLost) != 0u;
+                const uint64_t lm = __ballot(is_lost), om = __ballot(there && !is_lost);
+                if (is_lost)
+                    pend[lost + (uint32_t)__popcll(lm & lanes_below())] = i;
+                else if (there)
+                    undecided[kept + (uint32_t)__popcll(om & lanes_below())] = i;
+                lost += (uint32_t)__popcll(lm);
+                kept += (uint32_t)__popcll(om);
+                wave_lds_sync();
+            }
+            rpass = 1;
+            count = lost;
         }
-        wave_lds_sync();
-        return rw.kept;
+        for (;;) {
+            RepeatWave<W, M, true> rw(a, smem, orient, cache, st, tally, rpass, 0, false, undecided,
+                                      nullptr, table);
+            rw.kept = kept;
+            const uint32_t groups = (uint32_t)rw.groups, grp = (uint32_t)rw.grp;
+            for (uint32_t at = 0; at < count; at += groups) {
+                const bool active = grp < groups && at + grp < count;
+                rw.round(active, active ? list[at + grp] & ~kLost : 0u, 0u);
+            }
+            wave_lds_sync();
+            if (rpass >= a.runs)
+                break;
+            list = undecided;
+            count = rw.kept;
+            kept = 0;
+            rpass = pass_after(rpass);
+        }
+        npend = nlost = 0;
     };
 
     for (;;) {
         // -- lanes whose first run is over ------------------------------------
         const bool finish = busy && run_over(ev, st, gd.grid);
         if (__ballot(finish) != 0) {
-            bool done = false, candidate = false, det = false, pack = false;
+            bool done = false, candidate = false, det = false, pack = false, lost = false;
             int cls = 0, steps = st.steps;
             jatam_result_t rec{0, 0, 0u, 0};
             if (finish) {
@@ -159,8 +203,10 @@ __global__ __launch_bounds__(64, W == 16 ? 3 : 1) void solo_kernel(const BatchAr
                 if (fits)
                     packed = pack_shape(g, st, gd.grid, st.size(), key, x0, y0);
                 pack = packed_shape_valid(packed);
+                lost = M::kManyIds && st.lost != 0;
                 // a shape too large to wait for the others is checked at once
-                if (!pack && shape_is_guarded(m, g, st, gd.grid, fits, key, x0, y0)) {
+                if (!pack && !lost &&
+                    shape_is_guarded(m, g, TileIds{true, 0ull}, gd.grid, fits, key, x0, y0)) {
                     candidate = false;
                     det = true;
                     steps = st.steps * a.runs;
@@ -191,8 +237,10 @@ __global__ __launch_bounds__(64, W == 16 ? 3 : 1) void solo_kernel(const BatchAr
             nshapes += (uint32_t)__popcll(pm);
             const uint64_t um = __ballot(candidate && !pack);
             if (candidate && !pack)
-                pend[npend + (uint32_t)__popcll(um & lanes_below())] = idx;
+                pend[npend + (uint32_t)__popcll(um & lanes_below())] = idx | (lost ? kLost : 0u);
             npend += (uint32_t)__popcll(um);
+            if constexpr (M::kManyIds && !kOpen)
+                nlost += (uint32_t)__popcll(__ballot(candidate && !pack && lost));
         }
         // -- refill idle lanes once enough of them wait, unless the list of
         // unproven candidates has to be worked off first: every waiting shape
@@ -251,15 +299,10 @@ __global__ __launch_bounds__(64, W == 16 ? 3 : 1) void solo_kernel(const BatchAr
             const bool over = queued == 0 && starved;
             if (full || over) {
                 prove_shapes();
-                if constexpr (kOpen) {
+                if constexpr (kOpen)
                     hand_over();
-                } else if (a.runs > 2 * kRepeatFirstRuns) {
-                    const uint32_t left = rounds(kRepeatFirstRuns, pend, npend);
-                    rounds(a.runs, undecided, left);
-                } else {
-                    rounds(a.runs, pend, npend);
-                }
-                npend = 0;
+                else
+                    drain();
             }
             if (over)
                 break;

@@ -198,8 +198,8 @@ __global__ __launch_bounds__(64) void truth_narrow_kernel(TruthArgs a)
             m = build_bonds<M>(genome, a.t, a.bits, a.c);
             busy = true;
             if constexpr (M::kManyIds) {
-                // the first stage loses the id of the sixteenth oriented tile
-                // and proves nothing then: its proof is made up for here
+                // the first stage may not know where the sixteenth oriented tile
+                // lies and proves nothing then: its proof is made up for here
                 if (a.t == 4) {
                     bool guarded = false;
                     if (sub == 0) {
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(64) void truth_narrow_kernel(TruthArgs a)
                         uint64_t key = 0;
                         int x0 = 0, y0 = 0;
                         const bool fits = shape_key8(g, st, G, st.size(), key, x0, y0);
-                        guarded = shape_is_guarded(m, g, st, G, fits, key, x0, y0);
+                        guarded = shape_is_guarded(m, g, TileIds{true, 0ull}, G, fits, key, x0, y0);
                         if (guarded)
                             a.out[i] = jatam_result_t{JATAM_DET, st.size(), shape_hash(g, G), 0};
                     }

@@ -400,8 +400,9 @@ __device__ __forceinline__ uint64_t shfl64(uint64_t v, int lane)
 // skip + jr.  round() runs one candidate per group (active groups only) to
 // its record, or (a first pass without a witness) to the second queue.
 // kSolo: the second queue is a list of indices in LDS (queue_out, its length
-// in `kept`), orient has kSoloGroups columns, `out` may be null, and DET
-// records are counted in `table` if it has one.
+// in `kept`), orient has kSoloGroups columns, `out` may be null, DET records are
+// counted in `table` if it has one, and a pass of run 0 alone proves the shapes
+// that it can (those whose tiles' ids were lost had no proof before).
 constexpr int kSoloGroups = 32;   // candidates per round at two lanes each
 
 template <int W, class M, bool kSolo>
@@ -432,7 +433,7 @@ struct RepeatWave {
         : a(a_), first(slice_first(a_)), out(slice_out(a_)), g{smem + threadIdx.x},
           g0{smem}, orient(orient_), cache(cache_), st(st_), tally(tally_), skip(skip_),
           store_occ(store_occ_), all_runs(rpass >= a_.runs), R(rpass - skip_),
-          groups(64 / (rpass - skip_)), lane((int)threadIdx.x), grp(0), jr(0), run(0), lead(0),
+          groups(kSolo && rpass - skip_ < 2 ? kSoloGroups : 64 / (rpass - skip_)), lane((int)threadIdx.x), grp(0), jr(0), run(0), lead(0),
           tail(0), gmask(0), queue_out(queue_out_), count_out(count_out_), table(table_)
     {
         grp = lane / R;
@@ -451,10 +452,20 @@ struct RepeatWave {
     {
         Geno gd{};
         int ev = kEvNone;
+        bool proven = false;
         if (active) {
             gd = run_geno<W>(a, first, idx);
             const M src = build_bonds<M>(gd.genome, gd.t, a.bits, a.c);
             ev = run_assembly(src, g, st, gd.grid, run_key(a, gd, run));
+            if constexpr (kSolo && M::kManyIds) {
+                if (R == 1 && ev == kEvNone) {
+                    uint64_t shape = 0;
+                    int x0 = 0, y0 = 0;
+                    const bool fits = shape_key8(g, st, gd.grid, st.size(), shape, x0, y0);
+                    const TileIds ids = shape_ids(src, g, st, gd.grid, fits, shape, x0, y0);
+                    proven = shape_is_guarded(src, g, ids, gd.grid, fits, shape, x0, y0);
+                }
+            }
         }
         wave_lds_sync();   // every run's grid is final
         // a witness is a later run that hit an event or ended in another
@@ -507,10 +518,12 @@ struct RepeatWave {
         // the skipped runs made size0 - 1 each
         const int last = fw < R ? fw : R - 1;
         const int incl = wave_inclusive_sum(active && jr <= last ? st.steps : 0);
-        const int steps = __shfl(incl, tail) - __shfl(incl, lead) + __shfl(st.steps, lead) +
-                          skip * (size0 - 1);
+        int steps = __shfl(incl, tail) - __shfl(incl, lead) + __shfl(st.steps, lead) +
+                    skip * (size0 - 1);
+        if (proven)
+            steps = (size0 - 1) * a.runs;
         // without a witness in a first pass the candidate waits for the second
-        const bool undecided = active && fw == R && !all_runs && cls == JATAM_DET;
+        const bool undecided = active && fw == R && !all_runs && cls == JATAM_DET && !proven;
         const uint64_t um = __ballot(undecided && jr == 0);
         if (um != 0) {
             uint32_t at = kept;
