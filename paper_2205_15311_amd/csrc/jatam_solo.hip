@@ -8,8 +8,9 @@
 // (the proof of one candidate by its own lane would leave the others idle),
 // and the candidates that are not proven, whose repeat runs the wave makes in
 // rounds (RepeatWave) when its first runs are done, or before if the list fills
-// up: runs 0-3 of sixteen candidates at a time, then all R runs of those
-// without a witness; all R at once where R is at most eight.
+// up: runs 0-3 of sixteen candidates at a time, above 32 runs then runs 0-15 of
+// four, then all R runs of those without a witness; all R at once where R is at
+// most eight.
 //
 // Against the pipeline of jatam_batched.hip it needs one launch instead of
 // eight, no workspace and no staging (150 bytes a candidate through HBM), and no
@@ -24,6 +25,7 @@ namespace jatam {
 
 constexpr int kSoloPend = 128;    // unproven candidates: drained above 64
 constexpr int kSoloShapes = 64;   // packed shapes waiting for a proof
+constexpr int kSecondRuns = 16;   // runs of a second pass of three, and candidates for it
 // An unproven candidate (positions are below 2^31) whose tiles' ids were lost, so that
 // it has had no proof; from this many of them in a wave's list on they get one, with a
 // run 0 of their own.  (Uniform four-tile lists have a few a wave: 2^20 of them 200
@@ -125,10 +127,15 @@ __global__ __launch_bounds__(64, W == 16 ? 3 : 1) void solo_kernel(const BatchAr
     auto drain = [&]() {
         uint32_t* list = pend;
         uint32_t count = npend, kept = 0;
-        // runs 0-3 first
+        // runs 0-3 first; above 32 runs, where a round of all runs takes one candidate
+        // only, 16 if many are left.  (2^20 two-tile genotypes that run 0 calls
+        // deterministic and later runs do not, R = 64: 1.79 -> 1.06 ms; for few the
+        // pass does not pay, 2^20 uniform four-tile ones 180 -> 198 us.)
         auto pass_after = [&](int runs) {
             return runs < kRepeatFirstRuns && a.runs > 2 * kRepeatFirstRuns ? kRepeatFirstRuns
-                                                                            : a.runs;
+                   : runs < kSecondRuns && a.runs > 32 && count >= (uint32_t)kSecondRuns
+                       ? kSecondRuns
+                       : a.runs;
         };
         int rpass = pass_after(0);
         if (M::kManyIds && nlost >= kLostProof) {
