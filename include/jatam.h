@@ -224,8 +224,8 @@ int jatam_batch_set_refill(jatam_batch_t* batch, int idle_lanes);
 /*
  * Launch parameters of the pipeline for one grid class (G <= 16 or
  * 16 < G <= 32).  None of them changes a record.  Small calls (up to 2^20
- * genotypes for G <= 16, 2^19 above, fewer than 2^20 mixed items) without the
- * timing hook are made by one launch that does the whole
+ * genotypes for G <= 16, fewer above and of mixed items, 2^18 of up to two tiles
+ * above) without the timing hook are made by one launch that does the whole
  * classification, not by the pipeline, unless the caller has set other
  * parameters than the defaults for a grid class that the call may use (its G's;
  * both for mixed items) with jatam_batch_set_tuning, jatam_batch_set_refill or

@@ -1423,20 +1423,26 @@ constexpr int64_t kWindowMinItems = 1 << 20;
 //   t = 2, G = 16     50 : 123   113 : 163 143 : 179 189 : 207  214 : 237
 //   t = 3, G = 16     56 : 120   108 : 208 137 : 242 158 : 265  198 : 310
 //   large, G = 16                127 : 143 171 : 183 269 : 201  515 : 266
-//   t = 2, G = 32    172 : 255   368 : 402 404 : 415 493 : 449  596 : 532  595 : 610
-//   t = 3, G = 32     93 : 176   278 : 370 331 : 403 392 : 439  525 : 543  523 : 664
+//   t = 2, G = 20                          194 : 212 262 : 232  401 : 308
+//   t = 4, G = 20                          130 : 208 176 : 215  231 : 267
+//   t = 2, G = 32    172 : 255   368 : 402 404 : 423 484 : 452  636 : 531  595 : 609
+//   t = 3, G = 32     93 : 176   278 : 370 338 : 401 409 : 452  560 : 540  523 : 676
+//   t = 4, G = 32                          267 : 342 336 : 441  359 : 431  353 : 603
 //   large, G = 32                152 : 157 334 : 214 579 : 293 1048 : 459 1053 : 309
 //   mixed, 16 and 32 217 : 318   410 : 577 489 : 675 567 : 727  677 : 833  695 : 745
 //   mixed, large     104 : 227   227 : 270 343 : 338 489 : 395  876 : 515  855 : 300
 // So for G <= 16 the line lies where uniform lists still gain (at 2^22 they lose, 522
-// to 395), although lists of large shapes lose from 2^19 on; for G > 16 where the two
-// kinds balance; and for mixed items just below the size from which the window takes
-// the large ones (kWindowMinItems).
-constexpr int64_t kSoloNarrow = 1 << 20, kSoloWide = 1 << 19, kSoloMixed = kWindowMinItems - 1;
+// to 395), although lists of large shapes lose from 2^19 on; above, and for mixed
+// items, just below the size from which the window takes the large ones
+// (kWindowMinItems); and lower for two tiles there.
+constexpr int64_t kSoloNarrow = 1 << 20, kSoloWide = kWindowMinItems - 1, kSoloWideTwo = 1 << 18;
 
-static int64_t solo_items(int grid_limit)
+static int64_t solo_items(int grid_limit, int geno)
 {
-    return grid_limit == 0 ? kSoloMixed : grid_limit <= 16 ? kSoloNarrow : kSoloWide;
+    return grid_limit == 0 ? kSoloWide
+           : grid_limit <= 16 ? kSoloNarrow
+           : geno == kGenoTwo ? kSoloWideTwo
+                              : kSoloWide;
 }
 
 bool same_tuning(const jatam_tuning_t& x, const jatam_tuning_t& y)
@@ -1454,7 +1460,7 @@ int launch_tuned(const jatam_tuning_t tn[2], const BatchOccupancy& occ, int cus,
     const int geno = geno_kind(max_t, a.c);
     // Small calls: one launch instead of the pipeline's eight, but not with the
     // timing hook, which is about the pipeline's stages.
-    if (!pipeline && a.n <= solo_items(grid_limit) && marks == nullptr) {
+    if (!pipeline && a.n <= solo_items(grid_limit, geno) && marks == nullptr) {
         const bool one[2] = {grid_limit <= 16, grid_limit == 0 || grid_limit > 16};
         const int waves[2] = {occ.solo[0][geno] * cus, occ.solo[1][geno] * cus};
         return launch_solo(a, one, waves, geno, nullptr, 0, stream);

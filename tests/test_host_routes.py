@@ -53,9 +53,9 @@ class Batch:
             self.h, ctypes.c_uint64(0), ctypes.c_int64(n), 2, 8, grid, 20, ctypes.c_uint64(1),
             self.mem, None, None))
 
-    def list_(self, n, grid):
+    def list_(self, n, grid, t=2, c=8):
         return self.host.count(lambda: self.lib.jatam_batch_classify(
-            self.h, self.mem, ctypes.c_int64(n), 2, 8, grid, 20, ctypes.c_uint64(1), self.mem,
+            self.h, self.mem, ctypes.c_int64(n), t, c, grid, 20, ctypes.c_uint64(1), self.mem,
             None, None))
 
     def items(self, n, tune=None):
@@ -85,12 +85,19 @@ def batch(host):
     host.lib.jatam_batch_destroy(b.h)
 
 
-def test_size_decides_by_default(batch):
-    for grid, most in ((8, 1 << 20), (16, 1 << 20), (18, 1 << 19), (32, 1 << 19)):
-        for n in (1, SMALL, most):
-            assert batch.range_(n, grid) == ONE and batch.list_(n, grid) == ONE
-        for n in (most + 1, LARGE):
-            assert batch.range_(n, grid) == PIPE and batch.list_(n, grid) == PIPE
+@pytest.mark.parametrize("t,c,grid,most", [
+    (1, 8, 8, 1 << 20), (2, 8, 16, 1 << 20), (4, 16, 16, 1 << 20), (2, 8, 18, 1 << 18),
+    (1, 8, 32, 1 << 18), (3, 8, 18, (1 << 20) - 1), (4, 8, 32, (1 << 20) - 1),
+    (2, 16, 32, (1 << 20) - 1)])
+def test_size_decides_by_default(batch, t, c, grid, most):
+    for n in (1, SMALL, most):
+        assert batch.list_(n, grid, t, c) == ONE
+    for n in (most + 1, LARGE):
+        assert batch.list_(n, grid, t, c) == PIPE
+    assert batch.range_(SMALL, grid) == ONE and batch.range_(LARGE, grid) == PIPE
+
+
+def test_size_decides_for_items(batch):
     assert batch.items(SMALL) == ONE and batch.items((1 << 20) - 1) == ONE
     assert batch.items(1 << 20) == PIPE and batch.items(LARGE) == PIPE
 
