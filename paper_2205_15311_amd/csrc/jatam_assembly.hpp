@@ -1245,7 +1245,8 @@ __device__ __forceinline__ bool same_cells(LeanGrid<W>& g, LeanGrid<W>& h, int G
 // without replaying the run: .x/.y the anchored 8 x 8 bitmap (bit 8y + x),
 // .z/.w a 64-bit word holding the tile nibble of every cell in ascending bit
 // order (at most kPackedCells cells) and, in bits 58..63, the seed's bit.
-// All ones in .z/.w: no packed shape (larger box, more cells, or tiles' ids lost).
+// All ones in .z/.w: no packed shape (larger box, more cells or, with .x set, tiles'
+// ids lost).
 // ---------------------------------------------------------------------------
 constexpr int kPackedCells = 14;
 
@@ -1255,9 +1256,14 @@ __device__ __forceinline__ bool packed_shape_valid(const uint4& v)
 }
 
 // No packed shape.
-__device__ __forceinline__ uint4 packed_none()
+__device__ __forceinline__ uint4 packed_none(bool lost = false)
 {
-    return make_uint4(0u, 0u, 0xFFFFFFFFu, 0xFFFFFFFFu);
+    return make_uint4(lost ? 1u : 0u, 0u, 0xFFFFFFFFu, 0xFFFFFFFFu);
+}
+
+__device__ __forceinline__ bool packed_shape_lost(const uint4& v)
+{
+    return !packed_shape_valid(v) && v.x != 0u;
 }
 
 // What a clean run's grid says of its tiles' ids: with `known`, the id of a cell is
@@ -1333,8 +1339,9 @@ template <class Grid>
 __device__ __forceinline__ uint4 pack_shape(Grid& g, const RunState& st, int G, int size,
                                             uint64_t m, int x0, int y0)
 {
-    if (size > kPackedCells || (Grid::kLean && st.lost != 0))
-        return packed_none();
+    const bool lost = Grid::kLean && st.lost != 0;
+    if (size > kPackedCells || lost)
+        return packed_none(lost);
     uint64_t tiles = 0;
     int k = 0;
     for (uint64_t cells = m; cells != 0; cells &= cells - 1, k += 4) {

@@ -458,7 +458,8 @@ __global__ __launch_bounds__(256) void sort_scatter_kernel(BatchArgs a, int klas
 // ---------------------------------------------------------------------------
 // prove<W>: one lane per candidate (in size order) takes its run-0 shape as
 // the first-run stage packed it (the sort moved it beside the candidate), or
-// replays run 0 where it did not fit or its ids were lost, and checks whether the shape is guarded
+// replays run 0 where it did not fit (or, from kLostReplay of a wave's candidates
+// on, its ids were lost), and checks whether the shape is guarded
 // (shape_is_guarded; forced shapes are the case without conflicts): then
 // every run ends in it and the record is final without the repeat runs --
 // DET, run 0's size and hash, (size - 1) * R placements.  The other
@@ -470,6 +471,13 @@ __global__ __launch_bounds__(256) void sort_scatter_kernel(BatchArgs a, int klas
 // ---------------------------------------------------------------------------
 constexpr uint32_t kNoCandidate = 0xFFFFFFFFu;
 
+// Candidates whose tiles' ids were lost (LeanGrid) that make a wave replay and prove
+// them, if the queue gives every wave a chunk.  With fewer, or in a short queue, whose
+// time is one wave's chain and not the work, their repeat runs cost less.  1.3 x 10^6
+// uniform four-tile genotypes at G = 8, R = 20 (500 chunks) 217 us, with the proofs 276;
+// 2^22 of nothing else at G = 16 5.4 ms, with them 0.44.
+constexpr int kLostReplay = 32;
+
 // The proof of the candidate at queue position pos of the size-sorted queue
 // (lanes with `active`): a guarded shape gets its record here; otherwise
 // the candidate is kept (the return value) for the repeat runs.  Called by
@@ -478,25 +486,31 @@ template <int W, class M>
 __device__ __forceinline__ bool prove_one(const BatchArgs& a, uint64_t first,
                                           jatam_result_t* out, LeanGrid<W>& g, RunState& st,
                                           WaveShapeCache& cache, WaveTally& tally, int klass,
-                                          bool active, uint32_t pos, uint32_t& idx)
+                                          bool full_queue, bool active, uint32_t pos,
+                                          uint32_t& idx)
 {
     bool forced = false, packed = false;
     int size = 0;
     uint64_t key = 0;
     Geno gd{};
     idx = 0;
+    const uint4 sh = active ? a.ws.sorted_shape[pos] : packed_none();
+    bool replay = true;
+    if constexpr (M::kManyIds) {
+        const bool lost = packed_shape_lost(sh);
+        replay = !lost || (full_queue && __popcll(__ballot(lost)) >= kLostReplay);
+    }
     if (active) {
         idx = a.ws.sorted[klass][pos];
         gd = run_geno<W>(a, first, idx);
         const M src = build_bonds<M>(gd.genome, gd.t, a.bits, a.c);
-        const uint4 sh = a.ws.sorted_shape[pos];
         packed = packed_shape_valid(sh);
         if (packed) {
             // the first-run stage packed the shape: no replay
             key = ((uint64_t)sh.y << 32) | sh.x;
             size = __popcll(key);
             forced = packed_shape_is_guarded(src, sh);
-        } else {
+        } else if (replay) {
             const int ev = run_assembly(src, g, st, gd.grid, run_key(a, gd, 0));
             size = st.size();
             int x0 = 0, y0 = 0;
@@ -538,7 +552,8 @@ __global__ __launch_bounds__(64) void prove_kernel(const BatchArgs a, int klass)
         const bool active = pos < count;
         uint32_t idx;
         const bool kept =
-            prove_one<W, M>(a, first, out, g, st, cache, tally, klass, active, pos, idx);
+            prove_one<W, M>(a, first, out, g, st, cache, tally, klass, qchunks >= gridDim.x, active,
+                            pos, idx);
         if (active)
             keep[pos] = kept ? idx : kNoCandidate;
         const uint32_t kc = (uint32_t)__popcll(__ballot(kept));
@@ -677,7 +692,7 @@ __global__ __launch_bounds__(64) void prove_repeat_kernel(const BatchArgs a, int
         const uint32_t pos = c * 64 + lane;
         uint32_t idx;
         const bool kept = prove_one<W, M>(a, rw.first, rw.out, lg, st, cache, tally, klass,
-                                           pos < count, pos, idx);
+                                          qchunks >= gridDim.x, pos < count, pos, idx);
         const uint64_t km = __ballot(kept);
         if (kept)
             pend[npend + (uint32_t)__popcll(km & lanes_below())] = idx;
