@@ -10,7 +10,7 @@
 // rounds (RepeatWave) when its first runs are done, or before if the list fills
 // up: runs 0-3 of sixteen candidates at a time, above 32 runs then runs 0-15 of
 // four, then all R runs of those without a witness; all R at once where R is at
-// most eight.
+// most eight.  Up to four runs at G <= 16 it makes them without a proof.
 //
 // Against the pipeline of jatam_batched.hip it needs one launch instead of
 // eight, no workspace and no staging (150 bytes a candidate through HBM), and no
@@ -72,6 +72,11 @@ __global__ __launch_bounds__(64, W == 16 ? 3 : 1) void solo_kernel(const BatchAr
     const uint32_t n_items = (uint32_t)a.n;
     ChunkSource chunks;
     chunks.init(a, klass, (n_items + chunk_items - 1) / chunk_items);
+    // In the 16 x 16 layout up to four runs cost less than the proof: 2^20 genotypes at
+    // R = 2, G = 16, uniform two-tile ones 215 -> 177 us, deterministic ones 393 -> 324,
+    // some that run 0 calls deterministic and run 1 may not 542 -> 390.  At G = 32, where
+    // runs are longer, 2^20 uniform two-tile ones would take 955 instead of 602.
+    constexpr bool direct_runs = W == 16 && !kOpen;
     uint32_t head = 0, queued = 0, nshapes = 0, npend = 0, nlost = 0;   // wave-uniform
     bool busy = false, starved = false;
     uint32_t idx = 0;
@@ -206,7 +211,7 @@ __global__ __launch_bounds__(64, W == 16 ? 3 : 1) void solo_kernel(const BatchAr
             uint4 packed = packed_none();
             if (det || candidate)
                 fits = shape_key8(g, st, gd.grid, st.size(), key, x0, y0);
-            if (candidate) {
+            if (candidate && (!direct_runs || a.runs > kRepeatFirstRuns)) {
                 if (fits)
                     packed = pack_shape(g, st, gd.grid, st.size(), key, x0, y0);
                 pack = packed_shape_valid(packed);
