@@ -57,7 +57,6 @@ struct LaneGrid {
     __device__ __forceinline__ uint32_t& fr(int w) { return word(Geo::kFr + w); }
 
     __device__ __forceinline__ bool occupied(int p) { return (occ(p >> 5) >> (p & 31)) & 1u; }
-    __device__ __forceinline__ bool on_frontier(int p) { return (fr(p >> 5) >> (p & 31)) & 1u; }
     // every word of the lane's grid, PEND included (kernel start)
     __device__ __forceinline__ void clear_all()
     {

@@ -21,12 +21,19 @@ struct Geno {
     bool windowed;   // run in a window of its own grid (run_geno)
 };
 
-// `first`: the range mode's first genotype of this call (a.first, moved by
+// Input modes: a range (genome = first + i, no loads), a genome list or items, as a
+// compile-time choice where the kernel is compiled for each, else by the arguments.
+// With the mode fixed, a range call has no global loads in its loop, and so no waits
+// (the vector memory counter also counts the loop's record stores).
+enum { kInRange = 0, kInList = 1, kInItems = 2, kInRuntime = 3 };
+
+// Input i.  `first`: the range mode's first genotype of this call (a.first, moved by
 // the slice counter of a replayed enumeration).
+template <int kIn>
 __device__ __forceinline__ Geno fetch_geno(const BatchArgs& a, uint64_t first, uint32_t i)
 {
     Geno g;
-    if (a.items != nullptr) {
+    if (kIn == kInItems || (kIn == kInRuntime && a.items != nullptr)) {
         const jatam_item_t it = a.items[i];
         g.genome = it.genome;
         g.rng_id = it.rng_id;
@@ -36,7 +43,8 @@ __device__ __forceinline__ Geno fetch_geno(const BatchArgs& a, uint64_t first, u
         g.valid = g.t >= 1 && g.t <= 4 && gbits <= 64 && g.grid >= 8 && g.grid <= 32 &&
                   (g.grid & 1) == 0 && (gbits == 64 || (g.genome >> gbits) == 0);
     } else {
-        g.genome = a.genomes != nullptr ? a.genomes[i] : first + (uint64_t)i;
+        const bool list = kIn == kInList || (kIn == kInRuntime && a.genomes != nullptr);
+        g.genome = list ? a.genomes[i] : first + (uint64_t)i;
         g.t = a.t;
         g.grid = a.grid;
         g.rng_id = g.genome | ((uint64_t)(uint32_t)a.t << 56);
@@ -44,40 +52,6 @@ __device__ __forceinline__ Geno fetch_geno(const BatchArgs& a, uint64_t first, u
         g.valid = gbits == 64 || (g.genome >> gbits) == 0;
     }
     return g;
-}
-
-// Input modes, as a compile-time choice for the first-run kernel: a range
-// (genome = first + i, no loads), a genome list, or items.  With the mode
-// fixed, a range call has no global loads in its loop, and so no waits
-// (the vector memory counter also counts the loop's record stores).
-enum { kInRange = 0, kInList = 1, kInItems = 2, kInRuntime = 3 };
-
-template <int kIn>
-__device__ __forceinline__ Geno fetch_geno_in(const BatchArgs& a, uint64_t first, uint32_t i)
-{
-    if constexpr (kIn == kInRuntime) {
-        return fetch_geno(a, first, i);
-    } else if constexpr (kIn == kInItems) {
-        Geno g;
-        const jatam_item_t it = a.items[i];
-        g.genome = it.genome;
-        g.rng_id = it.rng_id;
-        g.t = it.t;
-        g.grid = it.grid;
-        const int gbits = 4 * g.t * a.bits;
-        g.valid = g.t >= 1 && g.t <= 4 && gbits <= 64 && g.grid >= 8 && g.grid <= 32 &&
-                  (g.grid & 1) == 0 && (gbits == 64 || (g.genome >> gbits) == 0);
-        return g;
-    } else {
-        Geno g;
-        g.genome = kIn == kInList ? a.genomes[i] : first + (uint64_t)i;
-        g.t = a.t;
-        g.grid = a.grid;
-        g.rng_id = g.genome | ((uint64_t)(uint32_t)a.t << 56);
-        const int gbits = 4 * a.t * a.bits;
-        g.valid = gbits == 64 || (g.genome >> gbits) == 0;
-        return g;
-    }
 }
 
 // The genotype as the kernels of a grid class run it: in the 16 x 16 layout
@@ -90,7 +64,7 @@ __device__ __forceinline__ Geno fetch_geno_in(const BatchArgs& a, uint64_t first
 template <int W, int kIn = kInRuntime>
 __device__ __forceinline__ Geno run_geno(const BatchArgs& a, uint64_t first, uint32_t i)
 {
-    Geno g = fetch_geno_in<kIn>(a, first, i);
+    Geno g = fetch_geno<kIn>(a, first, i);
     g.windowed = W == 16 && g.grid > 16;
     if constexpr (W == 16)
         g.grid = g.grid < 16 ? g.grid : 16;
@@ -226,7 +200,7 @@ __device__ __forceinline__ bool screen_item(const BatchArgs& a, uint64_t first, 
     }
     if (!in_range)
         return false;
-    const Geno s = fetch_geno_in<kIn>(a, first, i);
+    const Geno s = fetch_geno<kIn>(a, first, i);
     if (!s.valid) {
         // exactly one launched pass reports an invalid item: its grid's class,
         // or with the window on (the 32 x 32 class then reruns listed items
