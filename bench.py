@@ -5,7 +5,8 @@ One step = classification of all 2^24 two-tile genotypes (c=8, G=16, R=20,
 seed 1), no input read from HBM, 256 MiB of records written to HBM.  Four
 paths are timed on the same stream:
   plain      16 plain calls over 2^20-genotype ranges (one launch each),
-  graph      an enumeration in 16 slices of 2^20 genotypes (and in 4 of 2^22),
+  graph      an enumeration in 16 slices of 2^20 genotypes (and in 4 of 2^22;
+             one launch on this grid),
   surrogate  the trained network's predicted cost of every genotype, the
              queue ordered by it, the pipelined call in that order (scoring
              and ordering inside the timed step),
@@ -45,37 +46,33 @@ TOTAL = 1 << 24
 VALU_PEAK_OPS = 256 * 64 * 2.4e9
 
 
-OPS_GENOTYPE = 500.0     # decode, oriented tiles, bond options of the seed, record
+# Integer operations (one lane, one VALU instruction) that the method needs, each at or
+# below what the kernels execute for it.  Active lane-operations of the first-run kernel
+# by counters (instructions x 64 x share of active lanes) over 2^22 genotypes: 199 a
+# genotype for those that the seed's screen decides, 724 for runs ended by their first
+# placement, 903 by their second, so 180 a placement and 345 a run's start and end; over
+# all of S_2,8 1.25e10 executed, 1.08e10 counted here.  Of a shape's hash only the
+# lookup counts: S_2,8 has 13 deterministic shapes.
+OPS_GENOTYPE = 200.0     # decode, bond options of the seed's sites, record
+OPS_RUN = 300.0          # a first run: bond table, grid words, the ended run's class
 OPS_PLACEMENT = 160.0    # quarter Philox block, frontier select, 4 neighbour checks
-
-
-def hash_ops(count, size_sum):
-    """D4 shape hash: 8 orientations x (12 ops per cell + 40)."""
-    return 8.0 * (12.0 * size_sum + 40.0 * count)
-
-
-def algorithmic_ops(n, steps, det_count, det_size):
-    """Integer work the method itself needs for n genotypes."""
-    return OPS_GENOTYPE * n + OPS_PLACEMENT * steps + hash_ops(det_count, det_size)
-
-
+OPS_SHAPE = 40.0         # a deterministic shape: its bitmap, looked up
 OPS_PROOF_CELL = 100.0   # guarded-shape check: four neighbour lookups per cell
 
 
-def stage_ops(gold):
-    """The same work split over the pipeline's kernels (per whole-space call):
-    first runs (with the seed screen); the replayed first runs of the
-    candidates and the guarded-shape check (guarded candidates are final
-    there); the repeat runs of the other candidates."""
+def stage_ops(gold, started):
+    """The work of a whole-space call split over the pipeline's kernels: first runs
+    (with the seed screen; `started` genotypes have a first run to make), the
+    guarded-shape check of the candidates (guarded ones are final there), the
+    repeat runs of the other candidates (their first four in the proof's kernel
+    when there are two repeat passes)."""
     w = gold["work"]
     return {
-        "first_run_kernel<16>": OPS_GENOTYPE * gold["total"]
-        + hash_ops(w["monomer_det"], w["monomer_det"])
-        + OPS_PLACEMENT * w["run0_steps"] + hash_ops(w["run0_det"], w["run0_det_size"]),
-        "prove_kernel<16>": OPS_PLACEMENT * w["cand_steps0"] + OPS_PROOF_CELL * w["cand_size"]
-        + hash_ops(w["proven"], w["proven_size"]),
+        "first_run_kernel<16>": OPS_GENOTYPE * gold["total"] + OPS_RUN * started
+        + OPS_PLACEMENT * w["run0_steps"] + OPS_SHAPE * w["run0_det"],
+        "prove_kernel<16>": OPS_PROOF_CELL * w["cand_size"] + OPS_SHAPE * w["proven"],
         "repeat_kernel<16>": OPS_PLACEMENT * w["unproven_steps"]
-        + hash_ops(w["unproven_det"], w["unproven_det_size"]),
+        + OPS_SHAPE * w["unproven_det"],
     }
 
 
@@ -285,7 +282,7 @@ def misclass_report(args, jt, torch):
                           "misclassified": int((det & ~true_det).sum()),
                           "missed_true_det": int((true_det & ~det).sum())})
     # the same curve under the paper's own traversal, the LIFO movelist
-    # (plain variant kernel; the true class does not depend on the traversal)
+    # (variant kernel; the true class does not depend on the traversal)
     curve_lifo = []
     rec = torch.empty((TOTAL, 4), dtype=torch.int32, device=dev)
     t1 = time.perf_counter()
@@ -417,8 +414,8 @@ def maps_report(args, jt, torch):
     """Robustness and evolvability (section 1.1) of every genotype of S_{2,8}
     (G=16, R=20, seed 1; the space classified once, every single mutant's
     record gathered from it) and of a uniform sample of 2^20 three-tile
-    genotypes at G=32 (their 36 single mutants each classified by the
-    pipelined path).  Prints one JSON line."""
+    genotypes at G=32 (their 36 single mutants each classified in one
+    call).  Prints one JSON line."""
     import numpy as np
     from tests import inputs
     dev = torch.device("cuda:0")
@@ -702,6 +699,10 @@ def main():
             ok &= hashlib.sha256(blob).hexdigest() == s["sha256"]
         return bool(ok)
 
+    def runs_started():
+        # genotypes with a placement, from verified records
+        return int((out[:, 3] > 0).sum().item())
+
     def timed(step_fn, warm_fn, make_events=False):
         for _ in range(args.warmup):
             warm_fn()
@@ -739,9 +740,7 @@ def main():
         bit_exact &= plain_ok
         launch_ms = [a.elapsed_time(b) for ev in plain_launch_ms for a, b in ev]
         plain_mean_launch_s = sum(launch_ms) / len(launch_ms) / 1e3
-        plain_ops_per_launch = algorithmic_ops(SLICE, gold["steps"] / nslices,
-                                               gold["tally"][3] / nslices,
-                                               gold["det_size"] / nslices)
+        plain_ops_per_launch = sum(stage_ops(gold, runs_started()).values()) / nslices
         results["plain"] = {
             "value": TOTAL * args.steps / (plain_total_ms / 1e3),
             "ms_per_step": plain_total_ms / args.steps, "bit_exact": plain_ok,
@@ -794,7 +793,7 @@ def main():
     bit_exact &= batched_ok
     batched_value = TOTAL * args.steps / (batched_total_ms / 1e3)
 
-    ops = stage_ops(gold)
+    ops = stage_ops(gold, runs_started())
     stage_ms = {name: ms / max(n, 1) for name, (ms, n) in stages.items()}
     dominant = max(ops, key=lambda k: stage_ms.get(k, 0.0))
     dom_s = stage_ms[dominant] / 1e3
