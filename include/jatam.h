@@ -111,9 +111,10 @@ int jatam_classify_range(uint64_t first, int64_t n, int t, int c, int grid_limit
                          int runs, uint64_t seed, jatam_result_t* out, void* stream);
 
 /* ------------------------------------------------------------------------
- * Pipelined ("batched") classification.
+ * Batched classification.
  *
- * Same records as jatam_classify, produced by a pipeline that keeps lanes
+ * Same records as jatam_classify.  Small calls are made by one launch (see
+ * jatam_tuning_t for which), larger ones by a pipeline that keeps lanes
  * busy: a screen of every genotype's seed, a device queue of first runs
  * drained by persistent waves, and the repeat runs of deterministic
  * candidates ordered by their exact cost (run-0 size), one lane per run (the
@@ -146,8 +147,10 @@ typedef struct jatam_batch jatam_batch_t;
 
 /*
  * Creates a workspace for calls of up to max_n (1 <= max_n < 2^32) genotypes
- * on the current HIP device: 28 bytes of device memory per genotype plus a
- * few KiB.  Blocks until the workspace is initialised.  *batch receives the
+ * on the current HIP device: about 90 bytes of device memory per genotype
+ * (staged and sorted candidates with their packed shapes, stored occupancies,
+ * a list of reruns, records) and some 8 MiB for the waves' segments and
+ * counters.  Blocks until the workspace is initialised.  *batch receives the
  * handle; JATAM_E_HIP if device memory runs out.
  */
 int jatam_batch_create(int64_t max_n, jatam_batch_t** batch);
@@ -156,8 +159,7 @@ int jatam_batch_create(int64_t max_n, jatam_batch_t** batch);
 int jatam_batch_destroy(jatam_batch_t* batch);
 
 /*
- * Pipelined equivalents of jatam_classify / jatam_classify_range, and a
- * mixed-item call where every genotype carries its own t, grid and rng_id.
+ * jatam_classify / jatam_classify_range on a workspace, and a mixed-item call where every genotype carries its own t, grid and rng_id.
  *   batch  workspace from jatam_batch_create, same device, n <= its max_n
  *   tally  NULL, or device uint64[4] to which the number of UNBOUND,
  *          ND_SITE, ND_RUNS and DET records is ADDED (the caller zeroes it)
@@ -181,11 +183,11 @@ int jatam_batch_classify_items(jatam_batch_t* batch, const jatam_item_t* items, 
  * together by the one-launch kernel, which needs no room per genotype and reads
  * no launch parameters, unless the caller has set the class's parameters to
  * others than the defaults (see jatam_tuning_t).  Else, and for G > 16, with HIP
- * graphs and the workspace's launch parameters: the pipeline of one slice of `slice` genotypes (and, if
- * `shapes` is given, the shape histogram of its records) is captured once into
- * a graph whose kernels read the slice number from a device counter, then the
- * graph is launched `slices` times on `stream`, the counter advancing by one
- * per replay.
+ * graphs and the workspace's launch parameters: the pipeline of one slice of
+ * `slice` genotypes (and, if `shapes` is given, the shape histogram of its
+ * records) is captured once into a graph whose kernels read the slice number
+ * from a device counter, then the graph is launched `slices` times on `stream`,
+ * the counter advancing by one per replay.
  *   out     device, slice*slices records in genotype order, or NULL to keep
  *           only the tally and the histogram
  *   tally   NULL or device uint64[4], ADDED to (as jatam_batch_classify)
@@ -214,7 +216,7 @@ int jatam_batch_classify_items_ordered(jatam_batch_t* batch, const jatam_item_t*
                                        void* stream);
 
 /*
- * Tuning of the first-run stage: a wave refills its idle lanes (screening
+ * Tuning of the pipeline's first-run stage: a wave refills its idle lanes (screening
  * new genotypes and starting their first runs) once at least idle_lanes of
  * its 64 lanes are idle (1..64; default 24).  Sets both grid classes.
  * Records never depend on it.
@@ -478,8 +480,8 @@ int jatam_mlp_train_step(jatam_mlp_t* mlp, const uint64_t* genomes, const uint8_
 
 /* Screening score of each genome: P(DET) * exp(predicted log1p size) - 1,
  * the expected size of a deterministic structure (device float [n]).  One
- * fused pass (layer-1 gather, h1 W2 and the head on the matrix cores, 64
- * genomes per workgroup); n is not limited by max_batch and no activations
+ * fused pass (all three products on the matrix cores, 16 to 64 genomes per wave
+ * at a time); n is not limited by max_batch and no activations
  * are kept. */
 int jatam_mlp_score(jatam_mlp_t* mlp, const uint64_t* genomes, const uint8_t* t, int t_all,
                     int64_t n, float* scores, void* stream);
@@ -509,8 +511,8 @@ int jatam_mlp_predict(jatam_mlp_t* mlp, int kind, const uint64_t* genomes, const
  * ------------------------------------------------------------------------ */
 typedef struct jatam_ga jatam_ga_t;
 
-/* Workspace for up to max_candidates offspring per generation (about 24
- * bytes of device memory each). */
+/* Workspace for up to max_candidates offspring per generation (16 bytes of
+ * device memory each). */
 int jatam_ga_create(int64_t max_candidates, jatam_ga_t** ga);
 int jatam_ga_destroy(jatam_ga_t* ga);
 
@@ -537,7 +539,7 @@ typedef struct {
 
 /*
  * One generation of the GA (§2.2, §3.1): n offspring (next_pop, distinct
- * from pop), classified by the pipelined path of `batch` (n <= its max_n; R
+ * from pop), classified on the workspace `batch` (n <= its max_n; R
  * runs on grid_limit with assembly seed `seed`), and their fitness
  * next_fit[i] = size if DET else 0.
  *   surrogate  NULL: the plain GA (offspring i drawn as jatam_ga_offspring

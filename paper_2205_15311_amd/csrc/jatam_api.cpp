@@ -226,7 +226,7 @@ enum class Route { kBySize, kPipeline };
 // Sets a class's parameters.  Those a caller chose are meant for its calls, which
 // then run the pipeline; those the autotuner found are the pipeline's wherever it
 // runs, and the calls that the one launch makes faster than any of them keep it
-// (1,000 two-tile items 50 us, the pipeline 123; 2^20 215 and 255).
+// (1,000 two-tile items 50 us, the pipeline 123; 2^20 214 and 237).
 static void set_class_tuning(jatam_batch_t* b, int k, const jatam_tuning_t& t, bool by_caller)
 {
     b->tune[k] = t;
@@ -517,7 +517,12 @@ int jatam_batch_enumerate(jatam_batch_t* batch, uint64_t first, int64_t slice, i
     if (grid_limit <= 16 && route_of(batch, grid_limit) != Route::kPipeline) {
         // the one-launch kernel needs no staging, so the slices are taken
         // together, and counts shapes itself, so records that nobody asked
-        // for are not written at all
+        // for are not written at all.  All of S_{2,8} with tally and shapes takes
+        // it 1.11 ms in slices of any size; replayed pipelines of 2^20 genotypes
+        // 4.62, of 2^22 1.81, of 2^23 1.20, one of 2^24 0.98.  Three-tile
+        // genotypes: 2^26 4.1 ms, four pipelines of 2^24 the same; 2^27 7.9,
+        // two of 2^26 6.5 to 7.1.  Callers whose slices are that large can have
+        // the pipelines by setting launch parameters.
         const int geno = jatam::geno_kind(t, c);
         const bool classes[2] = {true, false};
         const int waves[2] = {batch->occ.solo[0][geno] * batch->cus, 1};

@@ -1,5 +1,5 @@
-// jatam_assembly.hpp - one lane's assembly run on gfx950, shared by the plain
-// and the pipelined classification kernels.
+// jatam_assembly.hpp - one lane's assembly run on gfx950, shared by the one-launch,
+// the pipeline's and the variants' kernels.
 //
 // A lane's grid lives in LDS as
 //   OCC   occupancy bitmap, W*W bits

@@ -87,17 +87,20 @@ __device__ __forceinline__ int mlp_tiles(int t) { return t >= 1 && t <= 3 ? t : 
 // barrier and writes no LDS.  The head's partial products, one per 32 hidden
 // features, are added in their order.
 //
-// Bound by the matrix cores: scores of all 2^24 two-tile genotypes take 2.2 to
-// 2.4 ms, 1.15 to 1.28 PFLOP/s, what a large library product reaches (1.21).  Eight waves that
-// shared a tile of 64 samples, each with 32 hidden columns and their weights in
-// registers, took 6.26 ms, most of it rounding to bf16 in integer steps, LDS
-// writes of single values and two barriers a tile.  (Same rounding points and k
-// order: the same bits.)
+// Bound by the matrix cores: scores of all 2^24 two-tile genotypes take 2.13 to
+// 2.22 ms.  That is 1.02 to 1.06 PFLOP/s of the 135,168 flops a genome that the
+// network asks for, and 1.3 of the 172,032 that are multiplied (the one-hot input's
+// zeros, and a head of 16 outputs for 4); a product of two 8192 x 8192 matrices
+// reaches 1.21.  Eight waves that shared a tile of 64 samples, each with 32 hidden
+// columns and their weights in registers, took 6.26 ms, most of it rounding to bf16
+// in integer steps, LDS writes of single values and two barriers a tile.  (Same
+// rounding points and k order: the same bits.)
 //
 // NB: more samples a wave mean fewer LDS reads per product, and fewer waves with
-// work.  Two-tile genomes, NB = 1 / 2 / 4: 32,768 of them 12.1 / 12.7 / 17.3 us,
-// 65,536 18.5 / 16.4 / 18.0, 131,072 30.2 / 26.1 / 24.8, 2^24 3.09 / 2.59 / 2.41 ms.
-// So NB rises once every wave of the chip has 16 samples, and again at 32.
+// work.  Two-tile genomes, NB = 1 / 2 / 4, in the first form of this kernel: 32,768 of
+// them 12.1 / 12.7 / 17.3 us, 65,536 18.5 / 16.4 / 18.0, 131,072 30.2 / 26.1 / 24.8,
+// 2^24 3.09 / 2.59 / 2.41 ms; now, by the rule, 11.3, 15.7, 24.0 us and 2.2 ms.  So
+// NB rises once every wave of the chip has 16 samples, and again at 32.
 // ---------------------------------------------------------------------------
 constexpr int kScoreWaves = 8;
 

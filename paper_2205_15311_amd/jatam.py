@@ -554,7 +554,7 @@ class Truth:
 
 class Batch:
     """A jatam_batch_t workspace (device queues for up to max_n genotypes per
-    call) and the pipelined calls that use it."""
+    call) and the calls that use it."""
 
     def __init__(self, max_n: int):
         handle = ctypes.c_void_p()
@@ -699,8 +699,8 @@ class Batch:
                   out: torch.Tensor | None = None, tally: torch.Tensor | None = None,
                   shapes: torch.Tensor | None = None, stream=None):
         """jatam_batch_enumerate over [first, first + slice_n * slices): one
-        launch for grid_limit <= 16, `slices` graph replays of one slice's
-        pipeline above.  out: None or an
+        launch for grid_limit <= 16 (unless launch parameters were set for
+        it), `slices` graph replays of one slice's pipeline else.  out: None or an
         int32 (slice_n * slices, 4) tensor; shapes: None or a table as for
         shape_histogram (int64 (capacity, 2))."""
         if out is not None:
