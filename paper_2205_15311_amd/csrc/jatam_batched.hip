@@ -11,7 +11,7 @@
 //                 by the waves that run out of work first.  A wave screens a
 //                 chunk (decode, bond options of the seed: an ambiguous seed
 //                 neighbour is ND_SITE, a seed with nothing to bond is a DET
-//                 monomer; ~59% of S_{2,8}) and keeps the survivors in an LDS
+//                 monomer; ~61% of S_{2,8}) and keeps the survivors in an LDS
 //                 ring.  Each lane runs the
 //                 first run of one survivor; a lane that finishes takes the
 //                 next survivor at once, so lanes stay busy while run lengths
